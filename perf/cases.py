@@ -12,6 +12,7 @@ Three kinds of case:
 import math
 
 import torch
+import torch.utils.checkpoint
 
 from paper_2410_07192_amd import binding as pf
 from paper_2410_07192_amd import device as dev
@@ -110,30 +111,40 @@ def _f32_bytes(md):
     return layer, emb
 
 
-def prepare(case, seed):
-    c, shape = case, _shape(case)
+def _draw(case, seed):
+    """Parameters and inputs of a case: layer blobs on the device, embedding and final LayerNorm, input, stage gradient."""
+    c = case
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
-    md = pf.model_desc(shape)
-    streamed, training = c["slots"] > 0, c["kind"] != "infer"
-    blobs = [dev.random_layer_blob(md, seed * 1000 + l, pinned=streamed) for l in range(c["layers"])]
-    tok = pos = None
+    md = pf.model_desc(_shape(c))
+    g = c["accum"] if c["kind"] == "stage" else c["g"]     # the stage keeps the step's microbatches in flight
+    blobs = [dev.random_layer_blob(md, seed * 1000 + l, pinned=c["slots"] > 0) for l in range(c["layers"])]
+    tok = pos = grad = None
     if c["vocab"]:
         tok = _storage((c["vocab"], c["d"]), c, gen, 0.02)
         pos = _storage((c["seq"], c["d"]), c, gen, 0.02)
     lnf_g = _storage((c["d"],), c, gen, 0.02, 1.0)
     lnf_b = _storage((c["d"],), c, gen, 0.02)
-    adam = pf.pf_adam(1e-4, 0.9, 0.999, 1e-8, c["accum"]) if training else None
-    g = c["accum"] if c["kind"] == "stage" else c["g"]     # the stage keeps the step's microbatches in flight
-    model = dev.RawModel(shape, blobs, tok, pos, lnf_g, lnf_b, g=g, streamed=streamed, n_slots=c["slots"],
-                         training=training, adam=adam)
-    s = dict(case=c, model=model)
     rows = (c["batch"], c["seq"])
     n_in = c["accum"] if c["kind"] == "train" else 1
     if c["vocab"]:
-        s["in"] = torch.randint(0, c["vocab"], (n_in, g) + rows, device="cuda", generator=gen, dtype=torch.int32)
+        x = torch.randint(0, c["vocab"], (n_in, g) + rows, device="cuda", generator=gen, dtype=torch.int32)
     else:
-        s["in"] = _storage((g,) + rows + (c["d"],), c, gen)
+        x = _storage((g,) + rows + (c["d"],), c, gen)
+    if c["kind"] == "stage":
+        grad = _storage((g,) + rows + (c["d"],), c, gen, 1e-3)
+    return md, g, n_in, blobs, tok, pos, lnf_g, lnf_b, x, grad
+
+
+def prepare(case, seed):
+    c, shape = case, _shape(case)
+    md, g, n_in, blobs, tok, pos, lnf_g, lnf_b, x, grad = _draw(c, seed)
+    training = c["kind"] != "infer"
+    adam = pf.pf_adam(1e-4, 0.9, 0.999, 1e-8, c["accum"]) if training else None
+    model = dev.RawModel(shape, blobs, tok, pos, lnf_g, lnf_b, g=g, streamed=c["slots"] > 0, n_slots=c["slots"],
+                         training=training, adam=adam)
+    s = {"case": c, "model": model, "in": x}
+    rows = (c["batch"], c["seq"])
     dt = torch.bfloat16 if c["dtype"] == "bf16" else torch.float32
     if c["kind"] == "infer":
         s["out"] = torch.empty((g,) + rows + (c["d"],), device="cuda", dtype=dt)
@@ -145,7 +156,7 @@ def prepare(case, seed):
         model.set_io(s["in"], n_in, None, 0)
         s["chunk"] = pf.pf_chunk(0, 0, 0, n_in * len(model.chain), 0, 0)
     else:
-        s["grad"] = _storage((g,) + rows + (c["d"],), c, gen, 1e-3)
+        s["grad"] = grad
         s["y"] = torch.empty(rows + (c["d"],), device="cuda", dtype=dt)
         s["dx"] = torch.empty_like(s["y"])
     n = c["layers"] * layer + emb
@@ -206,3 +217,86 @@ def tolerance(case):
     if case["dtype"] == "f32":
         return {"rel": 1e-5, "max": 1e-4}
     return {"rel": 2e-2, "max": 0.2 if case["kind"] == "infer" else 0.99}
+
+
+# rows and columns of a layer's parameters in blob order, as multiples of d and ff (0: a vector)
+_PARAMS = (("d", 0), ("d", 0), ("3d", "d"), ("3d", 0), ("d", "d"), ("d", 0), ("d", 0), ("d", 0), ("ff", "d"), ("ff", 0),
+           ("d", "ff"), ("d", 0))
+
+
+def _layer64(blob, md, c):
+    """The twelve parameters of a layer in 64 bits: LayerNorm gain and bias, QKV, output, LayerNorm, FFN 1, FFN 2."""
+    n = {"d": c["d"], "3d": 3 * c["d"], "ff": c["ff"], 0: 1}
+    flat = blob.cuda().view(torch.bfloat16 if c["dtype"] == "bf16" else torch.float32)
+    off = pf.pf_layer_blob_layout(md)[1]
+    out = []
+    for o, (r, k) in zip(off, _PARAMS):
+        o //= flat.element_size()
+        p = flat[o:o + n[r] * n[k]].double()
+        out.append(p.view(n[r], n[k]) if k else p)
+    return out
+
+
+def _forward64(x, P, c):
+    B, S, d = x.shape
+    h = c["heads"]
+    norm = lambda t, g, b: torch.nn.functional.layer_norm(t, (d,), g, b, 1e-5)
+    q, k, v = ((norm(x, P[0], P[1]) @ P[2].t() + P[3]).view(B, S, 3, h, d // h).permute(2, 0, 3, 1, 4).contiguous())
+    heads = []
+    for b in range(B):
+        s = q[b] @ k[b].transpose(1, 2).contiguous() / math.sqrt(d // h)
+        if c["causal"]:
+            s = s.masked_fill(torch.ones(S, S, dtype=torch.bool, device=x.device).triu(1), -math.inf)
+        heads.append((s.softmax(-1) @ v[b]).transpose(0, 1).reshape(S, d))
+    x = x + torch.stack(heads) @ P[4].t() + P[5]
+    u = torch.nn.functional.gelu(norm(x, P[6], P[7]) @ P[8].t() + P[9])
+    return x + u @ P[10].t() + P[11]
+
+
+def exact(case, seed):
+    """The same pass in 64-bit torch: hidden states, or the moments (1 - beta1) * mean gradient after the first step and,
+    for the stage, its output and input gradient.  Master weights have none: after one step Adam moves every weight by the
+    learning rate with the gradient's sign, which rounding decides where a gradient is as good as zero."""
+    c = case
+    md, g, n_in, blobs, tok, pos, lnf_g, lnf_b, x, grad = _draw(c, seed)
+    layers = [_layer64(b, md, c) for b in blobs]
+    emb = [t.double() for t in (tok, pos, lnf_g, lnf_b)] if c["vocab"] else []
+    final = [lnf_g.double(), lnf_b.double()]
+    d = c["d"]
+    norm = lambda t, a, b: torch.nn.functional.layer_norm(t, (d,), a, b, 1e-5)
+    if c["kind"] == "infer":
+        outs = []
+        with torch.no_grad():
+            for i in range(g):
+                t = emb[0][x[0, i].long()] + emb[1] if emb else x[i].double()
+                for P in layers:
+                    t = _forward64(t, P, c)
+                outs.append(norm(t, *final))
+        return torch.stack(outs)
+    leaves = [p.requires_grad_() for P in layers for p in P] + [t.requires_grad_() for t in emb]
+    y = dx = None
+    for i in range(c["accum"]):
+        if c["kind"] == "stage":
+            t0 = t = x[i].double().requires_grad_()
+        else:
+            ids = x[i, 0].long()
+            t = emb[0][ids] + emb[1]
+        for P in layers:
+            t = torch.utils.checkpoint.checkpoint(_forward64, t, P, c, use_reentrant=False)
+        if c["kind"] == "stage":
+            t.backward(grad[i].double())
+            y, dx = t.detach(), t0.grad
+        else:
+            logits = norm(t, emb[2], emb[3])[:, :-1] @ emb[0].t()
+            torch.nn.functional.cross_entropy(logits.reshape(-1, c["vocab"]), ids[:, 1:].reshape(-1)).backward()
+            del logits
+    layer, block = _f32_bytes(md)
+    up = lambda n: (n + 255) // 256 * 64
+    moment = torch.zeros((c["layers"] * layer + block) // 4, device="cuda", dtype=torch.float64)
+    at = 0
+    for i, p in enumerate(leaves):
+        moment[at:at + p.numel()] = p.grad.reshape(-1) * (0.1 / c["accum"])
+        n = (c["vocab"] + 63) // 64 * 64 * d if emb and i == len(leaves) - 4 else p.numel()   # the vocabulary is padded
+        at += up(n * 4)
+    out = dict(y=y, dx=dx) if c["kind"] == "stage" else {}
+    return dict(out, master=None, moment=moment)
