@@ -219,7 +219,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
     static_assert(!(EPI & E_DACT) || EPI == E_DACT, "GELU' multiplies the plain product only");
     const bool aligned16 = ((N & 7) == 0) && ((((uintptr_t)C | (uintptr_t)ep.resid | (uintptr_t)ep.preact_out |
                                                  (uintptr_t)ep.dact_in) & 15) == 0);
-    if (interior && aligned16 && N <= (1 << 21)) {
+    if (aligned16 && N <= (1 << 21)) {
       constexpr int SLOTS = BN / 8, NT = 64 * NW, PER = BM * BN / 8 / NT;
       // 16-byte slot of a row, moved per row so that the lanes of a wave (32 rows, same column group) spread
       // over the banks: XOR when the slot count is a power of two, rotation otherwise
@@ -230,16 +230,33 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       uint2* st8 = (uint2*)smem;
       // Piece i of a thread on the way out (and of the residual on the way in): 16 bytes of row i * RP + r0 when the
       // threads of a workgroup cover whole rows.  The tile's corner is the base of a raw buffer, the thread's place a
-      // 32-bit offset computed once, the rows of piece i a scalar offset (N <= 2^21 keeps all of it below 2^31): no
+      // 32-bit offset computed once, the rows of piece i added to it (N <= 2^21 keeps all of it below 2^31): no
       // 64-bit vector arithmetic per piece, which is what a lone wave per SIMD has least of.
+      // Tiles that stick out of C take the same route: the buffer ends with C's last row, and a thread whose eight
+      // columns lie past N has an offset beyond it, so the hardware drops its stores and its loads deliver zeros.
+      // (Edge tiles used to go element by element with their checks, 25 to 85 us per launch: 1659 x 768, K = 768 took
+      // 38 / 55 / 106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.)
       typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
       constexpr bool ROWWISE = NT % SLOTS == 0;
       constexpr int RP = ROWWISE ? NT / SLOTS : 1;
       const int r0 = tid / SLOTS, slot0 = tid % SLOTS;
-      const int voff = (int)((r0 * N + slot0 * 8) * 2);
+      constexpr int OUTSIDE = 0x7fffff00 - 256;   // past every buffer, with the rows added as well
+      const int ncols = (int)(N - n0 < BN ? N - n0 : BN), nrows = (int)(M - m0 < BM ? M - m0 : BM);
+      const int records = (int)((nrows - 1) * N + ncols) * 2, row_bytes = (int)N * 2;
+      // Without whole rows (24 slots on 512 threads) a thread's slot repeats after PERIOD pieces.
+      constexpr int PERIOD = ROWWISE ? 1 : 3;
+      static_assert((PERIOD * NT) % SLOTS == 0, "a thread's pieces repeat their slot");
+      constexpr int PERIOD_ROWS = PERIOD * NT / SLOTS;
+      int voff[PERIOD];
+#pragma unroll
+      for (int i = 0; i < PERIOD; ++i) {
+        const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
+        voff[i] = slot * 8 < ncols ? row * row_bytes + slot * 16 : OUTSIDE;
+      }
       auto tile_rsrc = [&](const void* p) {
-        return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + m0 * N + n0), 0, 0x7fffffff, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + m0 * N + n0), 0, records, 0x00020000);
       };
+      auto piece_off = [&](int i) { return (int)((unsigned)voff[i % PERIOD] + (unsigned)(i / PERIOD * PERIOD_ROWS * row_bytes)); };
       auto lds_at = [&](int i) {
         if constexpr (ROWWISE) {
           const int row = i * RP + r0;
@@ -249,44 +266,29 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
           return row * SLOTS + swz(slot, row);
         }
       };
-      auto piece_load = [&](__amdgpu_buffer_rsrc_t rs, const void* p, int i) -> uint4 {
-        if constexpr (ROWWISE) {
-          const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, (int)(i * RP * N * 2), 0);
-          return make_uint4(v[0], v[1], v[2], v[3]);
-        } else {
-          const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
-          return *(const uint4*)((const bf16_t*)p + (m0 + row) * N + n0 + slot * 8);
-        }
+      auto piece_load = [&](__amdgpu_buffer_rsrc_t rs, int i) -> uint4 {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, piece_off(i), 0, 0);
+        return make_uint4(v[0], v[1], v[2], v[3]);
       };
-      auto piece_store = [&](__amdgpu_buffer_rsrc_t rs, void* p, int i, uint4 v) {
-        if constexpr (ROWWISE) {
-          const u32x4 w = {v.x, v.y, v.z, v.w};
-          __builtin_amdgcn_raw_buffer_store_b128(w, rs, voff, (int)(i * RP * N * 2), 0);
-        } else {
-          const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
-          *(uint4*)((bf16_t*)p + (m0 + row) * N + n0 + slot * 8) = v;
-        }
+      auto piece_store = [&](__amdgpu_buffer_rsrc_t rs, int i, uint4 v) {
+        const u32x4 w = {v.x, v.y, v.z, v.w};
+        __builtin_amdgcn_raw_buffer_store_b128(w, rs, piece_off(i), 0, 0);
       };
       if constexpr (EPI & E_DACT) {
         // tile of the saved pre-activation: eight 16-byte pieces per thread at a time (more would not fit beside
         // the accumulators), then every lane picks up the values of its own accumulator elements
         constexpr int CH = PER < 8 ? PER : 8;
+        const __amdgpu_buffer_rsrc_t drsrc = tile_rsrc(ep.dact_in);
 #pragma unroll
         for (int i0 = 0; i0 < PER; i0 += CH) {
           uint4 t[CH];
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            if (i0 + i < PER) {
-              const int q = (i0 + i) * NT + tid, row = q / SLOTS, slot = q % SLOTS;
-              t[i] = *(const uint4*)((const bf16_t*)ep.dact_in + (m0 + row) * N + n0 + slot * 8);
-            }
+            if (i0 + i < PER) t[i] = piece_load(drsrc, i0 + i);
           }
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            if (i0 + i < PER) {
-              const int q = (i0 + i) * NT + tid, row = q / SLOTS, slot = q % SLOTS;
-              smem[row * SLOTS + swz(slot, row)] = t[i];
-            }
+            if (i0 + i < PER) smem[lds_at(i0 + i)] = t[i];
           }
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -307,14 +309,24 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();   // everyone has its values: the tile's place in LDS is free again
       }
+      // the bias of the tile's columns as a buffer of its own: columns past N read zeros
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      const __amdgpu_buffer_rsrc_t brsrc =
+          __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)ep.bias + n0), 0, ncols * 2, 0x00020000);
+      const int boff = (wn * TN * 32 + lk * 4) * 2;
       // accumulators (+ bias) (-> GELU) -> bf16 -> LDS in the swizzled row-major layout
       auto stage_tile = [&](auto with_gelu) {
         static_for<0, TN>([&](auto a) {
           float bias4[4][4] = {};
           if constexpr (EPI & E_BIAS) {
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg)
-              load4((const bf16_t*)ep.bias + n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4, bias4[rg]);
+            for (int rg = 0; rg < 4; ++rg) {
+              const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(brsrc, boff + (a * 32 + rg * 8) * 2, 0, 0);
+              bias4[rg][0] = bf16_bits_to_f32(t[0] & 0xffffu);
+              bias4[rg][1] = bf16_bits_to_f32(t[0] >> 16);
+              bias4[rg][2] = bf16_bits_to_f32(t[1] & 0xffffu);
+              bias4[rg][3] = bf16_bits_to_f32(t[1] >> 16);
+            }
           }
           static_for<0, TM>([&](auto b) {
             const int row = (wm * TM + b) * 32 + lr;
@@ -356,7 +368,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
         __builtin_amdgcn_s_barrier();
         const __amdgpu_buffer_rsrc_t prsrc = tile_rsrc(ep.preact_out);
 #pragma unroll
-        for (int i = 0; i < PER; ++i) piece_store(prsrc, ep.preact_out, i, smem[lds_at(i)]);
+        for (int i = 0; i < PER; ++i) piece_store(prsrc, i, smem[lds_at(i)]);
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
       }
@@ -367,12 +379,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       const __amdgpu_buffer_rsrc_t rrsrc = tile_rsrc((EPI & E_RESID) ? ep.resid : (const void*)C);
       if constexpr (EPI & E_RESID) {
 #pragma unroll
-        for (int i = 0; i < EARLY; ++i) rres[i] = piece_load(rrsrc, ep.resid, i);
+        for (int i = 0; i < EARLY; ++i) rres[i] = piece_load(rrsrc, i);
       }
       stage_tile(std::integral_constant<bool, (EPI & E_GELU) != 0>{});
       if constexpr (EPI & E_RESID) {   // the accumulators are dead now: the rest of the residual tile
 #pragma unroll
-        for (int i = EARLY; i < PER; ++i) rres[i] = piece_load(rrsrc, ep.resid, i);
+        for (int i = EARLY; i < PER; ++i) rres[i] = piece_load(rrsrc, i);
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);
       __builtin_amdgcn_s_barrier();
@@ -392,7 +404,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
           }
           v = make_uint4(ow[0], ow[1], ow[2], ow[3]);
         }
-        piece_store(crsrc, C, i, v);
+        piece_store(crsrc, i, v);
       }
       return;
     }
