@@ -7,8 +7,8 @@
 //    swizzle that keeps the later MFMA operand reads free of bank conflicts is applied on the global
 //    side (lane -> which chunk of the row it fetches).  Rows beyond M / N are clamped to the last
 //    valid row (their products are never stored).
-//  * Two LDS stages: the loads of step k+2 go into the stage that the barrier ending step k has
-//    freed.  They are issued one at a time between the MFMAs of the following blocks (a burst
+//  * Two LDS stages (four where a 128x128 workgroup has its CU to itself): the loads of step k+2 (k+4) go
+//    into the stage that the barrier ending step k has freed.  They are issued one at a time between the MFMAs of the following blocks (a burst
 //    blocks every wave at the address unit) and are inline assembly so that the compiler does not
 //    serialise every later LDS read behind them; vmcnt is waited by hand.
 //  * Operand fragments are double buffered in registers: the 16-byte LDS reads of sub-step kk+1
@@ -21,8 +21,9 @@
 //    steps x area; accumulating fp32 launches may split K (gemm_tile.h).
 //  * Workgroup ids are remapped so that each of the 8 XCDs (ids are dealt round-robin to them) works
 //    on a contiguous range of tiles and its L2 sees each operand panel once.
+// Launches too small to fill the chip, and fp32 with 16-byte aligned rows: gemm_ring.hip.
 // bf16 generic path (any K multiple of 8): register-staged LDS tiles, same MFMA layout.
-// fp32 path (small parity workload only): plain LDS-tiled FMA kernel with the same epilogue.
+// fp32 with odd rows: plain LDS-tiled FMA kernel with the same epilogue.
 #include "pf_kernels.h"
 #include "gemm_tile.h"
 
@@ -222,6 +223,14 @@ hipError_t dispatch_bf16(const void* X, const void* W, void* C, int64_t M, int64
       }
     }
   }
+  // The rest (K not a multiple of 64, scaled results, other combinations of epilogues): the generic kernel pays a memory
+  // latency per K step and is the faster one only where it fills the chip (1024 x 4096, K = 1000, 256 tiles: 29 us
+  // against 35; 64 tiles, 2048 x 512, K = 600: 17.9 us against 8.3).
+  if (aligned && ((M + 127) / 128) * ((N + 127) / 128) <= 192) {
+    int shape = 0;
+    ring_estimate(M, N, K, 2, &shape);
+    return launch_ring_shape<bf16_t, OutT>(shape, X, W, C, M, N, K, ep, stream);
+  }
   return launch_generic<OutT>(X, W, C, M, N, K, ep, stream);
 }
 
@@ -237,6 +246,12 @@ hipError_t gemm_nt(int32_t dtype, const void* X, const void* W, void* C, int64_t
     if (K % 8 != 0) return hipErrorInvalidValue;   // 16-byte operand loads
     if (out_f32) return dispatch_bf16<float>(X, W, C, M, N, K, ep, stream);
     return dispatch_bf16<bf16_t>(X, W, C, M, N, K, ep, stream);
+  }
+  // 2048 x 512, K = 2048: 297 -> 41 us; 512 x 256, K = 1024: 115 -> 10 us
+  if (K % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
+    int shape = 0;
+    ring_estimate(M, N, K, 4, &shape);
+    return launch_ring_shape<float, float>(shape, X, W, C, M, N, K, ep, stream);
   }
   dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
   hipLaunchKernelGGL(gemm_f32_nt_kernel<float>, grid, dim3(256), 0, stream, (const float*)X, (const float*)W,

@@ -122,6 +122,13 @@ __device__ __forceinline__ void epilogue4_static(float v[4], const float bias4[4
   store4(C + off, v);
 }
 
+// Kernel for launches that do not fill the chip (gemm_ring.hip): its estimated time in microseconds and the tile
+// shape to launch, and the launch.  Needs K a whole number of 16-byte chunks and 16-byte aligned X and W.
+double ring_estimate(int64_t M, int64_t N, int64_t K, int elem, int* shape);
+template <typename T, typename OutT>
+hipError_t launch_ring_shape(int shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
+                             const EpiDev& ep, hipStream_t stream);
+
 // compile-time loop: f(integral_constant<int, I>) for I in [0, N)
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -164,12 +171,12 @@ __device__ __forceinline__ void build_epilogue_tables(float2* gelu_tab) {
 // What a workgroup does with its finished accumulators: acc[a][b] is the 32x32 block at rows (wm * TM + b) * 32,
 // columns (wn * TN + a) * 32 of the BM x BN tile at (m0, n0).  smem: the two operand stages (free after the K loop)
 // followed by the table of build_epilogue_tables.
-template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI>
+template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS = 2>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem, OutT* __restrict__ C, int64_t M,
                                               int64_t N, const EpiDev& ep, int64_t m0, int64_t n0) {
   constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, NW = WGM * WGN;
   constexpr int STAGE = (BM + BN) * 8;
-  float2* gelu_tab = (float2*)(smem + 2 * STAGE);
+  float2* gelu_tab = (float2*)(smem + NS * STAGE);
   auto gelu_grad_tab = [&](float x) {
     const float u = __builtin_amdgcn_fmed3f(fmaf(x, 64.0f, 512.0f), 0.0f, 1023.996f);
     const float2 e = gelu_tab[(int)u];
@@ -442,7 +449,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   }
 }
 
-template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI>
+template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, OutT* __restrict__ C, int64_t M, int64_t N,
     int64_t K, EpiDev ep, int32_t tiles_m, int32_t tiles_n, int32_t group_m) {
@@ -451,7 +458,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
   constexpr int STAGE = (BM + BN) * 8;                          // uint4 per LDS stage
   static_assert(G % NW == 0 && GPW <= 32, "tile / wave mismatch");
   extern __shared__ uint4 smem[];
-  build_epilogue_tables<NW, OutT, EPI>((float2*)(smem + 2 * STAGE));
+  build_epilogue_tables<NW, OutT, EPI>((float2*)(smem + NS * STAGE));
   const int64_t tile = xcd_contiguous(blockIdx.x, (int64_t)tiles_m * tiles_n);
   const int64_t per_group = (int64_t)group_m * tiles_n;
   const int64_t grp = tile / per_group;
@@ -542,44 +549,53 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
   using I3 = std::integral_constant<int, 3>;
 
   const int64_t nk = k_len / 64;
-  // prologue: stage 0 completely; of stage 1 the share the block after a barrier issues
-  static_for<0, GPW>([&](auto i) { issue1(i, 0, 0); });
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // prologue: stages 0 .. NS-2 completely; of stage NS-1 the share the block after a barrier issues
+  static_assert(GPW * (NS - 2) < 64, "vmcnt holds six bits");
+  constexpr int LATER = GPW * (NS - 2);   // copies of a wave that may stay on their way when the next stage is needed
+  static_for<0, NS - 1>([&](auto st) {
+    if (st < nk) static_for<0, GPW>([&](auto i) { issue1(i, st, st * 64); });
+  });
+  if (nk >= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
-  if (nk > 1) {
+  if (nk > NS - 1) {
     static_for<0, MF>([&](auto mi) {
-      if constexpr (mi % EVERY == 0 && mi / EVERY < GPW) issue1(std::integral_constant<int, mi / EVERY>{}, 1, 64);
+      if constexpr (mi % EVERY == 0 && mi / EVERY < GPW)
+        issue1(std::integral_constant<int, mi / EVERY>{}, NS - 1, (NS - 1) * 64);
     });
   }
   load_frags(0, smem, 0);
+  static_assert((NS & (NS - 1)) == 0, "stage of a K step by mask");
   for (int64_t kt = 0; kt < nk; ++kt) {
-    const int cur = (int)(kt & 1);
+    const int cur = (int)(kt & (NS - 1)), last = (cur + NS - 1) & (NS - 1);
     const uint4* sc = smem + cur * STAGE;
-    const uint4* sn = smem + (cur ^ 1) * STAGE;
-    const bool more1 = kt + 1 < nk, more2 = kt + 2 < nk;
+    const uint4* sn = smem + ((cur + 1) & (NS - 1)) * STAGE;
+    const bool more1 = kt + NS - 1 < nk, more2 = kt + NS < nk;
+    const int64_t k_last = (kt + NS - 1) * 64;
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): fragments fetched during the previous MFMA block
     load_frags(1, sc, 1);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I1{}, I0{}, more1, cur ^ 1, (kt + 1) * 64);
+    mfma_block(I1{}, I0{}, more1, last, k_last);
     __builtin_amdgcn_sched_barrier(0);
     load_frags(0, sc, 2);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I2{}, I1{}, more1, cur ^ 1, (kt + 1) * 64);
+    mfma_block(I2{}, I1{}, more1, last, k_last);
     __builtin_amdgcn_sched_barrier(0);
     load_frags(1, sc, 3);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I3{}, I0{}, more1, cur ^ 1, (kt + 1) * 64);
+    mfma_block(I3{}, I0{}, more1, last, k_last);
     __builtin_amdgcn_sched_barrier(0);
     // every wave holds the last fragments of this stage in registers and the next stage has landed
-    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    if (NS > 2 && more1) __builtin_amdgcn_s_waitcnt(0x0070 | (LATER & 15) | (LATER >> 4 << 14));   // vmcnt(LATER) lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x0070);                                                        // vmcnt(0) lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
-    if (more1) load_frags(0, sn, 0);
+    if (kt + 1 < nk) load_frags(0, sn, 0);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I0{}, I1{}, more2, cur, (kt + 2) * 64);   // stage `cur` is free: start refilling it
+    mfma_block(I0{}, I1{}, more2, cur, (kt + NS) * 64);   // stage `cur` is free: start refilling it
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  tile_epilogue<WGM, WGN, TM, TN, OutT, EPI>(acc, smem, C, M, N, ep, m0, n0);
+  tile_epilogue<WGM, WGN, TM, TN, OutT, EPI, NS>(acc, smem, C, M, N, ep, m0, n0);
 }
 
 // The 256x256 tile on FOUR waves (one per SIMD, wave tile 128x128, accumulators in 256 registers): per K step the
@@ -762,9 +778,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
 
 template <typename OutT, typename Kern>
 hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, const void* X, const void* W, void* C,
-                        int64_t M, int64_t N, int64_t K, const EpiDev& ep, int32_t splits, hipStream_t stream) {
+                        int64_t M, int64_t N, int64_t K, const EpiDev& ep, int32_t splits, hipStream_t stream, int stages = 2) {
   const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const size_t lds = (size_t)2 * (BM + BN) * 8 * sizeof(uint4) + 8192;   // two stages + the GELU table
+  const size_t lds = (size_t)stages * (BM + BN) * 8 * sizeof(uint4) + 8192;   // operand stages + the GELU table
   if (!*attr_set) {   // raise the dynamic-LDS limit once per instantiation
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -779,6 +795,9 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 
 // Main kernel for one epilogue combination.  Tile shapes: 256x256 (the four-wave kernel above, wave tile 128x128),
 // 256x192 (8 waves as 4x2, wave tile 64x96), both one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
+// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two: with two, one K step
+// is in flight and costs a memory latency (0.85 to 1.1 us per step; with four 0.61: 2048 x 2048, K = 8192 117 -> 88 us,
+// 333 x 8192, K = 2048 37.6 -> 25.8 us).
 // A launch takes ceil(workgroups / resident workgroups) rounds of (K steps + a fixed cost of about 4 steps); the
 // shape with the least estimated time rounds x steps x area in flight per CU / efficiency is taken.  Efficiencies
 // are measured on MI355X relative to the 256x256 tile (0.96 and 0.85); a shape that leaves partial tiles along N
@@ -793,11 +812,11 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 template <typename OutT, int EPI>
 hipError_t launch_fast(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
                        hipStream_t stream) {
-  static bool attr_big = false, attr_wide = false, attr_small = false;
+  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false;
   struct Shape { int bm, bn, resident, eff100; } const shapes[3] = {{256, 256, 256, 100}, {256, 192, 256, 104},
                                                                       {128, 128, 512, 118}};
   int best = 0, best_splits = 1;
-  int64_t best_cost = -1;
+  int64_t best_cost = -1, best_wgs = 0;
   for (int i = 0; i < 3; ++i) {
     const Shape& sh = shapes[i];
     const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
@@ -808,11 +827,11 @@ hipError_t launch_fast(const void* X, const void* W, void* C, int64_t M, int64_t
       if (splits > 1 && (K % (128 * splits) != 0 || K / (128 * splits) < 8 || tiles * splits > sh.resident)) break;
       const int64_t wgs = tiles * splits;
       const int64_t rounds = (wgs + sh.resident - 1) / sh.resident;
-      const int64_t steps = K / (64 * splits) + 4;
-      // area in flight per CU x relative cost: a 128x128 workgroup that has its CU to itself runs 1.4x as fast as
-      // one of a pair, not twice
-      int64_t per_step = (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
-      if (i == 2 && wgs <= 256) per_step = (int64_t)sh.bm * sh.bn * 165;
+      const bool alone = i == 2 && wgs <= 256;   // a 128x128 workgroup that has its CU, and four stages, to itself
+      const int64_t steps = K / (64 * splits) + (alone ? 6 : 4);
+      // area in flight per CU x relative cost
+      const int64_t per_step = alone ? (int64_t)sh.bm * sh.bn * 141
+                                     : (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
       int64_t cost = rounds * steps * per_step;
       if (N % sh.bn) cost += cost * 3 / 10;
       // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate
@@ -821,15 +840,24 @@ hipError_t launch_fast(const void* X, const void* W, void* C, int64_t M, int64_t
         best_cost = cost;
         best = i;
         best_splits = splits;
+        best_wgs = wgs;
       }
     }
   }
+  // 3.8 M units of the estimate are a microsecond (256x256 tile: 1.72 us per K step).  The ring kernel takes what leaves
+  // the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192 122 -> 30 us (four stages: 81).
+  int ring_shape = 0;
+  if (ring_estimate(M, N, K, 2, &ring_shape) < (double)best_cost / 3.8e6)
+    return launch_ring_shape<bf16_t, OutT>(ring_shape, X, W, C, M, N, K, ep, stream);
   if (best == 0)
     return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
   if (best == 1)
-    return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI>, 256, 192, 512, &attr_wide, X, W, C, M, N, K, ep,
+    return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI, 2>, 256, 192, 512, &attr_wide, X, W, C, M, N, K, ep,
                               1, stream);
-  return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI>, 128, 128, 256, &attr_small, X, W, C, M, N, K, ep,
+  if (best_wgs <= 256)
+    return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 4>, 128, 128, 256, &attr_deep, X, W, C, M, N, K, ep,
+                              best_splits, stream, 4);
+  return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 2>, 128, 128, 256, &attr_small, X, W, C, M, N, K, ep,
                             best_splits, stream);
 }
 

@@ -148,6 +148,46 @@ def test_gemm_training_epilogues(dtype, M, N, K):
             pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out.data_ptr(), M, N, K, dact_in=dU.data_ptr(), **bad)
 
 
+# Grids that leave CUs idle: every tile of the ring kernel (32x32, 32x64, 64x64, 128x64) with ragged edges, columns in
+# fours and not, K shorter than one step, fewer steps than waves, a last step that is one chunk long; then the 128x128
+# tile with four LDS stages on one to five K steps.  fp32 sums of K terms: 1e-5 of the largest value.
+@pytest.mark.parametrize("dtype,M,N,K", [
+    ("bf16", 1, 1, 8), ("bf16", 33, 36, 72), ("bf16", 31, 770, 1032), ("bf16", 128, 2300, 776), ("bf16", 333, 772, 3080),
+    ("bf16", 450, 2044, 1992), ("bf16", 1659, 764, 3072), ("f32", 1, 3, 4), ("f32", 65, 99, 36), ("f32", 97, 1500, 260),
+    ("f32", 500, 772, 2052), ("bf16", 1999, 2040, 64), ("bf16", 1999, 2040, 128), ("bf16", 1999, 2040, 192),
+    ("bf16", 1999, 2040, 256), ("bf16", 1999, 2040, 320)])
+def test_gemm_grids_that_do_not_fill_the_chip(dtype, M, N, K):
+    pf, dev = _mods()
+    md = _md(dtype)
+    rng = np.random.default_rng(M + N + K)
+    X, W = _rand(rng, (M, K), dtype), _rand(rng, (N, K), dtype, 0.05)
+    bias, R = _rand(rng, (N,), dtype), _rand(rng, (M, N), dtype)
+    dX, dW, dB, dR = (dev.storage_tensor(a, md) for a in (X, W, bias, R))
+    ref0 = X.astype(np.float64) @ W.astype(np.float64).T
+    tol = 1e-2 if dtype == "bf16" else 1e-5
+    guard = dev.empty_storage((M + 1, N), md)          # one extra row behind C: must stay untouched
+    guard.zero_()
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), guard.data_ptr(), M, N, K, bias=dB.data_ptr(),
+                  resid=dR.data_ptr())
+    torch.cuda.synchronize()
+    g = dev.read_storage(guard, md)
+    assert rel_err(g[:M], ref0 + bias + R) < tol and not g[M].any()
+    pre = dev.empty_storage((M, N), md)
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), guard.data_ptr(), M, N, K, bias=dB.data_ptr(), gelu=1,
+                  preact_out=pre.data_ptr())
+    torch.cuda.synchronize()
+    assert rel_err(dev.read_storage(pre, md), ref0 + bias) < tol
+    assert rel_err(dev.read_storage(guard, md)[:M], ot.gelu(ref0 + bias)) < tol
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), guard.data_ptr(), M, N, K, dact_in=dR.data_ptr())
+    torch.cuda.synchronize()
+    assert rel_err(dev.read_storage(guard, md)[:M], ref0 * ot.gelu_grad(R.astype(np.float64))) < tol
+    acc = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), acc.data_ptr(), M, N, K, out_f32=1, accumulate=1)
+    torch.cuda.synchronize()
+    assert rel_err(acc.cpu().numpy(), 2 * ref0) < 1e-5
+
+
 # Weight-gradient shapes: small result, K = all tokens; C holds an earlier gradient that must be kept.
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 8192), (3072, 1024, 8192), (1000, 520, 4096), (256, 256, 2048)])
 def test_gemm_accumulate_long_k(M, N, K):
