@@ -416,6 +416,68 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       return;
     }
   }
+  // fp32 output (weight gradients): the lanes of a wave hold 32 rows, so storing from registers touches 32 rows in
+  // 32-byte pieces per instruction, once to read and once to write where C accumulates.  Instead each wave passes its
+  // 32-row blocks one by one through a corner of LDS of its own (no barrier) and reads and writes C in whole rows of
+  // its tile, 16 bytes a lane; a block's values of C are requested before it is staged.  Rows and
+  // columns past C's end are dropped by the buffer's bounds, as above.  8192 x 32768, K = 2048 accumulated: 1446 -> 1172 us
+  // (1 GiB read and 1 GiB written).
+  if constexpr (std::is_same<OutT, float>::value) {
+    if ((N & 3) == 0 && ((uintptr_t)C & 15) == 0 && N <= (1 << 20)) {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      constexpr int UNITS = TN * 8, PIECES = TN * 4;            // 16-byte units of a row; 1 KB pieces of a block
+      constexpr int XOR = UNITS % 16 == 0 ? 15 : 7;
+      static_assert(32 * UNITS * NW <= 2 * STAGE, "a block per wave fits the operand stages");
+      constexpr int OUTSIDE = 0x7fffff00;
+      float4* st = (float4*)smem + wave * 32 * UNITS;
+      const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);   // scalar buffers
+      const int64_t wm0 = m0 + wmu * TM * 32, wn0 = n0 + wnu * TN * 32;
+      const int ncols = (int)(N - wn0 < TN * 32 ? (N > wn0 ? N - wn0 : 0) : TN * 32);
+      const int nrows = (int)(M - wm0 < TM * 32 ? (M > wm0 ? M - wm0 : 0) : TM * 32);
+      const int row_bytes = (int)N * 4;
+      // block b of the wave: a buffer from its first row to its last inside C
+      auto block_rsrc = [&](int b) {
+        const int rows = nrows - b * 32 < 32 ? nrows - b * 32 : 32;
+        const bool any = ncols > 0 && rows > 0;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(any ? (float*)C + (wm0 + b * 32) * N + wn0 : (float*)C), 0,
+                                                 any ? (rows - 1) * row_bytes + ncols * 4 : 0, 0x00020000);
+      };
+      int voff[PIECES], lds_at[PIECES];
+#pragma unroll
+      for (int i = 0; i < PIECES; ++i) {
+        const int e = i * 64 + lane, row = e / UNITS, unit = e % UNITS;
+        voff[i] = unit * 4 < ncols ? row * row_bytes + unit * 16 : OUTSIDE;
+        lds_at[i] = row * UNITS + (unit ^ (row & XOR));
+      }
+      u32x4 cin[PIECES];
+      // (the last barrier of the K loop comes after every wave's last read of the operand stages)
+      asm volatile("" ::: "memory");
+      static_for<0, TM>([&](auto b) {
+        const __amdgpu_buffer_rsrc_t rsrc = block_rsrc(b);
+        if constexpr (EPI & E_ACC) {
+#pragma unroll
+          for (int i = 0; i < PIECES; ++i) cin[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff[i], 0, 0);
+        }
+        static_for<0, TN>([&](auto a) {
+          static_for<0, 4>([&](auto rg) {
+            st[lr * UNITS + ((a * 8 + rg * 2 + lk) ^ (lr & XOR))] =
+                make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
+          });
+        });
+        asm volatile("" ::: "memory");   // other lanes' values: a wave's LDS instructions execute in program order
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+          const float4 t = st[lds_at[i]];
+          f32x4 v = {t.x, t.y, t.z, t.w};
+          if constexpr (EPI & E_ACC) v += __builtin_bit_cast(f32x4, cin[i]);
+          const u32x4 w = __builtin_bit_cast(u32x4, v);
+          __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, voff[i], 0, 0);
+        }
+        asm volatile("" ::: "memory");
+      });
+      return;
+    }
+  }
   if (interior) {
     static_for<0, TN>([&](auto a) {
       float bias4[4][4] = {};
