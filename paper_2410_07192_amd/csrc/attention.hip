@@ -9,8 +9,9 @@
 // O^T = V^T P^T.  K and V tiles go global -> LDS directly, row-major as they lie in memory; the V^T "A" operand
 // comes out of the row-major V tile through the transposing LDS load (ds_read_b64_tr_b16), two per fragment.
 //
-// Generic path (fp32, or any d_head in {8,16,32,64,128}): one thread per query, keys staged in LDS,
-// online softmax key by key.  Used for the small fp32 parity workload and odd head sizes.
+// fp32, d_head 32, 64 or 128: fp32 MFMAs, 32 queries per workgroup (attn_fwd_f32_kernel).
+// Generic path (other d_head in {8,16,32,64,128}): one thread per query, keys staged in LDS,
+// online softmax key by key.
 #include "pf_kernels.h"
 #include "pf_device.h"
 
@@ -394,6 +395,148 @@ __global__ __launch_bounds__(64) void attn_fwd_generic_kernel(const T* __restric
   }
 }
 
+// fp32, d_head 32 / 64 / 128: the same S^T = K Q^T and O^T = V^T P^T, with 32x32x2 fp32 MFMAs.  A workgroup owns 32 queries
+// of one head; its four waves share the keys, 32 at a time (wave w: tiles w, w + 4, ...), straight from global memory (a
+// head's K and V stay in the caches), and their (maximum, sum, O) meet in LDS.  One thread per query left 128 tokens x 4
+// heads x 4 sequences (d_head 64) to 32 wavefronts, each a serial chain over the keys: 150 us, now 8.2.
+//  * Operand slots (lane half g, element j) of chunk pair kk hold column 8 kk + 4 g + j of K and Q alike.
+//  * A lane ends up with keys 8 (r / 4) + 4 g + r % 4 of ONE query in register r, which is the "B" operand of the r-th
+//    MFMA over the keys; the "A" operand is a row of V read as 32 consecutive floats.
+//  * A key that a query must not see has probability 0, and 0 x V would turn an infinity or NaN of such a V row into a
+//    NaN: masked tiles whose V rows are not all finite take their sum key by key, visible keys only.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
+                                                           float* __restrict__ lse, int32_t S, int32_t h,
+                                                           int32_t causal, float scale) {
+  constexpr int NW = 4, KK = DH / 8, DT = DH / 32, LD = DH + 4;
+  __shared__ __align__(16) float sO[NW][32][LD];   // O of the waves; before that, the slow path's probabilities
+  __shared__ float sM[NW][32], sL[NW][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 31, g = lane >> 5;
+  const int b = blockIdx.z, hd = blockIdx.y, q_blk = blockIdx.x * 32;
+  const int d = h * DH;
+  const int64_t rs = 3 * (int64_t)d;
+  const float* base = qkv + (int64_t)b * S * rs + hd * DH;
+  const int q_row = q_blk + lr;
+  f32x4 fq[KK];
+  {
+    const float* qp = base + (int64_t)(q_row < S ? q_row : S - 1) * rs + g * 4;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) fq[kk] = *(const f32x4*)(qp + kk * 8) * scale;
+  }
+  f32x16 accO[DT];
+#pragma unroll
+  for (int i = 0; i < DT; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accO[i][r] = 0.f;
+  float m = -INFINITY, l = 0.f;   // of the query; l: this lane's share
+  const int last_q = q_blk + 31 < S - 1 ? q_blk + 31 : S - 1;
+  const int k_end = causal ? last_q + 1 : S;
+  for (int k0 = wave * 32; k0 < k_end; k0 += NW * 32) {
+    const float* kp = base + d + (int64_t)(k0 + lr < S ? k0 + lr : S - 1) * rs + g * 4;
+    f32x4 fk[KK];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) fk[kk] = *(const f32x4*)(kp + kk * 8);
+    float fv[DT][16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + 8 * (r >> 2) + 4 * g + (r & 3);
+      const float* vp = base + 2 * d + (int64_t)(key < S ? key : S - 1) * rs + lr;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) fv[dt][r] = vp[dt * 32];
+    }
+    f32x16 accS;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accS[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) accS = __builtin_amdgcn_mfma_f32_32x32x2f32(fk[kk][j], fq[kk][j], accS, 0, 0, 0);
+    const bool masked = k0 + 31 >= S || (causal && k0 + 31 > q_blk);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = k0 + 8 * (r >> 2) + 4 * g + (r & 3);
+      if (masked && (key >= S || (causal && key > q_row))) accS[r] = -INFINITY;
+      mx = fmaxf(mx, accS[r]);
+    }
+    const float m_new = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
+    const float ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __expf(m - ref);   // no reference point yet: exp(-inf) = 0
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      accS[r] = __expf(accS[r] - ref);
+      l += accS[r];
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) accO[dt][r] *= alpha;
+    bool finite = true;
+    if (masked) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) finite = finite && fabsf(fv[dt][r]) < INFINITY;
+    }
+    if (!__any(!finite)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          accO[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(fv[dt][r], accS[r], accO[dt], 0, 0, 0);
+    } else {
+      float* sp = &sO[wave][0][0];   // [key][query], 32 x 32
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sp[(8 * (r >> 2) + 4 * g + (r & 3)) * 32 + lr] = accS[r];
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // within the wave: its LDS instructions execute in order
+      for (int key = k0; key < k0 + 32 && key < k_end; ++key) {
+        if (causal && key > q_row) continue;
+        const float p = sp[(key - k0) * 32 + lr];
+        const float* vp = base + 2 * d + (int64_t)key * rs + 4 * g;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) accO[dt][r] = fmaf(p, vp[dt * 32 + 8 * (r >> 2) + (r & 3)], accO[dt][r]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (g == 0) {
+    sM[wave][lr] = m;
+    sL[wave][lr] = l;
+  }
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg)
+      *(float4*)&sO[wave][lr][dt * 32 + rg * 8 + g * 4] =
+          make_float4(accO[dt][rg * 4], accO[dt][rg * 4 + 1], accO[dt][rg * 4 + 2], accO[dt][rg * 4 + 3]);
+  __syncthreads();
+  for (int e = tid; e < 32 * DH / 4; e += 256) {
+    const int q = e / (DH / 4), c = e % (DH / 4) * 4;
+    if (q_blk + q >= S) break;
+    float mq = sM[0][q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mq = fmaxf(mq, sM[w][q]);
+    const float ref = mq == -INFINITY ? 0.f : mq;
+    float lq = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = __expf(sM[w][q] - ref);   // 0 for a wave that saw no key of this query
+      lq += f * sL[w][q];
+      o += *(const f32x4*)&sO[w][q][c] * f;
+    }
+    const float inv = lq > 0.f ? 1.f / lq : 0.f;
+    *(f32x4*)(out + ((int64_t)b * S + q_blk + q) * d + hd * DH + c) = o * inv;
+    if (lse && c == 0) lse[((int64_t)b * h + hd) * S + q_blk + q] = mq + __logf(lq);
+  }
+}
+
 template <typename T>
 hipError_t launch_generic(const void* qkv, void* out, float* lse, int32_t B, int32_t S, int32_t h, int32_t dh,
                           int32_t causal, hipStream_t st) {
@@ -454,6 +597,16 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
     return hipGetLastError();
   }
   if (dtype == PF_DTYPE_BF16_) return launch_generic<bf16_t>(qkv, out, lse, B, S, h, dh, causal, stream);
+  if ((dh == 32 || dh == 64 || dh == 128) && (((uintptr_t)qkv | (uintptr_t)out) & 15) == 0) {   // 16-byte loads and stores
+    const dim3 grid((unsigned)((S + 31) / 32), (unsigned)h, (unsigned)B), block(256);
+    const float scale = 1.0f / sqrtf((float)dh);
+#define PF_ATT32(D) hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, grid, block, 0, stream, (const float*)qkv, (float*)out, lse, S, h, causal, scale)
+    if (dh == 32) PF_ATT32(32);
+    else if (dh == 64) PF_ATT32(64);
+    else PF_ATT32(128);
+#undef PF_ATT32
+    return hipGetLastError();
+  }
   return launch_generic<float>(qkv, out, lse, B, S, h, dh, causal, stream);
 }
 

@@ -284,6 +284,32 @@ def test_attention(dtype, B, S, h, dh, causal):
     assert np.abs(lse.cpu().numpy() - ref_lse).max() < (2e-2 if dtype == "bf16" else 1e-4)
 
 
+# fp32: 32-key tiles shared by four waves; one query, edges of a tile and of a round of four, waves without a key.  The
+# last token's V row holds an infinity and a NaN: causal queries before it must not notice.  fp32 sums: 1e-5.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,S,h,dh", [(1, 1, 1, 32), (2, 31, 3, 32), (1, 33, 2, 64), (2, 128, 2, 64), (1, 161, 2, 128)])
+def test_attention_fp32_tiles(B, S, h, dh, causal):
+    pf, dev = _mods()
+    md = _md("f32")
+    d = h * dh
+    rng = np.random.default_rng(S + dh)
+    qkv = _rand(rng, (B, S, 3 * d), "f32", 1.5)
+    q64 = qkv.astype(np.float64)
+    q, k, v = (ot.split_heads(q64[..., i * d:(i + 1) * d], h) for i in range(3))
+    ref = ot.merge_heads(ot.attention_probs(q, k, causal) @ v)
+    if causal:
+        qkv[:, -1, 2 * d:2 * d + 2] = (np.inf, np.nan)
+    dq = dev.storage_tensor(qkv, md)
+    out = dev.empty_storage((B, S, d), md)
+    pf.pf_op_attention(md.dtype, dq.data_ptr(), out.data_ptr(), B, S, h, dh, causal)
+    torch.cuda.synchronize()
+    got = dev.read_storage(out, md)
+    if causal:
+        assert np.isinf(got[:, -1, 0]).all() and np.isnan(got[:, -1, 1]).all()
+        got[:, -1, :2] = ref[:, -1, :2]
+    assert rel_err(got, ref) < 1e-5
+
+
 @pytest.mark.parametrize("B,S,h,dh", [(8, 1024, 16, 128), (3, 900, 22, 128), (8, 1024, 16, 64), (4, 1024, 16, 128)])
 def test_attention_where_the_kernel_reorders_causal_blocks(B, S, h, dh):
     # Causal attention at sizes where the kernel hands the query blocks out in an order of its own.  First two cases:
