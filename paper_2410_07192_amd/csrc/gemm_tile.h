@@ -863,7 +863,8 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 // A launch takes ceil(workgroups / resident workgroups) rounds of (K steps + a fixed cost of about 4 steps); the
 // shape with the least estimated time rounds x steps x area in flight per CU / efficiency is taken.  Efficiencies
 // are measured on MI355X relative to the 256x256 tile (0.96 and 0.85); a shape that leaves partial tiles along N
-// pays for their slower epilogue.  E.g. N = 768 or 2304 fills whole rounds with 192-wide tiles but wastes a quarter
+// is charged 30 %
+// (set when edge tiles were stored element by element; not measured again since they take the staged epilogue).  E.g. N = 768 or 2304 fills whole rounds with 192-wide tiles but wastes a quarter
 // of the last round with 256-wide ones, and a 8192 x 1024 result gives every CU work only with the small tile.
 // Accumulating fp32 launches (weight gradients: small M x N, K = all tokens) may split K over up to 8 workgroups
 // per 128x128 tile while that fills idle CUs and leaves each >= 8 K steps; the slices add into C with fp32 atomics
