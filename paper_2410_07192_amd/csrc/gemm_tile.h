@@ -91,37 +91,6 @@ __device__ __forceinline__ void epilogue4_scalar(float v[4], int64_t m, int64_t 
 // compiler can batch them); other combinations run on the generic kernel.
 enum : int { E_BIAS = 1, E_GELU = 2, E_RESID = 4, E_DACT = 8, E_PRE = 16, E_ACC = 32 };
 
-template <int EPI, typename OutT>
-__device__ __forceinline__ void epilogue4_static(float v[4], const float bias4[4], int64_t off, OutT* C,
-                                                 const EpiDev& ep) {
-  float t[4];
-  if constexpr (EPI & E_BIAS) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += bias4[j];
-  }
-  if constexpr (EPI & E_PRE) store4((bf16_t*)ep.preact_out + off, v);
-  if constexpr (EPI & E_GELU) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = gelu_bf16_f(v[j]);
-  }
-  if constexpr (EPI & E_DACT) {
-    load4((const bf16_t*)ep.dact_in + off, t);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] *= gelu_grad_f(t[j]);
-  }
-  if constexpr (EPI & E_RESID) {
-    load4((const bf16_t*)ep.resid + off, t);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += t[j];
-  }
-  if constexpr (EPI & E_ACC) {
-    load4(C + off, t);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] += t[j];
-  }
-  store4(C + off, v);
-}
-
 // Kernel for launches that do not fill the chip (gemm_ring.hip): its estimated time in microseconds and the tile
 // shape to launch, and the launch.  Needs K a whole number of 16-byte chunks and 16-byte aligned X and W.
 double ring_estimate(int64_t M, int64_t N, int64_t K, int elem, int* shape);
@@ -226,7 +195,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
     static_assert(!(EPI & E_DACT) || EPI == E_DACT, "GELU' multiplies the plain product only");
     const bool aligned16 = ((N & 7) == 0) && ((((uintptr_t)C | (uintptr_t)ep.resid | (uintptr_t)ep.preact_out |
                                                  (uintptr_t)ep.dact_in) & 15) == 0);
-    if (aligned16 && N <= (1 << 21)) {
+    if (interior && aligned16 && N <= (1 << 21)) {
       constexpr int SLOTS = BN / 8, NT = 64 * NW, PER = BM * BN / 8 / NT;
       // 16-byte slot of a row, moved per row so that the lanes of a wave (32 rows, same column group) spread
       // over the banks: XOR when the slot count is a power of two, rotation otherwise
@@ -237,33 +206,16 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       uint2* st8 = (uint2*)smem;
       // Piece i of a thread on the way out (and of the residual on the way in): 16 bytes of row i * RP + r0 when the
       // threads of a workgroup cover whole rows.  The tile's corner is the base of a raw buffer, the thread's place a
-      // 32-bit offset computed once, the rows of piece i added to it (N <= 2^21 keeps all of it below 2^31): no
+      // 32-bit offset computed once, the rows of piece i a scalar offset (N <= 2^21 keeps all of it below 2^31): no
       // 64-bit vector arithmetic per piece, which is what a lone wave per SIMD has least of.
-      // Tiles that stick out of C take the same route: the buffer ends with C's last row, and a thread whose eight
-      // columns lie past N has an offset beyond it, so the hardware drops its stores and its loads deliver zeros.
-      // (Edge tiles used to go element by element with their checks, 25 to 85 us per launch: 1659 x 768, K = 768 took
-      // 38 / 55 / 106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.)
       typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
       constexpr bool ROWWISE = NT % SLOTS == 0;
       constexpr int RP = ROWWISE ? NT / SLOTS : 1;
       const int r0 = tid / SLOTS, slot0 = tid % SLOTS;
-      constexpr int OUTSIDE = 0x7fffff00 - 256;   // past every buffer, with the rows added as well
-      const int ncols = (int)(N - n0 < BN ? N - n0 : BN), nrows = (int)(M - m0 < BM ? M - m0 : BM);
-      const int records = (int)((nrows - 1) * N + ncols) * 2, row_bytes = (int)N * 2;
-      // Without whole rows (24 slots on 512 threads) a thread's slot repeats after PERIOD pieces.
-      constexpr int PERIOD = ROWWISE ? 1 : 3;
-      static_assert((PERIOD * NT) % SLOTS == 0, "a thread's pieces repeat their slot");
-      constexpr int PERIOD_ROWS = PERIOD * NT / SLOTS;
-      int voff[PERIOD];
-#pragma unroll
-      for (int i = 0; i < PERIOD; ++i) {
-        const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
-        voff[i] = slot * 8 < ncols ? row * row_bytes + slot * 16 : OUTSIDE;
-      }
+      const int voff = (int)((r0 * N + slot0 * 8) * 2);
       auto tile_rsrc = [&](const void* p) {
-        return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + m0 * N + n0), 0, records, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)p + m0 * N + n0), 0, 0x7fffffff, 0x00020000);
       };
-      auto piece_off = [&](int i) { return (int)((unsigned)voff[i % PERIOD] + (unsigned)(i / PERIOD * PERIOD_ROWS * row_bytes)); };
       auto lds_at = [&](int i) {
         if constexpr (ROWWISE) {
           const int row = i * RP + r0;
@@ -273,29 +225,44 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
           return row * SLOTS + swz(slot, row);
         }
       };
-      auto piece_load = [&](__amdgpu_buffer_rsrc_t rs, int i) -> uint4 {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, piece_off(i), 0, 0);
-        return make_uint4(v[0], v[1], v[2], v[3]);
+      auto piece_load = [&](__amdgpu_buffer_rsrc_t rs, const void* p, int i) -> uint4 {
+        if constexpr (ROWWISE) {
+          const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, (int)(i * RP * N * 2), 0);
+          return make_uint4(v[0], v[1], v[2], v[3]);
+        } else {
+          const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
+          return *(const uint4*)((const bf16_t*)p + (m0 + row) * N + n0 + slot * 8);
+        }
       };
-      auto piece_store = [&](__amdgpu_buffer_rsrc_t rs, int i, uint4 v) {
-        const u32x4 w = {v.x, v.y, v.z, v.w};
-        __builtin_amdgcn_raw_buffer_store_b128(w, rs, piece_off(i), 0, 0);
+      auto piece_store = [&](__amdgpu_buffer_rsrc_t rs, void* p, int i, uint4 v) {
+        if constexpr (ROWWISE) {
+          const u32x4 w = {v.x, v.y, v.z, v.w};
+          __builtin_amdgcn_raw_buffer_store_b128(w, rs, voff, (int)(i * RP * N * 2), 0);
+        } else {
+          const int q = i * NT + tid, row = q / SLOTS, slot = q % SLOTS;
+          *(uint4*)((bf16_t*)p + (m0 + row) * N + n0 + slot * 8) = v;
+        }
       };
       if constexpr (EPI & E_DACT) {
         // tile of the saved pre-activation: eight 16-byte pieces per thread at a time (more would not fit beside
         // the accumulators), then every lane picks up the values of its own accumulator elements
         constexpr int CH = PER < 8 ? PER : 8;
-        const __amdgpu_buffer_rsrc_t drsrc = tile_rsrc(ep.dact_in);
 #pragma unroll
         for (int i0 = 0; i0 < PER; i0 += CH) {
           uint4 t[CH];
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            if (i0 + i < PER) t[i] = piece_load(drsrc, i0 + i);
+            if (i0 + i < PER) {
+              const int q = (i0 + i) * NT + tid, row = q / SLOTS, slot = q % SLOTS;
+              t[i] = *(const uint4*)((const bf16_t*)ep.dact_in + (m0 + row) * N + n0 + slot * 8);
+            }
           }
 #pragma unroll
           for (int i = 0; i < CH; ++i) {
-            if (i0 + i < PER) smem[lds_at(i0 + i)] = t[i];
+            if (i0 + i < PER) {
+              const int q = (i0 + i) * NT + tid, row = q / SLOTS, slot = q % SLOTS;
+              smem[row * SLOTS + swz(slot, row)] = t[i];
+            }
           }
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -316,24 +283,14 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();   // everyone has its values: the tile's place in LDS is free again
       }
-      // the bias of the tile's columns as a buffer of its own: columns past N read zeros
-      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      const __amdgpu_buffer_rsrc_t brsrc =
-          __builtin_amdgcn_make_buffer_rsrc((void*)((const bf16_t*)ep.bias + n0), 0, ncols * 2, 0x00020000);
-      const int boff = (wn * TN * 32 + lk * 4) * 2;
       // accumulators (+ bias) (-> GELU) -> bf16 -> LDS in the swizzled row-major layout
       auto stage_tile = [&](auto with_gelu) {
         static_for<0, TN>([&](auto a) {
           float bias4[4][4] = {};
           if constexpr (EPI & E_BIAS) {
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-              const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(brsrc, boff + (a * 32 + rg * 8) * 2, 0, 0);
-              bias4[rg][0] = bf16_bits_to_f32(t[0] & 0xffffu);
-              bias4[rg][1] = bf16_bits_to_f32(t[0] >> 16);
-              bias4[rg][2] = bf16_bits_to_f32(t[1] & 0xffffu);
-              bias4[rg][3] = bf16_bits_to_f32(t[1] >> 16);
-            }
+            for (int rg = 0; rg < 4; ++rg)
+              load4((const bf16_t*)ep.bias + n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4, bias4[rg]);
           }
           static_for<0, TM>([&](auto b) {
             const int row = (wm * TM + b) * 32 + lr;
@@ -375,7 +332,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
         __builtin_amdgcn_s_barrier();
         const __amdgpu_buffer_rsrc_t prsrc = tile_rsrc(ep.preact_out);
 #pragma unroll
-        for (int i = 0; i < PER; ++i) piece_store(prsrc, i, smem[lds_at(i)]);
+        for (int i = 0; i < PER; ++i) piece_store(prsrc, ep.preact_out, i, smem[lds_at(i)]);
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
       }
@@ -386,12 +343,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       const __amdgpu_buffer_rsrc_t rrsrc = tile_rsrc((EPI & E_RESID) ? ep.resid : (const void*)C);
       if constexpr (EPI & E_RESID) {
 #pragma unroll
-        for (int i = 0; i < EARLY; ++i) rres[i] = piece_load(rrsrc, i);
+        for (int i = 0; i < EARLY; ++i) rres[i] = piece_load(rrsrc, ep.resid, i);
       }
       stage_tile(std::integral_constant<bool, (EPI & E_GELU) != 0>{});
       if constexpr (EPI & E_RESID) {   // the accumulators are dead now: the rest of the residual tile
 #pragma unroll
-        for (int i = EARLY; i < PER; ++i) rres[i] = piece_load(rrsrc, i);
+        for (int i = EARLY; i < PER; ++i) rres[i] = piece_load(rrsrc, ep.resid, i);
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);
       __builtin_amdgcn_s_barrier();
@@ -411,104 +368,139 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
           }
           v = make_uint4(ow[0], ow[1], ow[2], ow[3]);
         }
-        piece_store(crsrc, i, v);
+        piece_store(crsrc, C, i, v);
       }
       return;
     }
   }
-  // fp32 output (weight gradients): the lanes of a wave hold 32 rows, so storing from registers touches 32 rows in
-  // 32-byte pieces per instruction, once to read and once to write where C accumulates.  Instead each wave passes its
-  // 32-row blocks one by one through a corner of LDS of its own (no barrier) and reads and writes C in whole rows of
-  // its tile, 16 bytes a lane; a block's values of C are requested before it is staged.  Rows and
-  // columns past C's end are dropped by the buffer's bounds, as above.  8192 x 32768, K = 2048 accumulated: 1446 -> 1172 us
-  // (1 GiB read and 1 GiB written).
-  if constexpr (std::is_same<OutT, float>::value) {
-    if ((N & 3) == 0 && ((uintptr_t)C & 15) == 0 && N <= (1 << 20)) {
-      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-      constexpr int UNITS = TN * 8, PIECES = TN * 4;            // 16-byte units of a row; 1 KB pieces of a block
-      constexpr int XOR = UNITS % 16 == 0 ? 15 : 7;
-      static_assert(32 * UNITS * NW <= 2 * STAGE, "a block per wave fits the operand stages");
-      constexpr int OUTSIDE = 0x7fffff00;
-      float4* st = (float4*)smem + wave * 32 * UNITS;
-      const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);   // scalar buffers
-      const int64_t wm0 = m0 + wmu * TM * 32, wn0 = n0 + wnu * TN * 32;
-      const int ncols = (int)(N - wn0 < TN * 32 ? (N > wn0 ? N - wn0 : 0) : TN * 32);
-      const int nrows = (int)(M - wm0 < TM * 32 ? (M > wm0 ? M - wm0 : 0) : TM * 32);
-      const int row_bytes = (int)N * 4;
-      // block b of the wave: a buffer from its first row to its last inside C
-      auto block_rsrc = [&](int b) {
-        const int rows = nrows - b * 32 < 32 ? nrows - b * 32 : 32;
-        const bool any = ncols > 0 && rows > 0;
-        return __builtin_amdgcn_make_buffer_rsrc((void*)(any ? (float*)C + (wm0 + b * 32) * N + wn0 : (float*)C), 0,
-                                                 any ? (rows - 1) * row_bytes + ncols * 4 : 0, 0x00020000);
-      };
-      int voff[PIECES], lds_at[PIECES];
+  // Everything else (fp32 results, bf16 tiles that stick out of C, operands or rows that are not aligned): the lanes of a
+  // wave hold 32 rows, so going through memory from the registers would touch 32 rows in small pieces per instruction.
+  // Instead each wave passes its 32-row blocks one by one, still in fp32, through a corner of LDS of its own (no barrier)
+  // and goes through C and the other operands of the epilogue in whole rows of its tile.  A bf16 element takes the steps of
+  // epilogue4_scalar: fp32, rounded once at the end, the formulas of GELU and GELU' (the staged route above rounds product +
+  // bias before it adds the residual).
+  //  * 16-byte pieces where rows and operands are aligned to them; what a block needs from memory is requested before it is
+  //    staged.  Rows and columns past C's end are dropped by the buffers' bounds: loads deliver zeros, stores go nowhere.
+  //    8192 x 32768, K = 2048 accumulated into fp32: 1446 us from the registers, 1172 this way (1 GiB read, 1 GiB written).
+  //    From the registers a ragged bf16 result took 25 to 85 us longer than a whole one: 1659 x 768, K = 768 38 / 55 /
+  //    106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.
+  //  * otherwise four columns at a time, element by element where they don't come in fours.
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  constexpr bool F32 = std::is_same<OutT, float>::value;
+  constexpr int CE = 16 / (int)sizeof(OutT);                // columns of a 16-byte piece
+  constexpr int UNITS = TN * 8;                             // 16-byte units of a row in LDS
+  constexpr int SLOTS = TN * 32 / CE, PIECES = SLOTS / 2;   // pieces of a row; 1 KB wave instructions of a block
+  constexpr int XOR = UNITS % 16 == 0 ? 15 : 7;
+  constexpr int OUTSIDE = 0x7fffff00;                       // past every buffer
+  static_assert(32 * UNITS * NW <= 2 * STAGE, "a block per wave fits the operand stages");
+  static_assert(!F32 || (EPI & ~E_ACC) == 0, "fp32 results have no epilogue but the sum");
+  float4* st = (float4*)smem + wave * 32 * UNITS;
+  const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);   // scalar buffers
+  const int64_t wm0 = m0 + wmu * TM * 32, wn0 = n0 + wnu * TN * 32;
+  uintptr_t ptrs = (uintptr_t)C;
+  if constexpr (EPI & E_BIAS) ptrs |= (uintptr_t)ep.bias;
+  if constexpr (EPI & E_RESID) ptrs |= (uintptr_t)ep.resid;
+  if constexpr (EPI & E_DACT) ptrs |= (uintptr_t)ep.dact_in;
+  if constexpr (EPI & E_PRE) ptrs |= (uintptr_t)ep.preact_out;
+  // (the last barrier of the K loop comes after every wave's last read of the operand stages)
+  auto stage_block = [&](auto b) {
+    asm volatile("" ::: "memory");   // other lanes' values: a wave's LDS instructions execute in program order
+    static_for<0, TN>([&](auto a) {
+      static_for<0, 4>([&](auto rg) {
+        float4 t = make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
+        // (copied out one register each: as four-register operands of the LDS store, next to the staged route's reads, the
+        // 256 accumulators of the four-wave kernel made the allocator spill 80 of them on every tile)
+        if constexpr (!F32) asm("" : "+v"(t.x), "+v"(t.y), "+v"(t.z), "+v"(t.w));
+        st[lr * UNITS + ((a * 8 + rg * 2 + lk) ^ (lr & XOR))] = t;
+      });
+    });
+    asm volatile("" ::: "memory");
+  };
+  if (N % CE == 0 && (ptrs & 15) == 0 && N <= (1 << 20)) {
+    const int ncols = (int)(N - wn0 < TN * 32 ? (N > wn0 ? N - wn0 : 0) : TN * 32);
+    const int nrows = (int)(M - wm0 < TM * 32 ? (M > wm0 ? M - wm0 : 0) : TM * 32);
+    const int row_bytes = (int)N * (int)sizeof(OutT);
+    // block b of the wave in an array of C's layout: a buffer from its first row to its last inside C
+    auto block_rsrc = [&](const void* p, int b) {
+      const int rows = nrows - b * 32 < 32 ? nrows - b * 32 : 32;
+      const bool any = ncols > 0 && rows > 0;
+      return __builtin_amdgcn_make_buffer_rsrc((void*)(any ? (const OutT*)p + (wm0 + b * 32) * N + wn0 : (const OutT*)p), 0,
+                                               any ? (rows - 1) * row_bytes + ncols * (int)sizeof(OutT) : 0, 0x00020000);
+    };
+    int voff[PIECES], lds_at[PIECES];
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) {
+      const int e = i * 64 + lane, row = e / SLOTS, slot = e % SLOTS;
+      voff[i] = slot * CE < ncols ? row * row_bytes + slot * 16 : OUTSIDE;
+      lds_at[i] = row * UNITS + ((slot * (CE / 4)) ^ (row & XOR));   // second unit of a bf16 piece: this ^ 1
+    }
+    u32x4 in[PIECES], bias[PIECES];   // in: C, the residual or the saved pre-activation
+    if constexpr (EPI & E_BIAS) {
+      const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)((const OutT*)ep.bias + (ncols > 0 ? wn0 : 0)), 0, ncols * (int)sizeof(OutT), 0x00020000);
+#pragma unroll
+      for (int i = 0; i < PIECES; ++i)
+        bias[i] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, (i * 64 + lane) % SLOTS * 16, 0, 0);
+    }
+    static_for<0, TM>([&](auto b) {
+      if constexpr (EPI & (E_ACC | E_RESID | E_DACT)) {
+        const __amdgpu_buffer_rsrc_t irsrc =
+            block_rsrc((EPI & E_ACC) ? (const void*)C : (EPI & E_RESID) ? ep.resid : ep.dact_in, b);
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) in[i] = __builtin_amdgcn_raw_buffer_load_b128(irsrc, voff[i], 0, 0);
+      }
+      stage_block(b);
+      const __amdgpu_buffer_rsrc_t crsrc = block_rsrc(C, b);
 #pragma unroll
       for (int i = 0; i < PIECES; ++i) {
-        const int e = i * 64 + lane, row = e / UNITS, unit = e % UNITS;
-        voff[i] = unit * 4 < ncols ? row * row_bytes + unit * 16 : OUTSIDE;
-        lds_at[i] = row * UNITS + (unit ^ (row & XOR));
-      }
-      u32x4 cin[PIECES];
-      // (the last barrier of the K loop comes after every wave's last read of the operand stages)
-      asm volatile("" ::: "memory");
-      static_for<0, TM>([&](auto b) {
-        const __amdgpu_buffer_rsrc_t rsrc = block_rsrc(b);
-        if constexpr (EPI & E_ACC) {
-#pragma unroll
-          for (int i = 0; i < PIECES; ++i) cin[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff[i], 0, 0);
-        }
-        static_for<0, TN>([&](auto a) {
-          static_for<0, 4>([&](auto rg) {
-            st[lr * UNITS + ((a * 8 + rg * 2 + lk) ^ (lr & XOR))] =
-                make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
-          });
-        });
-        asm volatile("" ::: "memory");   // other lanes' values: a wave's LDS instructions execute in program order
-#pragma unroll
-        for (int i = 0; i < PIECES; ++i) {
+        if constexpr (F32) {
           const float4 t = st[lds_at[i]];
           f32x4 v = {t.x, t.y, t.z, t.w};
-          if constexpr (EPI & E_ACC) v += __builtin_bit_cast(f32x4, cin[i]);
-          const u32x4 w = __builtin_bit_cast(u32x4, v);
-          __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, voff[i], 0, 0);
-        }
-        asm volatile("" ::: "memory");
-      });
-      return;
-    }
-  }
-  if (interior) {
-    static_for<0, TN>([&](auto a) {
-      float bias4[4][4] = {};
-      if constexpr (EPI & E_BIAS) {
+          if constexpr (EPI & E_ACC) v += __builtin_bit_cast(f32x4, in[i]);
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), crsrc, voff[i], 0, 0);
+        } else {
+          const float4 lo = st[lds_at[i]], hi = st[lds_at[i] ^ 1];
+          float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, t[8];
+          auto pack8 = [&]() {
+            const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+            return w;
+          };
+          if constexpr (EPI & E_BIAS) {
+            unpack8(bias[i], t);
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg)
-          load4((const bf16_t*)ep.bias + n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4, bias4[rg]);
+            for (int j = 0; j < 8; ++j) v[j] += t[j];
+          }
+          if constexpr (EPI & E_PRE)
+            __builtin_amdgcn_raw_buffer_store_b128(pack8(), block_rsrc(ep.preact_out, b), voff[i], 0, 0);
+          if constexpr (EPI & E_GELU) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = gelu_bf16_f(v[j]);
+          }
+          if constexpr (EPI & (E_DACT | E_RESID)) {
+            unpack8(in[i], t);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = (EPI & E_DACT) ? v[j] * gelu_grad_f(t[j]) : v[j] + t[j];
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(pack8(), crsrc, voff[i], 0, 0);
+        }
       }
-      static_for<0, TM>([&](auto b) {
-        const int64_t m = m0 + (wm * TM + b) * 32 + lr;
-        static_for<0, 4>([&](auto rg) {
-          const int64_t n = n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4;
-          float v[4] = {acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2],
-                        acc[a][b][rg * 4 + 3]};
-          epilogue4_static<EPI, OutT>(v, bias4[rg], m * N + n, C, ep);
-        });
-      });
     });
-  } else {
-    static_for<0, TN>([&](auto a) {
-      static_for<0, TM>([&](auto b) {
-        const int64_t m = m0 + (wm * TM + b) * 32 + lr;
-        static_for<0, 4>([&](auto rg) {
-          const int64_t n = n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4;
-          float v[4] = {acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2],
-                        acc[a][b][rg * 4 + 3]};
-          epilogue4_scalar<bf16_t, OutT>(v, m, n, M, N, C, ep);
-        });
-      });
-    });
+    return;
   }
+  const bool fours = (N & 3) == 0 && (ptrs & (F32 ? 15 : 7)) == 0;
+  static_for<0, TM>([&](auto b) {
+    stage_block(b);
+#pragma unroll 1
+    for (int i = 0; i < UNITS / 2; ++i) {
+      const int e = i * 64 + lane, row = e / UNITS, unit = e % UNITS;
+      const int64_t m = wm0 + b * 32 + row, n = wn0 + unit * 4;
+      if (m >= M || n >= N) continue;
+      const float4 t = st[row * UNITS + (unit ^ (row & XOR))];
+      float v[4] = {t.x, t.y, t.z, t.w};
+      if (fours) epilogue4_vec<bf16_t, OutT>(v, m, n, N, C, ep);
+      else epilogue4_scalar<bf16_t, OutT>(v, m, n, M, N, C, ep);
+    }
+  });
 }
 
 template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS>

@@ -188,6 +188,42 @@ def test_gemm_grids_that_do_not_fill_the_chip(dtype, M, N, K):
     assert rel_err(acc.cpu().numpy(), 2 * ref0) < 1e-5
 
 
+# Tiles that stick out of C keep their sums in fp32 until the last operand of the epilogue is in: small whole numbers make
+# product + bias exact, and the residual is minus its bf16 rounding, so the result is the rounding residue, exact in bf16
+# (a sum rounded before the residual is added gives zero).  They take GELU and GELU' by formula: NaN stays NaN.
+# Tiles, in order: 256x192, 256x256, 128x128 with four and with two LDS stages.
+@pytest.mark.parametrize("M,N", [(8292, 2368), (8292, 3112), (1999, 2040), (1659, 3072)])
+def test_gemm_edge_tiles_round_once(M, N):
+    pf, dev = _mods()
+    md = _md("bf16")
+    K, edge = 64, M // 128 * 128          # rows from `edge` on lie in tiles that stick out, whatever the tile
+    rng = np.random.default_rng(M + N)
+    ints = lambda shape, top: rng.integers(-top, top + 1, shape).astype(np.float32)
+    X, W, bias = ints((M, K), 16), ints((N, K), 16), ints((N,), 100)
+    total = X @ W.T + bias
+    R = -synth.round_to_bf16(total)
+    dX, dW, dB, dR = (dev.storage_tensor(a, md) for a in (X, W, bias, R))
+    out = dev.empty_storage((M, N), md)
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out.data_ptr(), M, N, K, bias=dB.data_ptr(),
+                  resid=dR.data_ptr())
+    torch.cuda.synchronize()
+    residue = (total + R)[edge:]
+    assert np.count_nonzero(residue) > residue.size // 4
+    assert np.array_equal(dev.read_storage(out, md)[edge:], residue)
+    bias[5] = np.nan
+    dB = dev.storage_tensor(bias, md)
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out.data_ptr(), M, N, K, bias=dB.data_ptr(), gelu=1)
+    torch.cuda.synchronize()
+    got = dev.read_storage(out, md)[edge:]
+    assert np.isnan(got[:, 5]).all() and np.isfinite(np.delete(got, 5, 1)).all()
+    R[edge:, 7] = np.nan
+    dR = dev.storage_tensor(R, md)
+    pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out.data_ptr(), M, N, K, dact_in=dR.data_ptr())
+    torch.cuda.synchronize()
+    got = dev.read_storage(out, md)[edge:]
+    assert np.isnan(got[:, 7]).all() and np.isfinite(np.delete(got, 7, 1)).all()
+
+
 # Weight-gradient shapes: small result, K = all tokens; C holds an earlier gradient that must be kept.
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 8192), (3072, 1024, 8192), (1000, 520, 4096), (256, 256, 2048)])
 def test_gemm_accumulate_long_k(M, N, K):
