@@ -522,12 +522,11 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(const float* __restri
     float mq = sM[0][q];
 #pragma unroll
     for (int w = 1; w < NW; ++w) mq = fmaxf(mq, sM[w][q]);
-    const float ref = mq == -INFINITY ? 0.f : mq;
-    float lq = 0.f;
+    float lq = 0.f;   // a query whose visible scores are all -inf has no softmax: exp(-inf - -inf) makes it NaN
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float f = __expf(sM[w][q] - ref);   // 0 for a wave that saw no key of this query
+      const float f = __expf(sM[w][q] - mq);   // 0 for a wave that saw no key of this query
       lq += f * sL[w][q];
       o += *(const f32x4*)&sO[w][q][c] * f;
     }

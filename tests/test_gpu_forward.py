@@ -346,6 +346,34 @@ def test_attention_fp32_tiles(B, S, h, dh, causal):
     assert rel_err(got, ref) < 1e-5
 
 
+# Scores of -inf: a query that sees nothing else has no softmax (NaN, as in the oracle), any other leaves those keys out,
+# also where a whole 32-key tile of a wave is among them.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,dh,gone", [(33, 32, 1), (161, 64, 40), (50, 128, 50)])
+def test_attention_fp32_scores_of_minus_infinity(S, dh, gone, causal):
+    pf, dev = _mods()
+    md = _md("f32")
+    rng = np.random.default_rng(S)
+    qkv = _rand(rng, (1, S, 3 * dh), "f32")
+    qkv[..., 0] = 1.0
+    qkv[:, :gone, dh] = -np.inf
+    q64 = qkv.astype(np.float64)
+    q, k, v = (ot.split_heads(q64[..., i * dh:(i + 1) * dh], 1) for i in range(3))
+    with np.errstate(invalid="ignore"):
+        ref = ot.merge_heads(ot.attention_probs(q, k, causal) @ v)
+    lost = np.isnan(ref).all(-1)[0]
+    assert lost.sum() == (gone if causal else S if gone == S else 0)
+    dq = dev.storage_tensor(qkv, md)
+    out = dev.empty_storage((1, S, dh), md)
+    lse = torch.empty((1, 1, S), dtype=torch.float32, device="cuda")
+    pf.pf_op_attention(md.dtype, dq.data_ptr(), out.data_ptr(), 1, S, 1, dh, causal, lse.data_ptr())
+    torch.cuda.synchronize()
+    got = dev.read_storage(out, md)
+    assert np.isnan(got[0, lost]).all() and np.array_equal(np.isnan(lse.cpu().numpy()[0, 0]), lost)
+    if not lost.all():
+        assert rel_err(got[0, ~lost], ref[0, ~lost]) < 1e-5
+
+
 @pytest.mark.parametrize("B,S,h,dh", [(8, 1024, 16, 128), (3, 900, 22, 128), (8, 1024, 16, 64), (4, 1024, 16, 128)])
 def test_attention_where_the_kernel_reorders_causal_blocks(B, S, h, dh):
     # Causal attention at sizes where the kernel hands the query blocks out in an order of its own.  First two cases:
