@@ -379,28 +379,26 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   // and goes through C and the other operands of the epilogue in whole rows of its tile.  A bf16 element takes the steps of
   // epilogue4_scalar: fp32, rounded once at the end, the formulas of GELU and GELU' (the staged route above rounds product +
   // bias before it adds the residual).
-  //  * 16-byte pieces where rows and operands are aligned to them; what a block needs from memory is requested before it is
-  //    staged.  Rows and columns past C's end are dropped by the buffers' bounds: loads deliver zeros, stores go nowhere.
-  //    8192 x 32768, K = 2048 accumulated into fp32: 1446 us from the registers, 1172 this way (1 GiB read, 1 GiB written).
-  //    From the registers a ragged bf16 result took 25 to 85 us longer than a whole one: 1659 x 768, K = 768 38 / 55 /
-  //    106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.
-  //  * otherwise four columns at a time, element by element where they don't come in fours.
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  //  * In pieces of 16 bytes (bf16 also 8) where rows and operands are aligned to them; what a block needs from memory is
+  //    requested before it is staged.  Rows and columns past C's end are dropped by the buffers' bounds: loads deliver zeros,
+  //    stores go nowhere.  8192 x 32768, K = 2048 accumulated into fp32: 1446 us from the registers, 1172 this way (1 GiB
+  //    read, 1 GiB written).  From the registers a ragged bf16 result took 25 to 85 us longer than a whole one: 1659 x 768,
+  //    K = 768 38 / 55 / 106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.
+  //  * Otherwise element by element, what is read from memory for four groups of four columns at a time.
   constexpr bool F32 = std::is_same<OutT, float>::value;
-  constexpr int CE = 16 / (int)sizeof(OutT);                // columns of a 16-byte piece
   constexpr int UNITS = TN * 8;                             // 16-byte units of a row in LDS
-  constexpr int SLOTS = TN * 32 / CE, PIECES = SLOTS / 2;   // pieces of a row; 1 KB wave instructions of a block
   constexpr int XOR = UNITS % 16 == 0 ? 15 : 7;
   constexpr int OUTSIDE = 0x7fffff00;                       // past every buffer
   static_assert(32 * UNITS * NW <= 2 * STAGE, "a block per wave fits the operand stages");
   static_assert(!F32 || (EPI & ~E_ACC) == 0, "fp32 results have no epilogue but the sum");
+  constexpr bool READS = (EPI & (E_ACC | E_RESID | E_DACT)) != 0;   // one operand of C's layout, at most
+  const void* const read_from = (EPI & E_ACC) ? (const void*)C : (EPI & E_RESID) ? ep.resid : ep.dact_in;
   float4* st = (float4*)smem + wave * 32 * UNITS;
   const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);   // scalar buffers
   const int64_t wm0 = m0 + wmu * TM * 32, wn0 = n0 + wnu * TN * 32;
   uintptr_t ptrs = (uintptr_t)C;
   if constexpr (EPI & E_BIAS) ptrs |= (uintptr_t)ep.bias;
-  if constexpr (EPI & E_RESID) ptrs |= (uintptr_t)ep.resid;
-  if constexpr (EPI & E_DACT) ptrs |= (uintptr_t)ep.dact_in;
+  if constexpr (READS) ptrs |= (uintptr_t)read_from;
   if constexpr (EPI & E_PRE) ptrs |= (uintptr_t)ep.preact_out;
   // (the last barrier of the K loop comes after every wave's last read of the operand stages)
   auto stage_block = [&](auto b) {
@@ -416,7 +414,42 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
     });
     asm volatile("" ::: "memory");
   };
-  if (N % CE == 0 && (ptrs & 15) == 0 && N <= (1 << 20)) {
+  // an element on its way out, given what was read for it
+  auto finish = [&](float x, float read) {
+    if constexpr (EPI & E_GELU) x = gelu_bf16_f(x);
+    if constexpr (EPI & E_DACT) x *= gelu_grad_f(read);
+    else if constexpr (READS) x += read;
+    return x;
+  };
+  auto by_pieces = [&](auto words) {
+    constexpr int W = decltype(words)::value;                         // of a piece: 32-bit words,
+    constexpr int CE = W * 4 / (int)sizeof(OutT), UP = CE / 4;        // columns, units in LDS
+    constexpr int SLOTS = TN * 32 / CE, PIECES = SLOTS / 2;           // pieces of a row; wave instructions of a block
+    typedef uint32_t piece_t __attribute__((ext_vector_type(W)));
+    auto load = [&](__amdgpu_buffer_rsrc_t rs, int off) -> piece_t {
+      if constexpr (W == 4) return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+      else return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+    };
+    auto store = [&](const float* v, __amdgpu_buffer_rsrc_t rs, int off) {
+      piece_t w;
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        if constexpr (F32) w[j] = __float_as_uint(v[j]);
+        else w[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
+      }
+      if constexpr (W == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b64(w, rs, off, 0, 0);
+    };
+    auto widen = [&](piece_t p, float* v) {
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        if constexpr (F32) v[j] = __uint_as_float(p[j]);
+        else {
+          v[2 * j] = bf16_bits_to_f32(p[j] & 0xffffu);
+          v[2 * j + 1] = bf16_bits_to_f32(p[j] >> 16);
+        }
+      }
+    };
     const int ncols = (int)(N - wn0 < TN * 32 ? (N > wn0 ? N - wn0 : 0) : TN * 32);
     const int nrows = (int)(M - wm0 < TM * 32 ? (M > wm0 ? M - wm0 : 0) : TM * 32);
     const int row_bytes = (int)N * (int)sizeof(OutT);
@@ -431,74 +464,87 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
 #pragma unroll
     for (int i = 0; i < PIECES; ++i) {
       const int e = i * 64 + lane, row = e / SLOTS, slot = e % SLOTS;
-      voff[i] = slot * CE < ncols ? row * row_bytes + slot * 16 : OUTSIDE;
-      lds_at[i] = row * UNITS + ((slot * (CE / 4)) ^ (row & XOR));   // second unit of a bf16 piece: this ^ 1
+      voff[i] = slot * CE < ncols ? row * row_bytes + slot * W * 4 : OUTSIDE;
+      lds_at[i] = row * UNITS + ((slot * UP) ^ (row & XOR));   // second unit of a piece: this ^ 1
     }
-    u32x4 in[PIECES], bias[PIECES];   // in: C, the residual or the saved pre-activation
+    piece_t in[PIECES], bias[PIECES];
     if constexpr (EPI & E_BIAS) {
       const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
           (void*)((const OutT*)ep.bias + (ncols > 0 ? wn0 : 0)), 0, ncols * (int)sizeof(OutT), 0x00020000);
 #pragma unroll
-      for (int i = 0; i < PIECES; ++i)
-        bias[i] = __builtin_amdgcn_raw_buffer_load_b128(brsrc, (i * 64 + lane) % SLOTS * 16, 0, 0);
+      for (int i = 0; i < PIECES; ++i) bias[i] = load(brsrc, (i * 64 + lane) % SLOTS * W * 4);
     }
     static_for<0, TM>([&](auto b) {
-      if constexpr (EPI & (E_ACC | E_RESID | E_DACT)) {
-        const __amdgpu_buffer_rsrc_t irsrc =
-            block_rsrc((EPI & E_ACC) ? (const void*)C : (EPI & E_RESID) ? ep.resid : ep.dact_in, b);
+      if constexpr (READS) {
+        const __amdgpu_buffer_rsrc_t irsrc = block_rsrc(read_from, b);
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) in[i] = __builtin_amdgcn_raw_buffer_load_b128(irsrc, voff[i], 0, 0);
+        for (int i = 0; i < PIECES; ++i) in[i] = load(irsrc, voff[i]);
       }
       stage_block(b);
       const __amdgpu_buffer_rsrc_t crsrc = block_rsrc(C, b);
 #pragma unroll
       for (int i = 0; i < PIECES; ++i) {
-        if constexpr (F32) {
-          const float4 t = st[lds_at[i]];
-          f32x4 v = {t.x, t.y, t.z, t.w};
-          if constexpr (EPI & E_ACC) v += __builtin_bit_cast(f32x4, in[i]);
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), crsrc, voff[i], 0, 0);
-        } else {
-          const float4 lo = st[lds_at[i]], hi = st[lds_at[i] ^ 1];
-          float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, t[8];
-          auto pack8 = [&]() {
-            const u32x4 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-            return w;
-          };
-          if constexpr (EPI & E_BIAS) {
-            unpack8(bias[i], t);
+        float v[CE], t[CE] = {};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] += t[j];
-          }
-          if constexpr (EPI & E_PRE)
-            __builtin_amdgcn_raw_buffer_store_b128(pack8(), block_rsrc(ep.preact_out, b), voff[i], 0, 0);
-          if constexpr (EPI & E_GELU) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = gelu_bf16_f(v[j]);
-          }
-          if constexpr (EPI & (E_DACT | E_RESID)) {
-            unpack8(in[i], t);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (EPI & E_DACT) ? v[j] * gelu_grad_f(t[j]) : v[j] + t[j];
-          }
-          __builtin_amdgcn_raw_buffer_store_b128(pack8(), crsrc, voff[i], 0, 0);
+        for (int j = 0; j < UP; ++j) {
+          const float4 u = st[lds_at[i] ^ j];
+          v[4 * j] = u.x; v[4 * j + 1] = u.y; v[4 * j + 2] = u.z; v[4 * j + 3] = u.w;
         }
+        if constexpr (EPI & E_BIAS) {
+          widen(bias[i], t);
+#pragma unroll
+          for (int j = 0; j < CE; ++j) v[j] += t[j];
+        }
+        if constexpr (EPI & E_PRE) store(v, block_rsrc(ep.preact_out, b), voff[i]);
+        if constexpr (READS) widen(in[i], t);
+#pragma unroll
+        for (int j = 0; j < CE; ++j) v[j] = finish(v[j], t[j]);
+        store(v, crsrc, voff[i]);
       }
     });
-    return;
+  };
+  if (N <= (1 << 23)) {   // 32 rows of C below 2^31 bytes
+    if (N % (16 / (int)sizeof(OutT)) == 0 && (ptrs & 15) == 0) {
+      by_pieces(std::integral_constant<int, 4>{});
+      return;
+    }
+    if constexpr (!F32) {
+      if (N % 4 == 0 && (ptrs & 7) == 0) {
+        by_pieces(std::integral_constant<int, 2>{});
+        return;
+      }
+    }
   }
-  const bool fours = (N & 3) == 0 && (ptrs & (F32 ? 15 : 7)) == 0;
   static_for<0, TM>([&](auto b) {
     stage_block(b);
 #pragma unroll 1
-    for (int i = 0; i < UNITS / 2; ++i) {
-      const int e = i * 64 + lane, row = e / UNITS, unit = e % UNITS;
-      const int64_t m = wm0 + b * 32 + row, n = wn0 + unit * 4;
-      if (m >= M || n >= N) continue;
-      const float4 t = st[row * UNITS + (unit ^ (row & XOR))];
-      float v[4] = {t.x, t.y, t.z, t.w};
-      if (fours) epilogue4_vec<bf16_t, OutT>(v, m, n, N, C, ep);
-      else epilogue4_scalar<bf16_t, OutT>(v, m, n, M, N, C, ep);
+    for (int i = 0; i < UNITS / 2; i += 4) {
+      float t[4][4] = {};
+      if constexpr (READS) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int e = (i + u) * 64 + lane;
+          const int64_t m = wm0 + b * 32 + e / UNITS, n = wn0 + e % UNITS * 4;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (m < M && n + j < N) t[u][j] = to_f32(((const OutT*)read_from)[m * N + n + j]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = (i + u) * 64 + lane, row = e / UNITS, unit = e % UNITS;
+        const int64_t m = wm0 + b * 32 + row, n = wn0 + unit * 4;
+        const float4 s = st[row * UNITS + (unit ^ (row & XOR))];
+        const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (m >= M || n + j >= N) continue;
+          float x = v[j];
+          if constexpr (EPI & E_BIAS) x += to_f32(((const OutT*)ep.bias)[n + j]);
+          if constexpr (EPI & E_PRE) ((OutT*)ep.preact_out)[m * N + n + j] = from_f32<OutT>(x);
+          C[m * N + n + j] = from_f32<OutT>(finish(x, t[u][j]));
+        }
+      }
     }
   });
 }

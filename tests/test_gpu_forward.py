@@ -224,6 +224,48 @@ def test_gemm_edge_tiles_round_once(M, N):
     assert np.isnan(got[:, 7]).all() and np.isfinite(np.delete(got, 7, 1)).all()
 
 
+# Rows and operands that don't come in 16-byte pieces: N in fours and odd, C and what the epilogue reads 8 bytes and one
+# element off, on the 256x192, 256x256 and 128x128 tile; K = 64 as whole numbers, so sums and their accumulation are exact.
+@pytest.mark.parametrize("off", [0, 4, 1])
+@pytest.mark.parametrize("M,N", [(4196, 2372), (8292, 3108), (1999, 2044), (8292, 2371)])
+def test_gemm_pieces_of_rows(M, N, off):
+    pf, dev = _mods()
+    md = _md("bf16")
+    K = 64
+    rng = np.random.default_rng(M + N)
+    ints = lambda shape, top: rng.integers(-top, top + 1, shape).astype(np.float32)
+    X, W, bias, R = ints((M, K), 3), ints((N, K), 3), ints((N,), 9), ints((M, N), 9) / 8
+    ref0 = X @ W.T
+
+    def shifted(a):          # the same values, `off` elements behind an aligned address
+        t = dev.storage_tensor(np.concatenate([np.zeros(off, np.float32), a.reshape(-1)]), md)
+        return t, t.data_ptr() + 2 * off
+
+    dX, dW = (dev.storage_tensor(a, md) for a in (X, W))
+    (tb, b), (tr, r) = shifted(bias), shifted(R)
+    out, pre = (shifted(np.zeros((M + 1, N), np.float32)) for _ in range(2))     # one extra row: must stay untouched
+
+    def run(**kw):
+        pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out[1], M, N, K, **kw)
+        torch.cuda.synchronize()
+        got = dev.read_storage(out[0], md)[off:].reshape(M + 1, N)
+        assert not got[M].any()
+        return got[:M]
+
+    # one rounding, or two where a whole tile's sum is rounded before the residual comes in: 2^-8 of the larger of both
+    assert rel_err(run(), ref0) < 2.0 ** -8
+    assert rel_err(run(bias=b, resid=r), ref0 + bias + R) < 2.0 ** -7
+    assert rel_err(run(bias=b, gelu=1, preact_out=pre[1]), ot.gelu(ref0 + bias)) < 2.0 ** -8
+    assert rel_err(dev.read_storage(pre[0], md)[off:].reshape(M + 1, N)[:M], ref0 + bias) < 2.0 ** -8
+    assert rel_err(run(dact_in=r), ref0 * ot.gelu_grad(R.astype(np.float64))) < 2.0 ** -7
+    acc = torch.ones(off + (M + 1) * N, dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), acc.data_ptr() + 4 * off, M, N, K, out_f32=1, accumulate=1)
+    torch.cuda.synchronize()
+    got = acc.cpu().numpy()
+    assert np.array_equal(got[off:off + M * N].reshape(M, N), 1 + 2 * ref0) and (got[:off] == 1).all() and (got[off + M * N:] == 1).all()
+
+
 # Weight-gradient shapes: small result, K = all tokens; C holds an earlier gradient that must be kept.
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 8192), (3072, 1024, 8192), (1000, 520, 4096), (256, 256, 2048)])
 def test_gemm_accumulate_long_k(M, N, K):
