@@ -30,14 +30,14 @@
 namespace pf {
 namespace gemm {
 
-extern template hipError_t launch_fast<bf16_t, 0>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<bf16_t, E_BIAS>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<bf16_t, E_BIAS | E_RESID>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU | E_PRE>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<bf16_t, E_DACT>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<float, 0>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-extern template hipError_t launch_fast<float, E_ACC>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, 0>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, E_BIAS>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, E_BIAS | E_RESID>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU | E_PRE>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<bf16_t, E_DACT>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<float, 0>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+extern template hipError_t launch_fast<float, E_ACC>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
 
 }  // namespace gemm
 
@@ -201,37 +201,27 @@ hipError_t launch_generic(const void* X, const void* W, void* C, int64_t M, int6
                             stream);
 }
 
+// One routed bf16 product.  Only epilogue combinations that have a tiled kernel are routed to one.
 template <typename OutT>
-hipError_t dispatch_bf16(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
-                         hipStream_t stream) {
-  const bool aligned = (((uintptr_t)X | (uintptr_t)W) & 15) == 0;
-  int epi = (ep.bias ? E_BIAS : 0) | (ep.gelu ? E_GELU : 0) | (ep.resid ? E_RESID : 0) | (ep.dact_in ? E_DACT : 0) |
-            (ep.preact_out ? E_PRE : 0) | (ep.accumulate ? E_ACC : 0);
-  if (K % 64 == 0 && aligned && ep.scale == 1.0f) {
-    if constexpr (std::is_same<OutT, float>::value) {
-      if (epi == 0) return launch_fast<float, 0>(X, W, C, M, N, K, ep, stream);
-      if (epi == E_ACC) return launch_fast<float, E_ACC>(X, W, C, M, N, K, ep, stream);
-    } else {
-      switch (epi) {
-        case 0: return launch_fast<bf16_t, 0>(X, W, C, M, N, K, ep, stream);
-        case E_BIAS: return launch_fast<bf16_t, E_BIAS>(X, W, C, M, N, K, ep, stream);
-        case E_BIAS | E_GELU: return launch_fast<bf16_t, E_BIAS | E_GELU>(X, W, C, M, N, K, ep, stream);
-        case E_BIAS | E_RESID: return launch_fast<bf16_t, E_BIAS | E_RESID>(X, W, C, M, N, K, ep, stream);
-        case E_BIAS | E_GELU | E_PRE: return launch_fast<bf16_t, E_BIAS | E_GELU | E_PRE>(X, W, C, M, N, K, ep, stream);
-        case E_DACT: return launch_fast<bf16_t, E_DACT>(X, W, C, M, N, K, ep, stream);
-        default: break;
-      }
+hipError_t dispatch_bf16(const Route& r, int epi, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
+                         const EpiDev& ep, hipStream_t stream) {
+  if (r.kernel == BF16_GENERIC) return launch_generic<OutT>(X, W, C, M, N, K, ep, stream);
+  if (r.kernel <= RING_128x64) return launch_ring_shape<bf16_t, OutT>(r.kernel, X, W, C, M, N, K, ep, stream);
+  if constexpr (std::is_same<OutT, float>::value) {
+    if (epi == 0) return launch_fast<float, 0>(r, X, W, C, M, N, K, ep, stream);
+    if (epi == E_ACC) return launch_fast<float, E_ACC>(r, X, W, C, M, N, K, ep, stream);
+  } else {
+    switch (epi) {
+      case 0: return launch_fast<bf16_t, 0>(r, X, W, C, M, N, K, ep, stream);
+      case E_BIAS: return launch_fast<bf16_t, E_BIAS>(r, X, W, C, M, N, K, ep, stream);
+      case E_BIAS | E_GELU: return launch_fast<bf16_t, E_BIAS | E_GELU>(r, X, W, C, M, N, K, ep, stream);
+      case E_BIAS | E_RESID: return launch_fast<bf16_t, E_BIAS | E_RESID>(r, X, W, C, M, N, K, ep, stream);
+      case E_BIAS | E_GELU | E_PRE: return launch_fast<bf16_t, E_BIAS | E_GELU | E_PRE>(r, X, W, C, M, N, K, ep, stream);
+      case E_DACT: return launch_fast<bf16_t, E_DACT>(r, X, W, C, M, N, K, ep, stream);
+      default: break;
     }
   }
-  // The rest (K not a multiple of 64, scaled results, other combinations of epilogues): the generic kernel pays a memory
-  // latency per K step and is the faster one only where it fills the chip (1024 x 4096, K = 1000, 256 tiles: 29 us
-  // against 35; 64 tiles, 2048 x 512, K = 600: 17.9 us against 8.3).
-  if (aligned && ((M + 127) / 128) * ((N + 127) / 128) <= 192) {
-    int shape = 0;
-    ring_estimate(M, N, K, 2, &shape);
-    return launch_ring_shape<bf16_t, OutT>(shape, X, W, C, M, N, K, ep, stream);
-  }
-  return launch_generic<OutT>(X, W, C, M, N, K, ep, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -242,17 +232,15 @@ hipError_t gemm_nt(int32_t dtype, const void* X, const void* W, void* C, int64_t
   EpiDev ep{e.bias, e.resid, e.dact_in, e.preact_out, e.gelu, e.accumulate, e.scale};
   const bool out_f32 = e.out_f32 || dtype == PF_DTYPE_F32_;
   if (e.accumulate && !out_f32) return hipErrorInvalidValue;
+  if (dtype == PF_DTYPE_BF16_ && K % 8 != 0) return hipErrorInvalidValue;   // 16-byte operand loads
+  const int epi = (ep.bias ? E_BIAS : 0) | (ep.gelu ? E_GELU : 0) | (ep.resid ? E_RESID : 0) | (ep.dact_in ? E_DACT : 0) |
+                  (ep.preact_out ? E_PRE : 0) | (ep.accumulate ? E_ACC : 0);
+  const Route r = route({dtype == PF_DTYPE_BF16_, M, N, K, (((uintptr_t)X | (uintptr_t)W) & 15) == 0, out_f32, ep.scale != 1.0f, epi});
   if (dtype == PF_DTYPE_BF16_) {
-    if (K % 8 != 0) return hipErrorInvalidValue;   // 16-byte operand loads
-    if (out_f32) return dispatch_bf16<float>(X, W, C, M, N, K, ep, stream);
-    return dispatch_bf16<bf16_t>(X, W, C, M, N, K, ep, stream);
+    if (out_f32) return dispatch_bf16<float>(r, epi, X, W, C, M, N, K, ep, stream);
+    return dispatch_bf16<bf16_t>(r, epi, X, W, C, M, N, K, ep, stream);
   }
-  // 2048 x 512, K = 2048: 297 -> 41 us; 512 x 256, K = 1024: 115 -> 10 us
-  if (K % 4 == 0 && (((uintptr_t)X | (uintptr_t)W) & 15) == 0) {
-    int shape = 0;
-    ring_estimate(M, N, K, 4, &shape);
-    return launch_ring_shape<float, float>(shape, X, W, C, M, N, K, ep, stream);
-  }
+  if (r.kernel != F32_FMA) return launch_ring_shape<float, float>(r.kernel, X, W, C, M, N, K, ep, stream);
   dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
   hipLaunchKernelGGL(gemm_f32_nt_kernel<float>, grid, dim3(256), 0, stream, (const float*)X, (const float*)W,
                      (float*)C, M, N, K, ep);

@@ -4,8 +4,8 @@
 namespace pf {
 namespace gemm {
 
-template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-template hipError_t launch_fast<bf16_t, E_DACT>(const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+template hipError_t launch_fast<bf16_t, E_BIAS | E_GELU>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+template hipError_t launch_fast<bf16_t, E_DACT>(const Route&, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
 
 }  // namespace gemm
 }  // namespace pf

@@ -216,14 +216,6 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   }
 }
 
-// Tile shapes: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of X, in
-// microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
-// product but spreads them over four times the CUs.  fp32 is bound by its MFMAs (64 cycles for two K), which
-// the 32x32 tile hides best; the 128x64 tile never wins there.
-struct RingShape { int bm, bn; double fixed, bf16_byte, f32_byte; };
-constexpr RingShape ring_shapes[] = {
-    {32, 32, 2.6, 0.00098, 0.0018}, {32, 64, 3.5, 0.0014, 0.0036}, {64, 64, 4.6, 0.0017, 0.0044}, {128, 64, 7.5, 0.0028, 0.011}};
-
 template <typename T, typename OutT, int TM, int TN, int WK, int DEPTH>
 hipError_t launch_ring(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
                        hipStream_t stream) {
@@ -246,33 +238,20 @@ hipError_t launch_ring(const void* X, const void* W, void* C, int64_t M, int64_t
 
 }  // namespace
 
-double ring_estimate(int64_t M, int64_t N, int64_t K, int elem, int* shape) {
-  double best = 1e30;
-  for (int i = 0; i < 4; ++i) {
-    const RingShape& s = ring_shapes[i];
-    const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
-    const double t = (double)((tiles + 255) / 256) * (s.fixed + (elem == 2 ? s.bf16_byte : s.f32_byte) * (double)(K * elem));
-    if (t < best) {
-      best = t;
-      *shape = i;
-    }
-  }
-  return best;
-}
-
 template <typename T, typename OutT>
-hipError_t launch_ring_shape(int shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
+hipError_t launch_ring_shape(Kernel shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                              const EpiDev& ep, hipStream_t stream) {
   switch (shape) {
-    case 0: return launch_ring<T, OutT, 1, 1, 8, 2>(X, W, C, M, N, K, ep, stream);
-    case 1: return launch_ring<T, OutT, 1, 2, 6, 2>(X, W, C, M, N, K, ep, stream);
-    case 2: return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
-    default: return launch_ring<T, OutT, 4, 2, 3, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_32x32: return launch_ring<T, OutT, 1, 1, 8, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_32x64: return launch_ring<T, OutT, 1, 2, 6, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_64x64: return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_128x64: return launch_ring<T, OutT, 4, 2, 3, 2>(X, W, C, M, N, K, ep, stream);
+    default: return hipErrorInvalidValue;
   }
 }
-template hipError_t launch_ring_shape<bf16_t, bf16_t>(int, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-template hipError_t launch_ring_shape<bf16_t, float>(int, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
-template hipError_t launch_ring_shape<float, float>(int, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+template hipError_t launch_ring_shape<bf16_t, bf16_t>(Kernel, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+template hipError_t launch_ring_shape<bf16_t, float>(Kernel, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
+template hipError_t launch_ring_shape<float, float>(Kernel, const void*, const void*, void*, int64_t, int64_t, int64_t, const EpiDev&, hipStream_t);
 
 }  // namespace gemm
 }  // namespace pf

@@ -1,0 +1,122 @@
+// Which GEMM kernel runs a product: estimated times, measured constants (MI355X).
+#include "gemm_route.h"
+
+#include "pf_internal.h"
+
+namespace pf {
+namespace gemm {
+namespace {
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Ring kernel, tile shapes: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of X,
+// in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
+// product but spreads them over four times the CUs.  fp32 is bound by its MFMAs (64 cycles for two K), which
+// the 32x32 tile hides best; the 128x64 tile never wins there.
+struct RingShape { int bm, bn; double fixed, bf16_byte, f32_byte; };
+constexpr RingShape ring_shapes[] = {
+    {32, 32, 2.6, 0.00098, 0.0018}, {32, 64, 3.5, 0.0014, 0.0036}, {64, 64, 4.6, 0.0017, 0.0044}, {128, 64, 7.5, 0.0028, 0.011}};
+
+double ring_estimate(const Product& p, Kernel* shape) {
+  const int elem = p.bf16 ? 2 : 4;
+  double best = 1e30;
+  for (int i = 0; i < 4; ++i) {
+    const RingShape& s = ring_shapes[i];
+    const int64_t tiles = ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn);
+    const double t = (double)ceil_div(tiles, 256) * (s.fixed + (elem == 2 ? s.bf16_byte : s.f32_byte) * (double)(p.K * elem));
+    if (t < best) {
+      best = t;
+      *shape = (Kernel)(RING_32x32 + i);
+    }
+  }
+  return best;
+}
+
+// Tiled kernels, and the ring kernel where it is faster.
+// Tile shapes: 256x256 (four waves, wave tile 128x128), 256x192 (8 waves as 4x2, wave tile 64x96), both one workgroup per
+// CU, and 128x128 (4 waves, two workgroups per CU).
+// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two: with two, one K step
+// is in flight and costs a memory latency (0.85 to 1.1 us per step; with four 0.61: 2048 x 2048, K = 8192 117 -> 88 us,
+// 333 x 8192, K = 2048 37.6 -> 25.8 us).
+// A launch takes ceil(workgroups / resident workgroups) rounds of (K steps + a fixed cost of about 4 steps); the
+// shape with the least estimated time rounds x steps x area in flight per CU / efficiency is taken.  Efficiencies
+// are measured on MI355X relative to the 256x256 tile (0.96 and 0.85); a shape that leaves partial tiles along N
+// is charged 30 % (set when edge tiles were stored element by element).  E.g. N = 768 or 2304 fills whole rounds with
+// 192-wide tiles but wastes a quarter of the last round with 256-wide ones, and a 8192 x 1024 result gives every CU work
+// only with the small tile.
+// Accumulating fp32 launches (weight gradients: small M x N, K = all tokens) may split K over up to 8 workgroups
+// per 128x128 tile while that fills idle CUs and leaves each >= 8 K steps; the slices add into C with fp32 atomics
+// (order-dependent in the last bits, like the other atomic reductions over tokens).  Those atomics go at about
+// 1.5 TB/s on MI355X, far below plain stores, so the estimate charges every slice for its tile: two slices usually
+// pay, eight rarely do.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
+// round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
+Route tiled_route(const Product& p) {
+  struct Shape { Kernel kernel; int bm, bn, resident, eff100; } const shapes[3] = {
+      {TILE_256x256, 256, 256, 256, 100}, {TILE_256x192, 256, 192, 256, 104}, {TILE_128x128, 128, 128, 512, 118}};
+  Route best{TILE_256x256, 1};
+  int64_t best_cost = -1;
+  for (const Shape& sh : shapes) {
+    const int64_t tiles = ceil_div(p.M, sh.bm) * ceil_div(p.N, sh.bn);
+    const bool small = sh.kernel == TILE_128x128;
+    const int max_splits = p.out_f32 && p.epi == E_ACC && small ? 8 : 1;
+    for (int splits = 1; splits <= max_splits; splits *= 2) {
+      // a slice keeps >= 8 K steps, and splitting only fills CUs that would otherwise idle
+      if (splits > 1 && (p.K % (128 * splits) != 0 || p.K / (128 * splits) < 8 || tiles * splits > sh.resident)) break;
+      const int64_t wgs = tiles * splits;
+      const int64_t rounds = ceil_div(wgs, sh.resident);
+      const bool alone = small && wgs <= 256;   // a 128x128 workgroup that has its CU, and four stages, to itself
+      const int64_t steps = p.K / (64 * splits) + (alone ? 6 : 4);
+      // area in flight per CU x relative cost
+      const int64_t per_step = alone ? (int64_t)sh.bm * sh.bn * 141 : (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
+      int64_t cost = rounds * steps * per_step;
+      if (p.N % sh.bn) cost += cost * 3 / 10;
+      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate
+      if (splits > 1) cost += p.M * p.N * splits * 10;
+      if (best_cost < 0 || cost < best_cost) {
+        best_cost = cost;
+        best = Route{alone ? TILE_128x128_DEEP : sh.kernel, splits};
+      }
+    }
+  }
+  // 3.8 M units of the estimate are a microsecond (256x256 tile: 1.72 us per K step).  The ring kernel takes what leaves
+  // the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192 122 -> 30 us (four stages: 81).
+  Kernel ring;
+  if (ring_estimate(p, &ring) < (double)best_cost / 3.8e6) return Route{ring, 1};
+  return best;
+}
+
+bool tiled(const Product& p) {
+  if (p.K % 64 != 0 || !p.aligned || p.scaled) return false;
+  if (p.out_f32) return p.epi == 0 || p.epi == E_ACC;
+  return p.epi == 0 || p.epi == E_BIAS || p.epi == (E_BIAS | E_GELU) || p.epi == (E_BIAS | E_RESID) ||
+         p.epi == (E_BIAS | E_GELU | E_PRE) || p.epi == E_DACT;
+}
+
+}  // namespace
+
+Route route(const Product& p) {
+  Kernel ring;
+  if (!p.bf16) {
+    // 2048 x 512, K = 2048: 297 -> 41 us; 512 x 256, K = 1024: 115 -> 10 us
+    if (p.K % 4 != 0 || !p.aligned) return Route{F32_FMA, 1};
+    ring_estimate(p, &ring);
+    return Route{ring, 1};
+  }
+  if (tiled(p)) return tiled_route(p);
+  // The rest (K not a multiple of 64, scaled results, other combinations of epilogues): the generic kernel pays a memory
+  // latency per K step and is the faster one only where it fills the chip (1024 x 4096, K = 1000, 256 tiles: 29 us
+  // against 35; 64 tiles, 2048 x 512, K = 600: 17.9 us against 8.3).
+  if (p.aligned && ceil_div(p.M, 128) * ceil_div(p.N, 128) <= 192) {
+    ring_estimate(p, &ring);
+    return Route{ring, 1};
+  }
+  return Route{BF16_GENERIC, 1};
+}
+
+}  // namespace gemm
+}  // namespace pf
+
+extern "C" int32_t pf_gemm_route(int32_t dtype, int64_t M, int64_t N, int64_t K, int32_t epi, int32_t flags) {
+  const pf::gemm::Route r = pf::gemm::route({dtype == PF_DTYPE_BF16, M, N, K, (flags & 1) == 0, (flags & 2) != 0, (flags & 4) != 0, epi});
+  return r.kernel | r.splits << 8;
+}

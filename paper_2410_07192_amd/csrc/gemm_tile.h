@@ -3,6 +3,7 @@
 // they compile in parallel.
 #pragma once
 
+#include "gemm_route.h"
 #include "pf_kernels.h"
 #include "pf_device.h"
 
@@ -87,15 +88,9 @@ __device__ __forceinline__ void epilogue4_scalar(float v[4], int64_t m, int64_t 
   }
 }
 
-// Epilogue features the main kernel is specialised on (so that its loads carry no branches and the
-// compiler can batch them); other combinations run on the generic kernel.
-enum : int { E_BIAS = 1, E_GELU = 2, E_RESID = 4, E_DACT = 8, E_PRE = 16, E_ACC = 32 };
-
-// Kernel for launches that do not fill the chip (gemm_ring.hip): its estimated time in microseconds and the tile
-// shape to launch, and the launch.  Needs K a whole number of 16-byte chunks and 16-byte aligned X and W.
-double ring_estimate(int64_t M, int64_t N, int64_t K, int elem, int* shape);
+// Ring kernel (gemm_ring.hip).  Needs K a whole number of 16-byte chunks and 16-byte aligned X and W.
 template <typename T, typename OutT>
-hipError_t launch_ring_shape(int shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
+hipError_t launch_ring_shape(Kernel shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                              const EpiDev& ep, hipStream_t stream);
 
 // compile-time loop: f(integral_constant<int, I>) for I in [0, N)
@@ -894,73 +889,26 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
   return hipGetLastError();
 }
 
-// Main kernel for one epilogue combination.  Tile shapes: 256x256 (the four-wave kernel above, wave tile 128x128),
-// 256x192 (8 waves as 4x2, wave tile 64x96), both one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
-// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two: with two, one K step
-// is in flight and costs a memory latency (0.85 to 1.1 us per step; with four 0.61: 2048 x 2048, K = 8192 117 -> 88 us,
-// 333 x 8192, K = 2048 37.6 -> 25.8 us).
-// A launch takes ceil(workgroups / resident workgroups) rounds of (K steps + a fixed cost of about 4 steps); the
-// shape with the least estimated time rounds x steps x area in flight per CU / efficiency is taken.  Efficiencies
-// are measured on MI355X relative to the 256x256 tile (0.96 and 0.85); a shape that leaves partial tiles along N
-// is charged 30 %
-// (set when edge tiles were stored element by element; not measured again since they take the staged epilogue).  E.g. N = 768 or 2304 fills whole rounds with 192-wide tiles but wastes a quarter
-// of the last round with 256-wide ones, and a 8192 x 1024 result gives every CU work only with the small tile.
-// Accumulating fp32 launches (weight gradients: small M x N, K = all tokens) may split K over up to 8 workgroups
-// per 128x128 tile while that fills idle CUs and leaves each >= 8 K steps; the slices add into C with fp32 atomics
-// (order-dependent in the last bits, like the other atomic reductions over tokens).  Those atomics go at about
-// 1.5 TB/s on MI355X, far below plain stores, so the estimate charges every slice for its tile: two slices usually
-// pay, eight rarely do.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
-// round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
+// The tiled kernel of one epilogue combination that the route names (gemm_route.cpp says why).
 template <typename OutT, int EPI>
-hipError_t launch_fast(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
-                       hipStream_t stream) {
+hipError_t launch_fast(const Route& r, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
+                       const EpiDev& ep, hipStream_t stream) {
   static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false;
-  struct Shape { int bm, bn, resident, eff100; } const shapes[3] = {{256, 256, 256, 100}, {256, 192, 256, 104},
-                                                                      {128, 128, 512, 118}};
-  int best = 0, best_splits = 1;
-  int64_t best_cost = -1, best_wgs = 0;
-  for (int i = 0; i < 3; ++i) {
-    const Shape& sh = shapes[i];
-    const int64_t tiles = ((M + sh.bm - 1) / sh.bm) * ((N + sh.bn - 1) / sh.bn);
-    int max_splits = 1;
-    if constexpr (std::is_same<OutT, float>::value && EPI == E_ACC) max_splits = (i == 2) ? 8 : 1;
-    for (int splits = 1; splits <= max_splits; splits *= 2) {
-      // a slice keeps >= 8 K steps, and splitting only fills CUs that would otherwise idle
-      if (splits > 1 && (K % (128 * splits) != 0 || K / (128 * splits) < 8 || tiles * splits > sh.resident)) break;
-      const int64_t wgs = tiles * splits;
-      const int64_t rounds = (wgs + sh.resident - 1) / sh.resident;
-      const bool alone = i == 2 && wgs <= 256;   // a 128x128 workgroup that has its CU, and four stages, to itself
-      const int64_t steps = K / (64 * splits) + (alone ? 6 : 4);
-      // area in flight per CU x relative cost
-      const int64_t per_step = alone ? (int64_t)sh.bm * sh.bn * 141
-                                     : (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
-      int64_t cost = rounds * steps * per_step;
-      if (N % sh.bn) cost += cost * 3 / 10;
-      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate
-      if (splits > 1) cost += M * N * splits * 10;
-      if (best_cost < 0 || cost < best_cost) {
-        best_cost = cost;
-        best = i;
-        best_splits = splits;
-        best_wgs = wgs;
-      }
-    }
+  switch (r.kernel) {
+    case TILE_256x256:
+      return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
+    case TILE_256x192:
+      return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI, 2>, 256, 192, 512, &attr_wide, X, W, C, M, N, K,
+                                ep, 1, stream);
+    case TILE_128x128_DEEP:
+      return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 4>, 128, 128, 256, &attr_deep, X, W, C, M, N, K,
+                                ep, r.splits, stream, 4);
+    case TILE_128x128:
+      return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 2>, 128, 128, 256, &attr_small, X, W, C, M, N, K,
+                                ep, r.splits, stream);
+    default:
+      return hipErrorInvalidValue;
   }
-  // 3.8 M units of the estimate are a microsecond (256x256 tile: 1.72 us per K step).  The ring kernel takes what leaves
-  // the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192 122 -> 30 us (four stages: 81).
-  int ring_shape = 0;
-  if (ring_estimate(M, N, K, 2, &ring_shape) < (double)best_cost / 3.8e6)
-    return launch_ring_shape<bf16_t, OutT>(ring_shape, X, W, C, M, N, K, ep, stream);
-  if (best == 0)
-    return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
-  if (best == 1)
-    return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI, 2>, 256, 192, 512, &attr_wide, X, W, C, M, N, K, ep,
-                              1, stream);
-  if (best_wgs <= 256)
-    return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 4>, 128, 128, 256, &attr_deep, X, W, C, M, N, K, ep,
-                              best_splits, stream, 4);
-  return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 2>, 128, 128, 256, &attr_small, X, W, C, M, N, K, ep,
-                            best_splits, stream);
 }
 
 }  // namespace gemm

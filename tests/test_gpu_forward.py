@@ -110,8 +110,9 @@ def test_gemm_large_tiles_with_ragged_edges(M, N, K):
     assert rel_err(acc.cpu().numpy(), 2 * ref0) < 1e-4
 
 
-# The two epilogues of the training backward, on whole 256-wide tiles (both tile shapes), with ragged edges
-# along M and N, with N not a multiple of 8, and on a shape that only the generic kernel takes.
+# The two epilogues of the training backward, on the 256-wide tiles (both shapes, whole and with ragged edges along M and
+# N) and on tiles of the ring kernel, with N not a multiple of 8 and with K not a multiple of 64.  The other kernels:
+# test_product_routes.py.
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("M,N,K", [(512, 512, 128), (768, 384, 64), (8292, 2368, 128), (4196, 3112, 64), (1030, 522, 64),
                                    (300, 200, 24)])
@@ -119,7 +120,7 @@ def test_gemm_training_epilogues(dtype, M, N, K):
     pf, dev = _mods()
     md = _md(dtype)
     if dtype == "f32" and M > 1100:
-        pytest.skip("the fp32 kernel has one code path; the small shapes cover it")
+        pytest.skip("the fp32 kernels are covered by the small shapes and by test_product_routes.py")
     rng = np.random.default_rng(M * 7 + N + K)
     X, W = _rand(rng, (M, K), dtype), _rand(rng, (N, K), dtype, 0.1)
     bias, U = _rand(rng, (N,), dtype), _rand(rng, (M, N), dtype, 1.5)
@@ -266,7 +267,8 @@ def test_gemm_pieces_of_rows(M, N, off):
     assert np.array_equal(got[off:off + M * N].reshape(M, N), 1 + 2 * ref0) and (got[:off] == 1).all() and (got[off + M * N:] == 1).all()
 
 
-# Weight-gradient shapes: small result, K = all tokens; C holds an earlier gradient that must be kept.
+# Weight-gradient shapes: small result, K = all tokens; C holds an earlier gradient that must be kept.  (Split K:
+# test_product_routes.py.)
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 8192), (3072, 1024, 8192), (1000, 520, 4096), (256, 256, 2048)])
 def test_gemm_accumulate_long_k(M, N, K):
     pf, dev = _mods()

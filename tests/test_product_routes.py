@@ -1,0 +1,124 @@
+"""Every GEMM kernel is run by some case here, and the case says by which: the rules that pick a kernel are host code, so
+the CPU part of this file fails when a rule moves a case to another kernel and leaves one without a test.
+
+Numbers (GPU part) against float64: tolerance 1e-2 of the largest value for bf16 results (one rounding is 2^-9 of a value),
+1e-5 for fp32 ones (K products of the inputs, which are exact, summed in fp32 in some order)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import transformer as ot          # noqa: E402
+from paper_2410_07192_amd import synth        # noqa: E402
+
+KERNELS = ("f32 fma", "bf16 generic", "ring 32x32", "ring 32x64", "ring 64x64", "ring 128x64", "tile 256x256",
+           "tile 256x192", "tile 128x128", "tile 128x128 deep")
+EPI = {"plain": 0, "bias": 1, "gelu": 3, "resid": 5, "pre": 19, "dact": 8, "sum": 32}   # sum: fp32 result, accumulated
+
+
+def route(dtype, M, N, K, epi="plain", misaligned=False):
+    """Kernel and number of K slices of a product."""
+    from paper_2410_07192_amd import binding as pf
+    f = pf.lib.pf_gemm_route
+    f.restype, f.argtypes = C.c_int32, [C.c_int32, C.c_int64, C.c_int64, C.c_int64, C.c_int32, C.c_int32]
+    f32 = dtype == "f32"
+    r = f(pf.PF_DTYPE_F32 if f32 else pf.PF_DTYPE_BF16, M, N, K, EPI[epi],
+          int(misaligned) | (2 if f32 or epi == "sum" else 0))
+    return KERNELS[r & 255], r >> 8
+
+
+ALL = tuple(EPI)
+# dtype, M, N, K, epilogues, kernel, K slices
+PATHS = [
+    # K no multiple of 64 on more tiles than the ring kernel takes: ragged, whole along M and N
+    ("bf16", 1800, 2300, 200, ALL, "bf16 generic", 1),
+    ("bf16", 2048, 1792, 72, ALL, "bf16 generic", 1),
+    # fp32 rows that are not whole 16-byte chunks
+    ("f32", 65, 99, 37, ALL, "f32 fma", 1),
+    ("f32", 130, 70, 6, ALL, "f32 fma", 1),
+    # fp32 on every tile of the ring kernel
+    ("f32", 97, 260, 36, ALL, "ring 32x32", 1),
+    ("f32", 1000, 260, 36, ALL, "ring 32x64", 1),
+    ("f32", 1023, 516, 36, ALL, "ring 64x64", 1),
+    ("f32", 2047, 772, 64, ALL, "ring 128x64", 1),
+    # K split over workgroups that have their CU to themselves (four LDS stages), ragged and whole, and that share it
+    ("bf16", 100, 132, 16384, ("sum",), "tile 128x128 deep", 8),
+    ("bf16", 1536, 512, 8192, ("sum",), "tile 128x128 deep", 4),
+    ("bf16", 384, 3072, 4096, ("sum",), "tile 128x128 deep", 2),
+    ("bf16", 900, 516, 16384, ("sum",), "tile 128x128", 8),
+    ("bf16", 1024, 3072, 16384, ("sum",), "tile 128x128", 2),
+]
+
+
+@pytest.mark.parametrize("dtype,M,N,K,epis,kernel,splits", PATHS)
+def test_the_case_runs_on_the_kernel_it_is_for(dtype, M, N, K, epis, kernel, splits):
+    assert {route(dtype, M, N, K, e) for e in epis} == {(kernel, splits)}
+
+
+# what other GPU tests are for: large tiles with ragged edges, edge tiles, the training epilogues, grids that do not
+# fill the chip, rows in pieces
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (8292, 2368, 128, "tile 256x192"), (8292, 2370, 64, "tile 256x192"), (4196, 2372, 64, "tile 256x192"),
+    (8292, 3112, 128, "tile 256x256"), (4196, 6150, 64, "tile 256x256"), (4196, 6152, 320, "tile 256x256"),
+    (4196, 3112, 64, "tile 256x256"), (8292, 3108, 64, "tile 256x256"), (8292, 2368, 64, "tile 256x192"),
+    (1659, 3072, 64, "tile 128x128"), (1999, 2044, 64, "tile 128x128 deep"), (1999, 2040, 64, "tile 128x128 deep"),
+    (1999, 2040, 320, "tile 128x128 deep"), (33, 36, 72, "ring 32x32"), (128, 2300, 776, "ring 32x64"),
+    (450, 2044, 1992, "ring 64x64"), (1659, 764, 3072, "ring 128x64")])
+def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
+    assert {route("bf16", M, N, K, e)[0] for e in ("bias", "gelu", "resid", "pre", "dact")} == {kernel}
+
+
+def test_misaligned_operands_go_to_the_kernels_without_16_byte_copies():
+    assert route("bf16", 128, 768, 768, misaligned=True) == ("bf16 generic", 1)
+    assert route("f32", 128, 768, 768, misaligned=True) == ("f32 fma", 1)
+
+
+def _product(dtype, M, N, K, epis):
+    from paper_2410_07192_amd import binding as pf
+    from paper_2410_07192_amd import device as dev
+    md = pf.pf_model_desc()
+    md.dtype = pf.PF_DTYPE_BF16 if dtype == "bf16" else pf.PF_DTYPE_F32
+    rng = np.random.default_rng(M + N + K)
+
+    def draw(shape, scale):
+        a = (rng.standard_normal(shape) * scale).astype(np.float32)
+        return synth.round_to_bf16(a) if dtype == "bf16" else a
+
+    X, W, bias, R = draw((M, K), 1.0), draw((N, K), 0.05), draw((N,), 1.0), draw((M, N), 1.5)
+    dX, dW, db, dR = (dev.storage_tensor(a, md) for a in (X, W, bias, R))
+    p = X.astype(np.float64) @ W.astype(np.float64).T
+    u = p + bias
+    pre = dev.empty_storage((M, N), md)
+    calls = {"plain": ({}, p), "bias": (dict(bias=db.data_ptr()), u),
+             "gelu": (dict(bias=db.data_ptr(), gelu=1), ot.gelu(u)),
+             "resid": (dict(bias=db.data_ptr(), resid=dR.data_ptr()), u + R),
+             "pre": (dict(bias=db.data_ptr(), gelu=1, preact_out=pre.data_ptr()), ot.gelu(u)),
+             "dact": (dict(dact_in=dR.data_ptr()), p * ot.gelu_grad(R.astype(np.float64)))}
+    err = lambda got, ref: float(np.abs(got - ref).max() / np.abs(ref).max())
+    tol = 1e-2 if dtype == "bf16" else 1e-5
+    for e in epis:
+        if e == "sum":
+            before = rng.standard_normal((M + 1, N)).astype(np.float32)
+            acc = torch.from_numpy(before).cuda()
+            for _ in range(2):
+                pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), acc.data_ptr(), M, N, K, out_f32=1, accumulate=1)
+            torch.cuda.synchronize()
+            got = acc.cpu().numpy()
+            assert err(got[:M], before[:M] + 2 * p) < 1e-5 and np.array_equal(got[M], before[M])
+            continue
+        out = dev.empty_storage((M + 1, N), md)          # one extra row behind C: must stay untouched
+        out.zero_()
+        pf.pf_op_gemm(md.dtype, dX.data_ptr(), dW.data_ptr(), out.data_ptr(), M, N, K, **calls[e][0])
+        torch.cuda.synchronize()
+        got = dev.read_storage(out, md)
+        assert err(got[:M], calls[e][1]) < tol and not got[M].any(), e
+        if e == "pre":
+            assert err(dev.read_storage(pre, md), u) < tol
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,N,K,epis,kernel,splits", PATHS)
+def test_numbers_of_every_path(dtype, M, N, K, epis, kernel, splits):
+    _product(dtype, M, N, K, epis)
