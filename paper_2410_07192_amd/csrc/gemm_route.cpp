@@ -3,33 +3,48 @@
 
 #include "pf_internal.h"
 
+#include <algorithm>
+
 namespace pf {
 namespace gemm {
 namespace {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Ring kernel, tile shapes: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of X,
-// in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
-// product but spreads them over four times the CUs.  fp32 is bound by its MFMAs (64 cycles for two K), which
-// the 32x32 tile hides best; the 128x64 tile never wins there.
-struct RingShape { int bm, bn; double fixed, bf16_byte, f32_byte; };
-constexpr RingShape ring_shapes[] = {
-    {32, 32, 2.6, 0.00098, 0.0018}, {32, 64, 3.5, 0.0014, 0.0036}, {64, 64, 4.6, 0.0017, 0.0044}, {128, 64, 7.5, 0.0028, 0.011}};
+// Ring kernel, tile shapes.  bf16: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of
+// X, in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
+// product but spreads them over four times the CUs.
+struct RingShape { int bm, bn; double fixed, byte; };
+constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.0014}, {64, 64, 4.6, 0.0017}, {128, 64, 7.5, 0.0028}};
+// fp32: start + rounds x (fixed + per_k x K), K rounded up to the elements that all waves of the workgroup take in one step
+// where few waves make that visible.  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
+// K = 512 25 / 28 / 28 / 33 us, K = 1024 on 2048 x 2048 124 / 127 / 87 / 105 us (32x32, 32x64, 64x64, 128x64).  The 128x64
+// tile wins by up to a tenth where it saves a round and K fits two steps (2048 x 2048, K = 192: 32.3 us, 64x64 35.3).
+struct RingShapeF32 { double start, fixed, per_k; int step; };
+constexpr RingShapeF32 ring_shapes_f32[] = {{1.5, 2.0, 0.0055, 1}, {1.2, 2.9, 0.0125, 1}, {1.0, 4.1, 0.017, 128}, {0.5, 7.4, 0.0417, 96}};
 
 double ring_estimate(const Product& p, Kernel* shape) {
-  const int elem = p.bf16 ? 2 : 4;
   double best = 1e30;
   for (int i = 0; i < 4; ++i) {
     const RingShape& s = ring_shapes[i];
-    const int64_t tiles = ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn);
-    const double t = (double)ceil_div(tiles, 256) * (s.fixed + (elem == 2 ? s.bf16_byte : s.f32_byte) * (double)(p.K * elem));
+    const double rounds = (double)ceil_div(ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn), 256);
+    double t = rounds * (s.fixed + s.byte * (double)(p.K * 2));
+    if (!p.bf16) {
+      const RingShapeF32& f = ring_shapes_f32[i];
+      t = f.start + rounds * (f.fixed + f.per_k * (double)(ceil_div(p.K, f.step) * f.step));
+    }
     if (t < best) {
       best = t;
       *shape = (Kernel)(RING_32x32 + i);
     }
   }
   return best;
+}
+
+// fp32 FMA kernel (64x64 tiles, many workgroups per CU): one workgroup's own time, or the chip's rate.
+double fma_estimate(const Product& p) {
+  const double tiles = (double)(ceil_div(p.M, 64) * ceil_div(p.N, 64)), k = (double)p.K;
+  return std::max(5.5 + 0.093 * k + 0.003 * tiles, 2.5 + tiles / 256 * (1.8 + 0.03 * k));
 }
 
 // Tiled kernels, and the ring kernel where it is faster.
@@ -97,9 +112,12 @@ bool tiled(const Product& p) {
 Route route(const Product& p) {
   Kernel ring;
   if (!p.bf16) {
-    // 2048 x 512, K = 2048: 297 -> 41 us; 512 x 256, K = 1024: 115 -> 10 us
+    // The ring kernel takes 2048 x 512, K = 2048 from 297 to 41 us and 512 x 256, K = 1024 from 115 to 10, but one workgroup
+    // a CU and rounds of 4 us lose where K is short and C large: 4096 x 2048, K = 64 45 us against 29, K = 128 60 against
+    // 46, K = 192 61 against 61, K = 256 69 against 78; 2048 x 576, K = 32 12.1 against 9.6, K = 64 12.2 against 12.9.
+    // (The FMA kernel's grid holds 65535 row tiles.)
     if (p.K % 4 != 0 || !p.aligned) return Route{F32_FMA, 1};
-    ring_estimate(p, &ring);
+    if (fma_estimate(p) < ring_estimate(p, &ring) && ceil_div(p.M, 64) <= 65535) return Route{F32_FMA, 1};
     return Route{ring, 1};
   }
   if (tiled(p)) return tiled_route(p);

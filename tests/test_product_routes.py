@@ -38,6 +38,8 @@ PATHS = [
     # fp32 rows that are not whole 16-byte chunks
     ("f32", 65, 99, 37, ALL, "f32 fma", 1),
     ("f32", 130, 70, 6, ALL, "f32 fma", 1),
+    # fp32, large C and short K: aligned rows on the same kernel
+    ("f32", 2047, 770, 16, ALL, "f32 fma", 1),
     # fp32 on every tile of the ring kernel
     ("f32", 97, 260, 36, ALL, "ring 32x32", 1),
     ("f32", 1000, 260, 36, ALL, "ring 32x64", 1),
@@ -68,6 +70,26 @@ def test_the_case_runs_on_the_kernel_it_is_for(dtype, M, N, K, epis, kernel, spl
     (450, 2044, 1992, "ring 64x64"), (1659, 764, 3072, "ring 128x64")])
 def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     assert {route("bf16", M, N, K, e)[0] for e in ("bias", "gelu", "resid", "pre", "dact")} == {kernel}
+
+
+# The faster kernel at sizes where two were timed on MI355X (times in us, the chosen one first): the rules follow them.
+@pytest.mark.parametrize("dtype,M,N,K,epi,kernels", [
+    # fp32: FMA kernel against the best ring tile
+    ("f32", 4096, 2048, 64, "bias", "f32 fma"),        # 29 / 45
+    ("f32", 8192, 1024, 128, "bias", "f32 fma"),       # 44 / 52
+    ("f32", 2048, 2048, 64, "bias", "f32 fma"),        # 18.7 / 23.7
+    ("f32", 2048, 576, 32, "bias", "f32 fma"),         # 9.6 / 12.0
+    ("f32", 2048, 576, 64, "bias", "ring"),            # 12.1 / 12.9
+    ("f32", 2048, 1024, 96, "bias", "ring"),           # 13.0 / 16.8
+    ("f32", 2048, 576, 128, "bias", "ring 64x64"),     # 13.7; 128x64 16.2, fma 20.8
+    ("f32", 2048, 2048, 192, "bias", "ring 128x64"),   # 32.3; 64x64 35.3, fma 38.0
+    ("f32", 2048, 576, 512, "bias", "ring 32x32"),     # 25.2; 64x64 27.6
+    ("f32", 4096, 2048, 256, "bias", "ring 64x64"),    # 69.4 / 78.3
+    ("f32", 512, 1024, 256, "gelu", "ring"),           # a layer of d 256 on 512 tokens
+    ("f32", 512, 256, 1024, "resid", "ring"),
+])
+def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
+    assert route(dtype, M, N, K, epi)[0].startswith(kernels)
 
 
 def test_misaligned_operands_go_to_the_kernels_without_16_byte_copies():
