@@ -15,7 +15,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // X, in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
 // product but spreads them over four times the CUs.
 struct RingShape { int bm, bn; double fixed, byte; };
-constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.0014}, {64, 64, 4.6, 0.0017}, {128, 64, 7.5, 0.0028}};
+constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.0014}, {64, 64, 4.6, 0.0017}, {128, 64, 7.9, 0.0032}};
 // fp32: start + rounds x (fixed + per_k x K), K rounded up to the elements that all waves of the workgroup take in one step
 // where few waves make that visible.  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
 // K = 512 25 / 28 / 28 / 33 us, K = 1024 on 2048 x 2048 124 / 127 / 87 / 105 us (32x32, 32x64, 64x64, 128x64).  The 128x64
@@ -39,6 +39,11 @@ double ring_estimate(const Product& p, Kernel* shape) {
     }
   }
   return best;
+}
+
+// Generic bf16 kernel on up to 256 whole tiles: a memory latency per K step, and C's layout read 32 rows at a time.
+double generic_estimate(const Product& p) {
+  return 5.8 + 0.98 * (double)ceil_div(p.K, 64) + (p.epi & (E_ACC | E_RESID | E_DACT) ? 5.7 : 0.0);
 }
 
 // fp32 FMA kernel (64x64 tiles, many workgroups per CU): one workgroup's own time, or the chip's rate.
@@ -121,12 +126,16 @@ Route route(const Product& p) {
     return Route{ring, 1};
   }
   if (tiled(p)) return tiled_route(p);
-  // The rest (K not a multiple of 64, scaled results, other combinations of epilogues): the generic kernel pays a memory
-  // latency per K step and is the faster one only where it fills the chip (1024 x 4096, K = 1000, 256 tiles: 29 us
-  // against 35; 64 tiles, 2048 x 512, K = 600: 17.9 us against 8.3).
+  // The rest (K not a multiple of 64, scaled results, other combinations of epilogues).  Above 192 tiles of 128x128 the ring
+  // kernel needs a round more (2048 x 1792, 224 tiles: K = 200 21.6 us against 15.5, K = 1000 34.3 against 28.2).  Up to there
+  // the estimates decide, for C in whole tiles; a ragged C costs the generic kernel 7 us, and the ring kernel nothing.
+  // Fitted to 32 .. 192 tiles, K = 40 .. 4104 (rows that don't start on a cache line cost the ring kernel 8 %); generic
+  // against ring, us: 2048 x 1536 K = 200 9.6 / 14.5, K = 1000 20.1 / 23.2, K = 2008 38.3 / 33.9, accumulating into fp32
+  // K = 600 21.2 / 22.1, K = 1000 27.6 / 26.8; 1024 x 2048 K = 40 6.8 / 8.3, K = 328 10.7 / 10.0; 512 x 512 K = 40 6.3 / 3.5.
   if (p.aligned && ceil_div(p.M, 128) * ceil_div(p.N, 128) <= 192) {
-    ring_estimate(p, &ring);
-    return Route{ring, 1};
+    const double t = ring_estimate(p, &ring);
+    const bool whole = p.M % 128 == 0 && p.N % 128 == 0;
+    if (!whole || 1.08 * t < generic_estimate(p)) return Route{ring, 1};
   }
   return Route{BF16_GENERIC, 1};
 }

@@ -87,6 +87,19 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("f32", 4096, 2048, 256, "bias", "ring 64x64"),    # 69.4 / 78.3
     ("f32", 512, 1024, 256, "gelu", "ring"),           # a layer of d 256 on 512 tokens
     ("f32", 512, 256, 1024, "resid", "ring"),
+    # K no multiple of 64: generic kernel against the best ring tile
+    ("bf16", 128, 24576, 200, "plain", "bf16 generic"),    # 10.5 / 15.4
+    ("bf16", 2048, 1536, 1000, "plain", "bf16 generic"),   # 20.1 / 23.2
+    ("bf16", 2048, 1536, 2008, "plain", "ring"),           # 33.9 / 38.3
+    ("bf16", 2048, 1536, 328, "resid", "bf16 generic"),    # 17.1 / 18.4
+    ("bf16", 2048, 1536, 600, "sum", "bf16 generic"),      # 21.2 / 22.1
+    ("bf16", 2048, 1536, 1000, "sum", "ring"),             # 26.8 / 27.6
+    ("bf16", 1024, 2048, 104, "plain", "bf16 generic"),    # 7.6 / 8.3
+    ("bf16", 1024, 2048, 328, "plain", "ring"),            # 10.0 / 10.7
+    ("bf16", 1024, 2048, 104, "sum", "ring"),              # 10.6 / 11.8
+    ("bf16", 512, 512, 40, "plain", "ring"),               # 3.5 / 6.3
+    ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 13.3 / 15.1
+    ("bf16", 2048, 512, 600, "sum", "ring"),               # weight gradients of 600 tokens, d 512
 ])
 def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
     assert route(dtype, M, N, K, epi)[0].startswith(kernels)
