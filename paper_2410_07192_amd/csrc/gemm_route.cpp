@@ -13,7 +13,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Ring kernel, tile shapes.  bf16: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of
 // X, in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
-// product but spreads them over four times the CUs.
+// product but spreads them over four times the CUs; on few CUs its bytes come faster (one tile 0.00062 us each).
 struct RingShape { int bm, bn; double fixed, byte; };
 constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.0014}, {64, 64, 4.6, 0.0017}, {128, 64, 7.9, 0.0032}};
 // fp32: start + rounds x (fixed + per_k x K), K rounded up to the elements that all waves of the workgroup take in one step
@@ -27,8 +27,10 @@ double ring_estimate(const Product& p, Kernel* shape) {
   double best = 1e30;
   for (int i = 0; i < 4; ++i) {
     const RingShape& s = ring_shapes[i];
-    const double rounds = (double)ceil_div(ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn), 256);
-    double t = rounds * (s.fixed + s.byte * (double)(p.K * 2));
+    const int64_t tiles = ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn);
+    const double rounds = (double)ceil_div(tiles, 256);
+    const double byte = i == 0 ? 0.00062 + 0.00036 * (double)std::min<int64_t>(tiles, 256) / 256 : s.byte;
+    double t = rounds * (s.fixed + byte * (double)(p.K * 2));
     if (!p.bf16) {
       const RingShapeF32& f = ring_shapes_f32[i];
       t = f.start + rounds * (f.fixed + f.per_k * (double)(ceil_div(p.K, f.step) * f.step));
@@ -68,7 +70,8 @@ double fma_estimate(const Product& p) {
 // per 128x128 tile while that fills idle CUs and leaves each >= 8 K steps; the slices add into C with fp32 atomics
 // (order-dependent in the last bits, like the other atomic reductions over tokens).  Those atomics go at about
 // 1.5 TB/s on MI355X, far below plain stores, so the estimate charges every slice for its tile: two slices usually
-// pay, eight rarely do.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
+// pay, eight rarely do.  Two slices that leave some CUs with one workgroup are charged between the alone and the paired
+// rate: 1024 x 3072, K = 8192 unsplit 86.6 us, two slices 76.3; 2048 x 1536 81.4 and 70.7; K = 4096 44.8 and 47.0.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
 // round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
 Route tiled_route(const Product& p) {
   struct Shape { Kernel kernel; int bm, bn, resident, eff100; } const shapes[3] = {
@@ -87,7 +90,9 @@ Route tiled_route(const Product& p) {
       const bool alone = small && wgs <= 256;   // a 128x128 workgroup that has its CU, and four stages, to itself
       const int64_t steps = p.K / (64 * splits) + (alone ? 6 : 4);
       // area in flight per CU x relative cost
-      const int64_t per_step = alone ? (int64_t)sh.bm * sh.bn * 141 : (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
+      const int64_t lone = (int64_t)sh.bm * sh.bn * 141, full = (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
+      const bool between = splits == 2 && wgs > 256 && wgs < 512;
+      const int64_t per_step = alone ? lone : between ? lone + (full - lone) * (wgs - 256) / 256 : full;
       int64_t cost = rounds * steps * per_step;
       if (p.N % sh.bn) cost += cost * 3 / 10;
       // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate

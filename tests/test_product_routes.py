@@ -100,9 +100,20 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("bf16", 512, 512, 40, "plain", "ring"),               # 3.5 / 6.3
     ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 13.3 / 15.1
     ("bf16", 2048, 512, 600, "sum", "ring"),               # weight gradients of 600 tokens, d 512
+    # weight gradients over long K: split or not, or few small tiles
+    ("bf16", 1024, 3072, 8192, "sum", "tile 128x128"),       # two slices 76.3 / unsplit 86.6
+    ("bf16", 64, 64, 8192, "sum", "ring 32x32"),             # 12.9 / eight slices 15.5
+    ("bf16", 1024, 3072, 4096, "sum", "tile 128x128 deep"),  # unsplit 44.8 / two slices 47.0
+    ("bf16", 384, 3072, 4096, "sum", "tile 128x128 deep"),   # two slices 29.8 / four 33.2, unsplit 42.5
+    ("bf16", 1024, 1024, 8192, "sum", "ring 64x64"),         # 29.9 / four slices 36.8
 ])
 def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
     assert route(dtype, M, N, K, epi)[0].startswith(kernels)
+
+
+def test_two_slices_where_they_are_faster():
+    assert [route("bf16", M, N, K, "sum")[1] for M, N, K in
+            ((1024, 3072, 8192), (3072, 1024, 8192), (2048, 1536, 8192), (1024, 3072, 4096), (2048, 2048, 8192))] == [2, 2, 2, 1, 1]
 
 
 def test_misaligned_operands_go_to_the_kernels_without_16_byte_copies():
