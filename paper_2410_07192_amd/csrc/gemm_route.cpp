@@ -95,8 +95,9 @@ Route tiled_route(const Product& p) {
       const int64_t per_step = alone ? lone : between ? lone + (full - lone) * (wgs - 256) / 256 : full;
       int64_t cost = rounds * steps * per_step;
       if (p.N % sh.bn) cost += cost * 3 / 10;
-      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate
-      if (splits > 1) cost += p.M * p.N * splits * 10;
+      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate, and 2.5 us
+      // whatever its size (128 x 128, K = 4096: 25.9, 16.6 and 11.9 us with two, four and eight slices)
+      if (splits > 1) cost += p.M * p.N * splits * 10 + 9500000;
       if (best_cost < 0 || cost < best_cost) {
         best_cost = cost;
         best = Route{alone ? TILE_128x128_DEEP : sh.kernel, splits};

@@ -46,8 +46,8 @@ PATHS = [
     ("f32", 1023, 516, 36, ALL, "ring 64x64", 1),
     ("f32", 2047, 772, 64, ALL, "ring 128x64", 1),
     # K split over workgroups that have their CU to themselves (four LDS stages), ragged and whole, and that share it
-    ("bf16", 100, 132, 16384, ("sum",), "tile 128x128 deep", 8),
-    ("bf16", 1536, 512, 8192, ("sum",), "tile 128x128 deep", 4),
+    ("bf16", 100, 768, 16384, ("sum",), "tile 128x128 deep", 8),
+    ("bf16", 1100, 512, 8192, ("sum",), "tile 128x128 deep", 4),
     ("bf16", 384, 3072, 4096, ("sum",), "tile 128x128 deep", 2),
     ("bf16", 900, 516, 16384, ("sum",), "tile 128x128", 8),
     ("bf16", 1024, 3072, 16384, ("sum",), "tile 128x128", 2),
@@ -106,6 +106,8 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("bf16", 1024, 3072, 4096, "sum", "tile 128x128 deep"),  # unsplit 44.8 / two slices 47.0
     ("bf16", 384, 3072, 4096, "sum", "tile 128x128 deep"),   # two slices 29.8 / four 33.2, unsplit 42.5
     ("bf16", 1024, 1024, 8192, "sum", "ring 64x64"),         # 29.9 / four slices 36.8
+    ("bf16", 1536, 512, 8192, "sum", "ring 64x64"),          # 28.0 / four slices 32.6
+    ("bf16", 100, 132, 16384, "sum", "ring 32x32"),          # 22.9 / eight slices 25.4
 ])
 def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
     assert route(dtype, M, N, K, epi)[0].startswith(kernels)
