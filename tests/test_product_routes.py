@@ -100,6 +100,10 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("bf16", 512, 512, 40, "plain", "ring"),               # 3.5 / 6.3
     ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 13.3 / 15.1
     ("bf16", 2048, 512, 600, "sum", "ring"),               # weight gradients of 600 tokens, d 512
+    # partial tiles along N for the chosen shape, none for the other
+    ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 54.2 / whole 128x128 tiles 70.8
+    ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 53.4 / whole 128x128 tiles 69.0
+    ("bf16", 1659, 960, 768, "resid", "tile 128x128 deep"),  # 12.6 / ring 13.1
     # weight gradients over long K: split or not, or few small tiles
     ("bf16", 1024, 3072, 8192, "sum", "tile 128x128"),       # two slices 76.3 / unsplit 86.6
     ("bf16", 64, 64, 8192, "sum", "ring 32x32"),             # 12.9 / eight slices 15.5
