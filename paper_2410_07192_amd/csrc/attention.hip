@@ -10,8 +10,8 @@
 // comes out of the row-major V tile through the transposing LDS load (ds_read_b64_tr_b16), two per fragment.
 //
 // fp32, d_head 32, 64 or 128: fp32 MFMAs, 32 queries per workgroup (attn_fwd_f32_kernel).
-// Generic path (other d_head in {8,16,32,64,128}): one thread per query, keys staged in LDS,
-// online softmax key by key.
+// Generic path (other d_head in {8,16,32,64,128}, and many heads of short sequences): one thread per query, keys staged in
+// LDS, online softmax key by key.
 #include "pf_kernels.h"
 #include "pf_device.h"
 
@@ -556,6 +556,22 @@ hipError_t launch_generic(const void* qkv, void* out, float* lse, int32_t B, int
   return hipGetLastError();
 }
 
+// fp32, d_head 32 / 64 / 128: whether 32x32 tiles beat one thread per query.  Up to 64 tokens a workgroup of the tiled kernel
+// computes whole tiles whatever S is, and with many heads that costs more than the serial chains it avoids.  Measured on
+// MI355X at S = 1 .. 128, 16 .. 8192 heads in all (us, one thread per query / tiles): 4096 heads of 16 tokens, d_head 32
+// 27 / 68; 2048 heads, d_head 64, S = 24 47 / 53, S = 32 60 / 47, S = 48 92 / 111, S = 64 125 / 96; d_head 128, S = 4 55 / 78,
+// S = 16 139 / 86; up to 128 heads the tiles win everywhere (16 heads of one token 6.9 / 6.0).
+bool f32_by_tiles(int64_t B, int64_t S, int64_t h, int32_t dh) {
+  if (dh != 32 && dh != 64 && dh != 128) return false;
+  if (S > 64) return true;
+  struct Cost { double tile, start, key, rate; };   // us: a round of 256 workgroups; a lone chain, per key; 256 waves, per key
+  const Cost c = dh == 32 ? Cost{4.4, 6.0, 0.43, 0.1} : dh == 64 ? Cost{6.0, 9.5, 0.9, 0.22} : Cost{9.7, 16.0, 2.7, 1.3};
+  const double units = (double)(B * h), blocks = units * (double)((S + 31) / 32);
+  const double tiles = 1.5 + c.tile * ceil(blocks / 256);
+  const double chains = fmax(c.start + c.key * (double)S, c.rate * (double)S * units / 256);
+  return tiles <= chains;
+}
+
 }  // namespace
 
 hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, int32_t B, int32_t S, int32_t h,
@@ -596,7 +612,7 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
     return hipGetLastError();
   }
   if (dtype == PF_DTYPE_BF16_) return launch_generic<bf16_t>(qkv, out, lse, B, S, h, dh, causal, stream);
-  if ((dh == 32 || dh == 64 || dh == 128) && (((uintptr_t)qkv | (uintptr_t)out) & 15) == 0) {   // 16-byte loads and stores
+  if (f32_by_tiles(B, S, h, dh) && (((uintptr_t)qkv | (uintptr_t)out) & 15) == 0) {   // 16-byte loads and stores
     const dim3 grid((unsigned)((S + 31) / 32), (unsigned)h, (unsigned)B), block(256);
     const float scale = 1.0f / sqrtf((float)dh);
 #define PF_ATT32(D) hipLaunchKernelGGL(attn_fwd_f32_kernel<D>, grid, block, 0, stream, (const float*)qkv, (float*)out, lse, S, h, causal, scale)
@@ -610,3 +626,8 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
 }
 
 }  // namespace pf
+
+// For tests: whether fp32 attention of this size runs on the tiled kernel.
+extern "C" int32_t pf_attention_f32_tiles(int64_t B, int64_t S, int64_t h, int32_t dh) {
+  return pf::f32_by_tiles(B, S, h, dh) ? 1 : 0;
+}

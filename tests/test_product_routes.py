@@ -170,6 +170,54 @@ def _product(dtype, M, N, K, epis):
             assert err(dev.read_storage(pre, md), u) < tol
 
 
+# fp32 attention, heads in all, tokens, d_head: tiles or one thread per query (us, the chosen one first)
+ATTENTION = [(4096, 16, 32, False),    # 27 / 68
+             (1024, 8, 64, False),     # 17.6 / 25.6
+             (2048, 24, 64, False),    # 47 / 53
+             (2048, 48, 64, False),    # 92 / 111
+             (2048, 4, 128, False),    # 55 / 78
+             (2048, 32, 64, True),     # 47 / 60
+             (2048, 64, 64, True),     # 96 / 125
+             (2048, 16, 128, True),    # 86 / 139
+             (512, 16, 32, True),      # 10.1 / 13.3
+             (16, 1, 32, True),        # 6.0 / 6.9
+             (16, 128, 64, True)]      # four sequences of 128 tokens, d 256: 7.7 / 129
+
+
+@pytest.mark.parametrize("units,S,dh,tiles", ATTENTION)
+def test_the_faster_fp32_attention_is_chosen(units, S, dh, tiles):
+    from paper_2410_07192_amd import binding as pf
+    f = pf.lib.pf_attention_f32_tiles
+    f.restype, f.argtypes = C.c_int32, [C.c_int64, C.c_int64, C.c_int64, C.c_int32]
+    assert {bool(f(units // h, S, h, dh)) for h in (1, 4, 16)} == {tiles}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("units,S,dh", [a[:3] for a in ATTENTION if not a[3]])
+def test_numbers_of_many_short_fp32_sequences(units, S, dh, causal):
+    from paper_2410_07192_amd import binding as pf
+    from paper_2410_07192_amd import device as dev
+    md = pf.pf_model_desc()
+    md.dtype = pf.PF_DTYPE_F32
+    h = 8
+    B, d = units // h, h * dh
+    rng = np.random.default_rng(S + dh)
+    qkv = rng.standard_normal((B, S, 3 * d), dtype=np.float32)
+    dq, out = dev.storage_tensor(qkv, md), dev.empty_storage((B, S, d), md)
+    lse = torch.empty((B, h, S), dtype=torch.float32, device="cuda")
+    pf.pf_op_attention(md.dtype, dq.data_ptr(), out.data_ptr(), B, S, h, dh, causal, lse.data_ptr())
+    torch.cuda.synchronize()
+    q, k, v = (ot.split_heads(qkv[..., i * d:(i + 1) * d].astype(np.float64), h) for i in range(3))
+    ref = ot.merge_heads(ot.attention_probs(q, k, causal) @ v)
+    s = q @ k.transpose(0, 1, 3, 2) / np.sqrt(dh)
+    if causal:
+        s = np.where(np.triu(np.ones((S, S), dtype=bool), 1), -np.inf, s)
+    ref_lse = np.log(np.exp(s).sum(-1))
+    assert np.abs(dev.read_storage(out, md) - ref).max() < 1e-5 * np.abs(ref).max()
+    assert np.abs(lse.cpu().numpy() - ref_lse).max() < 1e-4
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,M,N,K,epis,kernel,splits", PATHS)
 def test_numbers_of_every_path(dtype, M, N, K, epis, kernel, splits):
