@@ -20,8 +20,11 @@ constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.001
 // where few waves make that visible.  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
 // K = 512 25 / 28 / 28 / 33 us, K = 1024 on 2048 x 2048 124 / 127 / 87 / 105 us (32x32, 32x64, 64x64, 128x64).  The 128x64
 // tile wins by up to a tenth where it saves a round and K fits two steps (2048 x 2048, K = 192: 32.3 us, 64x64 35.3).
-struct RingShapeF32 { double start, fixed, per_k; int step; };
-constexpr RingShapeF32 ring_shapes_f32[] = {{1.5, 2.0, 0.0055, 1}, {1.2, 2.9, 0.0125, 1}, {1.0, 4.1, 0.017, 128}, {0.5, 7.4, 0.0417, 96}};
+// odd: what a round costs more when columns don't come in fours and every thread goes through its share of C element by
+// element (one group of four with the 32x32 tile, eleven with 128x64: 2958 x 418, K = 80 21 us, 4004 x 5119, K = 316 267).
+struct RingShapeF32 { double start, fixed, per_k; int step; double odd; };
+constexpr RingShapeF32 ring_shapes_f32[] = {
+    {1.5, 2.0, 0.0055, 1, 0.9}, {1.2, 2.9, 0.0125, 1, 2.2}, {1.0, 4.1, 0.017, 128, 2.9}, {0.5, 7.4, 0.0417, 96, 9.4}};
 
 double ring_estimate(const Product& p, Kernel* shape) {
   double best = 1e30;
@@ -33,7 +36,7 @@ double ring_estimate(const Product& p, Kernel* shape) {
     double t = rounds * (s.fixed + byte * (double)(p.K * 2));
     if (!p.bf16) {
       const RingShapeF32& f = ring_shapes_f32[i];
-      t = f.start + rounds * (f.fixed + f.per_k * (double)(ceil_div(p.K, f.step) * f.step));
+      t = f.start + rounds * (f.fixed + f.per_k * (double)(ceil_div(p.K, f.step) * f.step) + (p.N % 4 ? f.odd : 0.0));
     }
     if (t < best) {
       best = t;

@@ -85,6 +85,8 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("f32", 2048, 2048, 192, "bias", "ring 128x64"),   # 32.3; 64x64 35.3, fma 38.0
     ("f32", 2048, 576, 512, "bias", "ring 32x32"),     # 25.2; 64x64 27.6
     ("f32", 4096, 2048, 256, "bias", "ring 64x64"),    # 69.4 / 78.3
+    ("f32", 4004, 5119, 316, "bias", "f32 fma"),       # columns not in fours: 215 / 64x64 267
+    ("f32", 2958, 418, 80, "gelu", "f32 fma"),         # 16.3 / 128x64 21.4
     ("f32", 512, 1024, 256, "gelu", "ring"),           # a layer of d 256 on 512 tokens
     ("f32", 512, 256, 1024, "resid", "ring"),
     # K no multiple of 64: generic kernel against the best ring tile
