@@ -8,22 +8,22 @@
 //    side (lane -> which chunk of the row it fetches).  Rows beyond M / N are clamped to the last
 //    valid row (their products are never stored).
 //  * Two LDS stages (four where a 128x128 workgroup has its CU to itself): the loads of step k+2 (k+4) go
-//    into the stage that the barrier ending step k has freed.  They are issued one at a time between the MFMAs of the following blocks (a burst
-//    blocks every wave at the address unit) and are inline assembly so that the compiler does not
-//    serialise every later LDS read behind them; vmcnt is waited by hand.
+//    into the stage that the barrier ending step k has freed.  They are issued one at a time between the
+//    MFMAs of the following blocks (a burst blocks every wave at the address unit) and are inline assembly
+//    so that the compiler does not serialise every later LDS read behind them; vmcnt is waited by hand.
 //  * Operand fragments are double buffered in registers: the 16-byte LDS reads of sub-step kk+1
 //    are in flight while the MFMAs of sub-step kk issue.
 //  * The weight tile is the MFMA "A" operand and the activation tile the "B" operand, so each lane
-//    ends up with 4 consecutive output columns of one output row: bias / GELU are applied in
-//    registers; bf16 tiles then pass through LDS and leave as 16-byte row-contiguous stores (the
-//    residual is added on the way out), other epilogues store 8- or 16-byte pieces directly.
-//  * Three tile shapes (256x256, 256x192, 128x128), chosen per launch by an estimate of rounds x
-//    steps x area; accumulating fp32 launches may split K (gemm_tile.h).
+//    ends up with 4 consecutive output columns of one output row: bias / GELU of whole bf16 tiles are
+//    applied in registers; these then pass through LDS and leave as 16-byte row-contiguous stores (the
+//    residual is added on the way out).  Everything else passes through LDS in fp32.
+//  * Three tile shapes (256x256, 256x192, 128x128); accumulating fp32 launches may split K.
 //  * Workgroup ids are remapped so that each of the 8 XCDs (ids are dealt round-robin to them) works
 //    on a contiguous range of tiles and its L2 sees each operand panel once.
-// Launches too small to fill the chip, and fp32 with 16-byte aligned rows: gemm_ring.hip.
+// Launches too small to fill the chip, and most of fp32: gemm_ring.hip.
 // bf16 generic path (any K multiple of 8): register-staged LDS tiles, same MFMA layout.
-// fp32 with odd rows: plain LDS-tiled FMA kernel with the same epilogue.
+// fp32 with odd rows, or with short K on a large result: plain LDS-tiled FMA kernel with the same epilogue.
+// Which of them runs a product: gemm_route.cpp.
 #include "pf_kernels.h"
 #include "gemm_tile.h"
 

@@ -24,7 +24,9 @@ namespace pf {
 namespace gemm {
 namespace {
 
-template <typename T, typename OutT, int TM, int TN, int WK, int DEPTH>
+constexpr int DEPTH = 2;   // LDS stages of a wave
+
+template <typename T, typename OutT, int TM, int TN, int WK>
 __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict__ X, const T* __restrict__ W, OutT* C,
                                                             int64_t M, int64_t N, int64_t K, EpiDev ep,
                                                             int32_t tiles_m, int32_t tiles_n, int32_t vec) {
@@ -33,7 +35,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   constexpr int LPS = (TM + TN) * 4;                    // 1 KB copies per stage
   constexpr int STAGE = LPS * 64;                       // uint4 per stage
   constexpr int UNITS = BN / 4, ITEMS = BM * BN / 4, IT = (ITEMS + NT - 1) / NT;
-  static_assert(DEPTH == 2 && LPS < 64, "vmcnt holds six bits");
+  static_assert(LPS < 64, "vmcnt holds six bits: one stage may stay on its way");
   static_assert(BM * BN * 4 <= DEPTH * STAGE * 16, "the partial tiles fit the stages");
   extern __shared__ uint4 smem[];
 
@@ -216,12 +218,12 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   }
 }
 
-template <typename T, typename OutT, int TM, int TN, int WK, int DEPTH>
+template <typename T, typename OutT, int TM, int TN, int WK>
 hipError_t launch_ring(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
                        hipStream_t stream) {
   static bool attr = false;
   constexpr int lds = WK * DEPTH * (TM + TN) * 4096;
-  auto kern = gemm_ring_kernel<T, OutT, TM, TN, WK, DEPTH>;
+  auto kern = gemm_ring_kernel<T, OutT, TM, TN, WK>;
   if (!attr) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -242,10 +244,10 @@ template <typename T, typename OutT>
 hipError_t launch_ring_shape(Kernel shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                              const EpiDev& ep, hipStream_t stream) {
   switch (shape) {
-    case RING_32x32: return launch_ring<T, OutT, 1, 1, 8, 2>(X, W, C, M, N, K, ep, stream);
-    case RING_32x64: return launch_ring<T, OutT, 1, 2, 6, 2>(X, W, C, M, N, K, ep, stream);
-    case RING_64x64: return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
-    case RING_128x64: return launch_ring<T, OutT, 4, 2, 3, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_32x32: return launch_ring<T, OutT, 1, 1, 8>(X, W, C, M, N, K, ep, stream);
+    case RING_32x64: return launch_ring<T, OutT, 1, 2, 6>(X, W, C, M, N, K, ep, stream);
+    case RING_64x64: return launch_ring<T, OutT, 2, 2, 4>(X, W, C, M, N, K, ep, stream);
+    case RING_128x64: return launch_ring<T, OutT, 4, 2, 3>(X, W, C, M, N, K, ep, stream);
     default: return hipErrorInvalidValue;
   }
 }
