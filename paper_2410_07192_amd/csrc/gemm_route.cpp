@@ -14,17 +14,17 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Ring kernel, tile shapes.  bf16: time of a round of up to 256 workgroups (one per CU) = fixed + per_byte x bytes of a row of
 // X, in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
 // product but spreads them over four times the CUs; on few CUs its bytes come faster (one tile 0.00062 us each).
-struct RingShape { int bm, bn; double fixed, byte; };
-constexpr RingShape ring_shapes[] = {{32, 32, 2.6, 0.00098}, {32, 64, 3.5, 0.0014}, {64, 64, 4.6, 0.0017}, {128, 64, 7.9, 0.0032}};
+// odd: what a round costs more when columns don't come in fours and every thread goes through its share of C element by
+// element (one group of four with the 32x32 tile, eleven with 128x64).
+struct RingShape { int bm, bn; double fixed, byte, odd; };
+constexpr RingShape ring_shapes[] = {
+    {32, 32, 2.6, 0.00098, 0.9}, {32, 64, 3.5, 0.0014, 2.2}, {64, 64, 4.6, 0.0017, 2.9}, {128, 64, 7.9, 0.0032, 9.4}};
 // fp32: start + rounds x (fixed + per_k x K), K rounded up to the elements that all waves of the workgroup take in one step
 // where few waves make that visible.  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
 // K = 512 25 / 28 / 28 / 33 us, K = 1024 on 2048 x 2048 124 / 127 / 87 / 105 us (32x32, 32x64, 64x64, 128x64).  The 128x64
 // tile wins by up to a tenth where it saves a round and K fits two steps (2048 x 2048, K = 192: 32.3 us, 64x64 35.3).
-// odd: what a round costs more when columns don't come in fours and every thread goes through its share of C element by
-// element (one group of four with the 32x32 tile, eleven with 128x64: 2958 x 418, K = 80 21 us, 4004 x 5119, K = 316 267).
-struct RingShapeF32 { double start, fixed, per_k; int step; double odd; };
-constexpr RingShapeF32 ring_shapes_f32[] = {
-    {1.5, 2.0, 0.0055, 1, 0.9}, {1.2, 2.9, 0.0125, 1, 2.2}, {1.0, 4.1, 0.017, 128, 2.9}, {0.5, 7.4, 0.0417, 96, 9.4}};
+struct RingShapeF32 { double start, fixed, per_k; int step; };
+constexpr RingShapeF32 ring_shapes_f32[] = {{1.5, 2.0, 0.0055, 1}, {1.2, 2.9, 0.0125, 1}, {1.0, 4.1, 0.017, 128}, {0.5, 7.4, 0.0417, 96}};
 
 double ring_estimate(const Product& p, Kernel* shape) {
   double best = 1e30;
@@ -33,10 +33,11 @@ double ring_estimate(const Product& p, Kernel* shape) {
     const int64_t tiles = ceil_div(p.M, s.bm) * ceil_div(p.N, s.bn);
     const double rounds = (double)ceil_div(tiles, 256);
     const double byte = i == 0 ? 0.00062 + 0.00036 * (double)std::min<int64_t>(tiles, 256) / 256 : s.byte;
-    double t = rounds * (s.fixed + byte * (double)(p.K * 2));
+    const double odd = p.N % 4 ? s.odd : 0.0;
+    double t = rounds * (s.fixed + odd + byte * (double)(p.K * 2));
     if (!p.bf16) {
       const RingShapeF32& f = ring_shapes_f32[i];
-      t = f.start + rounds * (f.fixed + f.per_k * (double)(ceil_div(p.K, f.step) * f.step) + (p.N % 4 ? f.odd : 0.0));
+      t = f.start + rounds * (f.fixed + odd + f.per_k * (double)(ceil_div(p.K, f.step) * f.step));
     }
     if (t < best) {
       best = t;
@@ -63,26 +64,32 @@ double fma_estimate(const Product& p) {
 // A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two: with two, one K step
 // is in flight and costs a memory latency (0.85 to 1.1 us per step; with four 0.61: 2048 x 2048, K = 8192 117 -> 88 us,
 // 333 x 8192, K = 2048 37.6 -> 25.8 us).
-// A launch takes ceil(workgroups / resident workgroups) rounds of (K steps + a fixed cost of about 4 steps); the
-// shape with the least estimated time rounds x steps x area in flight per CU / efficiency is taken.  Efficiencies
-// are measured on MI355X relative to the 256x256 tile (0.96 and 0.85).  E.g. N = 768 or 2304 fills whole rounds with
-// 192-wide tiles but wastes a quarter of the last round with 256-wide ones, and a 8192 x 1024 result gives every CU work
-// only with the small tile.  Partial tiles along N cost a shape nothing beyond the area they waste: over 380 products whose
-// N is whole for some shapes and not for others the choice is 0.2 % off the best without a charge, 0.9 % with 30 %
+// A launch takes ceil(workgroups / resident workgroups) rounds of start + step x (K steps of 64), in microseconds, measured
+// on MI355X (844 products, every shape timed); the shape with the least estimate runs.  That choice is 0.3 % off the
+// fastest shape on average and 13 % at most (1024 x 33024, K = 2048: 256x192 tiles 159 us, 256x256 141).  E.g. N = 768 or 2304
+// fills whole rounds with 192-wide tiles but wastes a quarter of the last round with 256-wide ones, and a 8192 x 1024
+// result gives every CU work only with the small tile.  (A chip full of 256-wide tiles runs at 1.3 to 1.5 times these
+// step times, every shape alike: the power limit.)  Partial tiles along N cost a shape nothing beyond the area they waste
 // (4096 x 3456, K = 2048: 256x256 tiles 54 us, whole 128x128 ones 71).  Rows that do not come in fours go element by
-// element, on every shape: 1.3 to 2.5 times the estimate, charged 30 % against the ring kernel.
+// element, a fixed time per round that grows with the elements of a wave (odd; odd_read where an operand of C's layout is
+// read as well).  So do GELU and the way of GELU' through LDS (dact: 8192 x 9648, K = 320 218 us on 256x256 tiles, 139 on
+// 128x128 ones).
 // Accumulating fp32 launches (weight gradients: small M x N, K = all tokens) may split K over up to 8 workgroups
 // per 128x128 tile while that fills idle CUs and leaves each >= 8 K steps; the slices add into C with fp32 atomics
 // (order-dependent in the last bits, like the other atomic reductions over tokens).  Those atomics go at about
 // 1.5 TB/s on MI355X, far below plain stores, so the estimate charges every slice for its tile: two slices usually
-// pay, eight rarely do.  Two slices that leave some CUs with one workgroup are charged between the alone and the paired
-// rate: 1024 x 3072, K = 8192 unsplit 86.6 us, two slices 76.3; 2048 x 1536 81.4 and 70.7; K = 4096 44.8 and 47.0.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
+// pay, eight rarely do.  Slices that leave some CUs with one workgroup are charged between the alone and the paired
+// rate: 1024 x 3072, K = 8192 unsplit 86.6 us, two slices 76.3; 2048 x 1536 81.4 and 70.7; K = 4096 44.8 and 47.0;
+// 768 x 1536, K = 8192 two slices 47.7, four 44.1.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
 // round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
 Route tiled_route(const Product& p) {
-  struct Shape { Kernel kernel; int bm, bn, resident, eff100; } const shapes[3] = {
-      {TILE_256x256, 256, 256, 256, 100}, {TILE_256x192, 256, 192, 256, 104}, {TILE_128x128, 128, 128, 512, 118}};
+  struct Shape { Kernel kernel; int bm, bn, resident; double start, step, odd, odd_read, gelu, dact; };
+  const Shape shapes[3] = {{TILE_256x256, 256, 256, 256, 8.0, 1.06, 44, 76, 5, 16}, {TILE_256x192, 256, 192, 256, 6.0, 1.1, 20, 42, 4, 4},
+                           {TILE_128x128, 128, 128, 512, 4.1, 1.02, 11, 25, 1, 0}};
+  const double lone_start = 3.65, lone_step = 0.608;   // a 128x128 workgroup that has its CU, and four stages, to itself
+  const bool reads = (p.epi & (E_ACC | E_RESID | E_DACT)) != 0;
   Route best{TILE_256x256, 1};
-  int64_t best_cost = -1;
+  double best_time = 1e30;
   for (const Shape& sh : shapes) {
     const int64_t tiles = ceil_div(p.M, sh.bm) * ceil_div(p.N, sh.bn);
     const bool small = sh.kernel == TILE_128x128;
@@ -91,28 +98,27 @@ Route tiled_route(const Product& p) {
       // a slice keeps >= 8 K steps, and splitting only fills CUs that would otherwise idle
       if (splits > 1 && (p.K % (128 * splits) != 0 || p.K / (128 * splits) < 8 || tiles * splits > sh.resident)) break;
       const int64_t wgs = tiles * splits;
-      const int64_t rounds = ceil_div(wgs, sh.resident);
-      const bool alone = small && wgs <= 256;   // a 128x128 workgroup that has its CU, and four stages, to itself
-      const int64_t steps = p.K / (64 * splits) + (alone ? 6 : 4);
-      // area in flight per CU x relative cost
-      const int64_t lone = (int64_t)sh.bm * sh.bn * 141, full = (int64_t)(sh.resident / 256) * sh.bm * sh.bn * sh.eff100;
-      const bool between = splits == 2 && wgs > 256 && wgs < 512;
-      const int64_t per_step = alone ? lone : between ? lone + (full - lone) * (wgs - 256) / 256 : full;
-      int64_t cost = rounds * steps * per_step;
-      if (p.N % 4) cost += cost * 3 / 10;
-      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, in the units of this estimate, and 2.5 us
-      // whatever its size (128 x 128, K = 4096: 25.9, 16.6 and 11.9 us with two, four and eight slices)
-      if (splits > 1) cost += p.M * p.N * splits * 10 + 9500000;
-      if (best_cost < 0 || cost < best_cost) {
-        best_cost = cost;
+      const bool alone = small && wgs <= 256;
+      // share of the CUs that run two workgroups, as far as it shows in the time
+      const double paired = alone ? 0.0 : splits > 1 && wgs < 512 ? std::max(0.55, (double)(wgs - 256) / 256) : 1.0;
+      const double start = small ? lone_start + paired * (sh.start - lone_start) : sh.start;
+      const double step = small ? lone_step + paired * (sh.step - lone_step) : sh.step;
+      const double odd = p.N % 4 == 0 || splits > 1 ? 0.0 : reads ? sh.odd_read : sh.odd;
+      const double act = p.epi & E_DACT ? sh.dact : p.epi & E_GELU && !alone ? sh.gelu : 0.0;
+      double t = (double)ceil_div(wgs, sh.resident) * (start + odd + act + step * (double)(p.K / (64 * splits)));
+      // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, and 2.5 us whatever its size (128 x 128,
+      // K = 4096: 25.9, 16.6 and 11.9 us with two, four and eight slices)
+      if (splits > 1) t += (double)(p.M * p.N * splits) * 2.63e-6 + 2.5;
+      if (t < best_time) {
+        best_time = t;
         best = Route{alone ? TILE_128x128_DEEP : sh.kernel, splits};
       }
     }
   }
-  // 3.8 M units of the estimate are a microsecond (256x256 tile: 1.72 us per K step).  The ring kernel takes what leaves
-  // the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192 122 -> 30 us (four stages: 81).
+  // The ring kernel takes what leaves the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192
+  // 122 -> 30 us (four stages: 81).
   Kernel ring;
-  if (ring_estimate(p, &ring) < (double)best_cost / 3.8e6) return Route{ring, 1};
+  if (ring_estimate(p, &ring) < best_time) return Route{ring, 1};
   return best;
 }
 

@@ -78,7 +78,8 @@ def test_gemm_plain_and_epilogues(dtype, M, N, K):
 # Shapes that make the tile chooser take the 256x192 and the 256x256 tile with ragged last tiles along M and N
 # (8292 = 32 * 256 + 100), with N a multiple of 8 (16-byte row-contiguous stores) and not (8- and 2-byte stores).
 # K = 64, 128, 192 and 320 are one to five K steps: the 256x256 kernel's prologue alone, its two tail steps, and its
-# steady-state loop (a stage read, the next written, the one after loaded) run once and three times.
+# steady-state loop (a stage read, the next written, the one after loaded) run once and three times.  (With GELU, and where
+# N is no multiple of 4, these sizes now take the 128x128 tile; the large tiles under every epilogue: test_product_routes.py.)
 @pytest.mark.parametrize("M,N,K", [(8292, 2368, 128), (8292, 3112, 128), (8292, 2370, 64), (4196, 6150, 64),
                                    (8292, 3112, 192), (4196, 6152, 320)])
 def test_gemm_large_tiles_with_ragged_edges(M, N, K):
@@ -193,11 +194,11 @@ def test_gemm_grids_that_do_not_fill_the_chip(dtype, M, N, K):
 # product + bias exact, and the residual is minus its bf16 rounding, so the result is the rounding residue, exact in bf16
 # (a sum rounded before the residual is added gives zero).  They take GELU and GELU' by formula: NaN stays NaN.
 # Tiles, in order: 256x192, 256x256, 128x128 with four and with two LDS stages.
-@pytest.mark.parametrize("M,N", [(8292, 2368), (8292, 3112), (1999, 2040), (1659, 3072)])
-def test_gemm_edge_tiles_round_once(M, N):
+@pytest.mark.parametrize("M,N,K", [(1300, 6152, 128), (5000, 2368, 2048), (1999, 2040, 64), (1659, 3072, 64)])
+def test_gemm_edge_tiles_round_once(M, N, K):
     pf, dev = _mods()
     md = _md("bf16")
-    K, edge = 64, M // 128 * 128          # rows from `edge` on lie in tiles that stick out, whatever the tile
+    edge = M // 128 * 128                 # rows from `edge` on lie in tiles that stick out, whatever the tile
     rng = np.random.default_rng(M + N)
     ints = lambda shape, top: rng.integers(-top, top + 1, shape).astype(np.float32)
     X, W, bias = ints((M, K), 16), ints((N, K), 16), ints((N,), 100)

@@ -45,6 +45,18 @@ PATHS = [
     ("f32", 1000, 260, 36, ALL, "ring 32x64", 1),
     ("f32", 1023, 516, 36, ALL, "ring 64x64", 1),
     ("f32", 2047, 772, 64, ALL, "ring 128x64", 1),
+    # the tiled kernels: rows in 16- and 8-byte pieces and element by element, ragged along M, mostly along N
+    ("bf16", 5000, 2368, 2048, ALL, "tile 256x256", 1),
+    ("bf16", 5000, 2372, 2048, ("dact",), "tile 256x256", 1),
+    ("bf16", 1999, 6156, 192, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256", 1),
+    ("bf16", 5000, 2370, 2048, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256", 1),
+    ("bf16", 5000, 2370, 4096, ("dact",), "tile 256x256", 1),
+    ("bf16", 1300, 6152, 128, ALL, "tile 256x192", 1),
+    ("bf16", 1300, 6156, 128, ALL, "tile 256x192", 1),
+    ("bf16", 1300, 6154, 512, ALL, "tile 256x192", 1),
+    ("bf16", 1659, 3072, 64, ALL, "tile 128x128", 1),
+    ("bf16", 8292, 2370, 64, ALL, "tile 128x128", 1),
+    ("bf16", 8292, 2372, 64, ("gelu", "pre", "dact"), "tile 128x128", 1),
     # K split over workgroups that have their CU to themselves (four LDS stages), ragged and whole, and that share it
     ("bf16", 100, 768, 16384, ("sum",), "tile 128x128 deep", 8),
     ("bf16", 1100, 512, 8192, ("sum",), "tile 128x128 deep", 4),
@@ -59,17 +71,23 @@ def test_the_case_runs_on_the_kernel_it_is_for(dtype, M, N, K, epis, kernel, spl
     assert {route(dtype, M, N, K, e) for e in epis} == {(kernel, splits)}
 
 
-# what other GPU tests are for: large tiles with ragged edges, edge tiles, the training epilogues, grids that do not
-# fill the chip, rows in pieces
-@pytest.mark.parametrize("M,N,K,kernel", [
-    (8292, 2368, 128, "tile 256x192"), (8292, 2370, 64, "tile 256x192"), (4196, 2372, 64, "tile 256x192"),
-    (8292, 3112, 128, "tile 256x256"), (4196, 6150, 64, "tile 256x256"), (4196, 6152, 320, "tile 256x256"),
-    (4196, 3112, 64, "tile 256x256"), (8292, 3108, 64, "tile 256x256"), (8292, 2368, 64, "tile 256x192"),
-    (1659, 3072, 64, "tile 128x128"), (1999, 2044, 64, "tile 128x128 deep"), (1999, 2040, 64, "tile 128x128 deep"),
-    (1999, 2040, 320, "tile 128x128 deep"), (33, 36, 72, "ring 32x32"), (128, 2300, 776, "ring 32x64"),
-    (450, 2044, 1992, "ring 64x64"), (1659, 764, 3072, "ring 128x64")])
-def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
-    assert {route("bf16", M, N, K, e)[0] for e in ("bias", "gelu", "resid", "pre", "dact")} == {kernel}
+# what other GPU tests are for: large tiles on one to five K steps with ragged edges, edge tiles, grids that do not fill the
+# chip, rows in pieces
+MOST = ("plain", "bias", "resid", "sum")
+ROUNDED = ("gelu", "resid", "dact")
+
+
+@pytest.mark.parametrize("M,N,K,epis,kernel", [
+    (8292, 2368, 128, MOST, "tile 256x192"), (4196, 2372, 64, MOST + ("gelu", "pre"), "tile 256x192"),
+    (4196, 3112, 64, MOST, "tile 256x256"), (8292, 3112, 128, MOST, "tile 256x256"),
+    (8292, 3112, 192, MOST + ("gelu", "pre"), "tile 256x256"), (4196, 6152, 320, MOST + ("gelu", "pre"), "tile 256x256"),
+    (8292, 3108, 64, MOST, "tile 256x256"), (1300, 6152, 128, ROUNDED, "tile 256x192"),
+    (5000, 2368, 2048, ROUNDED, "tile 256x256"), (1999, 2040, 64, ROUNDED, "tile 128x128 deep"),
+    (1659, 3072, 64, ROUNDED, "tile 128x128"), (1999, 2044, 64, ALL, "tile 128x128 deep"),
+    (1999, 2040, 320, ALL, "tile 128x128 deep"), (33, 36, 72, ALL, "ring 32x32"), (128, 2300, 776, ALL, "ring 32x64"),
+    (450, 2044, 1992, ALL, "ring 64x64"), (1659, 764, 3072, ("bias", "gelu", "resid", "pre", "dact"), "ring 128x64")])
+def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
+    assert {route("bf16", M, N, K, e)[0] for e in epis} == {kernel}
 
 
 # The faster kernel at sizes where two were timed on MI355X (times in us, the chosen one first): the rules follow them.
@@ -106,12 +124,22 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, kernel):
     ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 54.2 / whole 128x128 tiles 70.8
     ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 53.4 / whole 128x128 tiles 69.0
     ("bf16", 1659, 960, 768, "resid", "tile 128x128 deep"),  # 12.6 / ring 13.1
+    # the 256x256 tile by its own rate, and what the epilogues cost it
+    ("bf16", 4096, 10048, 2048, "plain", "tile 256x256"),    # 153 / 256x192 187, 128x128 197
+    ("bf16", 8192, 50304, 1024, "plain", "tile 256x256"),    # 797 / 256x192 970
+    ("bf16", 50304, 1024, 8192, "sum", "tile 256x256"),      # 793 / 256x192 1020
+    ("bf16", 8192, 2304, 2048, "bias", "tile 256x192"),      # 84.2 / 256x256 89.5
+    ("bf16", 8192, 1024, 1024, "resid", "tile 128x128"),
+    ("bf16", 8192, 9648, 320, "dact", "tile 128x128"),       # 139 / 256x192 153, 256x256 218
+    ("bf16", 4096, 9648, 320, "pre", "tile 128x128"),        # 62 / 256x256 71
+    ("bf16", 8192, 5002, 768, "bias", "tile 128x128"),       # odd rows: 163 / 256x192 182, 256x256 265
     # weight gradients over long K: split or not, or few small tiles
     ("bf16", 1024, 3072, 8192, "sum", "tile 128x128"),       # two slices 76.3 / unsplit 86.6
     ("bf16", 64, 64, 8192, "sum", "ring 32x32"),             # 12.9 / eight slices 15.5
     ("bf16", 1024, 3072, 4096, "sum", "tile 128x128 deep"),  # unsplit 44.8 / two slices 47.0
     ("bf16", 384, 3072, 4096, "sum", "tile 128x128 deep"),   # two slices 29.8 / four 33.2, unsplit 42.5
     ("bf16", 1024, 1024, 8192, "sum", "ring 64x64"),         # 29.9 / four slices 36.8
+    ("bf16", 768, 1536, 8192, "sum", "tile 128x128"),        # four slices 44.1 / two 47.7
     ("bf16", 1536, 512, 8192, "sum", "ring 64x64"),          # 28.0 / four slices 32.6
     ("bf16", 100, 132, 16384, "sum", "ring 32x32"),          # 22.9 / eight slices 25.4
 ])
