@@ -376,7 +376,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   // bias before it adds the residual).
   //  * In pieces of 16 bytes (bf16 also 8) where rows and operands are aligned to them; what a block needs from memory is
   //    requested before it is staged.  Rows and columns past C's end are dropped by the buffers' bounds: loads deliver zeros,
-  //    stores go nowhere.  8192 x 32768, K = 2048 accumulated into fp32: 1446 us from the registers, 1172 this way (1 GiB
+  //    stores go nowhere.  8192 x 32768, K = 2048 accumulated into fp32: 1446 us from the registers, 1102 this way (1 GiB
   //    read, 1 GiB written).  From the registers a ragged bf16 result took 25 to 85 us longer than a whole one: 1659 x 768,
   //    K = 768 38 / 55 / 106 us with the 128- / 192- / 256-wide tiles, where 4096 x 768 took 14 / 20 / 21.
   //  * Otherwise element by element, what is read from memory for four groups of four columns at a time.
