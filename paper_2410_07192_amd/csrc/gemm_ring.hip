@@ -4,7 +4,11 @@
 // K step in flight per workgroup and, with few workgroups, pays a memory latency per step (0.8 us at 128 x 768,
 // K = 3072: 38.6 us for 48 steps on 6 of 256 CUs).  Here the waves of a workgroup share one small tile of C and
 // divide K between them: wave w takes K steps w, w + WK, ... through a ring of DEPTH LDS stages of its own, so no wave
-// waits for another (no barrier until the sums meet) and WK * DEPTH steps, about 128 KB per CU, are in flight at once.
+// waits for another (no barrier until the sums meet) and WK * DEPTH steps, 64 to 144 KB per workgroup, are in flight at once.
+// A stage goes to registers whole and is refilled before its MFMAs run.  Two waves per SIMD with one stage each (the small
+// tiles; the 32x32 one leaves room for two workgroups per CU) beat one wave with two stages, whose wait, LDS reads, copies
+// and MFMAs follow one another: 128 x 2304, K = 768 6.0 -> 5.3 us, 333 x 2048, K = 2048 on 32x32 tiles 15.8 -> 12.3 us, 600 x 512,
+// K = 2048 8.7 -> 7.6 us, 512 x 1536, K = 600 into fp32 7.6 -> 6.9 us.
 // A K step is 128 bytes of every row (64 bf16 or 32 fp32 elements); stages hold eight 16-byte chunks per row,
 // XOR-swizzled on the global side as in the tiled kernel.
 //   bf16: 32x32x16 MFMA.  fp32: 32x32x2 fp32 MFMA, four per pair of chunks: lane half lk supplies element j of chunk
@@ -14,7 +18,7 @@
 // K need only be a whole number of 16-byte chunks: loads past the end repeat the last chunk and the operands of the
 // last step are zeroed beyond K.
 // Measured (MI355X, weights from the memory-side cache, launches back to back; before -> after): 128 x 768, K = 768
-// 10.6 -> 3.9 us; 128 x 768, K = 3072 38.5 -> 7.6 us; 128 x 2304, K = 768 12.5 -> 6.1 us; 333 x 2048, K = 8192 122 -> 30 us
+// 10.6 -> 3.9 us; 128 x 768, K = 3072 38.5 -> 7.3 us; 128 x 2304, K = 768 12.5 -> 5.3 us; 333 x 2048, K = 8192 122 -> 30 us
 // (each of the 192 busy CUs takes in about 70 bytes per ns there, which is what now bounds it); 600-token weight gradient 2048 x 512
 // 17.9 -> 8.6 us; fp32 512 x 256, K = 1024 115 -> 10 us.
 #include "pf_kernels.h"
@@ -24,9 +28,7 @@ namespace pf {
 namespace gemm {
 namespace {
 
-constexpr int DEPTH = 2;   // LDS stages of a wave
-
-template <typename T, typename OutT, int TM, int TN, int WK>
+template <typename T, typename OutT, int TM, int TN, int WK, int DEPTH>
 __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict__ X, const T* __restrict__ W, OutT* C,
                                                             int64_t M, int64_t N, int64_t K, EpiDev ep,
                                                             int32_t tiles_m, int32_t tiles_n, int32_t vec) {
@@ -112,8 +114,8 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   const int sw = (lr >> 1) & 7;
   int slot = 0;
   for (int64_t s = 0; s < mine; ++s) {
-    // the younger stage may stay on its way; the last step has none behind it
-    if (s + 1 < mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
+    // the younger stage, if there is one, may stay on its way; the last step has none behind it
+    if (s + DEPTH <= mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * (DEPTH - 1)) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const uint4* st = smem + (wave * DEPTH + slot) * STAGE;
     uint4 fx[4][TM], fw[4][TN];
@@ -218,12 +220,12 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   }
 }
 
-template <typename T, typename OutT, int TM, int TN, int WK>
+template <typename T, typename OutT, int TM, int TN, int WK, int DEPTH>
 hipError_t launch_ring(const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K, const EpiDev& ep,
                        hipStream_t stream) {
   static bool attr = false;
   constexpr int lds = WK * DEPTH * (TM + TN) * 4096;
-  auto kern = gemm_ring_kernel<T, OutT, TM, TN, WK>;
+  auto kern = gemm_ring_kernel<T, OutT, TM, TN, WK, DEPTH>;
   if (!attr) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -244,10 +246,14 @@ template <typename T, typename OutT>
 hipError_t launch_ring_shape(Kernel shape, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                              const EpiDev& ep, hipStream_t stream) {
   switch (shape) {
-    case RING_32x32: return launch_ring<T, OutT, 1, 1, 8>(X, W, C, M, N, K, ep, stream);
-    case RING_32x64: return launch_ring<T, OutT, 1, 2, 6>(X, W, C, M, N, K, ep, stream);
-    case RING_64x64: return launch_ring<T, OutT, 2, 2, 4>(X, W, C, M, N, K, ep, stream);
-    case RING_128x64: return launch_ring<T, OutT, 4, 2, 3>(X, W, C, M, N, K, ep, stream);
+    case RING_32x32: return launch_ring<T, OutT, 1, 1, 8, 1>(X, W, C, M, N, K, ep, stream);
+    case RING_32x64: return launch_ring<T, OutT, 1, 2, 8, 1>(X, W, C, M, N, K, ep, stream);
+    case RING_64x64:
+      // Long rows: one wave per SIMD with two stages again (333 x 2048, K = 8192 30.3 us against 31.6, K = 2048 11.9 against 11.4;
+      // fp32 2048 x 512, K = 2048 45 against 63, 4096 x 2048, K = 256 69 against 63).
+      if (K * (int64_t)sizeof(T) > 4096) return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
+      return launch_ring<T, OutT, 2, 2, 8, 1>(X, W, C, M, N, K, ep, stream);
+    case RING_128x64: return launch_ring<T, OutT, 4, 2, 3, 2>(X, W, C, M, N, K, ep, stream);
     default: return hipErrorInvalidValue;
   }
 }
