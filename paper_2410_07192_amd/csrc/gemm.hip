@@ -1,23 +1,22 @@
 // GEMM kernels for gfx950:  C[M,N] = epilogue( X[M,K] * W[N,K]^T ).
 //
-// bf16 main path (K a multiple of 64): 32x32x16 bf16 MFMA, fp32 accumulators.  A workgroup of
-// WGM x WGN waves owns a (WGM*TM*32) x (WGN*TN*32) tile of C and walks K in steps of 64.
-//  * Operand tiles go from global memory straight into LDS (global_load_lds, 16 bytes per lane, no
-//    VGPR round trip).  A wave's 64 lanes fill 1 KB of consecutive LDS = 8 rows of 8 chunks; the XOR
+// bf16 main path (K a multiple of 64): bf16 MFMA, fp32 accumulators.  A workgroup of WGM x WGN waves owns a
+// (WGM*TM*32) x (WGN*TN*32) tile of C and walks K in steps of 64.
+//  * Operand tiles go from global memory straight into LDS (16 bytes per lane, no VGPR round trip; the 256x256
+//    tile goes through registers).  A wave's 64 lanes fill 1 KB of consecutive LDS = 8 rows of 8 chunks; the XOR
 //    swizzle that keeps the later MFMA operand reads free of bank conflicts is applied on the global
 //    side (lane -> which chunk of the row it fetches).  Rows beyond M / N are clamped to the last
 //    valid row (their products are never stored).
-//  * Two LDS stages (four where a 128x128 workgroup has its CU to itself): the loads of step k+2 (k+4) go
-//    into the stage that the barrier ending step k has freed.  They are issued one at a time between the
-//    MFMAs of the following blocks (a burst blocks every wave at the address unit) and are inline assembly
+//  * Two to four LDS stages: the loads of step k+NS go into the stage that a barrier of step k has freed.  They are
+//    issued one at a time between MFMAs (a burst blocks every wave at the address unit) and are inline assembly
 //    so that the compiler does not serialise every later LDS read behind them; vmcnt is waited by hand.
-//  * Operand fragments are double buffered in registers: the 16-byte LDS reads of sub-step kk+1
-//    are in flight while the MFMAs of sub-step kk issue.
+//  * Operand fragments are double buffered in registers: by slices of 32 k in the 256-wide tiles, by whole K steps in
+//    the others.
 //  * The weight tile is the MFMA "A" operand and the activation tile the "B" operand, so each lane
 //    ends up with 4 consecutive output columns of one output row: bias / GELU of whole bf16 tiles are
 //    applied in registers; these then pass through LDS and leave as 16-byte row-contiguous stores (the
 //    residual is added on the way out).  Everything else passes through LDS in fp32.
-//  * Three tile shapes (256x256, 256x192, 128x128); accumulating fp32 launches may split K.
+//  * Tile shapes 256x256, 256x192, 256x128, 128x128; accumulating fp32 launches may split K over 128x128 tiles.
 //  * Workgroup ids are remapped so that each of the 8 XCDs (ids are dealt round-robin to them) works
 //    on a contiguous range of tiles and its L2 sees each operand panel once.
 // Launches too small to fill the chip, and most of fp32: gemm_ring.hip.

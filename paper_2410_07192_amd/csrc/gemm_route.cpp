@@ -59,11 +59,9 @@ double fma_estimate(const Product& p) {
 }
 
 // Tiled kernels, and the ring kernel where it is faster.
-// Tile shapes: 256x256 (four waves, wave tile 128x128), 256x192 (8 waves as 4x2, wave tile 64x96), both one workgroup per
-// CU, and 128x128 (4 waves, two workgroups per CU).
-// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two: with two, one K step
-// is in flight and costs a memory latency (0.85 to 1.1 us per step; with four 0.61: 2048 x 2048, K = 8192 117 -> 88 us,
-// 333 x 8192, K = 2048 37.6 -> 25.8 us).
+// Tile shapes: 256x256 (four waves, wave tile 128x128), 256x192 (8 waves as 4x2, wave tile 64x96) and 256x128 (four waves, wave
+// tile 128x64), one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
+// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two.
 // A launch takes ceil(workgroups / resident workgroups) rounds of start + step x (K steps of 64), in microseconds, measured
 // on MI355X (844 products, every shape timed); the shape with the least estimate runs.  That choice is 0.3 % off the
 // fastest shape on average and 13 % at most (1024 x 33024, K = 2048: 256x192 tiles 159 us, 256x256 141).  E.g. N = 768 or 2304
@@ -84,15 +82,24 @@ double fma_estimate(const Product& p) {
 // round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
 Route tiled_route(const Product& p) {
   struct Shape { Kernel kernel; int bm, bn, resident; double start, step, odd, odd_read, gelu, dact; };
-  const Shape shapes[3] = {{TILE_256x256, 256, 256, 256, 8.0, 1.06, 44, 76, 5, 16}, {TILE_256x192, 256, 192, 256, 6.0, 1.1, 20, 42, 4, 4},
-                           {TILE_128x128, 128, 128, 512, 4.1, 1.02, 11, 25, 1, 0}};
-  const double lone_start = 3.65, lone_step = 0.608;   // a 128x128 workgroup that has its CU, and four stages, to itself
+  // 128x128 and 256x128: a whole K step of fragments in registers, timed for rows of whole 16-byte pieces, K from 512 on and
+  // no sum into C (8192 x 1024, K = 4096 58.6 us with both; K = 50304 858 and 725).  Elsewhere the 128x128 tile is taken as it
+  // was measured with a slice of fragments in registers: there the shapes are within a fifth of one another.
+  const bool timed = p.N % 8 == 0 && p.K >= 512 && !(p.epi & E_ACC);
+  const Shape pair = timed ? Shape{TILE_128x128, 128, 128, 512, 3.8, 0.82, 11, 25, 1, 0} : Shape{TILE_128x128, 128, 128, 512, 4.1, 1.02, 11, 25, 1, 0};
+  const Shape shapes[4] = {{TILE_256x256, 256, 256, 256, 8.0, 1.06, 44, 76, 5, 16}, {TILE_256x192, 256, 192, 256, 6.0, 1.1, 20, 42, 4, 4},
+                           pair, {TILE_256x128, 256, 128, 256, 6.3, 0.69, 0, 0, 2.5, 2}};
+  // a 128x128 workgroup that has its CU, and four stages, to itself; with nearly every CU busy a step takes longer
+  // (K = 2048: 144 workgroups 16.3 us, 256 20.5)
+  const double busy = std::min(1.0, std::max(0.0, ((double)(ceil_div(p.M, 128) * ceil_div(p.N, 128)) - 144) / 64));
+  const double lone_start = timed ? 4.7 : 3.65, lone_step = timed ? 0.36 + 0.14 * busy : 0.608;
   const bool reads = (p.epi & (E_ACC | E_RESID | E_DACT)) != 0;
   Route best{TILE_256x256, 1};
   double best_time = 1e30;
   for (const Shape& sh : shapes) {
     const int64_t tiles = ceil_div(p.M, sh.bm) * ceil_div(p.N, sh.bn);
     const bool small = sh.kernel == TILE_128x128;
+    if (sh.kernel == TILE_256x128 && !timed) continue;
     const int max_splits = p.out_f32 && p.epi == E_ACC && small ? 8 : 1;
     for (int splits = 1; splits <= max_splits; splits *= 2) {
       // a slice keeps >= 8 K steps, and splitting only fills CUs that would otherwise idle
@@ -116,7 +123,7 @@ Route tiled_route(const Product& p) {
     }
   }
   // The ring kernel takes what leaves the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192
-  // 122 -> 30 us (four stages: 81).
+  // 122 -> 30 us (four stages: 58).
   Kernel ring;
   if (ring_estimate(p, &ring) < best_time) return Route{ring, 1};
   return best;

@@ -16,6 +16,7 @@ enum Kernel : int32_t {
   RING_32x32, RING_32x64, RING_64x64, RING_128x64,   // gemm_ring.hip, bf16 and fp32
   TILE_256x256, TILE_256x192, TILE_128x128,       // gemm_tile.h; the last with two LDS stages,
   TILE_128x128_DEEP,                              // here with four
+  TILE_256x128,                                   // with three
 };
 
 struct Product {

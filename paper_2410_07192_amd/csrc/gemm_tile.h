@@ -132,12 +132,57 @@ __device__ __forceinline__ void build_epilogue_tables(float2* gelu_tab) {
   }
 }
 
-// What a workgroup does with its finished accumulators: acc[a][b] is the 32x32 block at rows (wm * TM + b) * 32,
-// columns (wn * TN + a) * 32 of the BM x BN tile at (m0, n0).  smem: the two operand stages (free after the K loop)
+// The accumulators of a wave: TN x TM blocks of 32 x 32, W rows (columns of C) by X rows (rows of C), from MFMAs of either
+// shape.  A lane has four quads of four consecutive columns in a block: quad q of block (a, b) lies in row row(b, q) and at
+// column 4 * unit(a, q) of the wave's part of the tile.
+//   32x32x16: D[i][j], lane holds j = lane % 32 (row of C) and i = 8 * q + 4 * (lane / 32) + r (column of C)
+//   16x16x32: four 16x16 blocks, q = 2 * (column half) + row half; j = lane % 16, i = 4 * (lane / 16) + r
+// Indices must be compile-time constants or the accumulators leave the register file.
+template <int SH, int TM, int TN>
+struct Accumulators;
+template <int TM, int TN>
+struct Accumulators<32, TM, TN> {
+  f32x16 v[TN][TM];
+  template <class A, class B, class Q>
+  __device__ __forceinline__ f32x4 quad(A a, B b, Q q) const {
+    constexpr int o = decltype(q)::value * 4;
+    const f32x16& t = v[decltype(a)::value][decltype(b)::value];
+    return f32x4{t[o], t[o + 1], t[o + 2], t[o + 3]};
+  }
+  template <class A, class B, class Q>
+  __device__ __forceinline__ void scale(A a, B b, Q q, f32x4 f) {
+    constexpr int o = decltype(q)::value * 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[decltype(a)::value][decltype(b)::value][o + r] *= f[r];
+  }
+  static __device__ __forceinline__ int row(int b, int, int lane) { return b * 32 + (lane & 31); }
+  static __device__ __forceinline__ int unit(int a, int q, int lane) { return a * 8 + q * 2 + (lane >> 5); }
+};
+template <int TM, int TN>
+struct Accumulators<16, TM, TN> {
+  f32x4 v[2 * TN][2 * TM];
+  template <class A, class B, class Q>
+  __device__ __forceinline__ f32x4 quad(A a, B b, Q q) const {
+    constexpr int qq = decltype(q)::value;
+    return v[2 * decltype(a)::value + qq / 2][2 * decltype(b)::value + qq % 2];
+  }
+  template <class A, class B, class Q>
+  __device__ __forceinline__ void scale(A a, B b, Q q, f32x4 f) {
+    constexpr int qq = decltype(q)::value;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[2 * decltype(a)::value + qq / 2][2 * decltype(b)::value + qq % 2][r] *= f[r];
+  }
+  static __device__ __forceinline__ int row(int b, int q, int lane) { return b * 32 + (q & 1) * 16 + (lane & 15); }
+  static __device__ __forceinline__ int unit(int a, int q, int lane) { return a * 8 + (q >> 1) * 4 + (lane >> 4); }
+};
+
+// What a workgroup does with its finished accumulators: block (a, b) lies at rows (wm * TM + b) * 32, columns
+// (wn * TN + a) * 32 of the BM x BN tile at (m0, n0).  smem: the two operand stages (free after the K loop)
 // followed by the table of build_epilogue_tables.
-template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS = 2>
-__device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem, OutT* __restrict__ C, int64_t M,
+template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS = 2, int SH>
+__device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uint4* smem, OutT* __restrict__ C, int64_t M,
                                               int64_t N, const EpiDev& ep, int64_t m0, int64_t n0) {
+  typedef Accumulators<SH, TM, TN> Acc;
   constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, NW = WGM * WGN;
   constexpr int STAGE = (BM + BN) * 8;
   float2* gelu_tab = (float2*)(smem + NS * STAGE);
@@ -148,9 +193,6 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   };
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
-  const int lr = lane & 31, lk = lane >> 5;
-  // D[i][j]: lane holds j = lane%32 (row of C) and i = 8*(r/4) + 4*(lane/32) + r%4 (column of C).
-  // Indices into acc must be compile-time constants or the accumulators leave the register file.
   const bool interior = (m0 + BM <= M) && (n0 + BN <= N) && ((N & 3) == 0);
   // Split K: the fp32 tile goes through LDS (row-major, 16-byte units XOR-swizzled by row) and is added to C with
   // hardware fp32 atomics, 64 consecutive columns of a row per wave instruction.  A lane-per-row atomic would touch 32
@@ -161,11 +203,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
       constexpr int UNITS = BN / 4, NT = 64 * NW;
       static_for<0, TN>([&](auto a) {
         static_for<0, TM>([&](auto b) {
-          const int row = (wm * TM + b) * 32 + lr;
-          static_for<0, 4>([&](auto rg) {
-            const int unit = ((wn * TN + a) * 32 + rg * 8 + lk * 4) / 4;
-            *(float4*)(stf + row * BN + ((unit ^ (row & (UNITS - 1))) * 4)) =
-                make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
+          static_for<0, 4>([&](auto q) {
+            const int row = Acc::row(wm * TM + b, q, lane), unit = Acc::unit(wn * TN + a, q, lane);
+            *(f32x4*)(stf + row * BN + ((unit ^ (row & (UNITS - 1))) * 4)) = acc.quad(a, b, q);
           });
         });
       });
@@ -185,7 +225,9 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   // tile, the residual being added on the way out from equally coalesced loads.  The two training forms use the same
   // route: the pre-activation is a second tile staged and stored before the activated one, and the saved tensor whose
   // GELU' multiplies the result comes in the other way round, coalesced loads -> LDS -> the accumulator layout.
-  constexpr bool STAGED = std::is_same<OutT, bf16_t>::value && !(EPI & E_ACC);
+  // Not the residual of the kernels with three or four stages: the route by fp32 rows below rounds once and is no slower
+  // (1659 x 768, K = 768 10.0 -> 9.8 us, 2048 x 2048, K = 2048 22 -> 21).
+  constexpr bool STAGED = std::is_same<OutT, bf16_t>::value && !(EPI & E_ACC) && !((EPI & E_RESID) && NS > 2);
   if constexpr (STAGED) {
     static_assert(!(EPI & E_DACT) || EPI == E_DACT, "GELU' multiplies the plain product only");
     const bool aligned16 = ((N & 7) == 0) && ((((uintptr_t)C | (uintptr_t)ep.resid | (uintptr_t)ep.preact_out |
@@ -264,14 +306,12 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
         __builtin_amdgcn_s_barrier();
         static_for<0, TN>([&](auto a) {
           static_for<0, TM>([&](auto b) {
-            const int row = (wm * TM + b) * 32 + lr;
-            static_for<0, 4>([&](auto rg) {
-              const int slot = (wn * TN + a) * 4 + rg;
-              const uint2 u = st8[row * (SLOTS * 2) + swz(slot, row) * 2 + lk];
-              acc[a][b][rg * 4 + 0] *= gelu_grad_tab(bf16_bits_to_f32(u.x & 0xffffu));
-              acc[a][b][rg * 4 + 1] *= gelu_grad_tab(bf16_bits_to_f32(u.x >> 16));
-              acc[a][b][rg * 4 + 2] *= gelu_grad_tab(bf16_bits_to_f32(u.y & 0xffffu));
-              acc[a][b][rg * 4 + 3] *= gelu_grad_tab(bf16_bits_to_f32(u.y >> 16));
+            static_for<0, 4>([&](auto q) {
+              const int row = Acc::row(wm * TM + b, q, lane), unit = Acc::unit(wn * TN + a, q, lane);
+              const uint2 u = st8[row * (SLOTS * 2) + swz(unit >> 1, row) * 2 + (unit & 1)];
+              const f32x4 f = {gelu_grad_tab(bf16_bits_to_f32(u.x & 0xffffu)), gelu_grad_tab(bf16_bits_to_f32(u.x >> 16)),
+                               gelu_grad_tab(bf16_bits_to_f32(u.y & 0xffffu)), gelu_grad_tab(bf16_bits_to_f32(u.y >> 16))};
+              acc.scale(a, b, q, f);
             });
           });
         });
@@ -284,17 +324,18 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
           float bias4[4][4] = {};
           if constexpr (EPI & E_BIAS) {
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg)
-              load4((const bf16_t*)ep.bias + n0 + (wn * TN + a) * 32 + rg * 8 + lk * 4, bias4[rg]);
+            for (int q = 0; q < 4; ++q)
+              if (SH == 32 || q % 2 == 0) load4((const bf16_t*)ep.bias + n0 + Acc::unit(wn * TN + a, q, lane) * 4, bias4[q]);
           }
           static_for<0, TM>([&](auto b) {
-            const int row = (wm * TM + b) * 32 + lr;
-            static_for<0, 4>([&](auto rg) {
-              float v[4] = {acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2],
-                            acc[a][b][rg * 4 + 3]};
+            static_for<0, 4>([&](auto q) {
+              constexpr int bq = SH == 32 ? decltype(q)::value : decltype(q)::value & 2;   // quads of one column share the bias
+              const int row = Acc::row(wm * TM + b, q, lane), unit = Acc::unit(wn * TN + a, q, lane);
+              const f32x4 t = acc.quad(a, b, q);
+              float v[4] = {t[0], t[1], t[2], t[3]};
               if constexpr (EPI & E_BIAS) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] += bias4[rg][j];
+                for (int j = 0; j < 4; ++j) v[j] += bias4[bq][j];
               }
               if constexpr (decltype(with_gelu)::value) {
                 // Eight waves: GELU from the table (9.5 VALU slots and one LDS gather per element; the second wave of
@@ -315,8 +356,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
               uint2 pk;
               pk.x = pack_bf16x2(v[0], v[1]);
               pk.y = pack_bf16x2(v[2], v[3]);
-              const int slot = (wn * TN + a) * 4 + rg;
-              st8[row * (SLOTS * 2) + swz(slot, row) * 2 + lk] = pk;
+              st8[row * (SLOTS * 2) + swz(unit >> 1, row) * 2 + (unit & 1)] = pk;
             });
           });
         });
@@ -399,12 +439,14 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   auto stage_block = [&](auto b) {
     asm volatile("" ::: "memory");   // other lanes' values: a wave's LDS instructions execute in program order
     static_for<0, TN>([&](auto a) {
-      static_for<0, 4>([&](auto rg) {
-        float4 t = make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
+      static_for<0, 4>([&](auto q) {
+        const int row = Acc::row(0, q, lane);
+        f32x4 t = acc.quad(a, b, q);
         // (copied out one register each: as four-register operands of the LDS store, next to the staged route's reads, the
         // 256 accumulators of the four-wave kernel made the allocator spill 80 of them on every tile)
-        if constexpr (!F32) asm("" : "+v"(t.x), "+v"(t.y), "+v"(t.z), "+v"(t.w));
-        st[lr * UNITS + ((a * 8 + rg * 2 + lk) ^ (lr & XOR))] = t;
+        float t0 = t[0], t1 = t[1], t2 = t[2], t3 = t[3];
+        if constexpr (!F32) asm("" : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3));
+        st[row * UNITS + (Acc::unit(a, q, lane) ^ (row & XOR))] = make_float4(t0, t1, t2, t3);
       });
     });
     asm volatile("" ::: "memory");
@@ -544,7 +586,32 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[TN][TM], uint4* smem
   });
 }
 
-template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS>
+__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 w, bf16x8 x, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, x, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_bf16(bf16x8 w, bf16x8 x, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
+}
+
+// Copies of 1 KB from a raw buffer straight into LDS (buffer_load_dwordx4 ... lds): lane i's 16 bytes at byte voff + soff of
+// the buffer land at LDS byte address dst + 16 i; dst, the buffer and soff are wave-uniform.  M0 as in lds_direct_load_1k.
+typedef uint32_t lds_buffer_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ lds_buffer_t lds_buffer(const void* p) {
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  return lds_buffer_t{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
+                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)), 0x7fffffffu, 0x00020000u};
+}
+__device__ __forceinline__ void lds_buffer_load_1k(uint32_t dst, lds_buffer_t buf, uint32_t voff, int32_t soff) {
+  uint32_t saved;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
+               : "=&s"(saved)
+               : "s"(dst), "v"(voff), "s"(buf), "s"(__builtin_amdgcn_readfirstlane(soff))
+               : "memory");
+}
+
+// 256x192 tile on eight waves (4x2, wave tile 64x96, two per SIMD), 32x32x16 MFMAs (inside a 12-layer encoder pass 16384 x 768,
+// K = 3072 takes 71.8 us with these and 74.1 with 16x16x32).
+template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, OutT* __restrict__ C, int64_t M, int64_t N,
     int64_t K, EpiDev ep, int32_t tiles_m, int32_t tiles_n, int32_t group_m) {
@@ -553,7 +620,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
   constexpr int STAGE = (BM + BN) * 8;                          // uint4 per LDS stage
   static_assert(G % NW == 0 && GPW <= 32, "tile / wave mismatch");
   extern __shared__ uint4 smem[];
-  build_epilogue_tables<NW, OutT, EPI>((float2*)(smem + NS * STAGE));
+  build_epilogue_tables<NW, OutT, EPI>((float2*)(smem + 2 * STAGE));
   const int64_t tile = xcd_contiguous(blockIdx.x, (int64_t)tiles_m * tiles_n);
   const int64_t per_group = (int64_t)group_m * tiles_n;
   const int64_t grp = tile / per_group;
@@ -565,12 +632,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
-  const int lr = lane & 31, lk = lane >> 5;
-
-  // split K (accumulating fp32 epilogue only): workgroup y works on columns [y, y+1) * K / gridDim.y of both operands
-  const int64_t k_len = K / gridDim.y;
-  X += (int64_t)blockIdx.y * k_len;
-  W += (int64_t)blockIdx.y * k_len;
+  const int lr = lane & 31, lg = lane >> 5;
 
   // global source of this lane for each 1 KB group the wave moves per K step
   const bf16_t* src[GPW];
@@ -594,103 +656,221 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
     const bf16_t* p = src[i] + k0;
     lds_direct_load_1k(dst, p);
   };
-  int offW[TN], offX[TM], swW[TN], swX[TM];
-#pragma unroll
-  for (int a = 0; a < TN; ++a) {
-    const int r = (wn * TN + a) * 32 + lr;
-    offW[a] = BM * 8 + r * 8;
-    swW[a] = (r >> 1) & 7;
-  }
-#pragma unroll
-  for (int b = 0; b < TM; ++b) {
-    const int r = (wm * TM + b) * 32 + lr;
-    offX[b] = r * 8;
-    swX[b] = (r >> 1) & 7;
-  }
-  f32x16 acc[TN][TM];
+  // A slice is 16 wide in k (one MFMA), a fragment 32 rows of it: the lane takes chunk 2 kk + lane / 32 of row lane % 32.
+  // Fragments start at multiples of 32 rows, so all of a lane's have the same swizzle.
+  const int sw = (lr >> 1) & 7;
+  const int offW = BM * 8 + (wn * TN * 32 + lr) * 8, offX = (wm * TM * 32 + lr) * 8;
+  Accumulators<32, TM, TN> acc;
 #pragma unroll
   for (int a = 0; a < TN; ++a)
 #pragma unroll
     for (int b = 0; b < TM; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc.v[a][b][r] = 0.f;
   bf16x8 fw[2][TN], fx[2][TM];
   auto load_frags = [&](int buf, const uint4* st, int kk) {
-    const int c = kk * 2 + lk;
+    const int c = (kk * 2 + lg) ^ sw;
 #pragma unroll
-    for (int a = 0; a < TN; ++a) fw[buf][a] = as_bf16x8(st[offW[a] + (c ^ swW[a])]);
+    for (int a = 0; a < TN; ++a) fw[buf][a] = as_bf16x8(st[offW + a * 256 + c]);
 #pragma unroll
-    for (int b = 0; b < TM; ++b) fx[buf][b] = as_bf16x8(st[offX[b] + (c ^ swX[b])]);
+    for (int b = 0; b < TM; ++b) fx[buf][b] = as_bf16x8(st[offX + b * 256 + c]);
   };
   // A burst of loads right after the barrier blocks every wave at the texture-address unit (1 KB per
   // instruction at 64 B/clk) while the MFMA pipe drains; instead one load is issued before every EVERY-th
-  // MFMA of the block after the barrier (index 0) and of the first SPREAD-1 blocks of the next iteration.
-  constexpr int MF = TM * TN, SPREAD = 3, EVERY = SPREAD * MF / GPW;
-  static_assert(EVERY >= 1 && EVERY * GPW <= SPREAD * MF, "load slots");
+  // MFMA of the block after the barrier (index 0) and of the blocks that follow, over three quarters of a K step.
+  constexpr int MF = TM * TN, SPAN = 3 * MF, EVERY = SPAN / GPW;
+  static_assert(EVERY >= 1 && EVERY * GPW <= SPAN, "load slots");
   auto mfma_block = [&](auto blkc, auto bufc, bool do_load, int stage, int64_t k0) {
     constexpr int blk = decltype(blkc)::value, buf = decltype(bufc)::value;
     static_for<0, MF>([&](auto mi) {
       constexpr int g = blk * MF + mi;
-      if constexpr (blk < SPREAD && g % EVERY == 0 && g / EVERY < GPW) {
+      if constexpr (g % EVERY == 0 && g / EVERY < GPW) {
         if (do_load) issue1(std::integral_constant<int, g / EVERY>{}, stage, k0);
       }
       constexpr int a = mi / TM, b = mi % TM;
-      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf][a], fx[buf][b], acc[a][b], 0, 0, 0);
+      acc.v[a][b] = mfma_bf16(fw[buf][a], fx[buf][b], acc.v[a][b]);
     });
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
 
-  const int64_t nk = k_len / 64;
-  // prologue: stages 0 .. NS-2 completely; of stage NS-1 the share the block after a barrier issues.  With two stages
-  // nothing is asked of nk that is always so: those two branches cost 1 to 1.5 % of the 256x192 launches of a 12-layer
-  // encoder on 16384 tokens (d 768).
-  static_assert(GPW * (NS - 2) < 64, "vmcnt holds six bits");
-  constexpr int LATER = GPW * (NS - 2);   // copies of a wave that may stay on their way when the next stage is needed
-  static_for<0, NS - 1>([&](auto st) {
-    if (st == 0 || st < nk) static_for<0, GPW>([&](auto i) { issue1(i, st, st * 64); });
-  });
-  if (NS == 2 || nk >= NS - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const int64_t nk = K / 64;
+  // prologue: stage 0 completely; of stage 1 the share the block after a barrier issues
+  static_for<0, GPW>([&](auto i) { issue1(i, 0, 0); });
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
-  if (nk > NS - 1) {
+  if (nk > 1) {
     static_for<0, MF>([&](auto mi) {
-      if constexpr (mi % EVERY == 0 && mi / EVERY < GPW)
-        issue1(std::integral_constant<int, mi / EVERY>{}, NS - 1, (NS - 1) * 64);
+      if constexpr (mi % EVERY == 0 && mi / EVERY < GPW) issue1(std::integral_constant<int, mi / EVERY>{}, 1, 64);
     });
   }
   load_frags(0, smem, 0);
-  static_assert((NS & (NS - 1)) == 0, "stage of a K step by mask");
   for (int64_t kt = 0; kt < nk; ++kt) {
-    const int cur = (int)(kt & (NS - 1)), last = (cur + NS - 1) & (NS - 1);
+    const int cur = (int)(kt & 1);
     const uint4* sc = smem + cur * STAGE;
-    const uint4* sn = smem + ((cur + 1) & (NS - 1)) * STAGE;
-    const bool more1 = kt + NS - 1 < nk, more2 = kt + NS < nk;
-    const int64_t k_last = (kt + NS - 1) * 64;
+    const uint4* sn = smem + (cur ^ 1) * STAGE;
+    const bool more1 = kt + 1 < nk, more2 = kt + 2 < nk;
+    const int64_t k1 = (kt + 1) * 64;
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): fragments fetched during the previous MFMA block
-    load_frags(1, sc, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I1{}, I0{}, more1, last, k_last);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(0, sc, 2);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I2{}, I1{}, more1, last, k_last);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(1, sc, 3);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I3{}, I0{}, more1, last, k_last);
-    __builtin_amdgcn_sched_barrier(0);
+    static_for<1, 4>([&](auto sl) {
+      load_frags(sl & 1, sc, sl);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_block(sl, std::integral_constant<int, (sl & 1) ^ 1>{}, more1, cur ^ 1, k1);
+      __builtin_amdgcn_sched_barrier(0);
+    });
     // every wave holds the last fragments of this stage in registers and the next stage has landed
-    if (NS > 2 && more1) __builtin_amdgcn_s_waitcnt(0x0070 | (LATER & 15) | (LATER >> 4 << 14));   // vmcnt(LATER) lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);                                                        // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     if (kt + 1 < nk) load_frags(0, sn, 0);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(I0{}, I1{}, more2, cur, (kt + NS) * 64);   // stage `cur` is free: start refilling it
+    mfma_block(I0{}, I1{}, more2, cur, (kt + 2) * 64);   // stage `cur` is free: start refilling it
     __builtin_amdgcn_sched_barrier(0);
   }
+
+  tile_epilogue<WGM, WGN, TM, TN, OutT, EPI>(acc, smem, C, M, N, ep, m0, n0);
+}
+
+// Four waves with room in the register file: the fragments of a WHOLE K step are double buffered.  While the MFMAs of step kt
+// run on one set, they are interleaved with the LDS reads that fill the other set with step kt + 1 and with the copies of
+// step kt + NS into the stage that step kt's reads have left.  One barrier a step, behind its first MFMAs (LAG), which cover
+// the reads that are still on their way there.  No MFMA waits for an LDS read of its own step; with a slice's reads in flight
+// at a time (the loop above, and what these tiles ran on before) a lone wave per SIMD waits for LDS at every slice, and that
+// wait, not memory, bound these tiles (every operand out of L2 changes their times by 5 %).
+//   128x128, four stages, a CU to itself (32x32x16 MFMAs): 0.61 -> 0.36 to 0.5 us a step, 333 x 6144, K = 2048 24.4 -> 16.3 us,
+//     2048 x 2048, K = 2048 29 -> 20.5, 1659 x 2304, K = 768 13.5 -> 10.7
+//   128x128, two stages, two workgroups per CU (16x16x32 MFMAs): 8192 x 1024, K = 4096 75 -> 59 us, 8192 x 4096, K = 1024 with
+//     GELU' 96 -> 82, 1659 x 3072, K = 768 with GELU 19.2 -> 16.7
+//   256x128 (wave tile 128x64), three stages (32x32x16): fewer operand bytes per product, for long K: 8192 x 1024, K = 50304
+//     858 us on 128x128 tiles, 725 here
+// Which MFMA: a full chip runs into the power limit, where 16x16x32 sustains more (2.1 against 1.82 PFLOP/s in a loop of
+// nothing else on random operands: half the accumulator traffic per product); a lone wave per SIMD needs the longer MFMA to
+// hide what it issues between two of them (333 x 6144, K = 2048 16.3 us on 32x32x16, 20.9 on 16x16x32).
+template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI, int NS, int SH>
+__global__ __launch_bounds__(64 * WGM * WGN, TM * TN <= 4 && NS == 2 ? 2 : 1) void gemm_bf16_nt_step_kernel(
+    const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, OutT* __restrict__ C, int64_t M, int64_t N,
+    int64_t K, EpiDev ep, int32_t tiles_m, int32_t tiles_n, int32_t group_m) {
+  constexpr int BM = WGM * TM * 32, BN = WGN * TN * 32, NW = WGM * WGN;
+  constexpr int GX = BM / 8, G = (BM + BN) / 8, GPW = G / NW;   // 8-row groups of 1 KB; per wave
+  constexpr int STAGE = (BM + BN) * 8;                          // uint4 per LDS stage
+  static_assert(G % NW == 0 && GX % NW == 0, "tile / wave mismatch");
+  static_assert(GPW * (NS - 1) < 64, "vmcnt holds six bits");
+  extern __shared__ uint4 smem[];
+  build_epilogue_tables<NW, OutT, EPI>((float2*)(smem + NS * STAGE));
+  const int64_t tile = xcd_contiguous(blockIdx.x, (int64_t)tiles_m * tiles_n);
+  const int64_t per_group = (int64_t)group_m * tiles_n;
+  const int64_t grp = tile / per_group;
+  const int32_t first_m = (int32_t)(grp * group_m);
+  const int32_t rows_in_group = (tiles_m - first_m < group_m) ? tiles_m - first_m : group_m;
+  const int32_t tm_i = first_m + (int32_t)((tile % per_group) % rows_in_group);
+  const int32_t tn_i = (int32_t)((tile % per_group) / rows_in_group);
+  const int64_t m0 = (int64_t)tm_i * BM, n0 = (int64_t)tn_i * BN;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WGM, wn = wave / WGM;
+  const int lr = lane & (SH - 1), lg = lane / SH;
+
+  // split K (accumulating fp32 epilogue only): workgroup y works on columns [y, y+1) * K / gridDim.y of both operands
+  const int64_t k_len = K / gridDim.y;
+  X += (int64_t)blockIdx.y * k_len;
+  W += (int64_t)blockIdx.y * k_len;
+
+  // Copies: the tile's first row is the base of a raw buffer, the lane's place a 32-bit offset (rows past the end repeat
+  // the last one), the K step a scalar offset.
+  uint32_t off[GPW];
+#pragma unroll
+  for (int i = 0; i < GPW; ++i) {
+    const bool isx = i < GX / NW;
+    const int g = wave + i * NW;
+    const int r = (isx ? g : g - GX) * 8 + (lane >> 3);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    const int64_t last = (isx ? M - m0 : N - n0) - 1;
+    const int64_t row = r <= last ? r : last;
+    off[i] = (uint32_t)((row * K + c * 8) * 2);
+  }
+  lds_buffer_t xbuf = lds_buffer(X + m0 * K), wbuf = lds_buffer(W + n0 * K);
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)smem) + (uint32_t)(wave * 1024);
+  auto issue1 = [&](auto ic, uint32_t stage_at, int32_t k_bytes) {
+    constexpr int i = decltype(ic)::value;
+    lds_buffer_load_1k(stage_at + (uint32_t)(i * NW * 1024), i < GX / NW ? xbuf : wbuf, off[i], k_bytes);
+  };
+  // a slice is KS wide in k (one MFMA), a fragment SH rows of it: the lane takes chunk kk * KS / 8 + lane / SH of row lane % SH
+  constexpr int KS = 512 / SH, SLICES = 64 / KS, FM = TM * 32 / SH, FN = TN * 32 / SH;
+  const int sw = (lr >> 1) & 7;
+  int at_x[SLICES], at_w[SLICES];   // chunk of slice kk in a stage
+#pragma unroll
+  for (int kk = 0; kk < SLICES; ++kk) {
+    const int c = (kk * (KS / 8) + lg) ^ sw;
+    at_x[kk] = (wm * TM * 32 + lr) * 8 + c;
+    at_w[kk] = BM * 8 + (wn * TN * 32 + lr) * 8 + c;
+  }
+  Accumulators<SH, TM, TN> acc;
+#pragma unroll
+  for (int a = 0; a < FN; ++a)
+#pragma unroll
+    for (int b = 0; b < FM; ++b)
+#pragma unroll
+      for (int r = 0; r < SH * SH / 64; ++r) acc.v[a][b][r] = 0.f;
+  bf16x8 fw[2][SLICES][FN], fx[2][SLICES][FM];
+  constexpr int MF = SLICES * FM * FN, NR = SLICES * (FM + FN);   // MFMAs and fragment reads of a step
+  constexpr int LAG = MF / 8;
+  auto read1 = [&](auto setc, auto jc, const uint4* st) {
+    constexpr int set = decltype(setc)::value, j = decltype(jc)::value, kk = j / (FM + FN), e = j % (FM + FN);
+    if constexpr (e == 0) fw[set][kk][0] = as_bf16x8(st[at_w[kk]]);
+    else if constexpr (e <= FM) fx[set][kk][e - 1] = as_bf16x8(st[at_x[kk] + (e - 1) * SH * 8]);
+    else fw[set][kk][e - FM] = as_bf16x8(st[at_w[kk] + (e - FM) * SH * 8]);
+  };
+  // Past the last step there is nothing to fetch: the copies go to buffers of no length (zeros, no memory traffic) and the
+  // last step reads the fragments of a stage nobody filled, so that one loop body serves every step and the counts of what
+  // is on its way always hold.
+  int32_t k_bytes = NS * 128;
+  int cur = 0;
+  const int64_t nk = k_len / 64;
+  int32_t left = (int32_t)nk - NS;   // steps still to fetch
+  auto step = [&](auto setc) {
+    constexpr int set = decltype(setc)::value;
+    const int nxt = cur + 1 == NS ? 0 : cur + 1;
+    const uint4* sn = smem + nxt * STAGE;
+    const uint32_t dst = lds_base + (uint32_t)(cur * STAGE * 16);
+    xbuf[2] = wbuf[2] = left > 0 ? 0x7fffffffu : 0u;
+    static_for<0, MF>([&](auto mi) {
+      constexpr int m = decltype(mi)::value, r = m - LAG, RM = MF - LAG;
+      if constexpr (r == 0) {
+        // Before the barrier: this wave's fragments of the step are in registers (its stage may be overwritten) and its copies
+        // of the next step have landed; the NS - 2 younger steps may stay on their way.
+        __builtin_amdgcn_s_waitcnt(0x0070 | (GPW * (NS - 2) & 15) | (GPW * (NS - 2) >> 4 << 14));   // vmcnt, lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (r >= 0) {
+        static_for<r * NR / RM, (r + 1) * NR / RM>([&](auto j) { read1(std::integral_constant<int, set ^ 1>{}, j, sn); });
+        static_for<r * GPW / RM, (r + 1) * GPW / RM>([&](auto i) { issue1(i, dst, k_bytes); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int kk = m / (FM * FN), a = m % (FM * FN) / FM, b = m % FM;
+      acc.v[a][b] = mfma_bf16(fw[set][kk][a], fx[set][kk][b], acc.v[a][b]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    k_bytes += 128;
+    --left;
+    cur = nxt;
+  };
+  static_for<0, NS>([&](auto st) {
+    if (st >= nk) xbuf[2] = wbuf[2] = 0;
+    static_for<0, GPW>([&](auto i) { issue1(i, lds_base + (uint32_t)(st * STAGE * 16), st * 128); });
+  });
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(GPW * (NS - 1)) : "memory");
+  __builtin_amdgcn_s_barrier();
+  static_for<0, NR>([&](auto j) { read1(std::integral_constant<int, 0>{}, j, smem); });
+  const int32_t end = 1 - NS;   // of `left` in the last step
+  for (;;) {
+    step(std::integral_constant<int, 0>{});
+    if (left < end) break;
+    step(std::integral_constant<int, 1>{});
+    if (left < end) break;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing writes to the stages any more,
+  __builtin_amdgcn_s_barrier();                                  // nobody reads them: the epilogue may have them
 
   tile_epilogue<WGM, WGN, TM, TN, OutT, EPI, NS>(acc, smem, C, M, N, ep, m0, n0);
 }
@@ -703,11 +883,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
 // hold one stage in flight, the memory pipeline never drains, and the one barrier of a step (in the middle of the
 // last MFMA block, so that queued MFMAs cover it) both publishes the next stage and frees the current one.
 // Plain loads and stores: the compiler derives the vmcnt / lgkmcnt waits; the scheduling fences keep its order.
+// 16x16x32 MFMAs: the power limit allows more of them than of 32x32x16 (16384 x 2048, K = 8192 424 -> 410 us, 2048 x 32768, K =
+// 8192 with GELU and copy 851 -> 810, 8192 x 8192, K = 2048 into fp32 300 -> 290).
 template <typename OutT, int EPI>
 __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, OutT* __restrict__ C, int64_t M, int64_t N,
     int64_t K, EpiDev ep, int32_t tiles_m, int32_t tiles_n, int32_t group_m) {
-  constexpr int WGM = 2, WGN = 2, TM = 4, TN = 4;
+  constexpr int WGM = 2, WGN = 2, TM = 4, TN = 4, FM = 2 * TM, FN = 2 * TN;   // fragments of 16 rows
   constexpr int BM = 256, BN = 256, NW = 4;
   constexpr int GX = BM / 8, G = (BM + BN) / 8, GPW = G / NW;   // 8-row groups of 1 KB; sixteen per wave
   constexpr int STAGE = (BM + BN) * 8;                          // uint4 per LDS stage
@@ -725,7 +907,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
-  const int lr = lane & 31, lk = lane >> 5;
+  const int lr = lane & 15, lg = lane >> 4;
 
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a first-class vector: a struct-typed quad would live in private memory
   // Global source of this lane for each group: a 32-bit byte offset from the tile's first row (rows past the end are
@@ -753,88 +935,96 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   };
   const int wro = wave * 64 + lane;   // group g of a stage starts at uint4 index g * 64: this lane's place in group `wave`
   // Fragment addresses without arithmetic in the loop.  Row r of a stage holds its 16-byte chunk c at position
-  // c ^ (r / 2) % 8, and the rows a lane reads are 32 apart, so every fragment of a lane has the same swizzle: the
-  // chunk of slice kk sits at ((kk ^ s1) * 2 + l0) with s1 and l0 fixed per lane.  One address per stage, operand and
-  // slice (sixteen registers); the 32-row blocks and nothing else go into the instructions' immediate offsets.
-  const uint4* fx_at[2][4];
-  const uint4* fw_at[2][4];
-  {
-    const int sw = (lr >> 1) & 7, s1 = sw >> 1, l0 = lk ^ (sw & 1);
+  // c ^ (r / 2) % 8, and the rows a lane reads are 16 apart, so every fragment of a lane has the same swizzle.  One
+  // address per stage, operand and slice (eight registers); the 16-row blocks go into the instructions' immediate offsets.
+  const uint4* fx_at[2][2];
+  const uint4* fw_at[2][2];
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+  for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int chunk = (kk ^ s1) * 2 + l0;
-        fx_at[st][kk] = smem + st * STAGE + ((wm * TM) * 32 + lr) * 8 + chunk;
-        fw_at[st][kk] = smem + st * STAGE + BM * 8 + ((wn * TN) * 32 + lr) * 8 + chunk;
-      }
-  }
-  f32x16 acc[TN][TM];
+    for (int kk = 0; kk < 2; ++kk) {
+      const int chunk = (kk * 4 + lg) ^ (lr >> 1);
+      fx_at[st][kk] = smem + st * STAGE + (wm * TM * 32 + lr) * 8 + chunk;
+      fw_at[st][kk] = smem + st * STAGE + BM * 8 + (wn * TN * 32 + lr) * 8 + chunk;
+    }
+  Accumulators<16, TM, TN> acc;
 #pragma unroll
-  for (int a = 0; a < TN; ++a)
+  for (int a = 0; a < FN; ++a)
 #pragma unroll
-    for (int b = 0; b < TM; ++b)
+    for (int b = 0; b < FM; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-  bf16x8 fw[2][TN], fx[2][TM];
+      for (int r = 0; r < 4; ++r) acc.v[a][b][r] = 0.f;
+  bf16x8 fw[FN], fx[2][FM];
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
-  // fragment j of a 16-wide slice, in the order the MFMAs first need them: W block 0, the four X blocks, W blocks 1..3
-  auto load_frag = [&](auto bufc, auto jc, auto stc, auto kkc) {
-    constexpr int buf = decltype(bufc)::value, j = decltype(jc)::value, st = decltype(stc)::value, kk = decltype(kkc)::value;
-    if constexpr (j == 0) fw[buf][0] = as_bf16x8(fw_at[st][kk][0]);
-    else if constexpr (j <= 4) fx[buf][j - 1] = as_bf16x8(fx_at[st][kk][(j - 1) * 256]);
-    else fw[buf][j - 4] = as_bf16x8(fw_at[st][kk][(j - 4) * 256]);
+  auto load_w = [&](auto jc, auto stc, auto kkc) {
+    constexpr int j = decltype(jc)::value, st = decltype(stc)::value, kk = decltype(kkc)::value;
+    fw[j] = as_bf16x8(fw_at[st][kk][j * 128]);
+  };
+  auto load_x = [&](auto jc, auto stc, auto kkc) {
+    constexpr int j = decltype(jc)::value, st = decltype(stc)::value, kk = decltype(kkc)::value;
+    fx[kk][j] = as_bf16x8(fx_at[st][kk][j * 128]);
   };
   u32x4 R[GPW];
-  constexpr int MF = TM * TN;   // 16 MFMAs per 16-wide slice of the K step
-  // One 16-wide slice KK of a K step: sixteen MFMAs on fragment buffer KK & 1, each preceded by exactly ONE memory
-  // instruction, so that none of them has to wait for an issue slot behind another (a wave issues in order, and with
-  // one wave per SIMD whatever stalls it stalls the MFMA pipe).  Slices 0..2: eight fragment reads for the next slice,
-  // then four times {write register quad q to the next stage, reload it for the stage after next}.  Slice 3: the last
-  // four writes and reloads first, the barrier behind the eighth MFMA, then the first fragments of the next stage.
+  constexpr int MF = FM * FN;   // 64 MFMAs per 32-wide slice of the K step
+  // One 32-wide slice KK of a K step: 64 MFMAs (16x16x32), every other one preceded by exactly ONE memory instruction, so
+  // that none of them has to wait for an issue slot behind another (a wave issues in order, and with one wave per SIMD
+  // whatever stalls it stalls the MFMA pipe).  The MFMAs go through the W blocks one after the other, so W needs one set
+  // of fragments: blocks 0..3 of the next slice replace this slice's once its first half is through, blocks 4..7 arrive
+  // in the first slots of the slice that uses them.  X has two sets.
+  // Slice 0, slots 0..31: W blocks 4..7; X of slice 1; two times {write register quad q to the next stage, reload it for
+  // the stage after next}; W blocks 0..3 of slice 1; six more writes and reloads.
+  // Slice 1: W blocks 4..7; the other eight writes; two reloads; the barrier; X and W blocks 0..3 of the next stage's slice
+  // 0; six reloads.
   // WR: stage kt + 1 exists (its groups wait in R); LD: stage kt + 2 exists.
   auto slice = [&](auto kkc, auto wrc, auto ldc, auto curc, int64_t k_next2) {
-    constexpr int KK = decltype(kkc)::value, buf = KK & 1, nbuf = buf ^ 1, CUR = decltype(curc)::value;
+    constexpr int KK = decltype(kkc)::value, CUR = decltype(curc)::value;
     uint4* const sn = smem + (CUR ^ 1) * STAGE;
     constexpr bool WR = decltype(wrc)::value, LD = decltype(ldc)::value;
+    using NEXT = std::integral_constant<int, CUR ^ 1>;
+    auto put = [&](auto q) {
+      if constexpr (WR) *(u32x4*)(sn + wro + q * NW * 64) = R[q];
+    };
+    auto get = [&](auto q) {
+      if constexpr (LD) R[q] = gload(q, k_next2);
+    };
     static_for<0, MF>([&](auto mi) {
-      // One wait per group instead of one per use (the compiler, which still places every wait that is needed,
-      // drops its own where these make them redundant): all eight fragments of this slice, read eight to sixteen
-      // instructions ago with four LDS stores behind them, at the slice's first MFMA; the four register quads about
-      // to be stored, loaded a K step ago with twelve younger loads behind them, at the first store.
-      if constexpr (mi == 0 && KK > 0) __builtin_amdgcn_s_waitcnt(0xc47f);                                   // lgkmcnt(4)
-      if constexpr (WR && LD && ((KK < 3 && mi == 8) || (KK == 3 && mi == 0))) __builtin_amdgcn_s_waitcnt(0x0f7c);   // vmcnt(12)
-      if constexpr (KK < 3) {
-        if constexpr (mi < 8) {
-          load_frag(std::integral_constant<int, nbuf>{}, mi, curc, std::integral_constant<int, (KK + 1) & 3>{});
-        } else {
-          constexpr int q = 4 * KK + (mi - 8) / 2;
-          if constexpr ((mi & 1) == 0) {
-            if constexpr (WR) *(u32x4*)(sn + wro + q * NW * 64) = R[q];
-          } else {
-            if constexpr (LD) R[q] = gload(std::integral_constant<int, q>{}, k_next2);
+      constexpr int slot = mi / 2;
+      // One wait per group instead of one per use (the compiler, which still places every wait that is needed, drops its
+      // own where these make them redundant): this slice's fragments at its first MFMA (behind them: six LDS stores in
+      // slice 0's tail), the eight register quads about to be stored, loaded a K step ago with eight younger loads behind
+      // them, at the first store.
+      if constexpr (mi == 0) __builtin_amdgcn_s_waitcnt(KK == 0 ? 0xc07f : 0xc67f);                          // lgkmcnt(0 / 6)
+      if constexpr (WR && LD && mi == (KK == 0 ? 24 : 8)) __builtin_amdgcn_s_waitcnt(0x0f78);                // vmcnt(8)
+      if constexpr (mi % 2 == 0) {
+        if constexpr (slot < 4) {
+          load_w(std::integral_constant<int, 4 + slot>{}, curc, kkc);
+        } else if constexpr (KK == 0) {
+          if constexpr (slot < 12) load_x(std::integral_constant<int, slot - 4>{}, curc, I1{});
+          else if constexpr (slot >= 16 && slot < 20) load_w(std::integral_constant<int, slot - 16>{}, curc, I1{});
+          else {
+            constexpr int i = slot < 16 ? slot - 12 : slot - 16;
+            if constexpr (i % 2 == 0) put(std::integral_constant<int, i / 2>{});
+            else get(std::integral_constant<int, i / 2>{});
           }
-        }
-      } else {
-        if constexpr (mi < 4) {
-          if constexpr (WR) *(u32x4*)(sn + wro + (12 + mi) * NW * 64) = R[12 + mi];
-        } else if constexpr (mi < 8) {
-          if constexpr (LD) R[8 + mi] = gload(std::integral_constant<int, 8 + mi>{}, k_next2);
         } else {
-          if constexpr (mi == 8) {
+          if constexpr (slot == 14) {
             __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): my LDS writes are done, my last fragments are in registers
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
           }
-          if constexpr (WR) load_frag(std::integral_constant<int, nbuf>{}, std::integral_constant<int, mi - 8>{}, std::integral_constant<int, CUR ^ 1>{}, I0{});
+          if constexpr (slot < 12) put(std::integral_constant<int, slot + 4>{});
+          else if constexpr (slot < 14) get(std::integral_constant<int, slot - 4>{});
+          else if constexpr (slot < 22) {
+            if constexpr (WR) load_x(std::integral_constant<int, slot - 14>{}, NEXT{}, I0{});
+          } else if constexpr (slot < 26) {
+            if constexpr (WR) load_w(std::integral_constant<int, slot - 22>{}, NEXT{}, I0{});
+          } else get(std::integral_constant<int, slot - 16>{});
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-      constexpr int a = mi / TM, b = mi % TM;
-      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf][a], fx[buf][b], acc[a][b], 0, 0, 0);
+      constexpr int a = mi / FM, b = mi % FM;
+      acc.v[a][b] = mfma_bf16(fw[a], fx[KK][b], acc.v[a][b]);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -844,8 +1034,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   auto step = [&](auto wrc, auto ldc, auto curc, int64_t k_next2) {
     slice(I0{}, wrc, ldc, curc, k_next2);
     slice(I1{}, wrc, ldc, curc, k_next2);
-    slice(I2{}, wrc, ldc, curc, k_next2);
-    slice(I3{}, wrc, ldc, curc, k_next2);
   };
 
   const int64_t nk = K / 64;
@@ -856,8 +1044,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   if (nk > 1) static_for<0, GPW>([&](auto i) { R[i] = gload(i, 64); });
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __builtin_amdgcn_s_barrier();
-  if (s0) static_for<0, 8>([&](auto j) { load_frag(I0{}, j, I1{}, I0{}); });
-  else static_for<0, 8>([&](auto j) { load_frag(I0{}, j, I0{}, I0{}); });
+  auto first_frags = [&](auto stc) {
+    static_for<0, 8>([&](auto j) { load_x(j, stc, I0{}); });
+    static_for<0, 4>([&](auto j) { load_w(j, stc, I0{}); });
+  };
+  if (s0) first_frags(I1{});
+  else first_frags(I0{});
   int64_t kt = 0;
   if (nk >= 3 && s0) {
     step(std::true_type{}, std::true_type{}, I1{}, 2 * 64);
@@ -894,19 +1086,22 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 template <typename OutT, int EPI>
 hipError_t launch_fast(const Route& r, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                        const EpiDev& ep, hipStream_t stream) {
-  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false;
+  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false, attr_tall = false;
   switch (r.kernel) {
     case TILE_256x256:
       return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
     case TILE_256x192:
-      return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI, 2>, 256, 192, 512, &attr_wide, X, W, C, M, N, K,
+      return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI>, 256, 192, 512, &attr_wide, X, W, C, M, N, K,
                                 ep, 1, stream);
+    case TILE_256x128:
+      return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 4, 2, OutT, EPI, 3, 32>, 256, 128, 256, &attr_tall, X, W, C, M, N, K,
+                                ep, 1, stream, 3);
     case TILE_128x128_DEEP:
-      return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 4>, 128, 128, 256, &attr_deep, X, W, C, M, N, K,
+      return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 2, 2, OutT, EPI, 4, 32>, 128, 128, 256, &attr_deep, X, W, C, M, N, K,
                                 ep, r.splits, stream, 4);
     case TILE_128x128:
-      return launch_tiles<OutT>(gemm_bf16_nt_kernel<2, 2, 2, 2, OutT, EPI, 2>, 128, 128, 256, &attr_small, X, W, C, M, N, K,
-                                ep, r.splits, stream);
+      return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 2, 2, OutT, EPI, 2, 16>, 128, 128, 256, &attr_small, X, W, C,
+                                M, N, K, ep, r.splits, stream);
     default:
       return hipErrorInvalidValue;
   }
