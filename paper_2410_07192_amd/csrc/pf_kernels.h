@@ -80,10 +80,23 @@ hipError_t ce_loss_inplace(int32_t dtype, void* logits, const int32_t* ids, floa
                            int64_t pitch, int32_t V, int32_t S, float inv_n, hipStream_t stream);
 hipError_t embed_bwd(int32_t dtype, const void* dx, const int32_t* ids, float* dtok, float* dpos, int64_t tokens,
                      int32_t S, int32_t d, int32_t V, hipStream_t stream);
-// Adam with bias correction on fp32 arrays; g holds the sum over `accum` microbatches and is cleared.
-// dry: the same kernel with a zero step and unit decay factors, so theta, m and v keep their values (for profiling).
-hipError_t adam_update(float* theta, float* m, float* v, float* g, int64_t n, float lr, float b1, float b2, float eps,
-                       int64_t step, int32_t accum, hipStream_t stream, bool dry = false);
+// Adam with bias correction on the arrays of one fp32 block, and their working copies; g holds the sum over `accum`
+// microbatches and is cleared.  dry: the same kernel with a zero step and unit decay factors, so theta, m and v keep their
+// values (for profiling).
+struct AdamPiece {
+  int64_t src;     // first element in theta, m, v and g (16-byte aligned)
+  void* dst;       // [R][C] in the model dtype
+  void* dst_t;     // [C][R], or null; with it R is a multiple of 8
+  int64_t R, C;    // C a multiple of 8
+  int64_t first;   // first workgroup (filled in by adam_write)
+};
+struct AdamPieces {
+  static constexpr int MAX = 12;
+  int32_t n;
+  AdamPiece p[MAX];
+};
+hipError_t adam_write(int32_t dtype, float* theta, float* m, float* v, float* g, AdamPieces ps, float lr, float b1, float b2,
+                      float eps, int64_t step, int32_t accum, hipStream_t st, bool dry = false);
 // fp32 [R][C] -> dst [R][C] in `dtype` and, if dst_t is not null, dst_t [C][R]
 hipError_t cast_from_f32(int32_t dtype, const float* src, void* dst, void* dst_t, int64_t R, int64_t C,
                          hipStream_t stream);

@@ -105,27 +105,37 @@ int64_t train_arena_bytes(const pf_model_desc& m, const pf_exec_config& cfg, con
   return t;
 }
 
-static int32_t recast_layer(pf_ctx* c, int32_t l, hipStream_t st) {
+// the arrays of a layer, or of the embedding block, in the fp32 block and where their working copies lie
+static AdamPieces layer_pieces(pf_ctx* c, int32_t l) {
   TrainState& t = *c->tr;
+  AdamPieces ps{};
+  ps.n = 12;
   for (int i = 0; i < 12; ++i) {
-    int64_t R, C;
-    param_shape(c->md, i, &R, &C);
-    void* dst_t = nullptr;
+    AdamPiece& p = ps.p[i];
+    param_shape(c->md, i, &p.R, &p.C);
+    p.src = t.off32[i] / 4;
+    p.dst = t.Wk[l] + c->lay.off[i];
     for (int k = 0; k < 4; ++k)
-      if (kMat[k] == i) dst_t = t.Wt[l] + t.wt_off[k];
-    PF_HIP(cast_from_f32(c->md.dtype, (const float*)((char*)t.master[l] + t.off32[i]), t.Wk[l] + c->lay.off[i], dst_t,
-                         R, C, st));
+      if (kMat[k] == i) p.dst_t = t.Wt[l] + t.wt_off[k];
   }
-  return PF_OK;
+  return ps;
 }
 
-static int32_t recast_emb(pf_ctx* c, hipStream_t st) {
+static AdamPieces emb_pieces(pf_ctx* c) {
   TrainState& t = *c->tr;
-  const pf_model_desc& m = c->md;
-  PF_HIP(cast_from_f32(m.dtype, (const float*)((char*)t.embM + t.emb32_off[0]), t.E_w, t.Et, t.Vp, m.d_model, st));
-  PF_HIP(cast_from_f32(m.dtype, (const float*)((char*)t.embM + t.emb32_off[1]), t.pos_w, nullptr, m.seq_len, m.d_model, st));
-  PF_HIP(cast_from_f32(m.dtype, (const float*)((char*)t.embM + t.emb32_off[2]), t.lnf_g_w, nullptr, 1, m.d_model, st));
-  PF_HIP(cast_from_f32(m.dtype, (const float*)((char*)t.embM + t.emb32_off[3]), t.lnf_b_w, nullptr, 1, m.d_model, st));
+  const int64_t d = c->md.d_model;
+  AdamPieces ps{};
+  ps.n = 4;
+  ps.p[0] = {t.emb32_off[0] / 4, t.E_w, t.Et, t.Vp, d, 0};
+  ps.p[1] = {t.emb32_off[1] / 4, t.pos_w, nullptr, c->md.seq_len, d, 0};
+  ps.p[2] = {t.emb32_off[2] / 4, t.lnf_g_w, nullptr, 1, d, 0};
+  ps.p[3] = {t.emb32_off[3] / 4, t.lnf_b_w, nullptr, 1, d, 0};
+  return ps;
+}
+
+static int32_t recast(pf_ctx* c, const AdamPieces& ps, const float* master, hipStream_t st) {
+  for (int i = 0; i < ps.n; ++i)
+    PF_HIP(cast_from_f32(c->md.dtype, master + ps.p[i].src, ps.p[i].dst, ps.p[i].dst_t, ps.p[i].R, ps.p[i].C, st));
   return PF_OK;
 }
 
@@ -198,7 +208,7 @@ int32_t train_create(pf_ctx* c, const pf_weights* w, char* base, hipStream_t st)
       PF_HIP(widen_to_f32(m.dtype, (const char*)w->layers[l] + c->lay.off[i], (float*)((char*)t.master[l] + z.off32[i]),
                           R * C, st));
     }
-    int32_t rc = recast_layer(c, (int32_t)l, st);
+    int32_t rc = recast(c, layer_pieces(c, (int32_t)l), t.master[l], st);
     if (rc != PF_OK) return rc;
   }
   if (z.Vp) {
@@ -207,7 +217,7 @@ int32_t train_create(pf_ctx* c, const pf_weights* w, char* base, hipStream_t st)
     PF_HIP(widen_to_f32(m.dtype, w->pos_emb, (float*)((char*)t.embM + z.emb32_off[1]), (int64_t)m.seq_len * m.d_model, st));
     PF_HIP(widen_to_f32(m.dtype, w->lnf_g, (float*)((char*)t.embM + z.emb32_off[2]), m.d_model, st));
     PF_HIP(widen_to_f32(m.dtype, w->lnf_b, (float*)((char*)t.embM + z.emb32_off[3]), m.d_model, st));
-    int32_t rc = recast_emb(c, st);
+    int32_t rc = recast(c, emb_pieces(c), t.embM, st);
     if (rc != PF_OK) return rc;
   }
   PF_HIP(hipMemsetAsync(t.loss, 0, 256, st));
@@ -367,17 +377,12 @@ static int32_t optimizer_step(pf_ctx* c, hipStream_t st) {
   const int64_t step = t.steps + 1;
   if (!t.dry) t.steps = step;
   const int32_t accum = (int32_t)t.mb_accum;
-  for (int64_t l = 0; l < c->md.n_layers; ++l) {
-    PF_HIP(adam_update(t.master[l], t.m[l], t.v[l], t.grad[l], t.blob32 / 4, a.lr, a.beta1, a.beta2, a.eps, step,
-                       accum, st, t.dry));
-    int32_t rc = recast_layer(c, (int32_t)l, st);
-    if (rc != PF_OK) return rc;
-  }
-  if (t.Vp) {
-    PF_HIP(adam_update(t.embM, t.embm, t.embv, t.embg, t.emb32 / 4, a.lr, a.beta1, a.beta2, a.eps, step, accum, st, t.dry));
-    int32_t rc = recast_emb(c, st);
-    if (rc != PF_OK) return rc;
-  }
+  for (int32_t l = 0; l < c->md.n_layers; ++l)
+    PF_HIP(adam_write(c->md.dtype, t.master[l], t.m[l], t.v[l], t.grad[l], layer_pieces(c, l), a.lr, a.beta1, a.beta2, a.eps,
+                      step, accum, st, t.dry));
+  if (t.Vp)
+    PF_HIP(adam_write(c->md.dtype, t.embM, t.embm, t.embv, t.embg, emb_pieces(c), a.lr, a.beta1, a.beta2, a.eps, step, accum,
+                      st, t.dry));
   t.mb_accum = 0;
   return PF_OK;
 }

@@ -543,20 +543,90 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const T* __restrict__ dx
   }
 }
 
-// ---- Adam ------------------------------------------------------------------------------------------------
-// g is the SUM over `accum` microbatches; the step uses g/accum and clears g.
-__global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
-                                                   float* __restrict__ g, int64_t n, float lr, float b1, float b2,
-                                                   float eps, float bc1, float bc2, float inv_accum) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const float gr = g[i] * inv_accum;
-  const float mi = b1 * m[i] + (1.f - b1) * gr;
-  const float vi = b2 * v[i] + (1.f - b2) * gr * gr;
-  m[i] = mi;
-  v[i] = vi;
-  theta[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-  g[i] = 0.f;
+// ---- Adam and the working copies -----------------------------------------------------------------------------
+// One launch updates the parameters of a layer (or of the embedding block) and writes their working copies in the model
+// dtype, a matrix's transposed copy included: a parameter costs 16 bytes read, 16 written and the copies.  Bound by HBM
+// (36 bytes per bf16 matrix element).  A workgroup takes a 64x64 tile of a matrix, whose transposition goes through LDS, or 4096
+// elements of an array without transposed copy; every load of a thread is requested before the first is used.
+// One Adam kernel and a cast per array before: 50 launches for four layers of d 512 and their embedding, now five.
+// g is the SUM over `accum` microbatches; the step uses g / accum and clears g.
+struct AdamConst { float lr, b1, b2, eps, bc1, bc2, inv_accum; };
+
+template <typename T>
+__global__ __launch_bounds__(256) void adam_write_kernel(float* __restrict__ theta, float* __restrict__ m, float* __restrict__ v,
+                                                         float* __restrict__ g, AdamPieces ps, AdamConst a) {
+  constexpr int PITCH = sizeof(T) == 2 ? 66 : 65;   // elements: the columns a wave writes and the rows it reads meet few banks twice
+  __shared__ __align__(16) T tile[64 * PITCH];
+  int i = 0;
+  while (i + 1 < ps.n && (int64_t)blockIdx.x >= ps.p[i + 1].first) ++i;
+  const AdamPiece& p = ps.p[i];
+  const int64_t block = (int64_t)blockIdx.x - p.first;
+  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
+  const bool matrix = p.dst_t != nullptr;
+  const int64_t tiles_c = (p.C + 63) / 64;
+  const int64_t r0 = matrix ? block / tiles_c * 64 : 0, c0 = matrix ? block % tiles_c * 64 : 0;
+  // four groups of four consecutive elements; one past the end reads the array's first group and is not written
+  int64_t at[4];
+  bool in[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (matrix) {
+      const int64_t r = r0 + ty + 16 * k, c = c0 + tx * 4;
+      in[k] = r < p.R && c < p.C;
+      at[k] = in[k] ? r * p.C + c : 0;
+    } else {
+      const int64_t e = (block * 1024 + k * 256 + t) * 4;
+      in[k] = e < p.R * p.C;
+      at[k] = in[k] ? e : 0;
+    }
+  }
+  f32x4 gr[4], mi[4], vi[4], th[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    gr[k] = *(const f32x4*)(g + p.src + at[k]);
+    mi[k] = *(const f32x4*)(m + p.src + at[k]);
+    vi[k] = *(const f32x4*)(v + p.src + at[k]);
+    th[k] = *(const f32x4*)(theta + p.src + at[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float gj = gr[k][j] * a.inv_accum;
+      mi[k][j] = a.b1 * mi[k][j] + (1.f - a.b1) * gj;
+      vi[k][j] = a.b2 * vi[k][j] + (1.f - a.b2) * gj * gj;
+      th[k][j] -= a.lr * (mi[k][j] / a.bc1) / (sqrtf(vi[k][j] / a.bc2) + a.eps);
+    }
+    float o[4] = {th[k][0], th[k][1], th[k][2], th[k][3]};
+    if (in[k]) {
+      *(f32x4*)(m + p.src + at[k]) = mi[k];
+      *(f32x4*)(v + p.src + at[k]) = vi[k];
+      *(f32x4*)(theta + p.src + at[k]) = th[k];
+      *(f32x4*)(g + p.src + at[k]) = f32x4{0.f, 0.f, 0.f, 0.f};
+      store4((T*)p.dst + at[k], o);
+    }
+    if (matrix) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) tile[(tx * 4 + j) * PITCH + ty + 16 * k] = from_f32<T>(o[j]);
+    }
+  }
+  if (!matrix) return;
+  __syncthreads();
+  // column c of the tile, eight rows per thread (rows and columns come in eights)
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int c = (t >> 3) + 32 * k, rr = (t & 7) * 8;
+    if (c0 + c >= p.C || r0 + rr >= p.R) continue;
+    const T* q = tile + c * PITCH + rr;
+    T* dst = (T*)p.dst_t + (c0 + c) * p.R + r0 + rr;
+    if constexpr (sizeof(T) == 2) {
+      const uint32_t* w = (const uint32_t*)q;
+      *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+      *(float4*)dst = make_float4(q[0], q[1], q[2], q[3]);
+      *(float4*)(dst + 4) = make_float4(q[4], q[5], q[6], q[7]);
+    }
+  }
 }
 
 // master (fp32) -> working copy in the model dtype; for a matrix [R][C] also the transposed copy [C][R]
@@ -744,16 +814,25 @@ hipError_t embed_bwd(int32_t dtype, const void* dx, const int32_t* ids, float* d
   return hipGetLastError();
 }
 
-hipError_t adam_update(float* theta, float* m, float* v, float* g, int64_t n, float lr, float b1, float b2, float eps,
-                       int64_t step, int32_t accum, hipStream_t st, bool dry) {
-  if (n <= 0 || step < 1 || accum < 1) return hipErrorInvalidValue;
-  const float bc1 = 1.f - powf(b1, (float)step), bc2 = 1.f - powf(b2, (float)step);
-  if (dry) {   // same loads, stores and arithmetic, but m, v and theta keep their values (finite gradients assumed): only g is cleared
-    lr = 0.f;
-    b1 = b2 = 1.f;
+hipError_t adam_write(int32_t dtype, float* theta, float* m, float* v, float* g, AdamPieces ps, float lr, float b1, float b2,
+                      float eps, int64_t step, int32_t accum, hipStream_t st, bool dry) {
+  if (ps.n < 1 || ps.n > AdamPieces::MAX || step < 1 || accum < 1) return hipErrorInvalidValue;
+  int64_t blocks = 0;
+  for (int i = 0; i < ps.n; ++i) {
+    AdamPiece& p = ps.p[i];
+    if (p.R < 1 || p.C < 1 || p.C % 8 != 0 || (p.dst_t && p.R % 8 != 0)) return hipErrorInvalidValue;
+    p.first = blocks;
+    blocks += p.dst_t ? ((p.R + 63) / 64) * ((p.C + 63) / 64) : (p.R * p.C + 4095) / 4096;
   }
-  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, theta, m, v, g, n, lr, b1, b2,
-                     eps, bc1, bc2, 1.f / (float)accum);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  AdamConst a{lr, b1, b2, eps, 1.f - powf(b1, (float)step), 1.f - powf(b2, (float)step), 1.f / (float)accum};
+  if (dry) {   // same loads, stores and arithmetic, but m, v and theta keep their values (finite gradients assumed): only g is cleared
+    a.lr = 0.f;
+    a.b1 = a.b2 = 1.f;
+  }
+  const dim3 grid((unsigned)blocks), block(256);
+  PF_BY_DTYPE(dtype, hipLaunchKernelGGL(adam_write_kernel<bf16_t>, grid, block, 0, st, theta, m, v, g, ps, a),
+              hipLaunchKernelGGL(adam_write_kernel<float>, grid, block, 0, st, theta, m, v, g, ps, a));
   return hipGetLastError();
 }
 

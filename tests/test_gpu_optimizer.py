@@ -1,0 +1,54 @@
+"""The optimizer step writes the working copies that the next microbatch runs on: sizes whose matrices end inside a 64x64 tile
+and whose vectors end inside a workgroup's share.  After one step the loss and every gradient of the next microbatch (input
+gradients go through the transposed copies) match the checker on the updated master weights, rounded to the model dtype."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import transformer as ot                                     # noqa: E402
+from paper_2410_07192_amd import synth                                   # noqa: E402
+from test_gpu_training import _mods, read_emb, read_layer, rel_err      # noqa: E402
+
+SHAPES = [synth.ModelShape(2, 200, 25, 328, 20, 2, 70, True, "f32"),       # d_head 8
+          synth.ModelShape(2, 72, 9, 136, 24, 2, 130, True, "bf16"),
+          synth.ModelShape(2, 192, 3, 520, 64, 2, 65, False, "bf16"),      # d_head 64, one row in the last tile of E
+          synth.ModelShape(2, 64, 1, 64, 8, 1, 64, True, "bf16")]          # whole tiles only
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"{s.dtype}-d{s.d_model}-f{s.d_ff}")
+def test_the_next_microbatch_runs_on_the_updated_weights(shape):
+    pf, dev = _mods()
+    tol = 1e-4 if shape.dtype == "f32" else 2e-2          # as for the first microbatch
+    params = synth.make_model_params(shape, seed=5, std=0.08)
+    m = dev.DeviceModel(shape, params, training=True, adam=pf.pf_adam(2e-2, 0.9, 0.999, 1e-8, 1))
+    try:
+        ids = np.stack([synth.make_token_ids(shape, seed=90 + i)[None] for i in range(2)])
+        m.set_io(dev.to_device(ids.astype(np.int32)), 2, None, 0)
+        nF = len(m.chain)
+        m.ctx.pf_fill_chunk(m.chunk(0, nF), m.chain)
+        m.ctx.pf_ctx_sync()
+        assert m.ctx.pf_ctx_train_state()[1] == 1
+        stored = synth.round_to_bf16 if shape.dtype == "bf16" else (lambda a: a)
+        P = ot.cast_params(params)
+        moved = 0.0
+        for l in range(shape.n_layers):
+            for k, v in read_layer(m, 1, l).items():
+                moved = max(moved, float(np.abs(P["layers"][l][k] - v).max()))
+                P["layers"][l][k] = stored(v.astype(np.float32)).astype(np.float64)
+        emb = read_emb(m, 1)
+        for k in ("tok_emb", "pos_emb", "lnf_g", "lnf_b"):
+            P[k] = stored(emb[k].astype(np.float32)).astype(np.float64)
+        assert moved > 1e-2                               # a step of 2e-2 in nearly every weight
+        m.ctx.pf_fill_chunk(m.chunk(nF, 2 * nF - 1), m.chain)      # the next microbatch up to its optimizer node
+        loss, _ = m.ctx.pf_ctx_train_state()
+        ref_loss, G = ot.model_loss_and_grads(ids[1, 0], P, shape.n_heads, shape.causal, shape.eps)
+        assert abs(loss - ref_loss) < tol * max(1.0, abs(ref_loss))
+        for l in range(shape.n_layers):
+            got = read_layer(m, 0, l)
+            for k, ref in G["layers"][l].items():
+                assert rel_err(got[k], ref) < tol, (l, k)
+    finally:
+        m.close()
