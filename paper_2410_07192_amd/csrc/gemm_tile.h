@@ -593,22 +593,6 @@ __device__ __forceinline__ f32x4 mfma_bf16(bf16x8 w, bf16x8 x, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
 }
 
-// Copies of 1 KB from a raw buffer straight into LDS (buffer_load_dwordx4 ... lds): lane i's 16 bytes at byte voff + soff of
-// the buffer land at LDS byte address dst + 16 i; dst, the buffer and soff are wave-uniform.  M0 as in lds_direct_load_1k.
-typedef uint32_t lds_buffer_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ lds_buffer_t lds_buffer(const void* p) {
-  const uint64_t a = (uint64_t)(uintptr_t)p;
-  return lds_buffer_t{(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a),
-                      (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)), 0x7fffffffu, 0x00020000u};
-}
-__device__ __forceinline__ void lds_buffer_load_1k(uint32_t dst, lds_buffer_t buf, uint32_t voff, int32_t soff) {
-  uint32_t saved;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
-               : "=&s"(saved)
-               : "s"(dst), "v"(voff), "s"(buf), "s"(__builtin_amdgcn_readfirstlane(soff))
-               : "memory");
-}
-
 // 256x192 tile on eight waves (4x2, wave tile 64x96, two per SIMD), 32x32x16 MFMAs (inside a 12-layer encoder pass 16384 x 768,
 // K = 3072 takes 71.8 us with these and 74.1 with 16x16x32).
 template <int WGM, int WGN, int TM, int TN, typename OutT, int EPI>

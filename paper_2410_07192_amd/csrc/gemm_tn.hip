@@ -2,14 +2,18 @@
 // i.e. both operands as the layer left them in memory (tokens are the slow index): dW = dY^T X needs no
 // transposed copies.  Optionally colsum[m] += sum over k of A[k][m], which is the bias gradient of the same layer.
 //
-// 128x128 tiles, 4 waves (2x2, wave tile 64x64 = 2x2 MFMA 32x32x16 tiles), K steps of 64, two LDS stages
-// of 32 KB, two workgroups per CU.  Operand slabs go global -> LDS directly, 4 k-rows x 256 bytes per wave
-// instruction, in the [k][m] order they have in memory.  MFMA wants, per lane, eight consecutive k of one m:
-// ds_read_b64_tr_b16 delivers exactly that from a k-major image (a 16-lane group reads a 4 k x 16 m block and
-// every lane receives the four k of its own m), two reads per fragment.  The 16-byte chunks of a k-row are
-// XOR-swizzled by 4 * (k % 4) (on the global side of the copy) so that the four rows a half-wave reads fall
-// on disjoint banks.
-// Split K: gridDim.y workgroups share a tile, each over K / gridDim.y; the fp32 tile goes through LDS and is
+// 128x128 tiles, 4 waves (2x2, wave tile 64x64 in 16x16x32 MFMAs), K steps of 64, two LDS stages of 32 KB, two
+// workgroups per CU.  Operand slabs go global -> LDS directly, 4 k-rows x 256 bytes per wave instruction, in the [k][m]
+// order they have in memory; rows past the end of K are past the end of the buffer and arrive as zeros, so K need not be
+// a multiple of anything.  MFMA wants, per lane, eight consecutive k of one m: ds_read_b64_tr_b16 delivers exactly that
+// from a k-major image (a 16-lane group reads a 4 k x 16 m block and every lane receives the four k of its own m), two
+// reads per fragment.  The 16-byte chunks of a k-row are XOR-swizzled by 4 * (k % 4) + 2 * (k / 8 % 2) (on the global
+// side of the copy), so that the eight half rows the two groups of a half-wave read fall on disjoint banks.
+// The fragments of a whole K step are double buffered in registers: while the MFMAs of one step run, its successor's 32
+// reads and the copies of the step after that are issued between them, one barrier a step (behind its first MFMAs).  With a
+// substep of reads in flight at a time and every copy of a step in one burst behind the barrier: 4096 x 1024, K = 8192 105 us,
+// now 85; 50304 x 1024, K = 8192 1162 -> 960, 8192 x 8192, K = 2048 585 -> 448, 512 x 512, K = 640 20 -> 10.
+// Split K: gridDim.y workgroups share a tile, each over a run of whole steps; the fp32 tile goes through LDS and is
 // added to C with fp32 atomics in coalesced order (plain read-add-write when K is not split).  The column sum
 // comes from one more MFMA per A fragment against a fragment of ones, on the waves of the first tile column.
 #include <type_traits>
@@ -39,129 +43,157 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
                                                                   const bf16_t* __restrict__ B, float* __restrict__ C,
                                                                   float* __restrict__ colsum, int64_t M, int64_t N,
                                                                   int64_t K, int32_t tiles_m, int32_t tiles_n) {
-  constexpr int BM = 128, BN = 128, TM = 2, TN = 2, NW = 4, STAGE = 32768, BOFF = 16384;
+  constexpr int BM = 128, BN = 128, FM = 4, FN = 4, NW = 4, STAGE = 32768, BOFF = 16384;
   extern __shared__ char smem[];
   const int64_t tile = xcd_contiguous(blockIdx.x, (int64_t)tiles_m * tiles_n);
   const int32_t tn_i = (int32_t)(tile % tiles_n), tm_i = (int32_t)(tile / tiles_n);
   const int64_t m0 = (int64_t)tm_i * BM, n0 = (int64_t)tn_i * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
-  const int lr = lane & 31, lk = lane >> 5;
-  const int64_t k_len = K / gridDim.y;
-  const int64_t kbeg = (int64_t)blockIdx.y * k_len;
-  const int64_t nk = k_len / 64;
+  const int li = lane & 15, lg = lane >> 4;
+  const int32_t steps = (int32_t)((K + 63) / 64), share = (steps + (int32_t)gridDim.y - 1) / (int32_t)gridDim.y;
+  const int32_t first = (int32_t)blockIdx.y * share;
+  const int32_t nk = steps - first < share ? steps - first : share;   // the launcher leaves no slice empty
 
-  // global source of this lane for each of the 8 copies the wave issues per stage (4 of A, 4 of B): copy q
-  // covers k-rows 4q..4q+3 of the step; the lane takes chunk (lane % 16) ^ 4 * (lane / 16) of row lane / 16
-  const int krow = lane >> 4;
-  const int cglob = (lane & 15) ^ (4 * krow);
-  const bf16_t* src[8];
+  // this lane's place in each of the 8 copies the wave issues per step (4 of A, 4 of B): copy q = wave + 4 i covers k-rows
+  // 4 q .. 4 q + 3 of the step; the lane takes chunk (lane % 16) ^ swizzle of row lane / 16.  A tile that sticks out along M
+  // or N takes any chunk of the row instead, the result is discarded.
+  const int cglob = li ^ (4 * lg) ^ (2 * ((wave >> 1) & 1));
+  const int64_t last_a = M - 8 - m0, last_b = N - 8 - n0;
+  const int64_t ca = cglob * 8 < last_a ? cglob * 8 : last_a, cb = cglob * 8 < last_b ? cglob * 8 : last_b;
+  uint32_t off[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int q = wave + 4 * i;   // 0..15 A, 16..31 B
-    const bool isa = q < 16;
-    const int64_t ld = isa ? M : N;
-    int64_t col = (isa ? m0 : n0) + cglob * 8;
-    if (col + 8 > ld) col = ld - 8;   // tile edge: any valid chunk, the result is discarded
-    src[i] = (isa ? A : B) + (kbeg + (q & 15) * 4 + krow) * ld + col;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t r = (wave + 4 * i) * 4 + lg;
+    off[i] = (uint32_t)((r * M + m0 + ca) * 2);
+    off[4 + i] = (uint32_t)((r * N + n0 + cb) * 2);
   }
-  const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)smem);
-  auto issue = [&](auto ic, int stage, int64_t kstep) {
-    constexpr int i = decltype(ic)::value;
-    const int q = wave + 4 * i;
-    const uint32_t dst =
-        __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)(stage * STAGE + (q < 16 ? 0 : BOFF) + (q & 15) * 1024));
-    const bf16_t* p = src[i] + kstep * 64 * (q < 16 ? M : N);
-    lds_direct_load_1k(dst, p);
+  // the rows of one K step are a raw buffer: rows past the end of K are outside it; a step past the slice has none
+  const char* arow = (const char*)A + (int64_t)first * 128 * M;
+  const char* brow = (const char*)B + (int64_t)first * 128 * N;
+  int64_t rows_left = K - (int64_t)first * 64;
+  int32_t left = nk;
+  lds_buffer_t abuf, bbuf;
+  auto next_rows = [&] {   // of the step that is copied next
+    const int32_t rows = left > 0 ? (int32_t)(rows_left < 64 ? rows_left : 64) : 0;
+    abuf = lds_buffer(arow, (uint32_t)(rows * (int32_t)M * 2));
+    bbuf = lds_buffer(brow, (uint32_t)(rows * (int32_t)N * 2));
+    arow += 128 * M;
+    brow += 128 * N;
+    rows_left -= 64;
+    --left;
+  };
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)smem) + (uint32_t)(wave * 1024);
+  auto issue = [&](auto ic, auto stc) {
+    constexpr int i = decltype(ic)::value, st = decltype(stc)::value;
+    lds_buffer_load_1k(lds_base + (uint32_t)(st * STAGE + (i < 4 ? 0 : BOFF) + (i & 3) * 4096), i < 4 ? abuf : bbuf, off[i], 0);
   };
 
-  // fragment addressing: lane 16 g + i points at k-row (g / 2) * 8 + r * 4 + i / 4 of the 16-row substep and at
-  // the four columns from (g % 2) * 16 + 4 * (i % 4) of its 32-column block, and receives column
-  // (g % 2) * 16 + i with the four k of read r: MFMA row lane % 32, k half lane / 32
-  const int g = lane >> 4, li = lane & 15, kq = li >> 2;
-  int offA[TM], offB[TN];
+  // fragment addressing: lane 16 g + i points at k-row 8 g + 4 r + i / 4 of the 32-row substep and at the four columns from
+  // 4 * (i % 4) of its 16-column block, and receives column i with the four k of read r
+  const int kq = li >> 2, swz = (4 * kq) ^ (2 * (lg & 1));
+  int offA[FM], offB[FN];
 #pragma unroll
-  for (int b = 0; b < TM; ++b) {
-    const int colb = ((wm * TM + b) * 32 + (g & 1) * 16 + 4 * (li & 3)) * 2;
-    offA[b] = ((g >> 1) * 8 + kq) * 256 + (((colb >> 4) ^ (4 * kq)) << 4) + (colb & 15);
+  for (int f = 0; f < 4; ++f) {
+    const int row = (8 * lg + kq) * 256 + 8 * (li & 1);
+    offA[f] = row + (((wm * 8 + 2 * f + ((li & 3) >> 1)) ^ swz) << 4);
+    offB[f] = BOFF + row + (((wn * 8 + 2 * f + ((li & 3) >> 1)) ^ swz) << 4);
   }
-#pragma unroll
-  for (int a = 0; a < TN; ++a) {
-    const int colb = ((wn * TN + a) * 32 + (g & 1) * 16 + 4 * (li & 3)) * 2;
-    offB[a] = BOFF + ((g >> 1) * 8 + kq) * 256 + (((colb >> 4) ^ (4 * kq)) << 4) + (colb & 15);
-  }
-  auto frag = [&](int stage, int off, int ks) {
-    lds_char_ptr base = (lds_char_ptr)(lds_void_ptr)smem + stage * STAGE + off + ks * 16 * 256;
-    const v4s r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)base);
-    const v4s r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(base + 4 * 256));
-    v8s o;
-    o[0] = r0[0]; o[1] = r0[1]; o[2] = r0[2]; o[3] = r0[3];
-    o[4] = r1[0]; o[5] = r1[1]; o[6] = r1[2]; o[7] = r1[3];
+  v4s fa[2][2][FM][2], fb[2][2][FN][2];   // [set][substep][block][read]
+  auto read1 = [&](auto setc, auto jc, auto stc) {   // order: the first A and B blocks of a substep first
+    constexpr int set = decltype(setc)::value, j = decltype(jc)::value, st = decltype(stc)::value;
+    constexpr int ks = j / 16, e = j % 16 / 2, r = j % 2;
+    constexpr int at = st * STAGE + ks * 8192 + r * 1024;
+    // e: B 0, A 0..3, B 1..3
+    constexpr bool isa = e >= 1 && e <= 4;
+    constexpr int f = e == 0 ? 0 : isa ? e - 1 : e - 4;
+    lds_char_ptr p = (lds_char_ptr)(lds_void_ptr)smem + (isa ? offA[f] : offB[f]) + at;
+    const v4s v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)p);
+    if constexpr (isa) fa[set][ks][f][r] = v;
+    else fb[set][ks][f][r] = v;
+  };
+  auto join = [](const v4s (&t)[2]) {
+    const v8s o = {t[0][0], t[0][1], t[0][2], t[0][3], t[1][0], t[1][1], t[1][2], t[1][3]};
     return __builtin_bit_cast(bf16x8, o);
   };
-
-  f32x16 acc[TN][TM], csum[TM];
+  f32x4 acc[FN][FM], csum[FM];
 #pragma unroll
-  for (int a = 0; a < TN; ++a)
+  for (int a = 0; a < FN; ++a)
 #pragma unroll
-    for (int b = 0; b < TM; ++b)
+    for (int b = 0; b < FM; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
 #pragma unroll
-  for (int b = 0; b < TM; ++b)
+  for (int b = 0; b < FM; ++b)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) csum[b][r] = 0.f;
+    for (int r = 0; r < 4; ++r) csum[b][r] = 0.f;
   v8s ones_s;
 #pragma unroll
   for (int j = 0; j < 8; ++j) ones_s[j] = (short)0x3f80;   // bf16 1.0
   const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_s);
   const bool do_sum = COLSUM && tn_i == 0 && wn == 0;
 
-  unrolled<0, 8>([&](auto i) { issue(i, 0, 0); });
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  for (int64_t kt = 0; kt < nk; ++kt) {
-    const int cur = (int)(kt & 1);
-    // the other stage was last read before the barrier that ended the previous step
-    if (kt + 1 < nk) unrolled<0, 8>([&](auto i) { issue(i, cur ^ 1, kt + 1); });
-    // fragments of substep ks + 1 are requested before the MFMAs of substep ks are issued
-    bf16x8 fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int b = 0; b < TM; ++b) fa[0][b] = frag(cur, offA[b], 0);
-#pragma unroll
-    for (int a = 0; a < TN; ++a) fb[0][a] = frag(cur, offB[a], 0);
-    unrolled<0, 4>([&](auto ksc) {
-      constexpr int ks = decltype(ksc)::value, buf = ks & 1;
-      if constexpr (ks + 1 < 4) {
-#pragma unroll
-        for (int b = 0; b < TM; ++b) fa[buf ^ 1][b] = frag(cur, offA[b], ks + 1);
-#pragma unroll
-        for (int a = 0; a < TN; ++a) fb[buf ^ 1][a] = frag(cur, offB[a], ks + 1);
+  constexpr int MF = 32, NR = 32, LAG = 4;
+  auto step = [&](auto setc) {   // step kt works on stage kt % 2 and on fragment set kt % 2
+    constexpr int set = decltype(setc)::value;
+    using NEXT = std::integral_constant<int, set ^ 1>;
+    next_rows();
+    unrolled<0, MF>([&](auto mi) {
+      constexpr int m = decltype(mi)::value, r = m - LAG, RM = MF - LAG;
+      if constexpr (r == 0) {
+        // this wave's fragments of the step are in registers (its stage may be overwritten), its copies of the next step
+        // have landed
+        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int a = 0; a < TN; ++a)
-#pragma unroll
-        for (int b = 0; b < TM; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[buf][a], fa[buf][b], acc[a][b], 0, 0, 0);
-      if constexpr (COLSUM) {
-        if (do_sum) {
-#pragma unroll
-          for (int b = 0; b < TM; ++b)
-            csum[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fa[buf][b], csum[b], 0, 0, 0);
-        }
+      if constexpr (r >= 0) {
+        unrolled<r * NR / RM, (r + 1) * NR / RM>([&](auto j) { read1(NEXT{}, j, NEXT{}); });
+        unrolled<r * 8 / RM, (r + 1) * 8 / RM>([&](auto i) { issue(i, setc); });
       }
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int ks = m / 16, a = m % 16 / 4, b = m % 4;
+      acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(join(fb[set][ks][a]), join(fa[set][ks][b]), acc[a][b], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     });
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-  }
-
-  // D[i][j]: lane holds j = lane % 32 (row of C) and i = 8 * (r / 4) + 4 * (lane / 32) + r % 4 (column of C).
-  if constexpr (COLSUM) {
-    // every row i of ones x A equals the column sums: row 0 sits in register 0 of lanes 0..31
-    if (do_sum && lane < 32) {
+    if constexpr (COLSUM) {
+      if (do_sum) {
 #pragma unroll
-      for (int b = 0; b < TM; ++b) {
-        const int64_t m = m0 + (wm * TM + b) * 32 + lane;
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int b = 0; b < FM; ++b)
+            csum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, join(fa[set][ks][b]), csum[b], 0, 0, 0);
+      }
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  next_rows();
+  unrolled<0, 8>([&](auto i) { issue(i, I0{}); });
+  next_rows();
+  unrolled<0, 8>([&](auto i) { issue(i, I1{}); });
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  unrolled<0, NR>([&](auto j) { read1(I0{}, j, I0{}); });
+  // Past the last step nothing is fetched (empty buffers) and the fragments of a stage of zeros are read: one loop body.
+  int32_t kt = 0;
+  for (;;) {
+    step(I0{});
+    if (++kt >= nk) break;
+    step(I1{});
+    if (++kt >= nk) break;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // nothing writes to the stages any more, nobody reads them
+  __builtin_amdgcn_s_barrier();
+
+  // D[i][j]: lane holds j = lane % 16 (row of C) and i = 4 * (lane / 16) + r (column of C).
+  if constexpr (COLSUM) {
+    // every row i of ones x A equals the column sums: row 0 sits in register 0 of lanes 0..15
+    if (do_sum && lane < 16) {
+#pragma unroll
+      for (int b = 0; b < FM; ++b) {
+        const int64_t m = m0 + wm * 64 + b * 16 + lane;
         if (m < M) unsafeAtomicAdd(colsum + m, csum[b][0]);
       }
     }
@@ -169,27 +201,42 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
   // the fp32 tile takes both LDS stages (row-major, 16-byte units XOR-swizzled by row) and leaves in rows
   float* stf = (float*)smem;
   constexpr int UNITS = BN / 4, NT = 64 * NW;
-  unrolled<0, TN>([&](auto a) {
-    unrolled<0, TM>([&](auto b) {
-      const int row = (wm * TM + b) * 32 + lr;
-      unrolled<0, 4>([&](auto rg) {
-        const int unit = ((wn * TN + a) * 32 + rg * 8 + lk * 4) / 4;
-        *(float4*)(stf + row * BN + ((unit ^ (row & (UNITS - 1))) * 4)) =
-            make_float4(acc[a][b][rg * 4 + 0], acc[a][b][rg * 4 + 1], acc[a][b][rg * 4 + 2], acc[a][b][rg * 4 + 3]);
-      });
+  unrolled<0, FN>([&](auto a) {
+    unrolled<0, FM>([&](auto b) {
+      const int row = wm * 64 + b * 16 + li, unit = wn * 16 + a * 4 + lg;
+      *(f32x4*)(stf + row * BN + ((unit ^ (row & (UNITS - 1))) * 4)) = acc[a][b];
     });
   });
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __builtin_amdgcn_s_barrier();
   const bool split = gridDim.y > 1;
+  if (split || ((uintptr_t)C & 15) != 0) {
 #pragma unroll 8
-  for (int i = 0; i < BM * BN / NT; ++i) {
-    const int e = i * NT + tid, row = e / BN, col = e % BN;
-    const float v = stf[row * BN + (((col >> 2) ^ (row & (UNITS - 1))) * 4) + (col & 3)];
-    if (m0 + row < M && n0 + col < N) {
-      float* p = C + (m0 + row) * N + n0 + col;
-      if (split) unsafeAtomicAdd(p, v);
-      else *p += v;
+    for (int i = 0; i < BM * BN / NT; ++i) {
+      const int e = i * NT + tid, row = e / BN, col = e % BN;
+      const float v = stf[row * BN + (((col >> 2) ^ (row & (UNITS - 1))) * 4) + (col & 3)];
+      if (m0 + row < M && n0 + col < N) {
+        float* p = C + (m0 + row) * N + n0 + col;
+        if (split) unsafeAtomicAdd(p, v);
+        else *p += v;
+      }
+    }
+    return;
+  }
+  // four columns at a time (N and the tile's columns come in eights), eight pieces requested before the first is used
+#pragma unroll 1
+  for (int i0 = 0; i0 < BM * UNITS / NT; i0 += 8) {
+    f32x4 c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = (i0 + i) * NT + tid, row = e / UNITS, unit = e % UNITS;
+      if (m0 + row < M && n0 + unit * 4 < N) c[i] = *(const f32x4*)(C + (m0 + row) * N + n0 + unit * 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = (i0 + i) * NT + tid, row = e / UNITS, unit = e % UNITS;
+      if (m0 + row < M && n0 + unit * 4 < N)
+        *(f32x4*)(C + (m0 + row) * N + n0 + unit * 4) = c[i] + *(const f32x4*)(stf + row * BN + (unit ^ (row & (UNITS - 1))) * 4);
     }
   }
 }
@@ -197,16 +244,18 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
 }  // namespace
 
 bool gemm_tn_acc_supported(int32_t dtype, const void* A, const void* B, int64_t M, int64_t N, int64_t K) {
-  return dtype == PF_DTYPE_BF16_ && M >= 8 && N >= 8 && M % 8 == 0 && N % 8 == 0 && K >= 64 && K % 64 == 0 &&
-         (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
+  return dtype == PF_DTYPE_BF16_ && M >= 8 && N >= 8 && M % 8 == 0 && N % 8 == 0 && M < (1 << 23) && N < (1 << 23) && K >= 8 &&
+         K % 8 == 0 && K < ((int64_t)1 << 36) && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
 }
 
-// The 128x128 tiles of this kernel reach about 650 TFLOP/s; the NT kernel's 256-wide tiles about 900 on results
-// large enough to fill the chip with them, but it needs both operands transposed first (4 K (M + N) bytes at about
-// 4 TB/s).  Equating the two gives M N / (M + N) = 1170: below that, or when 256x256 tiles would leave CUs idle,
+// The 128x128 tiles of this kernel reach 610 (8192 x 8192, K = 2048) to 810 TFLOP/s; the NT kernel's 256-wide tiles about 900 on
+// results large enough to fill the chip with them, but it needs both operands transposed first (4 K (M + N) bytes at about
+// 4 TB/s).  Equating the two at 650 gives M N / (M + N) = 1170 (8192 x 8192, K = 2048: 448 us here, 324 there): below that, or when 256x256 tiles would leave CUs idle,
 // this kernel is the faster way to a weight gradient.
 bool gemm_tn_acc_preferred(int64_t M, int64_t N, int64_t K) {
-  (void)K;   // both sides of the comparison are proportional to K
+  // The NT kernel's tiled forms take whole K steps only.  Up to 192 tiles its ring kernel and two transposes are faster (600 tokens,
+  // inside a training step: 2048 x 512 16.5 us in all, 19.6 here; 10048 x 512 50 and 23).  Otherwise K cancels out.
+  if (K % 64 != 0) return ((M + 127) / 128) * ((N + 127) / 128) > 192;
   const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
   return big_tiles < 256 || M * N < 1170 * (M + N);
 }
@@ -214,19 +263,19 @@ bool gemm_tn_acc_preferred(int64_t M, int64_t N, int64_t K) {
 hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, float* colsum, int64_t M, int64_t N,
                        int64_t K, hipStream_t stream) {
   if (!gemm_tn_acc_supported(dtype, A, B, M, N, K)) return hipErrorInvalidValue;
-  const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128, tiles = tiles_m * tiles_n;
+  const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128, tiles = tiles_m * tiles_n, steps = (K + 63) / 64;
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  // Slices of K per tile.  Measured on MI355X: a K step takes 0.93 us on a workgroup that has its CU to itself and
-  // 1.22 us on a pair that shares one; the atomic adds of a slice cost 0.67 us per MiB of fp32 tile.  Two
-  // workgroups per CU are resident; a slice keeps at least 8 steps.
+  // Slices of K per tile.  Measured on MI355X (us, one / two / four / eight slices): 4096 x 1024, K = 8192 95 / 85 / 102 / 139;
+  // 3072 x 1024 104 / 76 / 95 / 121; 1024 x 1024 87 / 49 / 39 / 48, K = 2048 30 / 20 / 22 / 34; 768 x 768, K = 2048 30 / 19 / 16 / 24;
+  // 2048 x 2048, K = 4096 55 / 58 / 80 / 125; 512 x 512, K = 640 12 / 11 / 10.  Per workgroup 11.6 us and 0.6 to 0.8 us a K step,
+  // by how many of them share the chip; the atomic adds of a slice cost 0.73 us per MiB of fp32 tile.
   int best = 1;
   double best_t = -1.0;
   for (int s = 1; s <= 16; s *= 2) {
-    if (s > 1 && (K % (64 * s) != 0 || K / (64 * s) < 8 || tiles * s > 512)) break;
-    const int64_t wgs = tiles * s, rounds = (wgs + 511) / 512;
-    const double steps = (double)(K / (64 * s)) + 4.0;
-    double t = (double)rounds * steps * (wgs <= 256 ? 0.93 : 1.22);
-    if (s > 1) t += (double)M * (double)N * 4.0 * s / 1048576.0 * 0.67;
+    const int64_t share = (steps + s - 1) / s, wgs = tiles * s;
+    if (s > 1 && (share < 2 || share * (s - 1) >= steps || wgs > 512)) break;
+    double t = (double)((wgs + 511) / 512) * (11.6 + (double)share * (wgs <= 128 ? 0.6 : wgs <= 256 ? 0.65 : 0.8));
+    if (s > 1) t += (double)M * (double)N * 4.0 * s / 1048576.0 * 0.73;
     if (best_t < 0 || t < best_t) {
       best_t = t;
       best = s;

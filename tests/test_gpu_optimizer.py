@@ -50,5 +50,30 @@ def test_the_next_microbatch_runs_on_the_updated_weights(shape):
             got = read_layer(m, 0, l)
             for k, ref in G["layers"][l].items():
                 assert rel_err(got[k], ref) < tol, (l, k)
+        got = read_emb(m, 0)
+        for k in ("lnf_g", "lnf_b"):
+            assert rel_err(got[k], G[k]) < tol, k
+    finally:
+        m.close()
+
+
+def test_tokens_past_the_last_are_zeros_whatever_lds_held():
+    """The weight-gradient kernel takes tokens 64 at a time; with 48 tokens the rest of its only step must not come from what an
+    earlier kernel left in LDS (here NaN, left by the same kernel).  Such token counts reach it above 192 tiles of 128x128: the
+    head's gradient, 8200 x 368."""
+    pf, dev = _mods()
+    bad = torch.full((1024, 2048), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sink = torch.zeros(2048, 2048, device="cuda")
+    pf.pf_op_gemm_tn(pf.PF_DTYPE_BF16, bad.data_ptr(), bad.data_ptr(), sink.data_ptr(), 2048, 2048, 1024)
+    shape = synth.ModelShape(1, 368, 46, 1480, 24, 2, 8200, True, "bf16")
+    params = synth.make_model_params(shape, seed=7, std=0.08)
+    m = dev.DeviceModel(shape, params, training=True, adam=pf.pf_adam(1e-3, 0.9, 0.999, 1e-8, 2))
+    try:
+        ids = synth.make_token_ids(shape, seed=8)
+        m.set_io(dev.to_device(ids[None, None].astype(np.int32)), 1, None, 0)
+        m.ctx.pf_fill_chunk(m.chunk(0, len(m.chain)), m.chain)      # one of two microbatches: gradients stay
+        m.ctx.pf_ctx_sync()
+        _, G = ot.model_loss_and_grads(ids, ot.cast_params(params), shape.n_heads, shape.causal, shape.eps)
+        assert rel_err(read_emb(m, 0)["tok_emb"], G["tok_emb"]) < 2e-2
     finally:
         m.close()
