@@ -337,6 +337,202 @@ __global__ __launch_bounds__(64 * NW, (DH == 64 ? 16 : 8) / NW) void attn_fwd_bf
 }
 
 // ------------------------------------------------------------------------------------------------
+// Few queries in all: 32 of one (batch, head) per workgroup, the keys shared by its four waves (wave w: tiles of 64 w, w + 4,
+// ...), each with LDS buffers of its own and no barrier until their (maximum, sum, O) meet.  Products, operand layouts and
+// swizzles are those of the kernel above, whose 256 or 128 queries per workgroup leave most CUs idle here and put all key
+// tiles of a query in one chain.  Bound by latencies (launch, Q and K, V, meeting), not by any unit: one sequence of 128, 12
+// heads of 64 6.7 -> 4.7 us, one prompt of 333, 16 heads of 128 12.5 -> 9.4, one of 8192, 4 heads of 64 145 -> 91.
+// Workgroups past the units, if the launch has any, read ahead (read_ahead).
+template <int DH>
+__global__ __launch_bounds__(256) void attn_fwd_small_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
+                                                             float* __restrict__ lse, int32_t S, int32_t h, int32_t causal,
+                                                             float scale_log2e, int32_t nq, int32_t n_units, ReadAhead ahead) {
+  constexpr int CPR = DH / 8, KS = DH / 16, DT = DH / 32, ROWB = DH * 2, TILE = 64 * ROWB, NI = TILE / 1024, RPI = 1024 / ROWB;
+  constexpr int NW = 4, LD = DH + 4;
+  static_assert(32 * LD * 4 <= 2 * TILE, "O of a wave fits its buffers");
+  extern __shared__ __align__(16) char dyn_smem[];   // per wave: K tile | V tile, later O
+  __shared__ float sM[NW][32], sL[NW][32];
+  if ((int32_t)blockIdx.x >= n_units) {
+    read_ahead(ahead, n_units);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, g = lane >> 5;
+  const int d = h * DH;
+  const int64_t rs = 3 * (int64_t)d;
+  const uint32_t rs32 = (uint32_t)rs;
+  const int u = (int)xcd_contiguous(blockIdx.x, n_units);   // the query blocks of a head on one XCD
+  const int b = u / (nq * h), hd = (u / nq) % h, pos = u % nq;
+  const int q_blk = (causal ? nq - 1 - pos : pos) * 32;
+  const bf16_t* base = qkv + (int64_t)b * S * rs + hd * DH;
+  const int q_row = q_blk + lr;
+  int n_tiles = (S + 63) / 64;
+  if (causal) {
+    const int last_q = q_blk + 31 < S - 1 ? q_blk + 31 : S - 1;
+    if (last_q / 64 + 1 < n_tiles) n_tiles = last_q / 64 + 1;
+  }
+  auto swz_k = [](int r) { return CPR == 8 ? ((r >> 1) & 7) : (r & 15); };
+  auto swz_v = [](int r) { return CPR == 8 ? (((r >> 1) & 1) << 1) : ((r & 3) << 1); };
+  char* const mine = dyn_smem + wave * 2 * TILE;
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)dyn_smem) + (uint32_t)(wave * 2 * TILE);
+  auto stage = [&](bool is_v, int k0) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = i * RPI + lane / CPR;
+      int row = k0 + r;
+      row = row < S ? row : S - 1;
+      const int col = is_v ? 2 * d + (((lane % CPR) ^ swz_v(r)) << 3) : d + (((lane % CPR) ^ swz_k(r)) << 3);
+      lds_direct_load_1k(__builtin_amdgcn_readfirstlane(lds_base + (uint32_t)((is_v ? TILE : 0) + i * 1024)),
+                         base + (uint64_t)(uint32_t)row * rs32 + col);
+    }
+  };
+  bf16x8 fq[KS];
+  {
+    const bf16_t* qp = base + (uint64_t)(uint32_t)(q_row < S ? q_row : S - 1) * rs32 + g * 8;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) fq[kk] = as_bf16x8(*(const uint4*)(qp + kk * 16));
+  }
+  if (wave < n_tiles) {
+    stage(false, wave * 64);
+    stage(true, wave * 64);
+  }
+  int v_off[DT];
+  {
+    const int pl = lane & 15, mb = (lane >> 4) & 1, row = 4 * g + (pl >> 2);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const int c = dt * 4 + mb * 2 + ((pl & 3) >> 1);
+      v_off[dt] = TILE + row * ROWB + ((c ^ swz_v(row)) << 4) + 8 * (pl & 1);
+    }
+  }
+  auto halves = [](float x, float& lo, float& hi) {   // as above
+    const unsigned w = __builtin_bit_cast(unsigned, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    unsigned a = r[0], c = r[1];
+    asm volatile("" : "+v"(a), "+v"(c));
+    lo = __builtin_bit_cast(float, a);
+    hi = __builtin_bit_cast(float, c);
+  };
+  f32x16 accO[DT];
+#pragma unroll
+  for (int i = 0; i < DT; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) accO[i][r] = 0.f;
+  float m = -INFINITY, l = 0.f;   // of the query; l: this lane's share
+  lds_char_ptr sVb = (lds_char_ptr)(lds_void_ptr)dyn_smem + wave * 2 * TILE;
+  for (int kt = wave; kt < n_tiles; kt += NW) {
+    const int k0 = kt * 64;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's tile
+    f32x16 accS[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) accS[ks][r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const int r = ks * 32 + lr, c = kk * 2 + g;
+        const uint4 fk = *(const uint4*)(mine + r * ROWB + ((c ^ swz_k(r)) << 4));
+        accS[ks] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fk), fq[kk], accS[ks], 0, 0, 0);
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // K is in registers: the next tile may come
+    if (kt + NW < n_tiles) stage(false, k0 + NW * 64);
+    if (k0 + 63 >= S || (causal && k0 + 63 > q_blk)) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + ks * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+          if (key >= S || (causal && key > q_row)) accS[ks][r] = -INFINITY;
+        }
+    }
+    float mx = fmaxf(accS[0][0], accS[1][0]);
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(fmaxf(mx, accS[0][r]), accS[1][r]);
+    float mlo, mhi;
+    halves(mx, mlo, mhi);
+    const float m_new = fmaxf(m, fmaxf(mlo, mhi) * scale_log2e);
+    const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - m_new);   // m = -inf: 0
+    const float neg_m = m_new == -INFINITY ? 0.f : -m_new;
+    m = m_new;
+    l *= alpha;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) accO[i][r] *= alpha;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        accS[ks][r] = __builtin_amdgcn_exp2f(fmaf(accS[ks][r], scale_log2e, neg_m));
+        l += accS[ks][r];
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      bf16x8 fp;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) fp[t] = (__bf16)accS[i >> 1][8 * (i & 1) + t];
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        lds_char_ptr vp = sVb + v_off[dt] + 16 * i * ROWB;
+        const v4s r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)vp);
+        const v4s r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(vp + 8 * ROWB));
+        v8s fv;
+        fv[0] = r0[0]; fv[1] = r0[1]; fv[2] = r0[2]; fv[3] = r0[3];
+        fv[4] = r1[0]; fv[5] = r1[1]; fv[6] = r1[2]; fv[7] = r1[3];
+        accO[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fv), fp, accO[dt], 0, 0, 0);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (kt + NW < n_tiles) stage(true, k0 + NW * 64);
+  }
+  {
+    float llo, lhi;
+    halves(l, llo, lhi);
+    l = llo + lhi;
+  }
+  if (g == 0) {
+    sM[wave][lr] = m;
+    sL[wave][lr] = l;
+  }
+  float* sO = (float*)mine;   // this wave's reads of its buffers are complete
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int rg = 0; rg < 4; ++rg)
+      *(f32x4*)(sO + lr * LD + dt * 32 + rg * 8 + g * 4) =
+          f32x4{accO[dt][rg * 4], accO[dt][rg * 4 + 1], accO[dt][rg * 4 + 2], accO[dt][rg * 4 + 3]};
+  __syncthreads();
+#pragma unroll
+  for (int e = tid; e < 32 * CPR; e += 256) {
+    const int q = e / CPR, c = e % CPR * 8;
+    if (q_blk + q >= S) continue;
+    float mq = sM[0][q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mq = fmaxf(mq, sM[w][q]);
+    float lq = 0.f, o[8] = {};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = mq == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(sM[w][q] - mq);   // 0 for a wave that saw no key
+      const float* po = (const float*)(dyn_smem + w * 2 * TILE) + q * LD + c;
+      const f32x4 a0 = *(const f32x4*)po, a1 = *(const f32x4*)(po + 4);
+      lq += f * sL[w][q];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        o[j] += f * a0[j];
+        o[4 + j] += f * a1[j];
+      }
+    }
+    const float inv = lq > 0.f ? 1.f / lq : 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] *= inv;
+    store8(out + ((int64_t)b * S + q_blk + q) * d + hd * DH + c, o);
+    if (lse && c == 0) lse[((int64_t)b * h + hd) * S + q_blk + q] = mq * LN2 + __logf(lq);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 template <typename T, int DH>
 __global__ __launch_bounds__(64) void attn_fwd_generic_kernel(const T* __restrict__ qkv, T* __restrict__ out,
                                                               float* __restrict__ lse, int32_t S, int32_t h,
@@ -572,10 +768,27 @@ bool f32_by_tiles(int64_t B, int64_t S, int64_t h, int32_t dh) {
   return tiles <= chains;
 }
 
+// bf16, d_head 64 / 128: whether 32 queries per workgroup are faster than 256 / 128.  Only where those leave CUs with one
+// workgroup or none; there a workgroup's own chain over the key tiles is the time, against a start, a share per workgroup and
+// the tiles of 32 queries by 64 keys of all workgroups (two resident per CU with d_head 64, one with 128).  Fitted to
+// B x S x heads (us, 256 or 128 queries / 32; c: causal): d_head 64 1 x 128 x 12 6.7 / 4.7, 8 x 128 x 12 7.1 / 5.9, 16 x 128 x 12
+// 7.7 / 8.4, 7 x 237 x 12 11.1 / 10.2, 3 x 200 x 8 c 9.7 / 5.3, 2 x 512 x 12 14.8 / 9.0, 4 x 512 x 12 15.6 / 12.9, 1 x 1024 x 16 c
+// 23.4 / 12.9, 2 x 1024 x 16 25.3 / 23.6, 1 x 8192 x 4 c 145 / 91; d_head 128 1 x 333 x 16 c 12.5 / 9.4, 2 x 333 x 16 14.2 / 17.1,
+// 4 x 333 x 16 c 13.6 / 21.3, 1 x 700 x 24 21.5 / 31.8, 1 x 1024 x 16 c 26.6 / 20.8, 1 x 2048 x 8 c 45.5 / 29.5, x 16 47.9 / 55.6.
+bool bf16_by_32(int64_t B, int64_t S, int64_t h, int32_t dh, int32_t causal) {
+  if (dh != 64 && dh != 128) return false;
+  const int64_t heads = B * h, qb = dh == 64 ? 256 : 128;
+  if (heads * ((S + qb - 1) / qb) > 256) return false;
+  const double tiles = (double)((S + 63) / 64), units = (double)(heads * ((S + 31) / 32));
+  const double work = units * (causal ? (tiles + 1) / 2 : tiles);
+  if (dh == 64) return 4.0 + 0.0035 * units + 0.001 * work < 4.3 + 1.27 * tiles;
+  return 6.5 + 0.011 * units + 0.0021 * work < 4.5 + 1.32 * tiles;
+}
+
 }  // namespace
 
 hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, int32_t B, int32_t S, int32_t h,
-                         int32_t dh, int32_t causal, hipStream_t stream) {
+                         int32_t dh, int32_t causal, hipStream_t stream, const ReadAhead* ahead) {
   if (B <= 0 || S <= 0 || h <= 0 || B > 65535 || h > 65535) return hipErrorInvalidValue;
   if (dtype == PF_DTYPE_BF16_ && (dh == 64 || dh == 128)) {
     // d_head 64: eight waves (256 queries) per workgroup share a K/V tile, which halves the copies per wave (-7 % on
@@ -586,6 +799,27 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
     if (n_units > 0x7fffffff) return hipErrorInvalidValue;
     const float sl = LOG2E / sqrtf((float)dh);
     const dim3 block((unsigned)(2 * qb));
+    if (bf16_by_32(B, S, h, dh, causal)) {
+      const int64_t nq32 = (S + 31) / 32, units = nq32 * h * B;
+      ReadAhead rest = ahead ? *ahead : ReadAhead{};
+      const dim3 grid((unsigned)launch_with_ahead(units, &rest)), blk(256);
+      static bool attr[2] = {false, false};
+#define PF_SMALL(D, I)                                                                                                       \
+  do {                                                                                                                       \
+    constexpr int lds = 4 * 2 * 64 * D * 2;                                                                                  \
+    if (!attr[I]) {                                                                                                          \
+      hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_small_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
+      if (e != hipSuccess) return e;                                                                                         \
+      attr[I] = true;                                                                                                        \
+    }                                                                                                                        \
+    hipLaunchKernelGGL(attn_fwd_small_kernel<D>, grid, blk, lds, stream, (const bf16_t*)qkv, (bf16_t*)out, lse, S, h, causal, sl, \
+                       (int32_t)nq32, (int32_t)units, rest);                                                 \
+  } while (0)
+      if (dh == 64) PF_SMALL(64, 0);
+      else PF_SMALL(128, 1);
+#undef PF_SMALL
+      return hipGetLastError();
+    }
     // The persistent form pays for causal d_head 128 (MI355X, same box: 116 -> 89 us on 64 heads of 2048 tokens,
     // 140 -> 122 us on 256 heads of 1024): units of unequal length even out over a workgroup's rounds and the next
     // unit's first loads hide behind the current one.  With equal units (not causal) the hardware's own dispatch
@@ -630,4 +864,9 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
 // For tests: whether fp32 attention of this size runs on the tiled kernel.
 extern "C" int32_t pf_attention_f32_tiles(int64_t B, int64_t S, int64_t h, int32_t dh) {
   return pf::f32_by_tiles(B, S, h, dh) ? 1 : 0;
+}
+
+// For tests: whether bf16 attention of this size runs with 32 queries per workgroup.
+extern "C" int32_t pf_attention_bf16_by_32(int64_t B, int64_t S, int64_t h, int32_t dh, int32_t causal) {
+  return pf::bf16_by_32(B, S, h, dh, causal) ? 1 : 0;
 }

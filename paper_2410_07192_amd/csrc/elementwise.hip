@@ -8,12 +8,20 @@
 namespace pf {
 namespace {
 
-template <typename T, int ITER>
+template <typename T, int ITER, bool AHEAD>
 __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict__ x, const T* __restrict__ g,
                                                             const T* __restrict__ b, T* __restrict__ y,
                                                             float* __restrict__ mean_out,
                                                             float* __restrict__ rstd_out, int64_t rows, int32_t d,
-                                                            float eps, const uint4* __restrict__ warm, int64_t warm_n) {
+                                                            float eps, const uint4* __restrict__ warm, int64_t warm_n,
+                                                            ReadAhead ahead) {
+  if constexpr (AHEAD) {
+    const int32_t used = (int32_t)((rows + 3) / 4);
+    if ((int32_t)blockIdx.x >= used) {
+      read_ahead(ahead, used);
+      return;
+    }
+  }
   // Optional side job: read warm_n 16-byte pieces (the weights of the GEMMs that follow) and drop them, so that
   // they sit in the memory-side cache when a GEMM's first round of tiles asks for them all at once.  A layer's
   // weights were last used a whole pass over the model earlier and are long evicted; with cold weights the
@@ -89,18 +97,26 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const T* __restrict_
 
 template <typename T>
 hipError_t launch_ln(const void* x, const void* g, const void* b, void* y, float* mo, float* ro, int64_t rows,
-                     int32_t d, float eps, const uint4* warm, int64_t warm_n, hipStream_t st) {
-  const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+                     int32_t d, float eps, const uint4* warm, int64_t warm_n, ReadAhead ahead, hipStream_t st) {
+  const dim3 grid((unsigned)launch_with_ahead((rows + 3) / 4, &ahead)), block(256);
   const int iters = (d + 511) / 512;
-#define PF_LN(I)                                                                                             \
-  hipLaunchKernelGGL((layernorm_fwd_kernel<T, I>), grid, block, 0, st, (const T*)x, (const T*)g, (const T*)b, \
-                     (T*)y, mo, ro, rows, d, eps, warm, warm_n)
-  if (iters <= 1) PF_LN(1);
-  else if (iters <= 2) PF_LN(2);
-  else if (iters <= 4) PF_LN(4);
-  else if (iters <= 8) PF_LN(8);
-  else if (iters <= 16) PF_LN(16);
-  else return hipErrorInvalidValue;
+#define PF_LN(I, AH)                                                                                              \
+  hipLaunchKernelGGL((layernorm_fwd_kernel<T, I, AH>), grid, block, 0, st, (const T*)x, (const T*)g, (const T*)b, \
+                     (T*)y, mo, ro, rows, d, eps, warm, warm_n, ahead)
+  if (iters > 16) return hipErrorInvalidValue;
+  if (ahead.workgroups > 0) {
+    if (iters <= 1) PF_LN(1, true);
+    else if (iters <= 2) PF_LN(2, true);
+    else if (iters <= 4) PF_LN(4, true);
+    else if (iters <= 8) PF_LN(8, true);
+    else PF_LN(16, true);
+  } else {
+    if (iters <= 1) PF_LN(1, false);
+    else if (iters <= 2) PF_LN(2, false);
+    else if (iters <= 4) PF_LN(4, false);
+    else if (iters <= 8) PF_LN(8, false);
+    else PF_LN(16, false);
+  }
 #undef PF_LN
   return hipGetLastError();
 }
@@ -133,7 +149,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t* __restric
 
 hipError_t layernorm_fwd(int32_t dtype, const void* x, const void* g, const void* b, void* y, float* mean_out,
                          float* rstd_out, int64_t rows, int32_t d, float eps, hipStream_t stream, const void* warm,
-                         int64_t warm_bytes) {
+                         int64_t warm_bytes, const ReadAhead* ahead) {
   if (rows <= 0 || d <= 0 || d % 8 != 0 || d > 8192) return hipErrorInvalidValue;
   // whole 16-byte pieces inside [warm, warm + warm_bytes)
   const uintptr_t w0 = ((uintptr_t)warm + 15) & ~(uintptr_t)15;
@@ -145,8 +161,8 @@ hipError_t layernorm_fwd(int32_t dtype, const void* x, const void* g, const void
   // 1.004, 1.013, 1.004.
   const int64_t warm_n = (warm && rows >= 1024 && warm_bytes > skip) ? (warm_bytes - skip) / 16 : 0;
   if (dtype == PF_DTYPE_BF16_)
-    return launch_ln<bf16_t>(x, g, b, y, mean_out, rstd_out, rows, d, eps, (const uint4*)w0, warm_n, stream);
-  return launch_ln<float>(x, g, b, y, mean_out, rstd_out, rows, d, eps, (const uint4*)w0, warm_n, stream);
+    return launch_ln<bf16_t>(x, g, b, y, mean_out, rstd_out, rows, d, eps, (const uint4*)w0, warm_n, ahead ? *ahead : ReadAhead{}, stream);
+  return launch_ln<float>(x, g, b, y, mean_out, rstd_out, rows, d, eps, (const uint4*)w0, warm_n, ahead ? *ahead : ReadAhead{}, stream);
 }
 
 hipError_t embed_fwd(int32_t dtype, const int32_t* ids, const void* tok, const void* pos, void* x, int64_t tokens,

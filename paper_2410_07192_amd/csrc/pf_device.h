@@ -214,4 +214,25 @@ __device__ __forceinline__ void lds_buffer_load_1k(uint32_t dst, lds_buffer_t bu
                : "memory");
 }
 
+// What a workgroup past the `used` ones of a launch does (ahead.workgroups of them, from the next multiple of 8 on)
+template <class R>
+__device__ __forceinline__ void read_ahead(const R& ahead, int32_t used) {
+  const int32_t j = (int32_t)blockIdx.x - ((used + 7) & ~7);
+  if (j < 0) return;
+  const int64_t per = ahead.workgroups >> 3, threads = blockDim.x;
+  const int64_t x = blockIdx.x & 7, i = j >> 3;
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const uint4* p = (const uint4*)ahead.at[r];
+    const int64_t n = ahead.bytes[r] / 16, hi = n * (x + 1) / 8;
+    for (int64_t k = n * x / 8 + i * threads + threadIdx.x; k < hi; k += 8 * per * threads) {
+      uint4 v[8];   // eight in flight
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[k + u * per * threads < hi ? k + u * per * threads : hi - 1];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) asm volatile("" ::"v"(v[u].x), "v"(v[u].y), "v"(v[u].z), "v"(v[u].w));
+    }
+  }
+}
+
 }  // namespace pf

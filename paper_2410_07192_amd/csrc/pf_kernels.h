@@ -33,19 +33,38 @@ bool gemm_tn_acc_preferred(int64_t M, int64_t N, int64_t K);
 hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, float* colsum, int64_t M, int64_t N,
                        int64_t K, hipStream_t stream);
 
+// ---- reading ahead ---------------------------------------------------------------------------------
+// Ranges of memory that workgroups on otherwise idle CUs read and drop while a small launch runs: the weights of the products
+// that follow, which then find them in the L2 they read through.  The products give every XCD (workgroup id % 8) a contiguous
+// run of W's rows as long as a single group of row tiles covers C, so XCD x reads the x-th eighth of each range.
+struct ReadAhead {
+  const void* at[3] = {nullptr, nullptr, nullptr};   // 16-byte aligned
+  int64_t bytes[3] = {0, 0, 0};
+  int32_t workgroups = 0;                             // set by the launch: those on CUs without one of its own, in eights
+};
+// workgroups of a launch that uses `used`: room for the others is what is left of one per CU (256), if it is worth it
+inline int64_t launch_with_ahead(int64_t used, ReadAhead* a) {
+  const int64_t first = (used + 7) / 8 * 8;
+  a->workgroups = a->bytes[0] > 0 && first <= 192 ? (int32_t)(256 - first) : 0;
+  return a->workgroups > 0 ? 256 : used;
+}
+
 // ---- LayerNorm ------------------------------------------------------------------------------------
 // y = g * (x - mean) / sqrt(var + eps) + b per row of d elements.  mean_out / rstd_out (fp32 [rows])
 // may be null.  warm / warm_bytes (optional): the kernel also reads that range and discards it, which leaves it
 // in the memory-side cache; the callers name the weights of the GEMM that consumes y.
+// ahead (optional): a launch that leaves CUs without a workgroup reads these ranges there instead.
 hipError_t layernorm_fwd(int32_t dtype, const void* x, const void* g, const void* b, void* y,
                          float* mean_out, float* rstd_out, int64_t rows, int32_t d, float eps,
-                         hipStream_t stream, const void* warm = nullptr, int64_t warm_bytes = 0);
+                         hipStream_t stream, const void* warm = nullptr, int64_t warm_bytes = 0,
+                         const ReadAhead* ahead = nullptr);
 
 // ---- attention ------------------------------------------------------------------------------------
 // qkv: [B*S, 3*d] rows = tokens, columns = Q | K | V blocks, head i at columns i*dh.. of each block.
 // out: [B*S, d].  lse (fp32 [B, h, S], may be null) receives log-sum-exp of the scaled scores.
+// ahead (optional): the launch may add workgroups that read these ranges and drop them.
 hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, int32_t B, int32_t S,
-                         int32_t h, int32_t dh, int32_t causal, hipStream_t stream);
+                         int32_t h, int32_t dh, int32_t causal, hipStream_t stream, const ReadAhead* ahead = nullptr);
 
 // ---- embedding ------------------------------------------------------------------------------------
 // x[t] = tok[ids[t]] + pos[t mod S];  ids outside [0, V) produce rows of zeros plus the position.

@@ -323,6 +323,29 @@ static int32_t drain_timing(pf_ctx* c) {
 // ---- one layer, one microbatch -------------------------------------------------------------------
 }  // extern "C"
 
+namespace pf {
+// Weights that idle CUs read during the small launches of a layer (ReadAhead): W_qkv during its LayerNorm; W_o, W_1 and W_2 during
+// attention.  Only where the tokens make one group of row tiles in every product (512: eight tiles of 64), so that an XCD's share
+// is the eighth it reads, and where the three fit the L2s (32 MB in all) beside the activations.  12 layers of d 768 on 128 tokens:
+// 483 us without, 447 with attention reading ahead, 436 with both.
+static ReadAhead read_ahead_of(const Layout& lay, const char* wb, int64_t T, int64_t d, int64_t f, bool attention) {
+  ReadAhead a;
+  const int64_t e = lay.esz, qkv = 3 * d * d * e, bytes[3] = {d * d * e, f * d * e, d * f * e};
+  if (T > 512 || qkv + bytes[0] + bytes[1] + bytes[2] > ((int64_t)28 << 20)) return a;
+  if (!attention) {
+    a.at[0] = wb + lay.off[2];
+    a.bytes[0] = qkv;
+    return a;
+  }
+  const int32_t at[3] = {4, 8, 10};
+  for (int i = 0; i < 3; ++i) {
+    a.at[i] = wb + lay.off[at[i]];
+    a.bytes[i] = bytes[i];
+  }
+  return a;
+}
+}  // namespace pf
+
 int32_t pf::layer_forward(pf_ctx* c, const char* wb, const void* x_in, void* x_out, hipStream_t st) {
   const pf_model_desc& m = c->md;
   const int64_t* o = c->lay.off;
@@ -330,8 +353,9 @@ int32_t pf::layer_forward(pf_ctx* c, const char* wb, const void* x_in, void* x_o
   const int32_t d = m.d_model, f = m.d_ff, dt = m.dtype;
   {
     TimedScope t(c, PF_K_LAYERNORM, st);
+    const pf::ReadAhead ahead = pf::read_ahead_of(c->lay, wb, T, d, f, false);
     PF_HIP(pf::layernorm_fwd(dt, x_in, wb + o[0], wb + o[1], c->ws_ln, nullptr, nullptr, T, d, m.eps, st, wb + o[2],
-                             pf::warm_bytes(o[4] - o[2])));   // also warms W_qkv, b_qkv
+                             pf::warm_bytes(o[4] - o[2]), &ahead));   // also warms W_qkv, b_qkv
   }
   pf::GemmEpilogue e1;
   e1.bias = wb + o[3];
@@ -341,8 +365,9 @@ int32_t pf::layer_forward(pf_ctx* c, const char* wb, const void* x_in, void* x_o
   }
   {
     TimedScope t(c, PF_K_ATTENTION, st);
+    const pf::ReadAhead ahead = pf::read_ahead_of(c->lay, wb, T, d, f, true);
     PF_HIP(pf::attention_fwd(dt, c->ws_qkv, c->ws_attn, nullptr, m.batch, m.seq_len, m.n_heads, d / m.n_heads,
-                             m.causal, st));
+                             m.causal, st, &ahead));
   }
   pf::GemmEpilogue e2;
   e2.bias = wb + o[5];
