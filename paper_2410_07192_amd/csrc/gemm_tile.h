@@ -458,14 +458,15 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
     else if constexpr (READS) x += read;
     return x;
   };
-  auto by_pieces = [&](auto words) {
+  auto by_pieces = [&](auto words, auto keep) {
     constexpr int W = decltype(words)::value;                         // of a piece: 32-bit words,
     constexpr int CE = W * 4 / (int)sizeof(OutT), UP = CE / 4;        // columns, units in LDS
     constexpr int SLOTS = TN * 32 / CE, PIECES = SLOTS / 2;           // pieces of a row; wave instructions of a block
     typedef uint32_t piece_t __attribute__((ext_vector_type(W)));
+    constexpr int AUX = decltype(keep)::value ? 0 : 2;                // 2: non-temporal
     auto load = [&](__amdgpu_buffer_rsrc_t rs, int off) -> piece_t {
-      if constexpr (W == 4) return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-      else return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+      if constexpr (W == 4) return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, AUX);
+      else return __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, AUX);
     };
     auto store = [&](const float* v, __amdgpu_buffer_rsrc_t rs, int off) {
       piece_t w;
@@ -474,8 +475,8 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
         if constexpr (F32) w[j] = __float_as_uint(v[j]);
         else w[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
       }
-      if constexpr (W == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, 0);
-      else __builtin_amdgcn_raw_buffer_store_b64(w, rs, off, 0, 0);
+      if constexpr (W == 4) __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, AUX);
+      else __builtin_amdgcn_raw_buffer_store_b64(w, rs, off, 0, AUX);
     };
     auto widen = [&](piece_t p, float* v) {
 #pragma unroll
@@ -542,12 +543,20 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
   };
   if (N <= (1 << 23)) {   // 32 rows of C below 2^31 bytes
     if (N % (16 / (int)sizeof(OutT)) == 0 && (ptrs & 15) == 0) {
-      by_pieces(std::integral_constant<int, 4>{});
+      // An accumulated C that no cache holds until it is read again (the memory-side cache has 256 MB) goes past them: 32768 x
+      // 8192, K = 2048 (1 GB) 1115 -> 1030 us, 24576 x 8192 (805 MB) 829 -> 774; 8192 x 8192 (268 MB) loses, 292 -> 312.
+      if constexpr ((EPI & E_ACC) != 0) {
+        if (M * N >= (int64_t)96 << 20) {
+          by_pieces(std::integral_constant<int, 4>{}, std::false_type{});
+          return;
+        }
+      }
+      by_pieces(std::integral_constant<int, 4>{}, std::true_type{});
       return;
     }
     if constexpr (!F32) {
       if (N % 4 == 0 && (ptrs & 7) == 0) {
-        by_pieces(std::integral_constant<int, 2>{});
+        by_pieces(std::integral_constant<int, 2>{}, std::true_type{});
         return;
       }
     }
