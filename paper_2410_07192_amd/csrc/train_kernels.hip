@@ -580,13 +580,19 @@ __global__ __launch_bounds__(4 * W) void adam_write_kernel(float* __restrict__ t
       at[k] = in[k] ? e : 0;
     }
   }
+  // (large layers: far more than any cache holds until the next step, so past the caches)
+  auto get = [](const float* q) { return W == 128 ? __builtin_nontemporal_load((const f32x4*)q) : *(const f32x4*)q; };
+  auto put = [](float* q, f32x4 x) {
+    if constexpr (W == 128) __builtin_nontemporal_store(x, (f32x4*)q);
+    else *(f32x4*)q = x;
+  };
   f32x4 gr[4], mi[4], vi[4], th[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    gr[k] = *(const f32x4*)(g + p.src + at[k]);
-    mi[k] = *(const f32x4*)(m + p.src + at[k]);
-    vi[k] = *(const f32x4*)(v + p.src + at[k]);
-    th[k] = *(const f32x4*)(theta + p.src + at[k]);
+    gr[k] = get(g + p.src + at[k]);
+    mi[k] = get(m + p.src + at[k]);
+    vi[k] = get(v + p.src + at[k]);
+    th[k] = get(theta + p.src + at[k]);
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -599,10 +605,10 @@ __global__ __launch_bounds__(4 * W) void adam_write_kernel(float* __restrict__ t
     }
     float o[4] = {th[k][0], th[k][1], th[k][2], th[k][3]};
     if (in[k]) {
-      *(f32x4*)(m + p.src + at[k]) = mi[k];
-      *(f32x4*)(v + p.src + at[k]) = vi[k];
-      *(f32x4*)(theta + p.src + at[k]) = th[k];
-      *(f32x4*)(g + p.src + at[k]) = f32x4{0.f, 0.f, 0.f, 0.f};
+      put(m + p.src + at[k], mi[k]);
+      put(v + p.src + at[k], vi[k]);
+      put(theta + p.src + at[k], th[k]);
+      put(g + p.src + at[k], f32x4{0.f, 0.f, 0.f, 0.f});
       store4((T*)p.dst + at[k], o);
     }
     if (matrix) {
@@ -817,7 +823,7 @@ hipError_t embed_bwd(int32_t dtype, const void* dx, const int32_t* ids, float* d
 hipError_t adam_write(int32_t dtype, float* theta, float* m, float* v, float* g, AdamPieces ps, float lr, float b1, float b2,
                       float eps, int64_t step, int32_t accum, hipStream_t st, bool dry) {
   if (ps.n < 1 || ps.n > AdamPieces::MAX || step < 1 || accum < 1) return hipErrorInvalidValue;
-  // Tiles of 128 columns read and write 512 bytes of a row at a time (805 M parameters 5860 -> 5430 us); small layers need the
+  // Tiles of 128 columns read and write 512 bytes of a row at a time (805 M parameters 5860 -> 5430 us, 5140 past the caches); small layers need the
   // workgroups (3.1 M parameters: 23.4 us on 64 columns, 25.1 on 128).
   int64_t total = 0, blocks = 0;
   for (int i = 0; i < ps.n; ++i) total += ps.p[i].R * ps.p[i].C;
