@@ -799,7 +799,7 @@ hipError_t attention_fwd(int32_t dtype, const void* qkv, void* out, float* lse, 
     if (n_units > 0x7fffffff) return hipErrorInvalidValue;
     const float sl = LOG2E / sqrtf((float)dh);
     const dim3 block((unsigned)(2 * qb));
-    if (bf16_by_32(B, S, h, dh, causal)) {
+    if (((uintptr_t)out & 15) == 0 && bf16_by_32(B, S, h, dh, causal)) {   // 16-byte stores
       const int64_t nq32 = (S + 31) / 32, units = nq32 * h * B;
       ReadAhead rest = ahead ? *ahead : ReadAhead{};
       const dim3 grid((unsigned)launch_with_ahead(units, &rest)), blk(256);

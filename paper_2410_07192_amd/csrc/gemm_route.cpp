@@ -131,6 +131,7 @@ Route tiled_route(const Product& p) {
 
 bool tiled(const Product& p) {
   if (p.K % 64 != 0 || !p.aligned || p.scaled) return false;
+  if (p.K >= 1 << 22) return false;   // 256 rows of an operand are one raw buffer, below 2^31 bytes
   if (p.out_f32) return p.epi == 0 || p.epi == E_ACC;
   return p.epi == 0 || p.epi == E_BIAS || p.epi == (E_BIAS | E_GELU) || p.epi == (E_BIAS | E_RESID) ||
          p.epi == (E_BIAS | E_GELU | E_PRE) || p.epi == E_DACT;
