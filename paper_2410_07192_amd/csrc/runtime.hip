@@ -325,13 +325,14 @@ static int32_t drain_timing(pf_ctx* c) {
 
 namespace pf {
 // Weights that idle CUs read during the small launches of a layer (ReadAhead): W_qkv during its LayerNorm; W_o, W_1 and W_2 during
-// attention.  Only where the tokens make one group of row tiles in every product (512: eight tiles of 64), so that an XCD's share
-// is the eighth it reads, and where the three fit the L2s (32 MB in all) beside the activations.  12 layers of d 768 on 128 tokens:
-// 483 us without, 447 with attention reading ahead, 436 with both.
+// attention.  Only where the tokens make one group of row tiles in every product (256: eight tiles of 32), so that an XCD's share
+// is the eighth it reads, and where they fit the L2s (32 MB in all) beside the activations.  12 layers of d 768 on 128 tokens:
+// 483 us without, 447 with attention reading ahead, 436 with both; on 16 tokens 366 and 361.  Nothing is gained on 500 tokens
+// (6 layers of d 768 299 and 299), and 4 layers of d 1024 on 512 lose (216 and 220).
 static ReadAhead read_ahead_of(const Layout& lay, const char* wb, int64_t T, int64_t d, int64_t f, bool attention) {
   ReadAhead a;
   const int64_t e = lay.esz, qkv = 3 * d * d * e, bytes[3] = {d * d * e, f * d * e, d * f * e};
-  if (T > 512 || qkv + bytes[0] + bytes[1] + bytes[2] > ((int64_t)28 << 20)) return a;
+  if (T > 256 || qkv + bytes[0] + bytes[1] + bytes[2] > ((int64_t)28 << 20)) return a;
   if (!attention) {
     a.at[0] = wb + lay.off[2];
     a.bytes[0] = qkv;
