@@ -7,7 +7,7 @@
 //    swizzle that keeps the later MFMA operand reads free of bank conflicts is applied on the global
 //    side (lane -> which chunk of the row it fetches).  Rows beyond M / N are clamped to the last
 //    valid row (their products are never stored).
-//  * Two to four LDS stages: the loads of step k+NS go into the stage that a barrier of step k has freed.  They are
+//  * Two to six LDS stages: the loads of step k+NS go into the stage that a barrier of step k has freed.  They are
 //    issued one at a time between MFMAs (a burst blocks every wave at the address unit) and are inline assembly
 //    so that the compiler does not serialise every later LDS read behind them; vmcnt is waited by hand.
 //  * Operand fragments are double buffered in registers: by slices of 32 k in the 256-wide tiles, by whole K steps in
@@ -16,7 +16,7 @@
 //    ends up with 4 consecutive output columns of one output row: bias / GELU of whole bf16 tiles are
 //    applied in registers; these then pass through LDS and leave as 16-byte row-contiguous stores (the
 //    residual is added on the way out).  Everything else passes through LDS in fp32.
-//  * Tile shapes 256x256, 256x192, 256x128, 128x128; accumulating fp32 launches may split K over 128x128 tiles.
+//  * Tile shapes 256x256, 256x192, 256x128, 128x128, 128x64; accumulating fp32 launches may split K over 128x128 tiles.
 //  * Workgroup ids are remapped so that each of the 8 XCDs (ids are dealt round-robin to them) works
 //    on a contiguous range of tiles and its L2 sees each operand panel once.
 // Launches too small to fill the chip, and most of fp32: gemm_ring.hip.

@@ -61,7 +61,7 @@ double fma_estimate(const Product& p) {
 // Tiled kernels, and the ring kernel where it is faster.
 // Tile shapes: 256x256 (four waves, wave tile 128x128), 256x192 (8 waves as 4x2, wave tile 64x96) and 256x128 (four waves, wave
 // tile 128x64), one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
-// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two.
+// A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two; 128x64 tiles below.
 // A launch takes ceil(workgroups / resident workgroups) rounds of start + step x (K steps of 64), in microseconds, measured
 // on MI355X (844 products, every shape timed); the shape with the least estimate runs.  That choice is 0.3 % off the
 // fastest shape on average and 13 % at most (1024 x 33024, K = 2048: 256x192 tiles 159 us, 256x256 141).  E.g. N = 768 or 2304
@@ -120,6 +120,18 @@ Route tiled_route(const Product& p) {
         best_time = t;
         best = Route{alone ? TILE_128x128_DEEP : sh.kernel, splits};
       }
+    }
+  }
+  // 128x64 tiles, six LDS stages, one workgroup per CU: where 128x128 ones leave half of the CUs idle (us, 128x128 deep / 128x64:
+  // 1659 x 768, K = 3072 22.6 / 18.6; 1659 x 1024, K = 4096 26.2 / 21.9; 600 x 2048, K = 2048 15.4 / 12.1; 1000 x 2048, K = 8192 63.8 /
+  // 50.7, ring 53.3; 333 x 6144, K = 2048 16.4 / 23.9; with a second result 1024 x 2048, K = 1024 13.3 / 15.3).
+  if (timed && p.K >= 1024) {
+    const int64_t wgs = ceil_div(p.M, 128) * ceil_div(p.N, 64);
+    const double step = 0.28 + 0.06 * std::min(1.0, std::max(0.0, (double)(wgs - 208) / 48));
+    const double t = (double)ceil_div(wgs, 256) * (4.4 + (p.epi & E_PRE ? 3.0 : 0.0) + step * (double)(p.K / 64));
+    if (t < best_time) {
+      best_time = t;
+      best = Route{TILE_128x64, 1};
     }
   }
   // The ring kernel takes what leaves the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192

@@ -17,6 +17,7 @@ enum Kernel : int32_t {
   TILE_256x256, TILE_256x192, TILE_128x128,       // gemm_tile.h; the last with two LDS stages,
   TILE_128x128_DEEP,                              // here with four
   TILE_256x128,                                   // with three
+  TILE_128x64,                                    // with six
 };
 
 struct Product {

@@ -225,7 +225,7 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
   // tile, the residual being added on the way out from equally coalesced loads.  The two training forms use the same
   // route: the pre-activation is a second tile staged and stored before the activated one, and the saved tensor whose
   // GELU' multiplies the result comes in the other way round, coalesced loads -> LDS -> the accumulator layout.
-  // Not the residual of the kernels with three or four stages: the route by fp32 rows below rounds once and is no slower
+  // Not the residual of the kernels with three stages or more: the route by fp32 rows below rounds once and is no slower
   // (1659 x 768, K = 768 10.0 -> 9.8 us, 2048 x 2048, K = 2048 22 -> 21).
   constexpr bool STAGED = std::is_same<OutT, bf16_t>::value && !(EPI & E_ACC) && !((EPI & E_RESID) && NS > 2);
   if constexpr (STAGED) {
@@ -733,6 +733,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_nt_kernel(
 //     2048 x 2048, K = 2048 29 -> 20.5, 1659 x 2304, K = 768 13.5 -> 10.7
 //   128x128, two stages, two workgroups per CU (16x16x32 MFMAs): 8192 x 1024, K = 4096 75 -> 59 us, 8192 x 4096, K = 1024 with
 //     GELU' 96 -> 82, 1659 x 3072, K = 768 with GELU 19.2 -> 16.7
+//   128x64 (wave tile 64x32), six stages (32x32x16), half as many products a step on twice the CUs: 1659 x 768, K = 3072 22.6 us on
+//     128x128 tiles, 18.6 here
 //   256x128 (wave tile 128x64), three stages (32x32x16): fewer operand bytes per product, for long K: 8192 x 1024, K = 50304
 //     858 us on 128x128 tiles, 725 here
 // Which MFMA: a full chip runs into the power limit, where 16x16x32 sustains more (2.1 against 1.82 PFLOP/s in a loop of
@@ -1079,7 +1081,7 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 template <typename OutT, int EPI>
 hipError_t launch_fast(const Route& r, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                        const EpiDev& ep, hipStream_t stream) {
-  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false, attr_tall = false;
+  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false, attr_tall = false, attr_slim = false;
   switch (r.kernel) {
     case TILE_256x256:
       return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
@@ -1089,6 +1091,9 @@ hipError_t launch_fast(const Route& r, const void* X, const void* W, void* C, in
     case TILE_256x128:
       return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 4, 2, OutT, EPI, 3, 32>, 256, 128, 256, &attr_tall, X, W, C, M, N, K,
                                 ep, 1, stream, 3);
+    case TILE_128x64:
+      return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 2, 1, OutT, EPI, 6, 32>, 128, 64, 256, &attr_slim, X, W, C, M, N, K,
+                                ep, 1, stream, 6);
     case TILE_128x128_DEEP:
       return launch_tiles<OutT>(gemm_bf16_nt_step_kernel<2, 2, 2, 2, OutT, EPI, 4, 32>, 128, 128, 256, &attr_deep, X, W, C, M, N, K,
                                 ep, r.splits, stream, 4);

@@ -7,7 +7,7 @@ torch = pytest.importorskip("torch")
 
 from test_product_routes import EPI, _product, route   # noqa: E402
 
-TILE_256x128 = 10   # position in the enumeration of gemm_route.h
+TILE_256x128, TILE_128x64 = 10, 11   # positions in the enumeration of gemm_route.h
 
 
 def raw_route(M, N, K, epi):
@@ -20,6 +20,7 @@ def raw_route(M, N, K, epi):
 
 TALL = [(4096, 2048, 4096), (4000, 2040, 2880), (3841, 1928, 3008)]
 TALL_EPI = ("plain", "bias", "gelu", "resid", "pre", "dact")
+SLIM = [(1659, 768, 3072), (600, 2048, 1024), (1000, 1032, 1088), (1500, 776, 1344)]
 # M, N, K, epilogues, kernel: K steps 1 .. 6 with four stages, 1 .. 4 with two
 SHORT = [(1999, 2040, 64 * k, TALL_EPI, "tile 128x128 deep") for k in range(1, 7)]
 SHORT += [(1659, 3072, 64 * k, ("bias", "gelu", "resid"), "tile 128x128") for k in range(1, 5)]
@@ -33,6 +34,17 @@ def test_these_run_on_256x128_tiles(M, N, K):
 @pytest.mark.parametrize("M,N,K,epis,kernel", SHORT)
 def test_these_run_on_128x128_tiles(M, N, K, epis, kernel):
     assert {route("bf16", M, N, K, e) for e in epis} == {(kernel, 1)}
+
+
+@pytest.mark.parametrize("M,N,K", SLIM)
+def test_these_run_on_128x64_tiles(M, N, K):
+    assert {raw_route(M, N, K, e) for e in ("plain", "bias", "gelu", "resid", "dact")} == {TILE_128x64}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", SLIM)
+def test_numbers_of_128x64_tiles(M, N, K):
+    _product("bf16", M, N, K, TALL_EPI)
 
 
 @pytest.mark.gpu
