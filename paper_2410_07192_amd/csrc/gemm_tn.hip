@@ -5,7 +5,7 @@
 // 128x128 tiles, 4 waves (2x2, wave tile 64x64 in 16x16x32 MFMAs), K steps of 64, two LDS stages of 32 KB, two
 // workgroups per CU.  Operand slabs go global -> LDS directly, 4 k-rows x 256 bytes per wave instruction, in the [k][m]
 // order they have in memory; rows past the end of K are past the end of the buffer and arrive as zeros, so K need not be
-// a multiple of anything.  MFMA wants, per lane, eight consecutive k of one m: ds_read_b64_tr_b16 delivers exactly that
+// a multiple of 64 (it comes in eights).  MFMA wants, per lane, eight consecutive k of one m: ds_read_b64_tr_b16 delivers exactly that
 // from a k-major image (a 16-lane group reads a 4 k x 16 m block and every lane receives the four k of its own m), two
 // reads per fragment.  The 16-byte chunks of a k-row are XOR-swizzled by 4 * (k % 4) + 2 * (k / 8 % 2) (on the global
 // side of the copy), so that the eight half rows the two groups of a half-wave read fall on disjoint banks.
@@ -16,6 +16,7 @@
 // Split K: gridDim.y workgroups share a tile, each over a run of whole steps; the fp32 tile goes through LDS and is
 // added to C with fp32 atomics in coalesced order (plain read-add-write when K is not split).  The column sum
 // comes from one more MFMA per A fragment against a fragment of ones, on the waves of the first tile column.
+// WIDE: M or N from 2^23 on, where 64 rows pass the 2^31 bytes of a raw buffer.  64-bit addresses per lane, whole K steps only.
 #include <type_traits>
 
 #include "pf_device.h"
@@ -38,7 +39,7 @@ __device__ __forceinline__ void unrolled(F&& f) {
   }
 }
 
-template <bool COLSUM>
+template <bool COLSUM, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* __restrict__ A,
                                                                   const bf16_t* __restrict__ B, float* __restrict__ C,
                                                                   float* __restrict__ colsum, int64_t M, int64_t N,
@@ -62,6 +63,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
   const int64_t last_a = M - 8 - m0, last_b = N - 8 - n0;
   const int64_t ca = cglob * 8 < last_a ? cglob * 8 : last_a, cb = cglob * 8 < last_b ? cglob * 8 : last_b;
   uint32_t off[8];
+  const bf16_t* const pa = A + ((int64_t)first * 64 + wave * 4 + lg) * M + m0 + ca;   // WIDE: copy 0 of the first step
+  const bf16_t* const pb = B + ((int64_t)first * 64 + wave * 4 + lg) * N + n0 + cb;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int64_t r = (wave + 4 * i) * 4 + lg;
@@ -74,7 +77,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
   int64_t rows_left = K - (int64_t)first * 64;
   int32_t left = nk;
   lds_buffer_t abuf, bbuf;
+  int64_t row = 0;         // WIDE: of the slice, where the step that is copied next begins
   auto next_rows = [&] {   // of the step that is copied next
+    if constexpr (WIDE) {   // a step past the slice is the last one again: nobody uses its fragments
+      if (left < nk && left > 0) row += 64;
+      --left;
+      return;
+    }
     const int32_t rows = left > 0 ? (int32_t)(rows_left < 64 ? rows_left : 64) : 0;
     abuf = lds_buffer(arow, (uint32_t)(rows * (int32_t)M * 2));
     bbuf = lds_buffer(brow, (uint32_t)(rows * (int32_t)N * 2));
@@ -86,7 +95,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_ptr)smem) + (uint32_t)(wave * 1024);
   auto issue = [&](auto ic, auto stc) {
     constexpr int i = decltype(ic)::value, st = decltype(stc)::value;
-    lds_buffer_load_1k(lds_base + (uint32_t)(st * STAGE + (i < 4 ? 0 : BOFF) + (i & 3) * 4096), i < 4 ? abuf : bbuf, off[i], 0);
+    const uint32_t dst = lds_base + (uint32_t)(st * STAGE + (i < 4 ? 0 : BOFF) + (i & 3) * 4096);
+    if constexpr (WIDE) lds_direct_load_1k(__builtin_amdgcn_readfirstlane(dst), (i < 4 ? pa : pb) + (row + (i & 3) * 16) * (i < 4 ? M : N));
+    else lds_buffer_load_1k(dst, i < 4 ? abuf : bbuf, off[i], 0);
   };
 
   // fragment addressing: lane 16 g + i points at k-row 8 g + 4 r + i / 4 of the 32-row substep and at the four columns from
@@ -243,9 +254,12 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tn_acc_kernel(const bf16_t* 
 
 }  // namespace
 
+static bool wide(int64_t M, int64_t N) { return M >= (1 << 23) || N >= (1 << 23); }   // 64 rows in a raw buffer: below 2^31 bytes
+
 bool gemm_tn_acc_supported(int32_t dtype, const void* A, const void* B, int64_t M, int64_t N, int64_t K) {
-  return dtype == PF_DTYPE_BF16_ && M >= 8 && N >= 8 && M % 8 == 0 && N % 8 == 0 && M < (1 << 23) && N < (1 << 23) && K >= 8 &&
-         K % 8 == 0 && K < ((int64_t)1 << 36) && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
+  // (K steps are counted in 32 bits; operands of 2^36 rows would take a terabyte)
+  return dtype == PF_DTYPE_BF16_ && M >= 8 && N >= 8 && M % 8 == 0 && N % 8 == 0 && K >= 8 && K % (wide(M, N) ? 64 : 8) == 0 &&
+         K < ((int64_t)1 << 36) && (((uintptr_t)A | (uintptr_t)B) & 15) == 0;
 }
 
 // The 128x128 tiles of this kernel reach 610 (8192 x 8192, K = 2048) to 810 TFLOP/s; the NT kernel's 256-wide tiles about 900 on
@@ -281,7 +295,7 @@ hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, fl
       best = s;
     }
   }
-  static bool attr[2] = {false, false};
+  static bool attr[4] = {false, false, false, false};
   auto launch = [&](auto kern, bool* attr_set) {
     if (!*attr_set) {
       hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
@@ -292,8 +306,12 @@ hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, fl
                        (const bf16_t*)B, C, colsum, M, N, K, (int32_t)tiles_m, (int32_t)tiles_n);
     return hipGetLastError();
   };
-  if (colsum) return launch(gemm_bf16_tn_acc_kernel<true>, &attr[0]);
-  return launch(gemm_bf16_tn_acc_kernel<false>, &attr[1]);
+  if (wide(M, N)) {
+    if (colsum) return launch(gemm_bf16_tn_acc_kernel<true, true>, &attr[2]);
+    return launch(gemm_bf16_tn_acc_kernel<false, true>, &attr[3]);
+  }
+  if (colsum) return launch(gemm_bf16_tn_acc_kernel<true, false>, &attr[0]);
+  return launch(gemm_bf16_tn_acc_kernel<false, false>, &attr[1]);
 }
 
 }  // namespace pf

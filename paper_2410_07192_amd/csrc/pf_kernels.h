@@ -25,7 +25,7 @@ hipError_t gemm_nt(int32_t dtype, const void* X, const void* W, void* C, int64_t
 
 // C[M,N] (fp32) += A^T B with A [K,M] and B [K,N] row-major bf16 (weight gradient dW = dY^T X from the tensors as
 // they lie in memory); colsum (fp32 [M], may be null): colsum[m] += sum over k of A[k][m].  Needs bf16, M, N and K
-// multiples of 8 and 16-byte aligned operands (gemm_tn_acc_supported); K may be split over workgroups, whose slices meet
+// multiples of 8 (K of 64 where M or N reaches 2^23) and 16-byte aligned operands (gemm_tn_acc_supported); K may be split over workgroups, whose slices meet
 // in C through fp32 atomics.
 bool gemm_tn_acc_supported(int32_t dtype, const void* A, const void* B, int64_t M, int64_t N, int64_t K);
 // whether it beats transposing both operands for the NT kernel (measured rates; large results favour the latter)

@@ -1109,7 +1109,7 @@ int32_t pf_op_gemm_tn(int32_t dtype, const void* A, const void* B, float* C, flo
                       int64_t K, void* stream) {
   if (bad_dtype(dtype) || !A || !B || !C || M <= 0 || N <= 0 || K <= 0)
     return pf::fail(PF_ERR_ARG, "pf_op_gemm_tn: bad argument");
-  if (K % 64 != 0 || !pf::gemm_tn_acc_supported(dtype, A, B, M, N, K))   // (the kernel itself takes K in eights)
+  if (K % 64 != 0 || !pf::gemm_tn_acc_supported(dtype, A, B, M, N, K))   // (the kernel itself takes K in eights, which training uses)
     return pf::fail(PF_ERR_ARG, "pf_op_gemm_tn: needs bf16, M and N multiples of 8, K a multiple of 64, 16-byte aligned operands");
   PF_HIP(pf::gemm_tn_acc(dtype, A, B, C, colsum_acc, M, N, K, (hipStream_t)stream));
   return PF_OK;

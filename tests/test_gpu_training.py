@@ -573,6 +573,31 @@ def test_gemm_tn_kernel(M, N, K, with_colsum):
         assert bool((acc == 0.5).all())
 
 
+@pytest.mark.parametrize("M,N,K", [((1 << 23) + 8, 8, 128), (8, (1 << 23) + 8, 64)])
+def test_gemm_tn_results_of_eight_million_rows_or_columns(M, N, K):
+    """Rows of an operand long enough that 64 of them pass 2^31 bytes: C and the column sums at both ends of the long side and in
+    its middle, against float64.  Each call adds to known values, twice."""
+    pf, dev = _mods()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M % 1000 + N)
+    A = torch.randn(K, M, device="cuda", generator=gen).to(torch.bfloat16)
+    B = torch.randn(K, N, device="cuda", generator=gen).to(torch.bfloat16)
+    C = torch.full((M, N), 0.25, device="cuda")
+    cs = torch.full((M,), 0.5, device="cuda")
+    for _ in range(2):
+        pf.pf_op_gemm_tn(pf.PF_DTYPE_BF16, A.data_ptr(), B.data_ptr(), C.data_ptr(), M, N, K, cs.data_ptr())
+    torch.cuda.synchronize()
+    long = max(M, N)
+    for first in (0, long // 2 - 100, long - 300):
+        a = A[:, first:first + 300].double() if M > N else A.double()
+        b = B[:, first:first + 300].double() if N > M else B.double()
+        got = C[first:first + 300] if M > N else C[:, first:first + 300]
+        scale = float((a.abs().t() @ b.abs()).max())
+        assert float((got.double() - 0.25 - 2 * (a.t() @ b)).abs().max()) <= 5e-5 * scale      # as in test_gemm_tn_kernel
+        s = cs[first:first + 300] if M > N else cs
+        assert float((s.double() - 0.5 - 2 * a.sum(0)).abs().max()) <= 5e-5 * float(a.abs().sum(0).max())
+
+
 def test_gemm_tn_argument_errors():
     pf, dev = _mods()
     t = torch.zeros(1 << 16, dtype=torch.int16, device="cuda")
