@@ -205,7 +205,7 @@ template <typename OutT>
 hipError_t dispatch_bf16(const Route& r, int epi, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                          const EpiDev& ep, hipStream_t stream) {
   if (r.kernel == BF16_GENERIC) return launch_generic<OutT>(X, W, C, M, N, K, ep, stream);
-  if (r.kernel <= RING_128x64) return launch_ring_shape<bf16_t, OutT>(r.kernel, X, W, C, M, N, K, ep, stream);
+  if (is_ring(r.kernel)) return launch_ring_shape<bf16_t, OutT>(r.kernel, X, W, C, M, N, K, ep, stream);
   if constexpr (std::is_same<OutT, float>::value) {
     if (epi == 0) return launch_fast<float, 0>(r, X, W, C, M, N, K, ep, stream);
     if (epi == E_ACC) return launch_fast<float, E_ACC>(r, X, W, C, M, N, K, ep, stream);

@@ -6,9 +6,10 @@
 // divide K between them: wave w takes K steps w, w + WK, ... through a ring of DEPTH LDS stages of its own, so no wave
 // waits for another (no barrier until the sums meet) and WK * DEPTH steps, 64 to 144 KB per workgroup, are in flight at once.
 // A stage goes to registers whole and is refilled before its MFMAs run.  Two waves per SIMD with one stage each (the small
-// tiles; the 32x32 one leaves room for two workgroups per CU) beat one wave with two stages, whose wait, LDS reads, copies
-// and MFMAs follow one another: 128 x 2304, K = 768 6.0 -> 5.3 us, 333 x 2048, K = 2048 on 32x32 tiles 15.8 -> 12.3 us, 600 x 512,
-// K = 2048 8.7 -> 7.6 us, 512 x 1536, K = 600 into fp32 7.6 -> 6.9 us.
+// tiles; the 32x32 one leaves room for two workgroups per CU) beat fewer waves with two stages, whose wait, LDS reads, copies
+// and MFMAs follow one another, as long as a wave has few steps or its MFMAs are short: 128 x 2304, K = 768 6.0 -> 5.3 us, 333 x
+// 2048, K = 2048 on 32x32 tiles 15.8 -> 12.3 us, 600 x 512, K = 2048 8.7 -> 7.6 us, 512 x 1536, K = 600 into fp32 7.6 -> 6.9 us.
+// Where both forms of a tile exist, gemm_route.cpp says which runs.
 // A K step is 128 bytes of every row (64 bf16 or 32 fp32 elements); stages hold eight 16-byte chunks per row,
 // XOR-swizzled on the global side as in the tiled kernel.
 //   bf16: 32x32x16 MFMA.  fp32: 32x32x2 fp32 MFMA, four per pair of chunks: lane half lk supplies element j of chunk
@@ -114,8 +115,9 @@ __global__ __launch_bounds__(64 * WK) void gemm_ring_kernel(const T* __restrict_
   const int sw = (lr >> 1) & 7;
   int slot = 0;
   for (int64_t s = 0; s < mine; ++s) {
-    // the younger stage, if there is one, may stay on its way; the last step has none behind it
-    if (s + DEPTH <= mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * (DEPTH - 1)) : "memory");
+    // the younger stage, if there is one, may stay on its way; the last step has none behind it.  (Written as s + DEPTH <= mine
+    // the compiler makes two copies of the loop's body: 3709 x 320, K = 248 on 128x64 tiles 9.1 -> 9.4 us.)
+    if (s + DEPTH - 1 < mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * (DEPTH - 1)) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const uint4* st = smem + (wave * DEPTH + slot) * STAGE;
     uint4 fx[4][TM], fw[4][TN];
@@ -248,12 +250,13 @@ hipError_t launch_ring_shape(Kernel shape, const void* X, const void* W, void* C
   switch (shape) {
     case RING_32x32: return launch_ring<T, OutT, 1, 1, 8, 1>(X, W, C, M, N, K, ep, stream);
     case RING_32x64: return launch_ring<T, OutT, 1, 2, 8, 1>(X, W, C, M, N, K, ep, stream);
-    case RING_64x64:
-      // Long rows: one wave per SIMD with two stages again (333 x 2048, K = 8192 30.3 us against 31.6, K = 2048 11.9 against 11.4;
-      // fp32 2048 x 512, K = 2048 45 against 63, 4096 x 2048, K = 256 69 against 63).
-      if (K * (int64_t)sizeof(T) > 4096) return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
-      return launch_ring<T, OutT, 2, 2, 8, 1>(X, W, C, M, N, K, ep, stream);
+    case RING_64x64: return launch_ring<T, OutT, 2, 2, 8, 1>(X, W, C, M, N, K, ep, stream);
     case RING_128x64: return launch_ring<T, OutT, 4, 2, 3, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_32x32_DEEP: return launch_ring<T, OutT, 1, 1, 8, 2>(X, W, C, M, N, K, ep, stream);
+    case RING_32x64_DEEP:   // fp32 only
+      if constexpr (std::is_same<T, float>::value) return launch_ring<T, OutT, 1, 2, 6, 2>(X, W, C, M, N, K, ep, stream);
+      return hipErrorInvalidValue;
+    case RING_64x64_DEEP: return launch_ring<T, OutT, 2, 2, 4, 2>(X, W, C, M, N, K, ep, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -20,7 +20,7 @@ struct RingShape { int bm, bn; double fixed, byte, odd; };
 constexpr RingShape ring_shapes[] = {
     {32, 32, 2.6, 0.00098, 0.9}, {32, 64, 3.5, 0.0014, 2.2}, {64, 64, 4.6, 0.0017, 2.9}, {128, 64, 7.9, 0.0032, 9.4}};
 // fp32: start + rounds x (fixed + per_k x K), K rounded up to the elements that all waves of the workgroup take in one step
-// where few waves make that visible.  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
+// where few waves make that visible (64x64: of its four-wave form, ring_form).  Bound by the MFMAs (64 cycles for two K), which small tiles hide best: 2048 x 576,
 // K = 512 25 / 28 / 28 / 33 us, K = 1024 on 2048 x 2048 124 / 127 / 87 / 105 us (32x32, 32x64, 64x64, 128x64).  The 128x64
 // tile wins by up to a tenth where it saves a round and K fits two steps (2048 x 2048, K = 192: 32.3 us, 64x64 35.3).
 struct RingShapeF32 { double start, fixed, per_k; int step; };
@@ -45,6 +45,35 @@ double ring_estimate(const Product& p, Kernel* shape) {
     }
   }
   return best;
+}
+
+// One LDS stage a wave, or two (deep)?  Measured on MI355X (us, one stage / two).  An fp32 step is 1024 cycles of MFMAs: a second
+// stage hides the next step's wait behind them as soon as a wave has more than one step.  In bf16 the steps are short and the
+// waves per SIMD, not their stages, hide the waits until a row is long.
+//  * fp32 64x64: one step of every wave is 256 elements.  512 x 512, K = 256 8.8 / 9.9, K = 264 12.2 / 12.0, K = 320 14.0 / 12.0,
+//    K = 1024 31.8 / 23.6, K = 4096 112 / 75; 2048 x 1024, K = 640 41.8 / 33.3.
+//  * fp32 32x64: nine or ten steps are two for some waves, be they six or eight.  512 x 512, K = 256 6.1 / 7.2, K = 264 7.7 / 7.2,
+//    K = 320 8.0 / 7.5, K = 352 8.1 / 8.5, K = 512 10.0 / 10.8.  Beyond one round of tiles one stage is no slower: 1024 x 1024,
+//    K = 320 14.1 / 14.4.
+//  * fp32 32x32: two workgroups per CU with one stage, one with two.  Alike on one round of tiles (512 x 512, K = 4096 29.4 / 29.5).
+//    More: 600 x 512, K = 512 10.9 / 11.4, K = 1056 19.2 / 18.7, K = 2048 34.0 / 29.9, K = 8192 119 / 94; 1024 x 1024, K = 1024
+//    32.8 / 33.8, K = 1568 48.2 / 47.7, K = 4096 119 / 102.
+//  * bf16 64x64: 333 x 2048, K = 2048 10.7 / 11.2, K = 3136 14.0 / 14.3, K = 4096 17.1 / 16.5, K = 8192 29.9 / 29.0.
+//  * bf16 32x32, one round of tiles, K from 1024 on: up to eight rows (nearly all operand bytes are W's) 1 x 208, K = 11392 15.1 /
+//    13.7, 3 x 952, K = 4224 8.1 / 7.6, 8 x 1472, K = 4864 8.7 / 8.2; rows that don't start on a cache line 46 x 896, K = 1688 6.1 /
+//    5.8, 43 x 2528, K = 3288 9.9 / 9.3; but 128 x 768, K = 1088 4.1 / 4.4, 512 x 512, K = 4096 8.9 / 9.3 and, with two workgroups
+//    per CU, 1024 x 1024, K = 2048 14.6 / 19.4.
+Kernel ring_form(const Product& p, Kernel shape) {
+  const int64_t tiles_n64 = ceil_div(p.N, 64), t32 = ceil_div(p.M, 32) * ceil_div(p.N, 32);
+  if (p.bf16) {
+    if (shape == RING_64x64 && p.K > 2048) return RING_64x64_DEEP;
+    if (shape == RING_32x32 && t32 <= 256 && p.K >= 1024 && (p.M <= 8 || p.K % 64 != 0)) return RING_32x32_DEEP;
+    return shape;
+  }
+  if (shape == RING_64x64 && p.K > 256) return RING_64x64_DEEP;
+  if (shape == RING_32x64 && p.K > 256 && p.K <= 320 && ceil_div(p.M, 32) * tiles_n64 <= 256) return RING_32x64_DEEP;
+  if (shape == RING_32x32 && t32 > 256 && p.K > (t32 <= 512 ? 1024 : 1536)) return RING_32x32_DEEP;
+  return shape;
 }
 
 // Generic bf16 kernel on up to 256 whole tiles: a memory latency per K step, and C's layout read 32 rows at a time.
@@ -137,7 +166,7 @@ Route tiled_route(const Product& p) {
   // The ring kernel takes what leaves the chip idle or waiting: 128 x 768, K = 3072 38.5 -> 7.5 us; 333 x 2048, K = 8192
   // 122 -> 30 us (four stages: 58).
   Kernel ring;
-  if (ring_estimate(p, &ring) < best_time) return Route{ring, 1};
+  if (ring_estimate(p, &ring) < best_time) return Route{ring_form(p, ring), 1};
   return best;
 }
 
@@ -160,7 +189,7 @@ Route route(const Product& p) {
     // (The FMA kernel's grid holds 65535 row tiles.)
     if (p.K % 4 != 0 || !p.aligned) return Route{F32_FMA, 1};
     if (fma_estimate(p) < ring_estimate(p, &ring) && ceil_div(p.M, 64) <= 65535) return Route{F32_FMA, 1};
-    return Route{ring, 1};
+    return Route{ring_form(p, ring), 1};
   }
   if (tiled(p)) return tiled_route(p);
   // The rest (K not a multiple of 64, scaled results, other combinations of epilogues).  Above 192 tiles of 128x128 the ring
@@ -172,7 +201,7 @@ Route route(const Product& p) {
   if (p.aligned && ceil_div(p.M, 128) * ceil_div(p.N, 128) <= 192) {
     const double t = ring_estimate(p, &ring);
     const bool whole = p.M % 128 == 0 && p.N % 128 == 0;
-    if (!whole || 1.08 * t < generic_estimate(p)) return Route{ring, 1};
+    if (!whole || 1.08 * t < generic_estimate(p)) return Route{ring_form(p, ring), 1};
   }
   return Route{BF16_GENERIC, 1};
 }

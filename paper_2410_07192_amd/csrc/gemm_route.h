@@ -13,12 +13,15 @@ enum : int { E_BIAS = 1, E_GELU = 2, E_RESID = 4, E_DACT = 8, E_PRE = 16, E_ACC 
 enum Kernel : int32_t {
   F32_FMA,                                        // gemm.hip
   BF16_GENERIC,
-  RING_32x32, RING_32x64, RING_64x64, RING_128x64,   // gemm_ring.hip, bf16 and fp32
+  RING_32x32, RING_32x64, RING_64x64, RING_128x64,   // gemm_ring.hip, bf16 and fp32: eight waves with one LDS stage each; 128x64: three, two
   TILE_256x256, TILE_256x192, TILE_128x128,       // gemm_tile.h; the last with two LDS stages,
   TILE_128x128_DEEP,                              // here with four
   TILE_256x128,                                   // with three
   TILE_128x64,                                    // with six
+  RING_32x32_DEEP, RING_32x64_DEEP, RING_64x64_DEEP, // the first three with two LDS stages a wave, on eight, six and four waves
 };
+
+inline bool is_ring(Kernel k) { return (k >= RING_32x32 && k <= RING_128x64) || (k >= RING_32x32_DEEP && k <= RING_64x64_DEEP); }
 
 struct Product {
   bool bf16;           // else fp32

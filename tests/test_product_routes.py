@@ -14,7 +14,8 @@ from oracle import transformer as ot          # noqa: E402
 from paper_2410_07192_amd import synth        # noqa: E402
 
 KERNELS = ("f32 fma", "bf16 generic", "ring 32x32", "ring 32x64", "ring 64x64", "ring 128x64", "tile 256x256",
-           "tile 256x192", "tile 128x128", "tile 128x128 deep")
+           "tile 256x192", "tile 128x128", "tile 128x128 deep", "tile 256x128", "tile 128x64", "ring 32x32 deep",
+           "ring 32x64 deep", "ring 64x64 deep")
 EPI = {"plain": 0, "bias": 1, "gelu": 3, "resid": 5, "pre": 19, "dact": 8, "sum": 32}   # sum: fp32 result, accumulated
 
 
@@ -45,6 +46,15 @@ PATHS = [
     ("f32", 1000, 260, 36, ALL, "ring 32x64", 1),
     ("f32", 1023, 516, 36, ALL, "ring 64x64", 1),
     ("f32", 2047, 772, 64, ALL, "ring 128x64", 1),
+    # and on its forms with two stages a wave: one to three steps a wave, the last one short or missing
+    ("f32", 611, 516, 1060, ALL, "ring 32x32 deep", 1),
+    ("f32", 2333, 516, 1796, ALL, "ring 32x32 deep", 1),
+    ("f32", 611, 516, 268, ALL, "ring 32x64 deep", 1),
+    ("f32", 1023, 1020, 260, ALL, "ring 64x64 deep", 1),
+    ("f32", 1023, 1022, 1060, ALL, "ring 64x64 deep", 1),
+    ("bf16", 7, 516, 1088, ALL, "ring 32x32 deep", 1),
+    ("bf16", 333, 518, 1096, ALL, "ring 32x32 deep", 1),
+    ("bf16", 333, 2044, 2312, ALL, "ring 64x64 deep", 1),
     # the tiled kernels: rows in 16- and 8-byte pieces and element by element, ragged along M, mostly along N
     ("bf16", 5000, 2368, 2048, ALL, "tile 256x256", 1),
     ("bf16", 5000, 2372, 2048, ("dact",), "tile 256x256", 1),
@@ -92,6 +102,17 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
 
 # The faster kernel at sizes where two were timed on MI355X (times in us, the chosen one first): the rules follow them.
 @pytest.mark.parametrize("dtype,M,N,K,epi,kernels", [
+    # ring kernel, one LDS stage a wave or two
+    ("f32", 1024, 1024, 256, "bias", "ring 64x64"),
+    ("f32", 1024, 1024, 320, "bias", "ring 64x64 deep"),     # 13.0 / 13.5
+    ("f32", 1024, 1024, 1024, "bias", "ring 64x64 deep"),    # 24.4 / 33.7
+    ("f32", 614, 2440, 740, "bias", "ring 64x64 deep"),      # 37.5 / 44.6
+    ("f32", 600, 512, 320, "bias", "ring 32x64 deep"),       # 7.6 / 8.0
+    ("f32", 699, 684, 6756, "plain", "ring 32x32 deep"),     # 84 / 101
+    ("f32", 2329, 544, 4624, "plain", "ring 32x32 deep"),    # 142 / 167
+    ("bf16", 3, 952, 4224, "gelu", "ring 32x32 deep"),       # 7.6 / 8.1
+    ("bf16", 46, 896, 1688, "gelu", "ring 32x32 deep"),      # 5.8 / 6.1
+    ("bf16", 333, 2048, 8192, "resid", "ring 64x64 deep"),   # 29.0 / 29.9
     # fp32: FMA kernel against the best ring tile
     ("f32", 4096, 2048, 64, "bias", "f32 fma"),        # 29 / 45
     ("f32", 8192, 1024, 128, "bias", "f32 fma"),       # 44 / 52
@@ -145,6 +166,12 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
 ])
 def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
     assert route(dtype, M, N, K, epi)[0].startswith(kernels)
+
+
+def test_one_stage_a_wave_where_it_is_faster():
+    assert {route(*p)[0] for p in (("f32", 1024, 1024, 256), ("bf16", 333, 2048, 2048))} == {"ring 64x64"}   # 8.8 / 9.9, 10.7 / 11.2
+    assert {route(*p)[0] for p in (("f32", 512, 512, 4096), ("bf16", 128, 768, 3072), ("bf16", 9, 768, 3072))} == {"ring 32x32"}
+    assert {route("f32", M, N, K)[0] for M, N, K in ((600, 512, 256), (600, 512, 352), (600, 512, 544))} == {"ring 32x64"}
 
 
 def test_two_slices_where_they_are_faster():
