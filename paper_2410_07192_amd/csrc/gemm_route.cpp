@@ -87,6 +87,18 @@ double fma_estimate(const Product& p) {
   return std::max(5.5 + 0.093 * k + 0.003 * tiles, 2.5 + tiles / 256 * (1.8 + 0.03 * k));
 }
 
+// 256x256 tiles with 16x16x32 MFMAs instead of 32x32x16: where the power limit sets the rate, i.e. on a chip that is full nearly
+// all the time, and K is long enough for that to outweigh the slower start.  Measured on MI355X, time with 16x16x32 by time with
+// 32x32x16, over 1660 pairs of results and epilogues: rounds filled to 0.93 or more, K < 512 1.07 (0.95 to 1.14), 512 .. 1000
+// 1.04, 1400 .. 2000 0.98 (to 1.04), 2048 0.98 (0.95 to 1.02), 2560 0.97, from 4096 on 0.96 (0.93 to 1.00); to 0.84: K = 2048 1.01,
+// 6208 1.01, from 8192 on 0.98 (408 x 28032, K = 10048 into fp32 1.05); less (964 x 10112, 160 tiles): 1.02 to 1.17 at any K.  4096 x 4096 us: K = 768 27.8 / 27.4, K = 2048
+// 56.7 / 58.3, K = 8192 190 / 201; sums into fp32 alike (8192 x 8192, K = 2048 293 / 296).
+bool by_16(const Product& p) {
+  const int64_t tiles = ceil_div(p.M, 256) * ceil_div(p.N, 256);
+  const double filled = (double)tiles / (double)(256 * ceil_div(tiles, 256));
+  return filled >= 0.93 && p.K >= 2048;
+}
+
 // Tiled kernels, and the ring kernel where it is faster.
 // Tile shapes: 256x256 (four waves, wave tile 128x128), 256x192 (8 waves as 4x2, wave tile 64x96) and 256x128 (four waves, wave
 // tile 128x64), one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
@@ -167,6 +179,7 @@ Route tiled_route(const Product& p) {
   // 122 -> 30 us (four stages: 58).
   Kernel ring;
   if (ring_estimate(p, &ring) < best_time) return Route{ring_form(p, ring), 1};
+  if (best.kernel == TILE_256x256 && by_16(p)) best.kernel = TILE_256x256_16;
   return best;
 }
 

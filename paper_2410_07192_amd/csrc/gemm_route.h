@@ -19,6 +19,7 @@ enum Kernel : int32_t {
   TILE_256x128,                                   // with three
   TILE_128x64,                                    // with six
   RING_32x32_DEEP, RING_32x64_DEEP, RING_64x64_DEEP, // the first three with two LDS stages a wave, on eight, six and four waves
+  TILE_256x256_16,                                // 256x256 with 16x16x32 MFMAs
 };
 
 inline bool is_ring(Kernel k) { return (k >= RING_32x32 && k <= RING_128x64) || (k >= RING_32x32_DEEP && k <= RING_64x64_DEEP); }

@@ -137,6 +137,8 @@ __device__ __forceinline__ void build_epilogue_tables(float2* gelu_tab) {
 // column 4 * unit(a, q) of the wave's part of the tile.
 //   32x32x16: D[i][j], lane holds j = lane % 32 (row of C) and i = 8 * q + 4 * (lane / 32) + r (column of C)
 //   16x16x32: four 16x16 blocks, q = 2 * (column half) + row half; j = lane % 16, i = 4 * (lane / 16) + r
+// slot, half: unit / 2 and unit % 2 (where the lane has no part in the slot, its swizzled place is one scalar expression per row:
+// 15724 x 1728, K = 384 with GELU and copy 55.1 us by the unit, 52.6 this way).
 // Indices must be compile-time constants or the accumulators leave the register file.
 template <int SH, int TM, int TN>
 struct Accumulators;
@@ -157,6 +159,8 @@ struct Accumulators<32, TM, TN> {
   }
   static __device__ __forceinline__ int row(int b, int, int lane) { return b * 32 + (lane & 31); }
   static __device__ __forceinline__ int unit(int a, int q, int lane) { return a * 8 + q * 2 + (lane >> 5); }
+  static __device__ __forceinline__ int slot(int a, int q, int) { return a * 4 + q; }
+  static __device__ __forceinline__ int half(int lane) { return lane >> 5; }
 };
 template <int TM, int TN>
 struct Accumulators<16, TM, TN> {
@@ -174,6 +178,8 @@ struct Accumulators<16, TM, TN> {
   }
   static __device__ __forceinline__ int row(int b, int q, int lane) { return b * 32 + (q & 1) * 16 + (lane & 15); }
   static __device__ __forceinline__ int unit(int a, int q, int lane) { return a * 8 + (q >> 1) * 4 + (lane >> 4); }
+  static __device__ __forceinline__ int slot(int a, int q, int lane) { return a * 4 + (q >> 1) * 2 + (lane >> 5); }
+  static __device__ __forceinline__ int half(int lane) { return lane >> 4 & 1; }
 };
 
 // What a workgroup does with its finished accumulators: block (a, b) lies at rows (wm * TM + b) * 32, columns
@@ -307,8 +313,8 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
         static_for<0, TN>([&](auto a) {
           static_for<0, TM>([&](auto b) {
             static_for<0, 4>([&](auto q) {
-              const int row = Acc::row(wm * TM + b, q, lane), unit = Acc::unit(wn * TN + a, q, lane);
-              const uint2 u = st8[row * (SLOTS * 2) + swz(unit >> 1, row) * 2 + (unit & 1)];
+              const int row = Acc::row(wm * TM + b, q, lane);
+              const uint2 u = st8[row * (SLOTS * 2) + swz(Acc::slot(wn * TN + a, q, lane), row) * 2 + Acc::half(lane)];
               const f32x4 f = {gelu_grad_tab(bf16_bits_to_f32(u.x & 0xffffu)), gelu_grad_tab(bf16_bits_to_f32(u.x >> 16)),
                                gelu_grad_tab(bf16_bits_to_f32(u.y & 0xffffu)), gelu_grad_tab(bf16_bits_to_f32(u.y >> 16))};
               acc.scale(a, b, q, f);
@@ -330,7 +336,7 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
           static_for<0, TM>([&](auto b) {
             static_for<0, 4>([&](auto q) {
               constexpr int bq = SH == 32 ? decltype(q)::value : decltype(q)::value & 2;   // quads of one column share the bias
-              const int row = Acc::row(wm * TM + b, q, lane), unit = Acc::unit(wn * TN + a, q, lane);
+              const int row = Acc::row(wm * TM + b, q, lane);
               const f32x4 t = acc.quad(a, b, q);
               float v[4] = {t[0], t[1], t[2], t[3]};
               if constexpr (EPI & E_BIAS) {
@@ -356,7 +362,7 @@ __device__ __forceinline__ void tile_epilogue(Accumulators<SH, TM, TN>& acc, uin
               uint2 pk;
               pk.x = pack_bf16x2(v[0], v[1]);
               pk.y = pack_bf16x2(v[2], v[3]);
-              st8[row * (SLOTS * 2) + swz(unit >> 1, row) * 2 + (unit & 1)] = pk;
+              st8[row * (SLOTS * 2) + swz(Acc::slot(wn * TN + a, q, lane), row) * 2 + Acc::half(lane)] = pk;
             });
           });
         });
@@ -878,13 +884,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, TM * TN <= 4 && NS == 2 ? 2 : 1) vo
 // hold one stage in flight, the memory pipeline never drains, and the one barrier of a step (in the middle of the
 // last MFMA block, so that queued MFMAs cover it) both publishes the next stage and frees the current one.
 // Plain loads and stores: the compiler derives the vmcnt / lgkmcnt waits; the scheduling fences keep its order.
-// 16x16x32 MFMAs: the power limit allows more of them than of 32x32x16 (16384 x 2048, K = 8192 424 -> 410 us, 2048 x 32768, K =
-// 8192 with GELU and copy 851 -> 810, 8192 x 8192, K = 2048 into fp32 300 -> 290).
-template <typename OutT, int EPI>
+// SH = 32, 32x32x16 MFMAs, or 16, 16x16x32 ones: the power limit allows more of the latter, but they need an instruction slot
+// twice as often and half as many fragment registers are reloaded at a time.  Which is faster where: gemm_route.cpp.
+template <typename OutT, int EPI, int SH>
 __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
     const bf16_t* __restrict__ X, const bf16_t* __restrict__ W, OutT* __restrict__ C, int64_t M, int64_t N,
     int64_t K, EpiDev ep, int32_t tiles_m, int32_t tiles_n, int32_t group_m) {
-  constexpr int WGM = 2, WGN = 2, TM = 4, TN = 4, FM = 2 * TM, FN = 2 * TN;   // fragments of 16 rows
+  constexpr int WGM = 2, WGN = 2, TM = 4, TN = 4, FM = TM * 32 / SH, FN = TN * 32 / SH;   // fragments of SH rows,
+  constexpr int KS = 512 / SH, SLICES = 64 / KS;                                             // KS wide in k
   constexpr int BM = 256, BN = 256, NW = 4;
   constexpr int GX = BM / 8, G = (BM + BN) / 8, GPW = G / NW;   // 8-row groups of 1 KB; sixteen per wave
   constexpr int STAGE = (BM + BN) * 8;                          // uint4 per LDS stage
@@ -902,7 +909,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave % WGM, wn = wave / WGM;
-  const int lr = lane & 15, lg = lane >> 4;
+  const int lr = lane & (SH - 1), lg = lane / SH;
 
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a first-class vector: a struct-typed quad would live in private memory
   // Global source of this lane for each group: a 32-bit byte offset from the tile's first row (rows past the end are
@@ -930,49 +937,104 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   };
   const int wro = wave * 64 + lane;   // group g of a stage starts at uint4 index g * 64: this lane's place in group `wave`
   // Fragment addresses without arithmetic in the loop.  Row r of a stage holds its 16-byte chunk c at position
-  // c ^ (r / 2) % 8, and the rows a lane reads are 16 apart, so every fragment of a lane has the same swizzle.  One
-  // address per stage, operand and slice (eight registers); the 16-row blocks go into the instructions' immediate offsets.
-  const uint4* fx_at[2][2];
-  const uint4* fw_at[2][2];
+  // c ^ (r / 2) % 8, and the rows a lane reads are SH apart, so every fragment of a lane has the same swizzle.  One
+  // address per stage, operand and slice (16 or 8 registers); the blocks of rows go into the instructions' immediate offsets.
+  const uint4* fx_at[2][SLICES];
+  const uint4* fw_at[2][SLICES];
 #pragma unroll
   for (int st = 0; st < 2; ++st)
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int chunk = (kk * 4 + lg) ^ (lr >> 1);
+    for (int kk = 0; kk < SLICES; ++kk) {
+      const int chunk = (kk * (KS / 8) + lg) ^ ((lr >> 1) & 7);
       fx_at[st][kk] = smem + st * STAGE + (wm * TM * 32 + lr) * 8 + chunk;
       fw_at[st][kk] = smem + st * STAGE + BM * 8 + (wn * TN * 32 + lr) * 8 + chunk;
     }
-  Accumulators<16, TM, TN> acc;
+  Accumulators<SH, TM, TN> acc;
 #pragma unroll
   for (int a = 0; a < FN; ++a)
 #pragma unroll
     for (int b = 0; b < FM; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc.v[a][b][r] = 0.f;
-  bf16x8 fw[FN], fx[2][FM];
+      for (int r = 0; r < SH * SH / 64; ++r) acc.v[a][b][r] = 0.f;
+  bf16x8 fw[SH == 32 ? 2 : 1][FN], fx[2][FM];
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
   auto load_w = [&](auto jc, auto stc, auto kkc) {
     constexpr int j = decltype(jc)::value, st = decltype(stc)::value, kk = decltype(kkc)::value;
-    fw[j] = as_bf16x8(fw_at[st][kk][j * 128]);
+    fw[SH == 32 ? kk & 1 : 0][j] = as_bf16x8(fw_at[st][kk][j * SH * 8]);
   };
   auto load_x = [&](auto jc, auto stc, auto kkc) {
     constexpr int j = decltype(jc)::value, st = decltype(stc)::value, kk = decltype(kkc)::value;
-    fx[kk][j] = as_bf16x8(fx_at[st][kk][j * 128]);
+    fx[kk & 1][j] = as_bf16x8(fx_at[st][kk][j * SH * 8]);
   };
   u32x4 R[GPW];
-  constexpr int MF = FM * FN;   // 64 MFMAs per 32-wide slice of the K step
-  // One 32-wide slice KK of a K step: 64 MFMAs (16x16x32), every other one preceded by exactly ONE memory instruction, so
-  // that none of them has to wait for an issue slot behind another (a wave issues in order, and with one wave per SIMD
-  // whatever stalls it stalls the MFMA pipe).  The MFMAs go through the W blocks one after the other, so W needs one set
-  // of fragments: blocks 0..3 of the next slice replace this slice's once its first half is through, blocks 4..7 arrive
-  // in the first slots of the slice that uses them.  X has two sets.
+  constexpr int MF = FM * FN;   // MFMAs per slice of the K step: 16 or 64
+  // WR: stage kt + 1 exists (its groups wait in R); LD: stage kt + 2 exists.  Every memory instruction sits alone between two
+  // MFMAs, so that none of them has to wait for an issue slot behind another (a wave issues in order, and with one wave per
+  // SIMD whatever stalls it stalls the MFMA pipe).
+  //
+  // 32x32x16: slice KK, sixteen MFMAs on fragment set KK & 1, each preceded by one memory instruction.  Slices 0..2: eight
+  // fragment reads for the next slice, in the order its MFMAs first need them (W block 0, the X blocks, W blocks 1..3), then
+  // four times {write register quad q to the next stage, reload it for the stage after next}.  Slice 3: the last four
+  // writes and reloads first, the barrier behind the eighth MFMA, then the first fragments of the next stage.
+  auto load_both = [&](auto jc, auto stc, auto kkc) {
+    constexpr int j = decltype(jc)::value;
+    if constexpr (j == 0) load_w(I0{}, stc, kkc);
+    else if constexpr (j <= 4) load_x(std::integral_constant<int, j - 1>{}, stc, kkc);
+    else load_w(std::integral_constant<int, j - 4>{}, stc, kkc);
+  };
+  auto slice32 = [&](auto kkc, auto wrc, auto ldc, auto curc, int64_t k_next2) {
+    constexpr int KK = decltype(kkc)::value, buf = KK & 1, CUR = decltype(curc)::value;
+    uint4* const sn = smem + (CUR ^ 1) * STAGE;
+    constexpr bool WR = decltype(wrc)::value, LD = decltype(ldc)::value;
+    static_for<0, MF>([&](auto mi) {
+      // One wait per group instead of one per use (the compiler, which still places every wait that is needed,
+      // drops its own where these make them redundant): all eight fragments of this slice, read eight to sixteen
+      // instructions ago with four LDS stores behind them, at the slice's first MFMA; the four register quads about
+      // to be stored, loaded a K step ago with twelve younger loads behind them, at the first store.
+      if constexpr (mi == 0 && KK > 0) __builtin_amdgcn_s_waitcnt(0xc47f);                                           // lgkmcnt(4)
+      if constexpr (WR && LD && ((KK < 3 && mi == 8) || (KK == 3 && mi == 0))) __builtin_amdgcn_s_waitcnt(0x0f7c);   // vmcnt(12)
+      if constexpr (KK < 3) {
+        if constexpr (mi < 8) {
+          load_both(mi, curc, std::integral_constant<int, (KK + 1) & 3>{});
+        } else {
+          constexpr int q = 4 * KK + (mi - 8) / 2;
+          if constexpr ((mi & 1) == 0) {
+            if constexpr (WR) *(u32x4*)(sn + wro + q * NW * 64) = R[q];
+          } else {
+            if constexpr (LD) R[q] = gload(std::integral_constant<int, q>{}, k_next2);
+          }
+        }
+      } else {
+        if constexpr (mi < 4) {
+          if constexpr (WR) *(u32x4*)(sn + wro + (12 + mi) * NW * 64) = R[12 + mi];
+        } else if constexpr (mi < 8) {
+          if constexpr (LD) R[8 + mi] = gload(std::integral_constant<int, 8 + mi>{}, k_next2);
+        } else {
+          if constexpr (mi == 8) {
+            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): my LDS writes are done, my last fragments are in registers
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (WR) load_both(std::integral_constant<int, mi - 8>{}, std::integral_constant<int, CUR ^ 1>{}, I0{});
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int a = mi / FM, b = mi % FM;
+      acc.v[a][b] = mfma_bf16(fw[buf][a], fx[buf][b], acc.v[a][b]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // 16x16x32: slice KK, 64 MFMAs, every other one preceded by one memory instruction.  The MFMAs go through the W blocks one
+  // after the other, so W needs one set of fragments: blocks 0..3 of the next slice replace this slice's once its first half
+  // is through, blocks 4..7 arrive in the first slots of the slice that uses them.  X has two sets.
   // Slice 0, slots 0..31: W blocks 4..7; X of slice 1; two times {write register quad q to the next stage, reload it for
   // the stage after next}; W blocks 0..3 of slice 1; six more writes and reloads.
   // Slice 1: W blocks 4..7; the other eight writes; two reloads; the barrier; X and W blocks 0..3 of the next stage's slice
   // 0; six reloads.
-  // WR: stage kt + 1 exists (its groups wait in R); LD: stage kt + 2 exists.
-  auto slice = [&](auto kkc, auto wrc, auto ldc, auto curc, int64_t k_next2) {
+  auto slice16 = [&](auto kkc, auto wrc, auto ldc, auto curc, int64_t k_next2) {
     constexpr int KK = decltype(kkc)::value, CUR = decltype(curc)::value;
     uint4* const sn = smem + (CUR ^ 1) * STAGE;
     constexpr bool WR = decltype(wrc)::value, LD = decltype(ldc)::value;
@@ -1019,7 +1081,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
         __builtin_amdgcn_sched_barrier(0);
       }
       constexpr int a = mi / FM, b = mi % FM;
-      acc.v[a][b] = mfma_bf16(fw[a], fx[KK][b], acc.v[a][b]);
+      acc.v[a][b] = mfma_bf16(fw[0][a], fx[KK][b], acc.v[a][b]);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -1027,8 +1089,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   // steps are separate instantiations.  Step kt works on stage (kt + nk) % 2: the last step is then always on stage
   // 1 and the one before it on stage 0 whatever nk is, and only the very first step of an odd nk stands alone.
   auto step = [&](auto wrc, auto ldc, auto curc, int64_t k_next2) {
-    slice(I0{}, wrc, ldc, curc, k_next2);
-    slice(I1{}, wrc, ldc, curc, k_next2);
+    if constexpr (SH == 32) {
+      slice32(I0{}, wrc, ldc, curc, k_next2);
+      slice32(I1{}, wrc, ldc, curc, k_next2);
+      slice32(I2{}, wrc, ldc, curc, k_next2);
+      slice32(I3{}, wrc, ldc, curc, k_next2);
+    } else {
+      slice16(I0{}, wrc, ldc, curc, k_next2);
+      slice16(I1{}, wrc, ldc, curc, k_next2);
+    }
   };
 
   const int64_t nk = K / 64;
@@ -1040,8 +1109,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_w4_kernel(
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __builtin_amdgcn_s_barrier();
   auto first_frags = [&](auto stc) {
-    static_for<0, 8>([&](auto j) { load_x(j, stc, I0{}); });
-    static_for<0, 4>([&](auto j) { load_w(j, stc, I0{}); });
+    if constexpr (SH == 32) {
+      static_for<0, 8>([&](auto j) { load_both(j, stc, I0{}); });
+    } else {
+      static_for<0, 8>([&](auto j) { load_x(j, stc, I0{}); });
+      static_for<0, 4>([&](auto j) { load_w(j, stc, I0{}); });
+    }
   };
   if (s0) first_frags(I1{});
   else first_frags(I0{});
@@ -1081,10 +1154,12 @@ hipError_t launch_tiles(Kern kern, int BM, int BN, int threads, bool* attr_set, 
 template <typename OutT, int EPI>
 hipError_t launch_fast(const Route& r, const void* X, const void* W, void* C, int64_t M, int64_t N, int64_t K,
                        const EpiDev& ep, hipStream_t stream) {
-  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false, attr_tall = false, attr_slim = false;
+  static bool attr_big = false, attr_wide = false, attr_small = false, attr_deep = false, attr_tall = false, attr_slim = false, attr_16 = false;
   switch (r.kernel) {
     case TILE_256x256:
-      return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
+      return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI, 32>, 256, 256, 256, &attr_big, X, W, C, M, N, K, ep, 1, stream);
+    case TILE_256x256_16:
+      return launch_tiles<OutT>(gemm_bf16_nt_w4_kernel<OutT, EPI, 16>, 256, 256, 256, &attr_16, X, W, C, M, N, K, ep, 1, stream);
     case TILE_256x192:
       return launch_tiles<OutT>(gemm_bf16_nt_kernel<4, 2, 2, 3, OutT, EPI>, 256, 192, 512, &attr_wide, X, W, C, M, N, K,
                                 ep, 1, stream);

@@ -15,7 +15,7 @@ from paper_2410_07192_amd import synth        # noqa: E402
 
 KERNELS = ("f32 fma", "bf16 generic", "ring 32x32", "ring 32x64", "ring 64x64", "ring 128x64", "tile 256x256",
            "tile 256x192", "tile 128x128", "tile 128x128 deep", "tile 256x128", "tile 128x64", "ring 32x32 deep",
-           "ring 32x64 deep", "ring 64x64 deep")
+           "ring 32x64 deep", "ring 64x64 deep", "tile 256x256 16")
 EPI = {"plain": 0, "bias": 1, "gelu": 3, "resid": 5, "pre": 19, "dact": 8, "sum": 32}   # sum: fp32 result, accumulated
 
 
@@ -61,6 +61,9 @@ PATHS = [
     ("bf16", 1999, 6156, 192, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256", 1),
     ("bf16", 5000, 2370, 2048, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256", 1),
     ("bf16", 5000, 2370, 4096, ("dact",), "tile 256x256", 1),
+    ("bf16", 4000, 4088, 2112, ALL, "tile 256x256 16", 1),
+    ("bf16", 4000, 4092, 2048, ALL, "tile 256x256 16", 1),
+    ("bf16", 4000, 4090, 2048, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256 16", 1),
     ("bf16", 1300, 6152, 128, ALL, "tile 256x192", 1),
     ("bf16", 1300, 6156, 128, ALL, "tile 256x192", 1),
     ("bf16", 1300, 6154, 512, ALL, "tile 256x192", 1),
@@ -172,6 +175,18 @@ def test_one_stage_a_wave_where_it_is_faster():
     assert {route(*p)[0] for p in (("f32", 1024, 1024, 256), ("bf16", 333, 2048, 2048))} == {"ring 64x64"}   # 8.8 / 9.9, 10.7 / 11.2
     assert {route(*p)[0] for p in (("f32", 512, 512, 4096), ("bf16", 128, 768, 3072), ("bf16", 9, 768, 3072))} == {"ring 32x32"}
     assert {route("f32", M, N, K)[0] for M, N, K in ((600, 512, 256), (600, 512, 352), (600, 512, 544))} == {"ring 32x64"}
+
+
+def test_16x16x32_mfmas_on_a_full_chip_and_long_k_only():
+    # us, the chosen form first
+    assert {route("bf16", *p)[0] for p in ((4096, 4096, 2048),            # 56.7 / 58.3
+                                           (8192, 2048, 8192))} == {"tile 256x256 16"}       # 191 / 202
+    assert {route("bf16", *p)[0] for p in ((4096, 4096, 768),             # 27.4 / 27.8
+                                           (15632, 7936, 320),            # 111 / 127
+                                           (964, 10112, 13696),           # 160 tiles: 243 / 284
+                                           (408, 28032, 10048),           # 220 tiles
+                                           (1400, 9216, 4160),            # 216 tiles: 93 / 97
+                                           (4096, 7168, 2112))} == {"tile 256x256"}          # 448 tiles: 108 / 111
 
 
 def test_two_slices_where_they_are_faster():
