@@ -17,6 +17,7 @@
 // added to C with fp32 atomics in coalesced order (plain read-add-write when K is not split).  The column sum
 // comes from one more MFMA per A fragment against a fragment of ones, on the waves of the first tile column.
 // WIDE: M or N from 2^23 on, where 64 rows pass the 2^31 bytes of a raw buffer.  64-bit addresses per lane, whole K steps only.
+#include <algorithm>
 #include <type_traits>
 
 #include "pf_device.h"
@@ -274,27 +275,39 @@ bool gemm_tn_acc_preferred(int64_t M, int64_t N, int64_t K) {
   return big_tiles < 256 || M * N < 1170 * (M + N);
 }
 
-hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, float* colsum, int64_t M, int64_t N,
-                       int64_t K, hipStream_t stream) {
-  if (!gemm_tn_acc_supported(dtype, A, B, M, N, K)) return hipErrorInvalidValue;
-  const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128, tiles = tiles_m * tiles_n, steps = (K + 63) / 64;
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  // Slices of K per tile.  Measured on MI355X (us, one / two / four / eight slices): 4096 x 1024, K = 8192 95 / 85 / 102 / 139;
-  // 3072 x 1024 104 / 76 / 95 / 121; 1024 x 1024 87 / 49 / 39 / 48, K = 2048 30 / 20 / 22 / 34; 768 x 768, K = 2048 30 / 19 / 16 / 24;
-  // 2048 x 2048, K = 4096 55 / 58 / 80 / 125; 512 x 512, K = 640 12 / 11 / 10.  Per workgroup 11.6 us and 0.6 to 0.8 us a K step,
-  // by how many of them share the chip; the atomic adds of a slice cost 0.73 us per MiB of fp32 tile.
-  int best = 1;
+// Slices of K per tile.  Measured on MI355X (us, one / two / four / eight slices): 4096 x 1024, K = 8192 95 / 85 / 102 / 139;
+// 3072 x 1024 104 / 76 / 95 / 121; 1024 x 1024 87 / 49 / 39 / 48, K = 2048 29.5 / 19.6 / 21.4 / 33; 1280 x 1280, K = 2048 31.2 / 23.7 /
+// 30.3; 832 x 1472, K = 1152 21.2 / 15.4 / 22.4; 2304 x 768, K = 2048 29.8 / 23.7 / 31.1, K = 1024 16.5 / 17.7 / 27.3; 2048 x 2048, K =
+// 4096 55 / 58 / 80 / 125.  A workgroup takes 6 us and 0.56 to 0.82 us a K step, by how many of them share the chip; one that keeps
+// its whole K waits for C as well, and the longer its K the less of the operands is in L2 (up to 5.9 us); slices add their fp32
+// tiles with atomics, 0.56 us per MiB while every workgroup has a CU, 0.83 beyond.  Fitted to 450 sizes timed with every number of
+// slices: 0.7 % off the fastest on average.  A slice keeps four steps (4608 x 64, K = 256 8.7 / 9.6).
+static int32_t tn_slices(int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), steps = (K + 63) / 64;
+  const double mib = (double)M * (double)N * 4.0 / 1048576.0;
+  int32_t best = 1;
   double best_t = -1.0;
-  for (int s = 1; s <= 16; s *= 2) {
+  for (int32_t s = 1; s <= 16; s *= 2) {
     const int64_t share = (steps + s - 1) / s, wgs = tiles * s;
-    if (s > 1 && (share < 2 || share * (s - 1) >= steps || wgs > 512)) break;
-    double t = (double)((wgs + 511) / 512) * (11.6 + (double)share * (wgs <= 128 ? 0.6 : wgs <= 256 ? 0.65 : 0.8));
-    if (s > 1) t += (double)M * (double)N * 4.0 * s / 1048576.0 * 0.73;
+    if (s > 1 && (share < 4 || share * (s - 1) >= steps || wgs > 512)) break;
+    const double step = wgs <= 128 ? 0.56 : wgs <= 256 ? 0.65 : 0.82;
+    const double unsplit = s == 1 ? std::min(5.9, 0.17 * (double)share) : 0.0;
+    double t = (double)((wgs + 511) / 512) * (6.0 + unsplit + (double)share * step);
+    if (s > 1) t += (wgs <= 256 ? 0.56 : 0.83) * mib * s;
     if (best_t < 0 || t < best_t) {
       best_t = t;
       best = s;
     }
   }
+  return best;
+}
+
+hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, float* colsum, int64_t M, int64_t N,
+                       int64_t K, hipStream_t stream) {
+  if (!gemm_tn_acc_supported(dtype, A, B, M, N, K)) return hipErrorInvalidValue;
+  const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128, tiles = tiles_m * tiles_n;
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  const int best = (int)tn_slices(M, N, K);
   static bool attr[4] = {false, false, false, false};
   auto launch = [&](auto kern, bool* attr_set) {
     if (!*attr_set) {
@@ -315,3 +328,6 @@ hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, fl
 }
 
 }  // namespace pf
+
+// For tests: K slices of a weight gradient.
+extern "C" int32_t pf_gemm_tn_slices(int64_t M, int64_t N, int64_t K) { return pf::tn_slices(M, N, K); }

@@ -194,6 +194,25 @@ def test_two_slices_where_they_are_faster():
             ((1024, 3072, 8192), (3072, 1024, 8192), (2048, 1536, 8192), (1024, 3072, 4096), (2048, 2048, 8192))] == [2, 2, 2, 1, 1]
 
 
+# The k-major weight-gradient kernel (C += A^T B): slices of K, the fastest first where more than one was timed (us).
+@pytest.mark.parametrize("M,N,K,slices", [(832, 1472, 1152, 2),      # 15.4; one 21.2, four 22.4
+                                          (1280, 1280, 2048, 2),     # 23.7; one 31.2, four 30.3
+                                          (512, 2560, 1536, 2),      # 18.3; one 25.6, four 24.5
+                                          (2304, 768, 2048, 2),      # 23.7; one 29.8, four 31.1
+                                          (2304, 768, 1024, 1),      # 16.5; two 17.7
+                                          (1024, 1024, 8192, 4),     # 39; two 49, eight 48
+                                          (512, 1792, 12032, 4),     # 44.6; eight 49.5, two 69.2
+                                          (4096, 1024, 8192, 2),     # 85; one 95, four 102
+                                          (2048, 2048, 4096, 1),     # 55; two 58
+                                          (4096, 1024, 1024, 1),     # 22.6; two 34.5
+                                          (50304, 1024, 8192, 1)])
+def test_the_fastest_number_of_slices(M, N, K, slices):
+    from paper_2410_07192_amd import binding as pf
+    f = pf.lib.pf_gemm_tn_slices
+    f.restype, f.argtypes = C.c_int32, [C.c_int64, C.c_int64, C.c_int64]
+    assert f(M, N, K) == slices
+
+
 def test_misaligned_operands_go_to_the_kernels_without_16_byte_copies():
     assert route("bf16", 128, 768, 768, misaligned=True) == ("bf16 generic", 1)
     assert route("f32", 128, 768, 768, misaligned=True) == ("f32 fma", 1)
