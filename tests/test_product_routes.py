@@ -205,6 +205,8 @@ def test_two_slices_where_they_are_faster():
                                           (4096, 1024, 8192, 2),     # 85; one 95, four 102
                                           (2048, 2048, 4096, 1),     # 55; two 58
                                           (4096, 1024, 1024, 1),     # 22.6; two 34.5
+                                          (4608, 64, 256, 1),        # 8.7; two 9.6
+                                          (64, 64, 704, 4),          # 8.1; two 9.3
                                           (50304, 1024, 8192, 1)])
 def test_the_fastest_number_of_slices(M, N, K, slices):
     from paper_2410_07192_amd import binding as pf
