@@ -133,7 +133,8 @@ Route tiled_route(const Product& p) {
   // a 128x128 workgroup that has its CU, and four stages, to itself; with nearly every CU busy a step takes longer
   // (K = 2048: 144 workgroups 16.3 us, 256 20.5)
   const double busy = std::min(1.0, std::max(0.0, ((double)(ceil_div(p.M, 128) * ceil_div(p.N, 128)) - 144) / 64));
-  const double lone_start = timed ? 4.7 : 3.65, lone_step = timed ? 0.36 + 0.14 * busy : 0.608;
+  const bool whole = p.N % 8 == 0 && !(p.epi & E_ACC);   // any K: 1659 x 960 with residual K = 64 5.6 us, 512 8.2, 1024 10.8
+  const double lone_start = whole ? 4.7 : 3.65, lone_step = timed ? 0.36 + 0.14 * busy : whole ? 0.36 : 0.608;
   const bool reads = (p.epi & (E_ACC | E_RESID | E_DACT)) != 0;
   Route best{TILE_256x256, 1};
   double best_time = 1e30;
@@ -152,7 +153,8 @@ Route tiled_route(const Product& p) {
       const double start = small ? lone_start + paired * (sh.start - lone_start) : sh.start;
       const double step = small ? lone_step + paired * (sh.step - lone_step) : sh.step;
       const double odd = p.N % 4 == 0 || splits > 1 ? 0.0 : reads ? sh.odd_read : sh.odd;
-      const double act = p.epi & E_DACT ? sh.dact : p.epi & E_GELU && !alone ? sh.gelu : 0.0;
+      double act = p.epi & E_DACT ? sh.dact : p.epi & E_GELU && !alone ? sh.gelu : 0.0;
+      if (alone && whole) act = p.epi & E_DACT ? 2.5 : p.epi & E_PRE ? 1.6 : p.epi & E_GELU ? 0.9 : 0.0;
       double t = (double)ceil_div(wgs, sh.resident) * (start + odd + act + step * (double)(p.K / (64 * splits)));
       // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, and 2.5 us whatever its size (128 x 128,
       // K = 4096: 25.9, 16.6 and 11.9 us with two, four and eight slices)
@@ -164,12 +166,14 @@ Route tiled_route(const Product& p) {
     }
   }
   // 128x64 tiles, six LDS stages, one workgroup per CU: where 128x128 ones leave half of the CUs idle (us, 128x128 deep / 128x64:
-  // 1659 x 768, K = 3072 22.6 / 18.6; 1659 x 1024, K = 4096 26.2 / 21.9; 600 x 2048, K = 2048 15.4 / 12.1; 1000 x 2048, K = 8192 63.8 /
-  // 50.7, ring 53.3; 333 x 6144, K = 2048 16.4 / 23.9; with a second result 1024 x 2048, K = 1024 13.3 / 15.3).
-  if (timed && p.K >= 1024) {
+  // 1659 x 768, K = 64 5.4 / 4.8, K = 768 9.4 / 8.1, K = 3072 22.6 / 18.6; 1659 x 960, K = 768 9.6 / 8.2; 1659 x 1024, K = 4096 26.2 /
+  // 21.9; 600 x 2048, K = 2048 15.4 / 12.1; 1000 x 2048, K = 8192 63.8 / 50.7, ring 53.3; 333 x 6144, K = 2048 16.4 / 23.9; with a
+  // second result 1024 x 2048, K = 1024 13.3 / 15.3).
+  if (whole) {
     const int64_t wgs = ceil_div(p.M, 128) * ceil_div(p.N, 64);
     const double step = 0.28 + 0.06 * std::min(1.0, std::max(0.0, (double)(wgs - 208) / 48));
-    const double t = (double)ceil_div(wgs, 256) * (4.4 + (p.epi & E_PRE ? 3.0 : 0.0) + step * (double)(p.K / 64));
+    const double act = p.epi & E_PRE ? 3.0 : p.epi & E_DACT ? 1.6 : p.epi & E_GELU ? 0.3 : 0.0;
+    const double t = (double)ceil_div(wgs, 256) * (4.4 + act + step * (double)(p.K / 64));
     if (t < best_time) {
       best_time = t;
       best = Route{TILE_128x64, 1};

@@ -147,7 +147,9 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
     # partial tiles along N for the chosen shape, none for the other
     ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 54.2 / whole 128x128 tiles 70.8
     ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 53.4 / whole 128x128 tiles 69.0
-    ("bf16", 1659, 960, 768, "resid", "tile 128x128 deep"),  # 12.6 / ring 13.1
+    ("bf16", 1659, 960, 768, "resid", "tile 128x64"),        # 8.2 / 128x128 deep 9.6, ring 12.5
+    ("bf16", 522, 2848, 64, "plain", "tile 128x64"),         # 4.6 / 128x128 deep 5.0
+    ("bf16", 1659, 768, 768, "resid", "tile 128x64"),        # 8.1 / 128x128 deep 9.4
     # the 256x256 tile by its own rate, and what the epilogues cost it
     ("bf16", 4096, 10048, 2048, "plain", "tile 256x256"),    # 153 / 256x192 187, 128x128 197
     ("bf16", 8192, 50304, 1024, "plain", "tile 256x256"),    # 797 / 256x192 970
