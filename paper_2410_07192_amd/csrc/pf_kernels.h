@@ -100,7 +100,7 @@ hipError_t ce_loss_inplace(int32_t dtype, void* logits, const int32_t* ids, floa
 hipError_t embed_bwd(int32_t dtype, const void* dx, const int32_t* ids, float* dtok, float* dpos, int64_t tokens,
                      int32_t S, int32_t d, int32_t V, hipStream_t stream);
 // Adam with bias correction on the arrays of one fp32 block, and their working copies; g holds the sum over `accum`
-// microbatches and is cleared.  dry: the same kernel with a zero step and unit decay factors, so theta, m and v keep their
+// microbatches and is cleared.  model: parameters of the whole model.  dry: the same kernel with a zero step and unit decay factors, so theta, m and v keep their
 // values (for profiling).
 struct AdamPiece {
   int64_t src;     // first element in theta, m, v and g (16-byte aligned)
@@ -115,7 +115,7 @@ struct AdamPieces {
   AdamPiece p[MAX];
 };
 hipError_t adam_write(int32_t dtype, float* theta, float* m, float* v, float* g, AdamPieces ps, float lr, float b1, float b2,
-                      float eps, int64_t step, int32_t accum, hipStream_t st, bool dry = false);
+                      float eps, int64_t step, int32_t accum, int64_t model, hipStream_t st, bool dry = false);
 // fp32 [R][C] -> dst [R][C] in `dtype` and, if dst_t is not null, dst_t [C][R]
 hipError_t cast_from_f32(int32_t dtype, const float* src, void* dst, void* dst_t, int64_t R, int64_t C,
                          hipStream_t stream);

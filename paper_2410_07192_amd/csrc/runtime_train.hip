@@ -377,12 +377,13 @@ static int32_t optimizer_step(pf_ctx* c, hipStream_t st) {
   const int64_t step = t.steps + 1;
   if (!t.dry) t.steps = step;
   const int32_t accum = (int32_t)t.mb_accum;
+  const int64_t model = c->md.n_layers * (t.blob32 / 4) + t.emb32 / 4;
   for (int32_t l = 0; l < c->md.n_layers; ++l)
     PF_HIP(adam_write(c->md.dtype, t.master[l], t.m[l], t.v[l], t.grad[l], layer_pieces(c, l), a.lr, a.beta1, a.beta2, a.eps,
-                      step, accum, st, t.dry));
+                      step, accum, model, st, t.dry));
   if (t.Vp)
     PF_HIP(adam_write(c->md.dtype, t.embM, t.embm, t.embv, t.embg, emb_pieces(c), a.lr, a.beta1, a.beta2, a.eps, step, accum,
-                      st, t.dry));
+                      model, st, t.dry));
   t.mb_accum = 0;
   return PF_OK;
 }

@@ -548,7 +548,7 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(const T* __restrict__ dx
 // dtype, a matrix's transposed copy included: a parameter costs 16 bytes read, 16 written and the copies.  Bound by HBM
 // (36 bytes per bf16 matrix element).  A workgroup takes a 64xW tile of a matrix, whose transposition goes through LDS, or 64 W
 // elements of an array without transposed copy; every load of a thread is requested before the first is used.
-// One Adam kernel and a cast per array before: 50 launches for four layers of d 512 and their embedding, now five.
+// One Adam kernel and a cast per array before: 57 launches for four layers of d 512 and their embedding, now five.
 // g is the SUM over `accum` microbatches; the step uses g / accum and clears g.
 struct AdamConst { float lr, b1, b2, eps, bc1, bc2, inv_accum; };
 
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(4 * W) void adam_write_kernel(float* __restrict__ t
       at[k] = in[k] ? e : 0;
     }
   }
-  // (large layers: far more than any cache holds until the next step, so past the caches)
+  // (large models: far more than any cache holds until the next step, so past the caches)
   auto get = [](const float* q) { return W == 128 ? __builtin_nontemporal_load((const f32x4*)q) : *(const f32x4*)q; };
   auto put = [](float* q, f32x4 x) {
     if constexpr (W == 128) __builtin_nontemporal_store(x, (f32x4*)q);
@@ -821,13 +821,15 @@ hipError_t embed_bwd(int32_t dtype, const void* dx, const int32_t* ids, float* d
 }
 
 hipError_t adam_write(int32_t dtype, float* theta, float* m, float* v, float* g, AdamPieces ps, float lr, float b1, float b2,
-                      float eps, int64_t step, int32_t accum, hipStream_t st, bool dry) {
+                      float eps, int64_t step, int32_t accum, int64_t model, hipStream_t st, bool dry) {
   if (ps.n < 1 || ps.n > AdamPieces::MAX || step < 1 || accum < 1) return hipErrorInvalidValue;
-  // Tiles of 128 columns read and write 512 bytes of a row at a time (805 M parameters 5860 -> 5430 us, 5140 past the caches); small layers need the
-  // workgroups (3.1 M parameters: 23.4 us on 64 columns, 25.1 on 128).
-  int64_t total = 0, blocks = 0;
-  for (int i = 0; i < ps.n; ++i) total += ps.p[i].R * ps.p[i].C;
-  const int64_t W = total >= ((int64_t)1 << 24) ? 128 : 64;
+  // Tiles of 128 columns read and write 512 bytes of a row at a time and go past the caches: where the state of the whole model
+  // (sixteen bytes a parameter) fits no cache until the next step.  805 M parameters in one launch 5860 us on 64 columns, 5430 on 128,
+  // 5140 past the caches.  Steps of whole models on 64 tokens, us on 64 / 128 columns: 1 layer of d 1024 (15 M parameters) 319 /
+  // 324, 4 of d 512 (14 M) 787 / 828, 2 of d 768 (16 M) 488 / 487, 4 of d 640 (21 M) 885 / 886, 2 of d 1024 (27 M) 632 / 573, 16 of d
+  // 512 (51 M) 3091 / 3043, 12 of d 1024 (153 M) 3556 / 3477.
+  int64_t blocks = 0;
+  const int64_t W = model >= 20000000 ? 128 : 64;
   for (int i = 0; i < ps.n; ++i) {
     AdamPiece& p = ps.p[i];
     if (p.R < 1 || p.C < 1 || p.C % 8 != 0 || (p.dst_t && p.R % 8 != 0)) return hipErrorInvalidValue;
