@@ -332,3 +332,8 @@ hipError_t gemm_tn_acc(int32_t dtype, const void* A, const void* B, float* C, fl
 
 // For tests: K slices of a weight gradient.
 extern "C" int32_t pf_gemm_tn_slices(int64_t M, int64_t N, int64_t K) { return pf::tn_slices(M, N, K); }
+// For tests: the kernel itself, which takes K in eights (pf_op_gemm_tn: whole steps only); 0 or -1.
+extern "C" int32_t pf_gemm_tn_eights(const void* A, const void* B, float* C, float* colsum, int64_t M, int64_t N, int64_t K,
+                                     void* stream) {
+  return pf::gemm_tn_acc(pf::PF_DTYPE_BF16_, A, B, C, colsum, M, N, K, (hipStream_t)stream) == hipSuccess ? 0 : -1;
+}

@@ -573,6 +573,49 @@ def test_gemm_tn_kernel(M, N, K, with_colsum):
         assert bool((acc == 0.5).all())
 
 
+# Tokens that are no whole number of K steps: less than one step, one to ten steps and a rest, slices of K whose last one ends in
+# a rest; ragged edges.  slices: how many the launch takes.
+GEMM_TN_EIGHTS = [(128, 128, 8, 1), (200, 136, 72, 1), (72, 1000, 200, 1), (256, 384, 600, 4), (8, 8, 328, 2), (512, 1280, 1000, 2),
+                  (1536, 2120, 4040, 2)]
+
+
+@pytest.mark.parametrize("with_colsum", [False, True])
+@pytest.mark.parametrize("M,N,K,slices", GEMM_TN_EIGHTS)
+def test_gemm_tn_kernel_ends_inside_a_step(M, N, K, slices, with_colsum):
+    """As test_gemm_tn_kernel, with LDS left full of NaN: rows past the last token must not come from there, nor from what follows
+    the operands in memory (NaN as well)."""
+    import ctypes as ct
+    pf, dev = _mods()
+    assert pf.lib.pf_gemm_tn_slices(ct.c_int64(M), ct.c_int64(N), ct.c_int64(K)) == slices
+    f = pf.lib.pf_gemm_tn_eights
+    f.restype, f.argtypes = ct.c_int32, [ct.c_void_p] * 4 + [ct.c_int64] * 3 + [ct.c_void_p]
+    rng = np.random.default_rng(M + 2 * N + K)
+    A = synth.round_to_bf16(rng.standard_normal((K, M)).astype(np.float32))
+    B = synth.round_to_bf16((rng.standard_normal((K, N)) * 0.5).astype(np.float32))
+
+    def on_gpu(a):      # 64 rows of NaN behind it
+        t = torch.full((K + 64, a.shape[1]), float("nan"), dtype=torch.bfloat16, device="cuda")
+        t[:K] = torch.from_numpy(a).cuda().to(torch.bfloat16)
+        return t
+    dA, dB = on_gpu(A), on_gpu(B)
+    C0 = rng.standard_normal((M, N)).astype(np.float32)
+    dC = dev.to_device(C0)
+    acc = torch.full((M,), 0.5, dtype=torch.float32, device="cuda")
+    bad = torch.full((1024, 2048), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sink = torch.zeros(2048, 2048, device="cuda")
+    for _ in range(2):
+        pf.pf_op_gemm_tn(pf.PF_DTYPE_BF16, bad.data_ptr(), bad.data_ptr(), sink.data_ptr(), 2048, 2048, 1024)
+        assert f(dA.data_ptr(), dB.data_ptr(), dC.data_ptr(), acc.data_ptr() if with_colsum else None, M, N, K, None) == 0
+    torch.cuda.synchronize()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    scale = np.abs(A64).T @ np.abs(B64)
+    assert np.abs(dC.cpu().numpy() - C0 - 2.0 * (A64.T @ B64)).max() <= 5e-5 * scale.max() + 1e-5      # as in test_gemm_tn_kernel
+    if with_colsum:
+        assert np.abs(acc.cpu().numpy() - 0.5 - 2.0 * A64.sum(axis=0)).max() <= 5e-5 * np.abs(A64).sum(axis=0).max() + 1e-5
+    else:
+        assert bool((acc == 0.5).all())
+
+
 @pytest.mark.parametrize("M,N,K", [((1 << 23) + 8, 8, 128), (8, (1 << 23) + 8, 64)])
 def test_gemm_tn_results_of_eight_million_rows_or_columns(M, N, K):
     """Rows of an operand long enough that 64 of them pass 2^31 bytes: C and the column sums at both ends of the long side and in

@@ -70,6 +70,8 @@ PATHS = [
     ("bf16", 1659, 3072, 64, ALL, "tile 128x128", 1),
     ("bf16", 8292, 2370, 64, ALL, "tile 128x128", 1),
     ("bf16", 8292, 2372, 64, ("gelu", "pre", "dact"), "tile 128x128", 1),
+    ("bf16", 3841, 1928, 3008, ("plain", "bias", "gelu", "resid", "pre", "dact"), "tile 256x128", 1),
+    ("bf16", 1500, 776, 192, ("plain", "bias", "gelu", "resid", "dact"), "tile 128x64", 1),
     # K split over workgroups that have their CU to themselves (four LDS stages), ragged and whole, and that share it
     ("bf16", 100, 768, 16384, ("sum",), "tile 128x128 deep", 8),
     ("bf16", 1100, 512, 8192, ("sum",), "tile 128x128 deep", 4),
@@ -82,6 +84,10 @@ PATHS = [
 @pytest.mark.parametrize("dtype,M,N,K,epis,kernel,splits", PATHS)
 def test_the_case_runs_on_the_kernel_it_is_for(dtype, M, N, K, epis, kernel, splits):
     assert {route(dtype, M, N, K, e) for e in epis} == {(kernel, splits)}
+
+
+def test_every_kernel_has_a_case():
+    assert {p[5] for p in PATHS} == set(KERNELS)
 
 
 # what other GPU tests are for: large tiles on one to five K steps with ragged edges, edge tiles, grids that do not fill the
@@ -263,6 +269,32 @@ def _product(dtype, M, N, K, epis):
         assert err(got[:M], calls[e][1]) < tol and not got[M].any(), e
         if e == "pre":
             assert err(dev.read_storage(pre, md), u) < tol
+
+
+# Sums into an fp32 C of 96 M elements or more go past the caches (on tiled kernels with rows in pieces of 16 bytes).
+LARGE_SUMS = [(10250, 9828, 64), (7162, 16380, 2048)]
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [a + (k,) for a, k in zip(LARGE_SUMS, ("tile 256x256", "tile 256x256 16"))])
+def test_large_sums_run_on_tiled_kernels(M, N, K, kernel):
+    assert M * N >= 96 << 20 and N % 4 == 0 and M % 256 and N % 256 and route("bf16", M, N, K, "sum") == (kernel, 1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K", LARGE_SUMS)
+def test_numbers_of_large_sums(M, N, K):
+    from paper_2410_07192_amd import binding as pf
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N)
+    X = torch.randn(M, K, device="cuda", generator=gen).to(torch.bfloat16)
+    W = (torch.randn(N, K, device="cuda", generator=gen) * 0.05).to(torch.bfloat16)
+    acc = torch.randn(M + 1, N, device="cuda", generator=gen)          # a row behind C: must stay untouched
+    ref, last = acc[:M].double(), acc[M].clone()
+    for _ in range(2):
+        pf.pf_op_gemm(pf.PF_DTYPE_BF16, X.data_ptr(), W.data_ptr(), acc.data_ptr(), M, N, K, out_f32=1, accumulate=1)
+    torch.cuda.synchronize()
+    ref += 2 * (X.double() @ W.double().t())
+    assert float((acc[:M] - ref).abs().max() / ref.abs().max()) < 1e-5 and torch.equal(acc[M], last)
 
 
 # fp32 attention, heads in all, tokens, d_head: tiles or one thread per query (us, the chosen one first)
