@@ -57,7 +57,9 @@ double ring_estimate(const Product& p, Kernel* shape) {
 //    K = 320 14.1 / 14.4.
 //  * fp32 32x32: two workgroups per CU with one stage, one with two.  Alike on one round of tiles (512 x 512, K = 4096 29.4 / 29.5).
 //    More: 600 x 512, K = 512 10.9 / 11.4, K = 1056 19.2 / 18.7, K = 2048 34.0 / 29.9, K = 8192 119 / 94; 1024 x 1024, K = 1024
-//    32.8 / 33.8, K = 1568 48.2 / 47.7, K = 4096 119 / 102.
+//    32.8 / 33.8, K = 1568 48.2 / 47.7, K = 4096 119 / 102.  The last of three nearly full rounds leaves half of the CUs with two
+//    workgroups and the others idle where two fit (704 x 1024, K = 228 10.3 / 11.8, K = 292 14.2 / 13.5, K = 932 29.6 / 26.8), the last
+//    of five a little (1280 x 1024, K = 1060 46.2 / 45.7, K = 1572 64.2 / 60.4).
 //  * bf16 64x64: 333 x 2048, K = 2048 10.7 / 11.2, K = 3136 14.0 / 14.3, K = 4096 17.1 / 16.5, K = 8192 29.9 / 29.0.
 //  * bf16 32x32, one round of tiles, K from 1024 on: up to eight rows (nearly all operand bytes are W's) 1 x 208, K = 11392 15.1 /
 //    13.7, 3 x 952, K = 4224 8.1 / 7.6, 8 x 1472, K = 4864 8.7 / 8.2; rows that don't start on a cache line 46 x 896, K = 1688 6.1 /
@@ -72,7 +74,12 @@ Kernel ring_form(const Product& p, Kernel shape) {
   }
   if (shape == RING_64x64 && p.K > 256) return RING_64x64_DEEP;
   if (shape == RING_32x64 && p.K > 256 && p.K <= 320 && ceil_div(p.M, 32) * tiles_n64 <= 256) return RING_32x64_DEEP;
-  if (shape == RING_32x32 && t32 > 256 && p.K > (t32 <= 512 ? 1024 : 1536)) return RING_32x32_DEEP;
+  if (shape == RING_32x32 && t32 > 256) {
+    const int64_t rounds = ceil_div(t32, 256);
+    const bool last_full = t32 > rounds * 256 - 128;
+    const int64_t longest = rounds == 2 ? 1024 : rounds == 3 && last_full ? 256 : rounds == 5 && last_full ? 1056 : 1536;
+    if (p.K > longest) return RING_32x32_DEEP;
+  }
   return shape;
 }
 

@@ -281,8 +281,9 @@ bool gemm_tn_acc_preferred(int64_t M, int64_t N, int64_t K) {
 // 4096 55 / 58 / 80 / 125.  A workgroup takes 6 us and 0.56 to 0.82 us a K step, by how many of them share the chip; one that keeps
 // its whole K waits for C as well, and the longer its K the less of the operands is in L2 (up to 5.9 us); slices add their fp32
 // tiles with atomics, 0.56 us per MiB while every workgroup has a CU, 0.83 beyond.  Fitted to 450 sizes timed with every number of
-// slices: 0.7 % off the fastest on average.  Fewer than six steps stay together (4608 x 64, K = 256 8.7 / 9.6),
-// more come in slices of two where few tiles make that the fastest (64 x 64, K = 704 8.1 us with four slices, 9.3 with two).
+// slices: 0.7 % off the fastest on average.  Fewer than six steps stay together (4608 x 64, K = 256 8.7 / 9.6)
+// unless the result is small (64 x 376, K = 256 8.3 / 7.5); more come in slices of two where few tiles make that the fastest (64 x 64,
+// K = 704 8.1 us with four slices, 9.3 with two).
 static int32_t tn_slices(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128), steps = (K + 63) / 64;
   const double mib = (double)M * (double)N * 4.0 / 1048576.0;
@@ -290,7 +291,7 @@ static int32_t tn_slices(int64_t M, int64_t N, int64_t K) {
   double best_t = -1.0;
   for (int32_t s = 1; s <= 16; s *= 2) {
     const int64_t share = (steps + s - 1) / s, wgs = tiles * s;
-    if (s > 1 && (steps < 6 || share < 2 || share * (s - 1) >= steps || wgs > 512)) break;
+    if (s > 1 && ((steps < 6 && mib > 0.3) || share < 2 || share * (s - 1) >= steps || wgs > 512)) break;
     const double step = wgs <= 128 ? 0.56 : wgs <= 256 ? 0.65 : 0.82;
     const double unsplit = s == 1 ? std::min(5.9, 0.17 * (double)share) : 0.0;
     double t = (double)((wgs + 511) / 512) * (6.0 + unsplit + (double)share * step);

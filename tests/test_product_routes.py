@@ -119,6 +119,7 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
     ("f32", 600, 512, 320, "bias", "ring 32x64 deep"),       # 7.6 / 8.0
     ("f32", 699, 684, 6756, "plain", "ring 32x32 deep"),     # 84 / 101
     ("f32", 2329, 544, 4624, "plain", "ring 32x32 deep"),    # 142 / 167
+    ("f32", 4700, 144, 1304, "pre", "ring 32x32 deep"),      # 735 tiles: 33.9 / 39.0
     ("bf16", 3, 952, 4224, "gelu", "ring 32x32 deep"),       # 7.6 / 8.1
     ("bf16", 46, 896, 1688, "gelu", "ring 32x32 deep"),      # 5.8 / 6.1
     ("bf16", 333, 2048, 8192, "resid", "ring 64x64 deep"),   # 29.0 / 29.9
@@ -215,6 +216,7 @@ def test_two_slices_where_they_are_faster():
                                           (4096, 1024, 1024, 1),     # 22.6; two 34.5
                                           (4608, 64, 256, 1),        # 8.7; two 9.6
                                           (64, 64, 704, 4),          # 8.1; two 9.3
+                                          (64, 376, 256, 2),         # 7.5; one 8.3
                                           (50304, 1024, 8192, 1)])
 def test_the_fastest_number_of_slices(M, N, K, slices):
     from paper_2410_07192_amd import binding as pf
