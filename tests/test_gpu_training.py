@@ -575,7 +575,7 @@ def test_gemm_tn_kernel(M, N, K, with_colsum):
 
 # Tokens that are no whole number of K steps: less than one step, one to ten steps and a rest, slices of K whose last one ends in
 # a rest; ragged edges.  slices: how many the launch takes.
-GEMM_TN_EIGHTS = [(128, 128, 8, 1), (200, 136, 72, 1), (72, 1000, 200, 1), (256, 384, 600, 4), (8, 8, 328, 2), (512, 1280, 1000, 2),
+GEMM_TN_EIGHTS = [(128, 128, 8, 1), (200, 136, 72, 1), (72, 1000, 200, 2), (136, 2000, 200, 1), (256, 384, 600, 4), (8, 8, 328, 2), (512, 1280, 1000, 2),
                   (1536, 2120, 4040, 2)]
 
 
