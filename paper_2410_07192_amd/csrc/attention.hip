@@ -17,7 +17,6 @@
 
 #include <algorithm>
 
-
 namespace pf {
 namespace {
 
@@ -776,7 +775,7 @@ bool f32_by_tiles(int64_t B, int64_t S, int64_t h, int32_t dh) {
 // and a start of its own for those beyond the resident ones (two per CU with d_head 64, one with 128).  Fitted to 830 random
 // sizes timed both ways (MI355X): 0.1 and 0.8 % off the faster form on average, 3 % at most where 32 are chosen.
 // B x S x heads (us, 256 or 128 queries / 32; c: causal): d_head 64 1 x 128 x 12 6.7 / 4.7, 8 x 128 x 12 7.1 / 5.9, 16 x 128 x 12
-// 7.7 / 8.4, 3 x 200 x 8 c 9.7 / 5.3, 2 x 512 x 12 14.8 / 9.0, 4 x 512 x 12 15.6 / 12.9, 4 x 438 x 20 c 13.5 / 15.8, 1 x 1024 x 16 c
+// 7.7 / 8.4, 7 x 237 x 12 11.1 / 10.2, 3 x 200 x 8 c 9.7 / 5.3, 2 x 512 x 12 14.8 / 9.0, 4 x 512 x 12 15.6 / 12.9, 4 x 438 x 20 c 13.5 / 15.8, 1 x 1024 x 16 c
 // 23.4 / 12.9, 2 x 4400 x 4 84 / 94, 1 x 8192 x 4 c 145 / 91; d_head 128 1 x 333 x 16 c 12.5 / 9.4, 2 x 333 x 16 14.2 / 17.1, 1 x 426 x
 // 20 c 13.7 / 14.3, 4 x 333 x 16 c 13.6 / 21.3, 1 x 700 x 24 21.5 / 31.8, 1 x 1024 x 16 c 26.6 / 20.8, 1 x 2048 x 16 47.9 / 55.6.
 bool bf16_by_32(int64_t B, int64_t S, int64_t h, int32_t dh, int32_t causal) {
@@ -787,7 +786,7 @@ bool bf16_by_32(int64_t B, int64_t S, int64_t h, int32_t dh, int32_t causal) {
   const double tiles = (double)t, few = (double)std::min<int64_t>(t, 8), quarter = (double)((t + 3) / 4);
   const double work = (double)units * (causal ? (tiles + 1) / 2 : tiles);
   if (dh == 64)
-    return 2.7 + 0.0022 * (double)units + (causal ? 0.00079 : 0.0006) * work + 0.87 * quarter + (units > 512 ? 2.25 : 0.0) <
+    return 2.7 + 0.0022 * (double)units + (causal ? 0.00079 : 0.0006) * work + 0.87 * quarter + (units > 512 ? (causal ? 2.25 : 2.0) : 0.0) <
            4.7 + 1.04 * few + 0.88 * (tiles - few);
   return 5.0 + 0.0018 * work + 1.5 * quarter + (units > 256 ? 6.3 : 0.0) < 5.1 + 1.32 * few + 1.2 * (tiles - few);
 }

@@ -20,6 +20,7 @@ TIMED = [((16, 128, 12, 64, False), 7.7, 8.4), ((8, 128, 12, 64, False), 7.1, 5.
          ((1, 700, 24, 128, False), 21.5, 31.8), ((1, 1024, 16, 128, True), 26.6, 20.8), ((1, 2048, 16, 128, True), 47.9, 55.6),
          ((1, 2048, 8, 128, True), 45.5, 29.5), ((32, 512, 12, 64, False), 42.0, 58.0),
          # more workgroups than are resident, with and without a mask
+         ((7, 237, 12, 64, False), 11.1, 10.2),
          ((4, 438, 20, 64, True), 13.5, 15.8), ((2, 4400, 4, 64, False), 84.1, 94.0), ((47, 274, 2, 64, True), 10.8, 11.8),
          ((3, 370, 24, 64, True), 11.8, 12.3), ((1, 2318, 20, 64, True), 45.7, 47.3),
          ((1, 426, 20, 128, True), 13.7, 14.3), ((3, 719, 4, 128, False), 21.1, 21.7), ((2, 4547, 1, 128, False), 92.3, 87.8),
