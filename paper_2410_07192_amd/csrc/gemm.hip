@@ -10,8 +10,8 @@
 //  * Two to six LDS stages: the loads of step k+NS go into the stage that a barrier of step k has freed.  They are
 //    issued one at a time between MFMAs (a burst blocks every wave at the address unit) and are inline assembly
 //    so that the compiler does not serialise every later LDS read behind them; vmcnt is waited by hand.
-//  * Operand fragments are double buffered in registers: by slices of 32 k in the 256-wide tiles, by whole K steps in
-//    the others.
+//  * Operand fragments are double buffered in registers: by slices of a K step in the 256x256 (16 or 32 k) and 256x192 tiles
+//    (16 k), by whole K steps in the others.
 //  * The weight tile is the MFMA "A" operand and the activation tile the "B" operand, so each lane
 //    ends up with 4 consecutive output columns of one output row: bias / GELU of whole bf16 tiles are
 //    applied in registers; these then pass through LDS and leave as 16-byte row-contiguous stores (the

@@ -15,7 +15,10 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // X, in microseconds, measured on MI355X over K = 256 .. 8192.  The small tile moves twice the bytes of the 64x64 one per
 // product but spreads them over four times the CUs; on few CUs its bytes come faster (one tile 0.00062 us each).
 // odd: what a round costs more when columns don't come in fours and every thread goes through its share of C element by
-// element (one group of four with the 32x32 tile, eleven with 128x64).
+// element (one group of four with the 32x32 tile, eleven with 128x64).  These are times with two LDS stages a wave; one stage
+// (ring_form) is up to a third faster, which the choice between tiles does not see: over 846 products of small grids, bf16 and
+// fp32, every tile and form timed, it is 0.4 % off the fastest on average, by more than a tenth in six (1536 x 1024, K = 512 in fp32
+// 28.2 us on 64x64 tiles, 23.5 on 32x64).
 struct RingShape { int bm, bn; double fixed, byte, odd; };
 constexpr RingShape ring_shapes[] = {
     {32, 32, 2.6, 0.00098, 0.9}, {32, 64, 3.5, 0.0014, 2.2}, {64, 64, 4.6, 0.0017, 2.9}, {128, 64, 7.9, 0.0032, 9.4}};
@@ -111,8 +114,11 @@ bool by_16(const Product& p) {
 // tile 128x64), one workgroup per CU, and 128x128 (4 waves, two workgroups per CU).
 // A 128x128 grid that leaves every workgroup a CU of its own gets four LDS stages instead of two; 128x64 tiles below.
 // A launch takes ceil(workgroups / resident workgroups) rounds of start + step x (K steps of 64), in microseconds, measured
-// on MI355X (844 products, every shape timed); the shape with the least estimate runs.  That choice is 0.3 % off the
-// fastest shape on average and 13 % at most (1024 x 33024, K = 2048: 256x192 tiles 159 us, 256x256 141).  E.g. N = 768 or 2304
+// on MI355X; the shape with the least estimate runs.  On 520 random products, every shape (and number of slices) timed: rows in
+// eights and K from 512 on 0.8 % off the fastest on average, 3 of 211 by more than a tenth (774 x 9560, K = 1856: 256x192 tiles
+// 45.5 us, 256x256 40.4); shorter K 1.9 %, 9 of 125 (5753 x 7744, K = 192 with GELU 53.9, 128x128 45.3).  Sums 4.6 %, 22 of 136, and
+// other rows 5 %, 7 of 48: there the 128x64 tile, which is not among the candidates, would be the fastest (284 x 4096, K = 1408
+// into fp32 18.3, 10.8).  E.g. N = 768 or 2304
 // fills whole rounds with 192-wide tiles but wastes a quarter of the last round with 256-wide ones, and a 8192 x 1024
 // result gives every CU work only with the small tile.  (A chip full of 256-wide tiles runs at 1.3 to 1.5 times these
 // step times, every shape alike: the power limit.)  Partial tiles along N cost a shape nothing beyond the area they waste
@@ -125,14 +131,15 @@ bool by_16(const Product& p) {
 // (order-dependent in the last bits, like the other atomic reductions over tokens).  Those atomics go at about
 // 1.5 TB/s on MI355X, far below plain stores, so the estimate charges every slice for its tile: two slices usually
 // pay, eight rarely do.  Slices that leave some CUs with one workgroup are charged between the alone and the paired
-// rate: 1024 x 3072, K = 8192 unsplit 86.6 us, two slices 76.3; 2048 x 1536 81.4 and 70.7; K = 4096 44.8 and 47.0;
-// 768 x 1536, K = 8192 two slices 47.7, four 44.1.  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
+// rate, fitted to the loop by slices of fragments.  With the present one, us: 1024 x 3072, K = 8192 unsplit 60.0, two slices 71.5 (which
+// are chosen); 2048 x 1536 55.4 and 66.5; K = 4096 31.2 and 46.4; 768 x 1536, K = 8192 two slices 34.0, four 43.8 (chosen).  (256-wide tiles with split K were measured too: their atomic bursts at the end of the one
 // round are not hidden by anything and they lose to the small tile on every weight-gradient shape tried.)
 Route tiled_route(const Product& p) {
   struct Shape { Kernel kernel; int bm, bn, resident; double start, step, odd, odd_read, gelu, dact; };
   // 128x128 and 256x128: a whole K step of fragments in registers, timed for rows of whole 16-byte pieces, K from 512 on and
-  // no sum into C (8192 x 1024, K = 4096 58.6 us with both; K = 50304 858 and 725).  Elsewhere the 128x128 tile is taken as it
-  // was measured with a slice of fragments in registers: there the shapes are within a fifth of one another.
+  // no sum into C (8192 x 1024, K = 4096 58.6 us with both; K = 50304 858 and 725).  Elsewhere a pair of 128x128 tiles (and for
+  // sums and other rows a lone one) is taken with the times of its loop by slices of fragments, which it no longer runs: its own
+  // start and step are shorter, and the choice is as far off as stated above.
   const bool timed = p.N % 8 == 0 && p.K >= 512 && !(p.epi & E_ACC);
   const Shape pair = timed ? Shape{TILE_128x128, 128, 128, 512, 3.8, 0.82, 11, 25, 1, 0} : Shape{TILE_128x128, 128, 128, 512, 4.1, 1.02, 11, 25, 1, 0};
   const Shape shapes[4] = {{TILE_256x256, 256, 256, 256, 8.0, 1.06, 44, 76, 5, 16}, {TILE_256x192, 256, 192, 256, 6.0, 1.1, 20, 42, 4, 4},
@@ -221,7 +228,9 @@ Route route(const Product& p) {
   // the estimates decide, for C in whole tiles; a ragged C costs the generic kernel 7 us, and the ring kernel nothing.
   // Fitted to 32 .. 192 tiles, K = 40 .. 4104 (rows that don't start on a cache line cost the ring kernel 8 %); generic
   // against ring, us: 2048 x 1536 K = 200 9.6 / 14.5, K = 1000 20.1 / 23.2, K = 2008 38.3 / 33.9, accumulating into fp32
-  // K = 600 21.2 / 22.1, K = 1000 27.6 / 26.8; 1024 x 2048 K = 40 6.8 / 8.3, K = 328 10.7 / 10.0; 512 x 512 K = 40 6.3 / 3.5.
+  // K = 600 21.2 / 22.1, K = 1000 27.6 / 26.8; 1024 x 2048 K = 40 6.8 / 8.3, K = 328 10.7 / 10.0; 512 x 512 K = 40 6.3 / 3.5.  (Ring
+  // tiles with two LDS stages a wave.  With one, 2048 x 1536 takes 21.8 us at K = 1000 and, accumulating, 19.0 at K = 600, where the
+  // generic kernel still runs.)
   if (p.aligned && ceil_div(p.M, 128) * ceil_div(p.N, 128) <= 192) {
     const double t = ring_estimate(p, &ring);
     const bool whole = p.M % 128 == 0 && p.N % 128 == 0;

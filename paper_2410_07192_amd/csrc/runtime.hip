@@ -326,9 +326,14 @@ static int32_t drain_timing(pf_ctx* c) {
 namespace pf {
 // Weights that idle CUs read during the small launches of a layer (ReadAhead): W_qkv during its LayerNorm; W_o, W_1 and W_2 during
 // attention.  Only where the tokens make one group of row tiles in every product (256: eight tiles of 32), so that an XCD's share
-// is the eighth it reads, and where they fit the L2s (32 MB in all) beside the activations.  12 layers of d 768 on 128 tokens:
-// 483 us without, 447 with attention reading ahead, 436 with both; on 16 tokens 366 and 361.  Nothing is gained on 500 tokens
-// (6 layers of d 768 299 and 299), and 4 layers of d 1024 on 512 lose (216 and 220).
+// is the eighth it reads, and where they fit the L2s (32 MB in all) beside the activations.  Measured on MI355X, us a pass without /
+// with.  Weights that no cache holds, as a fill job finds them after other work (several models in turn, 700 MB): bf16, 12 layers of
+// d 768 on 16 tokens 434 / 386, 128 481 / 435, 256 535 / 490; 8 of d 512 on 128 264 / 248; 6 of d 1024 on 256 291 / 271; 6 of d
+// 1088 (27 MiB a layer) on 16 251 / 229, 128 289 / 268, 192 301 / 287, 256 348 / 323; fp32 alike (6 of d 512 on 128 306 / 306).  The
+// same model pass after pass, its weights in the memory-side cache: 403 / 403 (d 768, 128 tokens), 240 / 238 (d 512), 248 / 248 (d
+// 1024 on 256), but 240 / 247 and 289 / 299 (d 1088 on 128 and 256) and 211 / 221 (d 512 on 8).  Beyond either bound such passes
+// lose (4 layers of d 1024 on 512 tokens 216 / 220, 6 of d 1280, 38 MiB a layer, on 128 257 / 275) where weights out of the caches would
+// gain (12 of d 768 on 500 tokens 645 / 577, 6 of d 1280 on 16 270 / 245).
 static ReadAhead read_ahead_of(const Layout& lay, const char* wb, int64_t T, int64_t d, int64_t f, bool attention) {
   ReadAhead a;
   const int64_t e = lay.esz, qkv = 3 * d * d * e, bytes[3] = {d * d * e, f * d * e, d * f * e};

@@ -109,7 +109,8 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
     assert {route("bf16", M, N, K, e)[0] for e in epis} == {kernel}
 
 
-# The faster kernel at sizes where two were timed on MI355X (times in us, the chosen one first): the rules follow them.
+# The faster kernel at sizes where two were timed on MI355X (times in us, the chosen one first): the rules follow them.  Where the
+# kernels have changed since and a third one is faster now, it comes last, after "not chosen".
 @pytest.mark.parametrize("dtype,M,N,K,epi,kernels", [
     # ring kernel, one LDS stage a wave or two
     ("f32", 1024, 1024, 256, "bias", "ring 64x64"),
@@ -124,57 +125,57 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
     ("bf16", 46, 896, 1688, "gelu", "ring 32x32 deep"),      # 5.8 / 6.1
     ("bf16", 333, 2048, 8192, "resid", "ring 64x64 deep"),   # 29.0 / 29.9
     # fp32: FMA kernel against the best ring tile
-    ("f32", 4096, 2048, 64, "bias", "f32 fma"),        # 29 / 45
-    ("f32", 8192, 1024, 128, "bias", "f32 fma"),       # 44 / 52
-    ("f32", 2048, 2048, 64, "bias", "f32 fma"),        # 18.7 / 23.7
-    ("f32", 2048, 576, 32, "bias", "f32 fma"),         # 9.6 / 12.0
-    ("f32", 2048, 576, 64, "bias", "ring"),            # 12.1 / 12.9
-    ("f32", 2048, 1024, 96, "bias", "ring"),           # 13.0 / 16.8
-    ("f32", 2048, 576, 128, "bias", "ring 64x64"),     # 13.7; 128x64 16.2, fma 20.8
-    ("f32", 2048, 2048, 192, "bias", "ring 128x64"),   # 32.3; 64x64 35.3, fma 38.0
-    ("f32", 2048, 576, 512, "bias", "ring 32x32"),     # 25.2; 64x64 27.6
-    ("f32", 4096, 2048, 256, "bias", "ring 64x64"),    # 69.4 / 78.3
-    ("f32", 4004, 5119, 316, "bias", "f32 fma"),       # columns not in fours: 215 / 64x64 267
-    ("f32", 2958, 418, 80, "gelu", "f32 fma"),         # 16.3 / 128x64 21.4
+    ("f32", 4096, 2048, 64, "bias", "f32 fma"),        # 28.8 / 44.8
+    ("f32", 8192, 1024, 128, "bias", "f32 fma"),       # 44 / 46
+    ("f32", 2048, 2048, 64, "bias", "f32 fma"),        # 18.7 / 24.0
+    ("f32", 2048, 576, 32, "bias", "f32 fma"),         # 9.7 / 128x64 12.1; not chosen: 32x32 9.3
+    ("f32", 2048, 576, 64, "bias", "ring"),            # 12.1 / 12.8; not chosen: 32x32 10.9
+    ("f32", 2048, 1024, 96, "bias", "ring"),           # 13.2 / 16.8
+    ("f32", 2048, 576, 128, "bias", "ring 64x64"),     # 12.4; 128x64 16.2, fma 20.8; not chosen: 32x32 10.9
+    ("f32", 2048, 2048, 192, "bias", "ring 128x64"),   # 32.5; 64x64 32.7, fma 38.0
+    ("f32", 2048, 576, 512, "bias", "ring 32x32"),     # 22.5; 64x64 27.9
+    ("f32", 4096, 2048, 256, "bias", "ring 64x64"),    # 63.6 / 75.0
+    ("f32", 4004, 5119, 316, "bias", "f32 fma"),       # columns not in fours: 211 / 64x64 251
+    ("f32", 2958, 418, 80, "gelu", "f32 fma"),         # 16.1 / 128x64 21.4; not chosen: 32x32 13.9
     ("f32", 512, 1024, 256, "gelu", "ring"),           # a layer of d 256 on 512 tokens
     ("f32", 512, 256, 1024, "resid", "ring"),
     # K no multiple of 64: generic kernel against the best ring tile
-    ("bf16", 128, 24576, 200, "plain", "bf16 generic"),    # 10.5 / 15.4
-    ("bf16", 2048, 1536, 1000, "plain", "bf16 generic"),   # 20.1 / 23.2
-    ("bf16", 2048, 1536, 2008, "plain", "ring"),           # 33.9 / 38.3
-    ("bf16", 2048, 1536, 328, "resid", "bf16 generic"),    # 17.1 / 18.4
-    ("bf16", 2048, 1536, 600, "sum", "bf16 generic"),      # 21.2 / 22.1
-    ("bf16", 2048, 1536, 1000, "sum", "ring"),             # 26.8 / 27.6
-    ("bf16", 1024, 2048, 104, "plain", "bf16 generic"),    # 7.6 / 8.3
-    ("bf16", 1024, 2048, 328, "plain", "ring"),            # 10.0 / 10.7
-    ("bf16", 1024, 2048, 104, "sum", "ring"),              # 10.6 / 11.8
+    ("bf16", 128, 24576, 200, "plain", "bf16 generic"),    # 10.7 / 14.3
+    ("bf16", 2048, 1536, 1000, "plain", "bf16 generic"),   # 20.5 / 21.8
+    ("bf16", 2048, 1536, 2008, "plain", "ring"),           # 31.7 / 38.6
+    ("bf16", 2048, 1536, 328, "resid", "bf16 generic"),    # 17.2 / 128x64 20.5; not chosen: 64x64 15.9
+    ("bf16", 2048, 1536, 600, "sum", "bf16 generic"),      # 21.1 / 32x32 23.3; not chosen: 64x64 19.0
+    ("bf16", 2048, 1536, 1000, "sum", "ring"),             # 23.8 / 27.6
+    ("bf16", 1024, 2048, 104, "plain", "bf16 generic"),    # 7.7 / 8.2
+    ("bf16", 1024, 2048, 328, "plain", "ring"),            # 10.2 / 10.9
+    ("bf16", 1024, 2048, 104, "sum", "ring"),              # 10.3 / 11.8
     ("bf16", 512, 512, 40, "plain", "ring"),               # 3.5 / 6.3
-    ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 13.3 / 15.1
+    ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 12.6 / 15.3
     ("bf16", 2048, 512, 600, "sum", "ring"),               # weight gradients of 600 tokens, d 512
     # partial tiles along N for the chosen shape, none for the other
-    ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 54.2 / whole 128x128 tiles 70.8
-    ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 53.4 / whole 128x128 tiles 69.0
+    ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 52.8 / whole 128x128 tiles 58.3
+    ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 52.1 / whole 128x128 tiles 56.8
     ("bf16", 1659, 960, 768, "resid", "tile 128x64"),        # 8.2 / 128x128 deep 9.6, ring 12.5
     ("bf16", 522, 2848, 64, "plain", "tile 128x64"),         # 4.6 / 128x128 deep 5.0
     ("bf16", 1659, 768, 768, "resid", "tile 128x64"),        # 8.1 / 128x128 deep 9.4
     # the 256x256 tile by its own rate, and what the epilogues cost it
-    ("bf16", 4096, 10048, 2048, "plain", "tile 256x256"),    # 153 / 256x192 187, 128x128 197
-    ("bf16", 8192, 50304, 1024, "plain", "tile 256x256"),    # 797 / 256x192 970
-    ("bf16", 50304, 1024, 8192, "sum", "tile 256x256"),      # 793 / 256x192 1020
-    ("bf16", 8192, 2304, 2048, "bias", "tile 256x192"),      # 84.2 / 256x256 89.5
+    ("bf16", 4096, 10048, 2048, "plain", "tile 256x256"),    # 146 / 256x192 187, 128x128 172
+    ("bf16", 8192, 50304, 1024, "plain", "tile 256x256"),    # 743 / 256x192 920
+    ("bf16", 50304, 1024, 8192, "sum", "tile 256x256"),      # 752 / 256x192 977
+    ("bf16", 8192, 2304, 2048, "bias", "tile 256x192"),      # 87.0 / 256x256 90.0; not chosen: 128x128 82.0
     ("bf16", 8192, 1024, 1024, "resid", "tile 128x128"),
-    ("bf16", 8192, 9648, 320, "dact", "tile 128x128"),       # 139 / 256x192 153, 256x256 218
-    ("bf16", 4096, 9648, 320, "pre", "tile 128x128"),        # 62 / 256x256 71
-    ("bf16", 8192, 5002, 768, "bias", "tile 128x128"),       # odd rows: 163 / 256x192 182, 256x256 265
+    ("bf16", 8192, 9648, 320, "dact", "tile 128x128"),       # 138 / 256x192 154, 256x256 217
+    ("bf16", 4096, 9648, 320, "pre", "tile 128x128"),        # 55 / 256x256 71
+    ("bf16", 8192, 5002, 768, "bias", "tile 128x128"),       # odd rows: 131 / 256x192 155, 256x256 195
     # weight gradients over long K: split or not, or few small tiles
-    ("bf16", 1024, 3072, 8192, "sum", "tile 128x128"),       # two slices 76.3 / unsplit 86.6
-    ("bf16", 64, 64, 8192, "sum", "ring 32x32"),             # 12.9 / eight slices 15.5
-    ("bf16", 1024, 3072, 4096, "sum", "tile 128x128 deep"),  # unsplit 44.8 / two slices 47.0
-    ("bf16", 384, 3072, 4096, "sum", "tile 128x128 deep"),   # two slices 29.8 / four 33.2, unsplit 42.5
-    ("bf16", 1024, 1024, 8192, "sum", "ring 64x64"),         # 29.9 / four slices 36.8
-    ("bf16", 768, 1536, 8192, "sum", "tile 128x128"),        # four slices 44.1 / two 47.7
-    ("bf16", 1536, 512, 8192, "sum", "ring 64x64"),          # 28.0 / four slices 32.6
-    ("bf16", 100, 132, 16384, "sum", "ring 32x32"),          # 22.9 / eight slices 25.4
+    ("bf16", 1024, 3072, 8192, "sum", "tile 128x128"),       # two slices 71.5 / unsplit pairs 88.0; not chosen: deep, unsplit, 60.0
+    ("bf16", 64, 64, 8192, "sum", "ring 32x32"),             # 11.8 / eight slices 11.7
+    ("bf16", 1024, 3072, 4096, "sum", "tile 128x128 deep"),  # unsplit 31.0 / two slices 46.2
+    ("bf16", 384, 3072, 4096, "sum", "tile 128x128 deep"),   # two slices 23.2 / four 32.2, unsplit 27.2; not chosen: 128x64 21.1
+    ("bf16", 1024, 1024, 8192, "sum", "ring 64x64"),         # 32.2 / two slices 32.4, four 32.5
+    ("bf16", 768, 1536, 8192, "sum", "tile 128x128"),        # four slices 43.8 / unsplit 46.9; not chosen: deep, two slices, 34.0
+    ("bf16", 1536, 512, 8192, "sum", "ring 64x64"),          # 30.4 / two slices 30.6; not chosen: deep, four slices, 27.2
+    ("bf16", 100, 132, 16384, "sum", "ring 32x32"),          # 21.7; not chosen: deep, eight slices, 17.8
 ])
 def test_the_faster_kernel_is_chosen(dtype, M, N, K, epi, kernels):
     assert route(dtype, M, N, K, epi)[0].startswith(kernels)
@@ -199,6 +200,8 @@ def test_16x16x32_mfmas_on_a_full_chip_and_long_k_only():
 
 
 def test_two_slices_where_they_are_faster():
+    # than pairs of 128x128 tiles that keep their K (unsplit, with a CU each, the first three take 60, 60 and 55 us now, two slices
+    # 71, 71 and 67: the estimate does not see it)
     assert [route("bf16", M, N, K, "sum")[1] for M, N, K in
             ((1024, 3072, 8192), (3072, 1024, 8192), (2048, 1536, 8192), (1024, 3072, 4096), (2048, 2048, 8192))] == [2, 2, 2, 1, 1]
 
