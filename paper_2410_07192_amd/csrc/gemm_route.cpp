@@ -98,15 +98,21 @@ double fma_estimate(const Product& p) {
 }
 
 // 256x256 tiles with 16x16x32 MFMAs instead of 32x32x16: where the power limit sets the rate, i.e. on a chip that is full nearly
-// all the time, and K is long enough for that to outweigh the slower start.  Measured on MI355X, time with 16x16x32 by time with
-// 32x32x16, over 1660 pairs of results and epilogues: rounds filled to 0.93 or more, K < 512 1.07 (0.95 to 1.14), 512 .. 1000
-// 1.04, 1400 .. 2000 0.98 (to 1.04), 2048 0.98 (0.95 to 1.02), 2560 0.97, from 4096 on 0.96 (0.93 to 1.00); to 0.84: K = 2048 1.01,
-// 6208 1.01, from 8192 on 0.98 (408 x 28032, K = 10048 into fp32 1.05); less (964 x 10112, 160 tiles): 1.02 to 1.17 at any K.  4096 x 4096 us: K = 768 27.8 / 27.4, K = 2048
-// 56.7 / 58.3, K = 8192 190 / 201; sums into fp32 alike (8192 x 8192, K = 2048 293 / 296).
+// all the time, and K is long enough for that to outweigh the slower start.  Measured on MI355X both alone (1660 pairs of results
+// and epilogues, time with 16x16x32 by time with 32x32x16) and inside whole passes of 2 to 11 layers (146 passes, all such products
+// of one by either form), which keep the chip at its power limit and decide where the two disagree:
+//  * one round: alone, filled to 0.93 or more, K < 512 1.07, 512 .. 1000 1.04, 1400 .. 2000 0.98, 2048 0.98, from 4096 on 0.96; passes 0.96
+//    to 1.00 from K = 1024 on (3840 x 4352, K = 1088 545 -> 523 us of three layers), 0.97 to 1.01 below; filled less 1.00 to 1.04 (160
+//    to 225 tiles: 3804 x 2688, K = 10752 661 -> 689).
+//  * more rounds, filled to 0.74 or more, K from 1024 on: passes 0.96 to 1.01, 0.985 on average (16384 x 4904, K = 1472 3217 -> 3095,
+//    8192 x 6192, K = 1536 2162 -> 2097, 14720 x 4864, K = 1216 2132 -> 2157); alone 0.96 to 1.03 (4096 x 7168, K = 2112 108 -> 111).
+//  * more rounds, K 512 .. 1000: passes 0.988 on average filled to 0.9 (17920 x 3384, K = 832 1697 -> 1652, 20480 x 3840, K = 960 1890 ->
+//    1908), 1.00 below that (18 of them 0.98 to 1.01); alone 1.04.  K = 320 alone: 15632 x 7832 120 -> 137.
 bool by_16(const Product& p) {
   const int64_t tiles = ceil_div(p.M, 256) * ceil_div(p.N, 256);
   const double filled = (double)tiles / (double)(256 * ceil_div(tiles, 256));
-  return filled >= 0.93 && p.K >= 2048;
+  if (tiles <= 256) return p.K >= 1024 && filled >= 0.93;
+  return (p.K >= 1024 && filled >= 0.74) || (p.K >= 512 && filled >= 0.9);
 }
 
 // Tiled kernels, and the ring kernel where it is faster.

@@ -64,6 +64,7 @@ PATHS = [
     ("bf16", 4000, 4088, 2112, ALL, "tile 256x256 16", 1),
     ("bf16", 4000, 4092, 2048, ALL, "tile 256x256 16", 1),
     ("bf16", 4000, 4090, 2048, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256 16", 1),
+    ("bf16", 4001, 8184, 576, ("plain", "bias", "gelu", "resid", "pre", "sum"), "tile 256x256 16", 1),   # two rounds, nine steps
     ("bf16", 1300, 6152, 128, ALL, "tile 256x192", 1),
     ("bf16", 1300, 6156, 128, ALL, "tile 256x192", 1),
     ("bf16", 1300, 6154, 512, ALL, "tile 256x192", 1),
@@ -188,15 +189,22 @@ def test_one_stage_a_wave_where_it_is_faster():
 
 
 def test_16x16x32_mfmas_on_a_full_chip_and_long_k_only():
-    # us, the chosen form first
+    # us, the chosen form first; "in": of a pass of layers with this product
     assert {route("bf16", *p)[0] for p in ((4096, 4096, 2048),            # 56.7 / 58.3
-                                           (8192, 2048, 8192))} == {"tile 256x256 16"}       # 191 / 202
+                                           (8192, 2048, 8192),            # 191 / 202
+                                           (3840, 4352, 1088),            # 255 tiles: in 523 / 545
+                                           (16384, 4904, 1472),           # five full rounds: in 3095 / 3217
+                                           (8192, 6192, 1536),            # 800 tiles, filled to 0.78: in 2097 / 2162
+                                           (17920, 3384, 832),            # filled to 0.96: in 1652 / 1697
+                                           (4096, 7168, 2112))} == {"tile 256x256 16"}       # 448 tiles: alone 111 / 108
     assert {route("bf16", *p)[0] for p in ((4096, 4096, 768),             # 27.4 / 27.8
                                            (15632, 7936, 320),            # 111 / 127
+                                           (18560, 1792, 448),            # 511 tiles: in 638 / 640
+                                           (9600, 2816, 704),             # 418 tiles: in 625 / 631
+                                           (3332, 3840, 960),             # 210 tiles: in 609 / 615
                                            (964, 10112, 13696),           # 160 tiles: 243 / 284
                                            (408, 28032, 10048),           # 220 tiles
-                                           (1400, 9216, 4160),            # 216 tiles: 93 / 97
-                                           (4096, 7168, 2112))} == {"tile 256x256"}          # 448 tiles: 108 / 111
+                                           (1400, 9216, 4160))} == {"tile 256x256"}          # 216 tiles: 93 / 97
 
 
 def test_two_slices_where_they_are_faster():
