@@ -174,7 +174,11 @@ Route tiled_route(const Product& p) {
       const double step = small ? lone_step + paired * (sh.step - lone_step) : sh.step;
       const double odd = p.N % 4 == 0 || splits > 1 ? 0.0 : reads ? sh.odd_read : sh.odd;
       double act = p.epi & E_DACT ? sh.dact : p.epi & E_GELU && !alone ? sh.gelu : 0.0;
-      if (alone && whole) act = p.epi & E_DACT ? 2.5 : p.epi & E_PRE ? 1.6 : p.epi & E_GELU ? 0.9 : 0.0;
+      // (up to 32 rows, weights from memory, us on 128x128 / 32x64 ring tiles: GELU hides behind the other waves' waits, 32 x 19968, K =
+      // 4992 49.7 / 51.3, with a copy 24 x 18856, K = 5760 55.8 / 56.9; GELU' costs more than a second round of a few ring tiles, 16 x
+      // 17408, K = 4352 44.4 / 42.2, 8 x 16912, K = 5312 50.4 / 48.4, but no more than one of 40, 32 x 19968, K = 4992 50.9 / 51.5)
+      if (alone && whole && p.M <= 32) act = p.epi & E_DACT && busy == 0.0 ? 2.5 : 0.0;
+      else if (alone && whole) act = p.epi & E_DACT ? 2.5 : p.epi & E_PRE ? 1.6 : p.epi & E_GELU ? 0.9 : 0.0;
       double t = (double)ceil_div(wgs, sh.resident) * (start + odd + act + step * (double)(p.K / (64 * splits)));
       // every slice adds its whole fp32 tile with atomics: about 0.67 us per MiB, and 2.5 us whatever its size (128 x 128,
       // K = 4096: 25.9, 16.6 and 11.9 us with two, four and eight slices)

@@ -153,6 +153,11 @@ def test_other_gpu_cases_run_on_the_kernel_they_are_for(M, N, K, epis, kernel):
     ("bf16", 512, 512, 40, "plain", "ring"),               # 3.5 / 6.3
     ("bf16", 1000, 3072, 104, "plain", "ring"),            # ragged: 12.6 / 15.3
     ("bf16", 2048, 512, 600, "sum", "ring"),               # weight gradients of 600 tokens, d 512
+    # few rows, weights from memory: 128x128 against 32x64 ring tiles
+    ("bf16", 32, 19968, 4992, "gelu", "tile 128x128 deep"),  # 49.7 / 51.3
+    ("bf16", 24, 18856, 5760, "pre", "tile 128x128 deep"),   # 55.8 / 56.9
+    ("bf16", 24, 18856, 5760, "dact", "tile 128x128 deep"),  # 56.7 / 56.9
+    ("bf16", 16, 17408, 4352, "dact", "ring 32x64"),         # 42.2 / 44.4
     # partial tiles along N for the chosen shape, none for the other
     ("bf16", 4096, 3456, 2048, "bias", "tile 256x256"),      # 52.8 / whole 128x128 tiles 58.3
     ("bf16", 8192, 1664, 2048, "bias", "tile 256x256"),      # 52.1 / whole 128x128 tiles 56.8
